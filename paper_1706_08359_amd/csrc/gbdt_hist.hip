@@ -462,14 +462,13 @@ int build_wg_per_cu(int cap, bool indexed, bool wide = false) {
 // up to 4 passes, aiming at 500-1000 workgroups in all.  (2,000 features x 63 bins, 64
 // histograms: 188 us with 8 features per workgroup as for a lone histogram, 85 us with 16 x 4;
 // 137 x 255, 64 histograms: 113 us with one feature per workgroup, 40 us with 7 x 2.)
+constexpr int64_t kSplitManyWgs = 1024;  // workgroups of a launch from which residency counts
 struct SplitGrouping {
   int group, passes, n_wg;
 };
 SplitGrouping split_grouping(int32_t n_features, int32_t n_bins, int32_t n_hists) {
   SplitGrouping g;
-  int cap = kSplitLdsBudget / split_feature_bytes(n_bins);
-  if (cap > 16) cap = 16;
-  if (cap < 1) cap = 1;
+  const int cap = split_max_group(n_bins);
   const int spread = (n_features + 255) / 256;  // a lone histogram: about 256 groups
   const int64_t total = (int64_t)n_features * (n_hists > 0 ? n_hists : 1);
   const int64_t shared = (total + 511) / 512;   // many histograms: about 512 groups in all
@@ -624,16 +623,21 @@ int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, 
   int rc = get_workspace((size_t)n_hists * sg.n_wg * sizeof(SplitCand), s, &ws);
   if (rc != GBDT_OK) return rc;
   const size_t lds = (size_t)sg.group * split_feature_bytes(n_bins);
-  SplitSiblings sib;
-  if (siblings) {
-    sib = *siblings;
-  } else {
-    memset(&sib, 0, sizeof sib);
-  }
   // (only with siblings does the kernel write to the histograms)
-  hipLaunchKernelGGL(split_gain_kernel, dim3(sg.n_wg, n_hists), dim3(kSplitThreads), lds, s,
-                     const_cast<gbdt_bin_t*>(hists), hist_stride, n_features, n_bins, sg.group, sg.passes,
-                     (double)lambda, (double)min_child_hess, (SplitCand*)ws, splits_out, host_mirror, sib);
+  const bool few_steps = split_steps(n_bins, sg.group) <= 4;
+  auto launch = [&](auto kernel, const auto& sib) {
+    hipLaunchKernelGGL(kernel, dim3(sg.n_wg, n_hists), dim3(kSplitThreads), lds, s,
+                       const_cast<gbdt_bin_t*>(hists), hist_stride, n_features, n_bins, sg.group, sg.passes,
+                       (double)lambda, (double)min_child_hess, (SplitCand*)ws, splits_out, host_mirror, sib);
+  };
+  const bool many = (int64_t)sg.n_wg * n_hists > kSplitManyWgs;
+  if (siblings) {
+    launch(few_steps ? (many ? split_gain_kernel<4, true, SplitSiblings> : split_gain_kernel<4, false, SplitSiblings>)
+                     : split_gain_kernel<kSplitSteps, true, SplitSiblings>, *siblings);
+  } else {
+    launch(few_steps ? (many ? split_gain_kernel<4, true, NoSiblings> : split_gain_kernel<4, false, NoSiblings>)
+                     : split_gain_kernel<kSplitSteps, true, NoSiblings>, NoSiblings{});
+  }
   HIP_TRY(hipGetLastError());
   return GBDT_OK;
 }
@@ -1834,6 +1838,8 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
   std::vector<Entry> frontier = {{0, 0}};
   int n_nodes = 1;
   bool root_done = false;
+  SplitSiblings level_sib;  // the level's siblings, where the split search forms them
+  level_sib.n = 0;
   for (int depth = 0;; ++depth) {
     // ---- best split of every open node of the level, one launch, one read-back
     std::vector<int> open;  // indices into frontier, in histogram slot order
@@ -1842,7 +1848,12 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     std::sort(open.begin(), open.end(), [&](int a, int b) { return frontier[a].slot < frontier[b].slot; });
     const int n_open = (int)open.size();
     if (n_open == 0) break;
-    rc = gbdt_best_split_batch(hist_buf[cur], n_open, lambda, min_child_hess, recs, n_features, n_bins, s);
+    if (level_sib.n > 0) {
+      rc = launch_split(hist_buf[cur], (int64_t)hist_elems, n_open, lambda, min_child_hess, recs, n_features, n_bins,
+                        s, nullptr, &level_sib);
+    } else {
+      rc = gbdt_best_split_batch(hist_buf[cur], n_open, lambda, min_child_hess, recs, n_features, n_bins, s);
+    }
     if (rc != GBDT_OK) return rc;
     HIP_TRY(hipMemcpyAsync(pinned, recs, (size_t)n_open * sizeof(gbdt_split_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -1958,7 +1969,11 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     rc = gbdt_hist_build_batch(bin_matrix, n_rows, n_features, n_bins, small_rows, small_offs.data(), k, grad,
                                hess, hist_buf[nxt], s);
     if (rc != GBDT_OK) return rc;
-    for (int j0 = 0; j0 < k; j0 += kSiblingTable) {
+    level_sib.pool = hist_buf[cur];
+    level_sib.first = k;
+    level_sib.n = k <= kSplitSiblings && 2 * k <= kSplitMaxHists ? k : 0;
+    for (int j = 0; j < level_sib.n; ++j) level_sib.parent_slot[j] = parent_slot[j];
+    for (int j0 = 0; j0 < k && level_sib.n == 0; j0 += kSiblingTable) {
       SiblingTable t;
       const int ns = k - j0 < kSiblingTable ? k - j0 : kSiblingTable;
       for (int j = 0; j < ns; ++j) t.parent_slot[j] = parent_slot[j0 + j];

@@ -7,6 +7,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "../../include/gbdt_hist.h"
 
 namespace {
@@ -67,27 +69,50 @@ __device__ __forceinline__ SplitCand load_cand(const SplitCand* src) {
   memcpy(&c, w, sizeof c);
   return c;
 }
-__device__ __forceinline__ double load_cand_gain(const SplitCand* src) {
-  const unsigned long long w = __hip_atomic_load(
-      const_cast<unsigned long long*>(reinterpret_cast<const unsigned long long*>(src)), __ATOMIC_RELAXED,
-      __HIP_MEMORY_SCOPE_AGENT);
-  double g;
-  memcpy(&g, &w, sizeof g);
-  return g;
-}
-__device__ __forceinline__ int32_t load_cand_feature(const SplitCand* src) {
-  // word 6 = (feature, bin)
-  const unsigned long long w = __hip_atomic_load(
-      const_cast<unsigned long long*>(reinterpret_cast<const unsigned long long*>(src)) + 6, __ATOMIC_RELAXED,
-      __HIP_MEMORY_SCOPE_AGENT);
-  return (int32_t)(uint32_t)(w & 0xffffffffull);
-}
-
 // LDS bytes one feature needs in split_gain_kernel: fp64 running sums of gradient,
 // hessian and count per bin (bins padded to a multiple of kSplitBlock), + the feature's parent term.
+// A row is two doubles longer than that: the prefix pass walks down all rows of a group at once,
+// 16 bytes per lane, and with rows an odd multiple of 16 bytes apart the lanes fall on different banks
+// (with rows a multiple of 128 bytes apart, as they were, all of them fell on the same: 16 features
+// x 64 bins took 6,100 cycles there).
 constexpr int kSplitBlock = 16;  // bins the prefix loop adds per register block
 __host__ __device__ inline int split_padded_bins(int n_bins) { return (n_bins + kSplitBlock - 1) & ~(kSplitBlock - 1); }
-__host__ __device__ inline int split_feature_bytes(int n_bins) { return 24 * split_padded_bins(n_bins) + 8; }
+__host__ __device__ inline int split_row(int n_bins) { return split_padded_bins(n_bins) + 2; }
+__host__ __device__ inline int split_feature_bytes(int n_bins) { return 24 * split_row(n_bins) + 8; }
+
+// How the workgroup's wavefronts walk over the (feature, bin) pairs of a group, in steps of 64: up to 64 bins
+// a step is 64 / lanes rows side by side (lanes = the bins rounded up to a power of two), beyond that a
+// row takes `chunks` steps.  No division per thread, and a step's loads are whole rows.
+constexpr int kSplitSteps = 8;  // steps a wavefront takes of a group at most: 32 steps a group
+struct SplitWalk {
+  int lane_bits;  // log2 of the lanes per row
+  int rows;       // rows per step
+  int chunks;     // steps per row
+  int per_chunk;  // (s * per_chunk) >> 16 == s / chunks for the few steps s there are
+};
+__host__ __device__ inline SplitWalk split_walk(int n_bins) {
+  SplitWalk w;
+  w.lane_bits = n_bins <= 16 ? 4 : (n_bins <= 32 ? 5 : 6);
+  w.rows = 64 >> w.lane_bits;
+  w.chunks = (n_bins + 63) / 64;
+  w.per_chunk = 65536 / w.chunks + 1;
+  return w;
+}
+// features per group at most: what fits the local memory budget
+constexpr int kSplitMaxGroup = 16;
+inline int split_max_group(int n_bins) {
+  int cap = kSplitLdsBudget / split_feature_bytes(n_bins);
+  if (cap > kSplitMaxGroup) cap = kSplitMaxGroup;
+  const SplitWalk w = split_walk(n_bins);
+  constexpr int most = kSplitSteps * (kSplitThreads / 64);
+  if (cap > most / w.chunks * w.rows) cap = most / w.chunks * w.rows;
+  return cap < 1 ? 1 : cap;
+}
+// steps a wavefront takes of a group
+inline int split_steps(int n_bins, int group) {
+  const SplitWalk w = split_walk(n_bins);
+  return ((group + w.rows - 1) / w.rows * w.chunks + kSplitThreads / 64 - 1) / (kSplitThreads / 64);
+}
 
 // Arg-max over the threads of a workgroup under the order "larger gain, then smaller index"
 // (index < 0: no candidate): exchanges inside each wavefront, then the four wavefront
@@ -136,7 +161,9 @@ __device__ __forceinline__ void block_argmax(double& gain, int32_t& idx, double*
 //     the order "larger gain, then smaller feature, then smaller bin".
 // Feature totals are the prefix at the last bin, right = total - left, a threshold is
 // admissible when both sides hold >= 1 sample and >= min_child_hess of hessian.
-// and keeps the best pair over its groups in registers.
+// and keeps the best pair over its groups in registers.  (Requesting the rows of the next group before
+// the prefix sums of the present one costs more registers than the wait is worth: 165 instead of 95, two
+// workgroups per CU fewer, 64 histograms of 2,000 x 63 bins in 66 us instead of 50.)
 //  4. The workgroup that finishes last for its histogram (a ticket taken after its own
 //     candidate is written and fenced; nobody waits) reduces the candidates of all
 //     workgroups to the histogram's split record: workgroups hold ascending feature
@@ -151,129 +178,187 @@ __device__ __forceinline__ void block_argmax(double& gain, int32_t& idx, double*
 // element as hist_subtract_kernel does it, as (pool histogram parent_slot[j]) - (histogram j of
 // the call, the built child), written to its place and searched in the same pass: every
 // (feature, bin) is read by exactly one workgroup, which also writes the difference.
-constexpr int kSplitSiblings = 32;
+constexpr int kSplitSiblings = 512;
 struct SplitSiblings {
   const gbdt_bin_t* pool;  // histograms of hist_elems bins each
   int32_t first, n;
   int32_t parent_slot[kSplitSiblings];
 };
+struct NoSiblings {};  // (a launch without siblings does not carry the table)
 
+// STEPS: register rows for the steps of a wavefront (4 or kSplitSteps; groups of few steps leave more
+// workgroups room on a CU).  MANY: a launch of more workgroups than the machine holds at once, where
+// workgroups per CU count more than one workgroup's time.  SIB: SplitSiblings or NoSiblings.
+template <int STEPS, bool MANY, typename SIB>
 __global__ void __launch_bounds__(kSplitThreads)
 split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
                   int32_t n_bins, int32_t group, int32_t passes, double lambda, double min_child_hess,
                   SplitCand* __restrict__ cand, gbdt_split_t* __restrict__ out,
-                  gbdt_split_t* __restrict__ mirror, SplitSiblings sib) {
+                  gbdt_split_t* __restrict__ mirror, SIB sib) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double s_gain[kSplitThreads / 64];
   __shared__ int32_t s_pair[kSplitThreads / 64];
   __shared__ int s_last;
-  const int tid = threadIdx.x;
-  const int32_t sib_j = (int32_t)blockIdx.y - sib.first;
-  const bool is_sib = sib_j >= 0 && sib_j < sib.n;
-  const gbdt_bin_t* built = hist + (int64_t)(is_sib ? sib_j : 0) * hist_stride;  // the sibling's built twin
-  const gbdt_bin_t* sib_parent = is_sib ? sib.pool + (int64_t)sib.parent_slot[sib_j] * hist_stride : nullptr;
+  constexpr int kWaves = kSplitThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  bool is_sib = false;
+  const gbdt_bin_t *built = nullptr, *sib_parent = nullptr;  // the sibling's built twin, and their parent
+  if constexpr (std::is_same_v<SIB, SplitSiblings>) {
+    const int32_t sib_j = (int32_t)blockIdx.y - sib.first;
+    is_sib = sib_j >= 0 && sib_j < sib.n;
+    if (is_sib) {
+      built = hist + (int64_t)sib_j * hist_stride;
+      sib_parent = sib.pool + (int64_t)sib.parent_slot[sib_j] * hist_stride;
+    }
+  }
   hist += (int64_t)blockIdx.y * hist_stride;
   cand += (size_t)blockIdx.y * gridDim.x;
   out += blockIdx.y;
   const int B = n_bins;
   const int Bp = split_padded_bins(B);
-  // layout (doubles): pg[group][Bp] | ph[group][Bp] | pn[group][Bp] | parent[group]
+  const int S = split_row(B);
+  // layout (doubles): pg[group][S] | ph[group][S] | pn[group][S] | parent[group]
   double* pg = reinterpret_cast<double*>(smem);
-  double* ph = pg + (size_t)group * Bp;
-  double* pn = ph + (size_t)group * Bp;
-  double* parent = pn + (size_t)group * Bp;
+  double* ph = pg + (size_t)group * S;
+  double* pn = ph + (size_t)group * S;
+  double* parent = pn + (size_t)group * S;
+
+  const SplitWalk walk = split_walk(B);
+  const int row_lane = lane >> walk.lane_bits;               // row of the step
+  const int bin_lane = lane & ((1 << walk.lane_bits) - 1);   // bin inside the step's chunk
+  // step i of this wavefront: (first row, first bin); rows are dealt over the wavefronts step by step
+  auto step_at = [&](int i, int& row0, int& bin0) {
+    const int s = i * kWaves + wave;
+    const int r = (s * walk.per_chunk) >> 16;
+    row0 = r * walk.rows;
+    bin0 = (s - r * walk.chunks) * 64;
+  };
+  // this lane's place relative to its step's first row and bin (the rest is uniform): in a histogram, in LDS
+  const uint32_t lane_bin = (uint32_t)(row_lane * B + bin_lane);
+  const int lane_cell = row_lane * S + bin_lane;
 
   // The workgroup takes `passes` groups of `group` consecutive features one after the other and
   // keeps, per thread, the best pair seen so far with everything the record needs: one
   // candidate and one ticket per workgroup, however many features it looked at.
   const int32_t f_first = (int32_t)blockIdx.x * passes * group;
+  gbdt_bin_t held[STEPS], held_parent[STEPS];
+  auto request = [&](int32_t f0, int32_t nf) {
+    const gbdt_bin_t* src = (is_sib ? built : hist) + (size_t)f0 * B;
+    const gbdt_bin_t* src_parent = is_sib ? sib_parent + (size_t)f0 * B : nullptr;
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      int row0, bin0;
+      step_at(i, row0, bin0);
+      gbdt_bin_t v = {0.0f, 0.0f, 0u}, q = {0.0f, 0.0f, 0u};
+      if (row0 + row_lane < nf && bin0 + bin_lane < B) {
+        v = (src + (row0 * B + bin0))[lane_bin];
+        if (is_sib) q = (src_parent + (row0 * B + bin0))[lane_bin];
+      }
+      held[i] = v;
+      held_parent[i] = q;
+    }
+  };
+  auto features_of = [&](int32_t f0) { return n_features - f0 < group ? n_features - f0 : group; };
+
   double best_gain = 0.0;
   int32_t best_pair = -1;  // (feature - f_first) * (B - 1) + bin, ascending in (feature, bin)
   double best_gl = 0.0, best_hl = 0.0, best_nl = 0.0, best_g = 0.0, best_h = 0.0, best_n = 0.0;
   for (int32_t pass = 0; pass < passes; ++pass) {
     const int32_t f0 = f_first + pass * group;
     if (f0 >= n_features) break;  // (the same for every thread)
-    const int32_t nf = (n_features - f0 < group) ? (n_features - f0) : group;
+    const int32_t nf = features_of(f0);
     if (pass > 0) __syncthreads();  // the sums of the group before are no longer needed
 
     // 1. every bin's (gradient, hessian, count) as doubles (all exact), zeros in the padding
-    for (int e = tid; e < nf * Bp; e += kSplitThreads) {
-      const int fl = e / Bp;
-      const int b = e - fl * Bp;
-      gbdt_bin_t v = {0.0f, 0.0f, 0u};
-      if (b < B) {
-        const size_t at = (size_t)(f0 + fl) * B + b;
+    request(f0, nf);
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      int row0, bin0;
+      step_at(i, row0, bin0);
+      if (row0 + row_lane < nf && bin0 + bin_lane < Bp) {
+        gbdt_bin_t v = held[i];
         if (is_sib) {
-          const gbdt_bin_t pv = sib_parent[at];
-          const gbdt_bin_t c = built[at];
-          v.grad = pv.grad - c.grad;
-          v.hess = pv.hess - c.hess;
-          v.count = pv.count - c.count;
-          hist[at] = v;
-        } else {
-          v = hist[at];
+          v.grad = held_parent[i].grad - v.grad;
+          v.hess = held_parent[i].hess - v.hess;
+          v.count = held_parent[i].count - v.count;
+          if (bin0 + bin_lane < B) (hist + ((size_t)f0 * B + row0 * B + bin0))[lane_bin] = v;
         }
+        const int e = row0 * S + bin0 + lane_cell;
+        pg[e] = (double)v.grad;
+        ph[e] = (double)v.hess;
+        pn[e] = (double)v.count;
       }
-      pg[e] = (double)v.grad;
-      ph[e] = (double)v.hess;
-      pn[e] = (double)v.count;
     }
     __syncthreads();
 
     // 2. running sums in place, strictly left to right, one lane per (statistic, feature).
-    // The chain of dependent fp64 adds is the critical path (about 30 cycles a link).  Two
+    // The chain of dependent fp64 adds is the critical path of a lone histogram: there two
     // register blocks of kSplitBlock bins are used in turn, without copies: while one is added
     // and written back, the other one's values are on their way from local memory.
     if (tid < 3 * nf) {
       const int st = tid / nf;
       const int fl = tid - st * nf;
-      double* p = pg + ((size_t)st * group + fl) * Bp;
-      double va[kSplitBlock], vb[kSplitBlock];
+      double2* p = reinterpret_cast<double2*>(pg + ((size_t)st * group + fl) * S);
+      constexpr int kPairs = kSplitBlock / 2;
+      const int n_blocks = Bp / kSplitBlock;
+      double2 va[kPairs];
 #pragma unroll
-      for (int i = 0; i < kSplitBlock; ++i) va[i] = p[i];
+      for (int i = 0; i < kPairs; ++i) va[i] = p[i];
       double acc = 0.0;
-      for (int b0 = 0; b0 < Bp; b0 += 2 * kSplitBlock) {
-        const bool has_b = b0 + kSplitBlock < Bp;
-        if (has_b) {
+      auto add_block = [&](double2 (&v)[kPairs], int block) {
 #pragma unroll
-          for (int i = 0; i < kSplitBlock; ++i) vb[i] = p[b0 + kSplitBlock + i];
+        for (int i = 0; i < kPairs; ++i) {
+          v[i].x = acc + v[i].x;
+          v[i].y = v[i].x + v[i].y;
+          acc = v[i].y;
         }
 #pragma unroll
-        for (int i = 0; i < kSplitBlock; ++i) {
-          acc = acc + va[i];
-          va[i] = acc;
-        }
+        for (int i = 0; i < kPairs; ++i) p[block * kPairs + i] = v[i];
+      };
+      if constexpr (MANY) {
+        for (int k = 0; k < n_blocks; ++k) {
+          if (k > 0) {
 #pragma unroll
-        for (int i = 0; i < kSplitBlock; ++i) p[b0 + i] = va[i];
-        if (b0 + 2 * kSplitBlock < Bp) {
-#pragma unroll
-          for (int i = 0; i < kSplitBlock; ++i) va[i] = p[b0 + 2 * kSplitBlock + i];
-        }
-        if (has_b) {
-#pragma unroll
-          for (int i = 0; i < kSplitBlock; ++i) {
-            acc = acc + vb[i];
-            vb[i] = acc;
+            for (int i = 0; i < kPairs; ++i) va[i] = p[k * kPairs + i];
           }
+          add_block(va, k);
+        }
+      } else {
+        double2 vb[kPairs];
+        for (int k = 0; k < n_blocks; k += 2) {
+          const bool has_b = k + 1 < n_blocks;
+          if (has_b) {
 #pragma unroll
-          for (int i = 0; i < kSplitBlock; ++i) p[b0 + kSplitBlock + i] = vb[i];
+            for (int i = 0; i < kPairs; ++i) vb[i] = p[(k + 1) * kPairs + i];
+          }
+          add_block(va, k);
+          if (k + 2 < n_blocks) {
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) va[i] = p[(k + 2) * kPairs + i];
+          }
+          if (has_b) add_block(vb, k + 1);
         }
       }
     }
-    __syncthreads();
+    // (the sums were written by this wavefront's own lanes: 3 * group <= 64)
     if (tid < nf) {
-      const double G = pg[tid * Bp + B - 1], H = ph[tid * Bp + B - 1];
+      const double G = pg[tid * S + B - 1], H = ph[tid * S + B - 1];
       parent[tid] = __ddiv_rn(__dmul_rn(G, G), H + lambda);
     }
     __syncthreads();
 
     // 3. the gains of this group's (feature, threshold) pairs
-    const int n_pairs = nf * (B - 1);
-    for (int e = tid; e < n_pairs; e += kSplitThreads) {
-      const int fl = e / (B - 1);
-      const int t = e - fl * (B - 1);
-      const double GL = pg[fl * Bp + t], HL = ph[fl * Bp + t], NL = pn[fl * Bp + t];
-      const double G = pg[fl * Bp + B - 1], H = ph[fl * Bp + B - 1], N = pn[fl * Bp + B - 1];
+#pragma unroll 1
+    for (int i = 0; i < STEPS; ++i) {
+      int row0, bin0;
+      step_at(i, row0, bin0);
+      if (row0 >= nf) break;  // (the same for the whole wavefront)
+      const int fl = row0 + row_lane, t = bin0 + bin_lane;
+      if (fl >= nf || t >= B - 1) continue;
+      const int e = row0 * S + bin0 + lane_cell, last = fl * S + B - 1;
+      const double GL = pg[e], HL = ph[e], NL = pn[e];
+      const double G = pg[last], H = ph[last], N = pn[last];
       const double GR = G - GL, HR = H - HL;
       const double NR = N - NL;  // counts are exact in fp64
       const bool ok = NL >= 1.0 && NR >= 1.0 && HL >= min_child_hess && HR >= min_child_hess;
@@ -346,39 +431,41 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
 
   // ---- the histogram's last workgroup: arg-max over all candidates.  Each thread folds
   // a strided subset in ascending order, then a tree reduction.
+  // (A candidate's words are all requested at once and the winner's owner writes the record: one round
+  // trip to the other workgroups' results instead of three.)
   const int32_t n_cand = (int32_t)gridDim.x;
   double bg = 0.0;
   int32_t bi = -1;
+  SplitCand mine;
+  mine.feature = -1;
   for (int32_t i = tid; i < n_cand; i += kSplitThreads) {
-    if (load_cand_feature(cand + i) >= 0) {
-      const double g = load_cand_gain(cand + i);
-      if (bi < 0 || g > bg) {  // i ascends, so ties keep the smaller feature
-        bg = g;
-        bi = i;
-      }
+    const SplitCand c = load_cand(cand + i);
+    if (c.feature >= 0 && (bi < 0 || c.gain > bg)) {  // i ascends, so ties keep the smaller feature
+      bg = c.gain;
+      bi = i;
+      mine = c;
     }
   }
+  const int32_t my_cand = bi;
   block_argmax(bg, bi, s_gain, s_pair);
-  if (tid == 0) {
+  if (bi < 0 ? tid == 0 : my_cand == bi) {
     gbdt_split_t r;
-    const int32_t i = bi;
-    if (i < 0) {
+    if (bi < 0) {
       r.feature = -1;
       r.bin = -1;
       r.gain = 0.0f;
       r.left_grad = r.left_hess = r.right_grad = r.right_hess = 0.0f;
       r.left_count = r.right_count = 0;
     } else {
-      const SplitCand c = load_cand(cand + i);
-      r.feature = c.feature;
-      r.bin = c.bin;
-      r.gain = (float)c.gain;
-      r.left_grad = (float)c.gl;
-      r.left_hess = (float)c.hl;
-      r.left_count = c.nl;
-      r.right_grad = (float)c.gr;
-      r.right_hess = (float)c.hr;
-      r.right_count = c.nr;
+      r.feature = mine.feature;
+      r.bin = mine.bin;
+      r.gain = (float)mine.gain;
+      r.left_grad = (float)mine.gl;
+      r.left_hess = (float)mine.hl;
+      r.left_count = mine.nl;
+      r.right_grad = (float)mine.gr;
+      r.right_hess = (float)mine.hr;
+      r.right_count = mine.nr;
     }
     *out = r;
     if (mirror) mirror[blockIdx.y] = r;
