@@ -12,23 +12,87 @@ constexpr int kBatchLeaves = 224;  // leaves per launch: the table travels as ke
 struct BatchLeaf {
   uint32_t row_off;   // first entry of the leaf's row list
   uint32_t n;         // its length
-  uint32_t first_wg;  // workgroups per tile of all earlier leaves of the launch
-  uint32_t wgs_unit;  // workgroups per tile | epochs per unit << 16
+  uint32_t first_wg;  // workgroups per tile of all earlier leaves of the table
+  uint32_t packed;    // workgroups per tile | epochs per unit << 16 | number of the leaf in the call's launch << 24
 };
+GBDT_HD uint32_t batch_leaf_pack(uint32_t wgs, uint32_t unit_epochs, uint32_t leaf) {
+  return wgs | (unit_epochs << 16) | (leaf << 24);
+}
+GBDT_HD uint32_t batch_wgs(const BatchLeaf& l) { return l.packed & 0xffffu; }
+GBDT_HD uint32_t batch_unit_epochs(const BatchLeaf& l) { return (l.packed >> 16) & 0xffu; }
+GBDT_HD uint32_t batch_leaf_no(const BatchLeaf& l) { return l.packed >> 24; }
+static_assert(kBatchLeaves <= 256, "a leaf's number has 8 bits");
+
+// Blocks of a launch with `cols` workgroup columns (one workgroup of every tile): block ->
+// (tile, column).  Workgroups that read the same cache lines -- the tiles of one line of the
+// matrix, same column and so the same rows at the same time -- are kept on one XCD, whose L2 then
+// fetches the line once.  Consecutive blocks go to the 8 XCDs in turn, so eight (line, column)
+// pairs are dealt out at a time and their tiles follow one another 8 blocks apart; the
+// pairs left over (fewer than 8) come last.  In a batched launch pairs are numbered column after
+// column, so that blocks start in the order of the columns, the longest first; a single leaf's blocks
+// all start at once, and there a line's columns are numbered through, so that (with a multiple
+// of 8 columns) the lines of a column, which read the same gradients and hessians, share an XCD too.
+constexpr uint32_t kXcds = 8;
+struct LineBlock {
+  int32_t tile;
+  uint32_t col;
+};
+GBDT_HD void line_deal(uint32_t b, uint32_t n_pairs, uint32_t tiles, uint32_t* pair, uint32_t* tile) {
+  const uint32_t dealt = n_pairs / kXcds * kXcds;
+  if (b < dealt * tiles) {
+    const uint32_t i = b / kXcds;
+    *pair = i / tiles * kXcds + b % kXcds;
+    *tile = i % tiles;
+  } else {
+    const uint32_t r = b - dealt * tiles, rest = n_pairs - dealt;
+    *pair = dealt + r % rest;
+    *tile = r / rest;
+  }
+}
+GBDT_HD LineBlock line_block(int32_t n_main, int32_t wr, int32_t line_tiles, uint32_t cols, bool by_column,
+                             uint32_t b) {
+  LineBlock r;
+  if (n_main + (wr ? 1 : 0) == 1) {
+    r.tile = 0;
+    r.col = b;
+    return r;
+  }
+  if (line_tiles == 1) {  // a region per tile: neighbouring blocks take different tiles
+    const uint32_t main_blocks = (uint32_t)n_main * cols;
+    r.tile = b < main_blocks ? (int32_t)(b % (uint32_t)n_main) : n_main;
+    r.col = b < main_blocks ? b / (uint32_t)n_main : b - main_blocks;
+    return r;
+  }
+  const uint32_t lines = (uint32_t)(n_main / line_tiles);
+  uint32_t pair = 0, tile = 0;
+  const uint32_t line_blocks = lines * cols * (uint32_t)line_tiles;
+  if (b < line_blocks) {
+    line_deal(b, lines * cols, (uint32_t)line_tiles, &pair, &tile);
+    const uint32_t line = by_column ? pair % lines : pair / cols;
+    r.tile = (int32_t)(line * (uint32_t)line_tiles + tile);
+    r.col = by_column ? pair / lines : pair % cols;
+    return r;
+  }
+  const uint32_t first = lines * (uint32_t)line_tiles;  // the tiles that make no whole line
+  line_deal(b - line_blocks, cols, (uint32_t)n_main - first + (wr ? 1u : 0u), &pair, &tile);
+  r.tile = (int32_t)(first + tile);
+  r.col = pair;
+  return r;
+}
 
 struct BatchBlock {
-  int32_t leaf;  // leaf of the launch
+  int32_t leaf;  // its place in the table
   int32_t tile;  // feature tile
   int32_t wg;    // workgroup of (leaf, tile)
 };
 
-// The leaf whose blocks contain block b: the last one that starts at or before it (a
-// leaf without rows has no blocks and is never the last such leaf of a live block).
-GBDT_HD int32_t batch_leaf_of(const BatchLeaf* leaf, int32_t n_leaves, uint32_t n_tiles, uint32_t b) {
+// The leaf that owns workgroup column `col`: the last one that starts at or before it (a
+// leaf without rows has no columns and is never the last such leaf of a live column).
+GBDT_HD int32_t batch_leaf_of(const BatchLeaf* leaf, int32_t n_leaves, uint32_t col) {
   int32_t lo = 0, hi = n_leaves - 1;
   while (lo < hi) {
     const int32_t mid = (lo + hi + 1) >> 1;
-    if (leaf[mid].first_wg * n_tiles <= b) {
+    if (leaf[mid].first_wg <= col) {
       lo = mid;
     } else {
       hi = mid - 1;
@@ -37,19 +101,13 @@ GBDT_HD int32_t batch_leaf_of(const BatchLeaf* leaf, int32_t n_leaves, uint32_t 
   return lo;
 }
 
-// Leaf l owns blocks [first_wg * n_tiles, (first_wg + wgs) * n_tiles), in the order of a
-// single-leaf launch: consecutive blocks take different main tiles of the same rows, the
-// remainder tile's workgroups come last.
 GBDT_HD BatchBlock batch_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t n_main, int32_t wr,
-                               uint32_t b) {
-  const uint32_t n_tiles = (uint32_t)(n_main + (wr ? 1 : 0));
+                               int32_t line_tiles, uint32_t cols, uint32_t b) {
+  const LineBlock lb = line_block(n_main, wr, line_tiles, cols, true, b);
   BatchBlock r;
-  r.leaf = batch_leaf_of(leaf, n_leaves, n_tiles, b);
-  const int32_t wgs = (int32_t)(leaf[r.leaf].wgs_unit & 0xffffu);
-  const int32_t local = (int32_t)(b - leaf[r.leaf].first_wg * n_tiles);
-  const int32_t main_blocks = n_main * wgs;
-  r.tile = local < main_blocks ? local % n_main : n_main;
-  r.wg = local < main_blocks ? local / n_main : local - main_blocks;
+  r.leaf = batch_leaf_of(leaf, n_leaves, lb.col);
+  r.tile = lb.tile;
+  r.wg = (int32_t)(lb.col - leaf[r.leaf].first_wg);
   return r;
 }
 

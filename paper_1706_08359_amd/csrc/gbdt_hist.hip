@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 #include <unordered_map>
@@ -373,6 +374,17 @@ void plan_leaf_units(int64_t n_epochs, int64_t budget, int* wgs_out, int* unit_e
   *one_unit_each_out = one_each;
 }
 
+// A leaf of more units than that: every workgroup starts with one long unit, which together hold this
+// share of the epochs, and only the rest is handed out at run time, in small units, to even out
+// the ends.  A workgroup then reads one stretch of rows for most of its life instead of a piece here and a
+// piece there, and workgroups that share cache lines stay side by side.  Measured against units of 4
+// epochs handed out from the start: categorical root (fused columns) 289 -> 258 us, dense_wide root with a
+// region per tile 176 -> 170 us, dense_tall root 129 -> 124 us; 85 to 98 % are within 2 % of each other, and
+// tiles that share lines want the most (dense_wide root 181 us at 85 %, 179 at 95).
+constexpr int kFirstUnitPercent = 95;
+constexpr int kTailUnitEpochs = 3;  // the fewest the pipeline's look-ahead allows
+static_assert(kTailUnitEpochs >= 3, "a unit's successor is taken in its third-last epoch");
+
 // Chooses the grid: as many workgroups per tile as fit the machine at once (they stay
 // until their tile's units are used up), and the unit size.  wg_per_cu: resident
 // workgroups per CU of the kernel variant as reported by the runtime (<= 0: estimate
@@ -579,35 +591,88 @@ size_t variant_column_words(const TilePlan& p) {
   return column_words<CAP, WM, NIB, NT>(p.n_main, p.wr);
 }
 
-// Plan of one batched launch: leaves [l0, l0 + n) of the call share the machine in
-// proportion to their epochs, at least one workgroup per tile each.
+// Plan of one batched launch: leaves [l0, l0 + n) of the call share the machine, at least one
+// workgroup per tile each, so that the launch ends early: with T the most epochs a workgroup
+// gets, leaf i takes ceil(epochs / T) workgroups per tile ("columns" of workgroups).  Either all columns
+// fit the machine at once and the launch lasts T epochs, or columns are dealt out, the longest first, as places
+// come free, and it lasts their average and half of a last one.  A column costs kBatchColumnEpochs on
+// top (clearing and draining its histograms, filling its pipeline, writing its sums), a leaf of several
+// columns the reduction pass over them: kBatchMergeEpochs of a column for every block of sums written or
+// read.  T is the cheapest of a dozen candidates around the average of one machine-full of columns.  (Shares of the machine rounded
+// down, as it was, left the largest of 64 leaves of 1.5 M x 500 x 255 bins alone with 167 epochs
+// where the average place had 92: 787 us, now 440.)
 struct BatchPlan {
-  BatchLeaf leaf[kBatchLeaves];
+  BatchLeaf leaf[kBatchLeaves];  // most epochs per workgroup first
   int n = 0;
   uint32_t total_wgs = 0;  // workgroups per tile over all leaves
 };
+constexpr double kBatchColumnEpochs = 3.0;
+constexpr double kBatchMergeEpochs = 2.0;
+constexpr double kBatchMergeLaunchEpochs = 1.5;
 
 BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t resident,
-                     int n_tiles) {
+                     int n_tiles, const uint32_t* seg_off = nullptr) {
   BatchPlan b;
   b.n = n;
+  uint32_t epochs[kBatchLeaves], most = 1;  // (leaves hold fewer than 2^31 rows)
   int64_t total_epochs = 0;
-  for (int i = 0; i < n; ++i)
-    total_epochs += (leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] + kEpochRows - 1) / kEpochRows;
+  int n_live = 0;
+  for (int i = 0; i < n; ++i) {
+    epochs[i] = (uint32_t)((leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] + kEpochRows - 1) / kEpochRows);
+    total_epochs += epochs[i];
+    if (epochs[i] > most) most = epochs[i];
+    n_live += epochs[i] > 0;
+  }
   int64_t budget = resident / n_tiles;
   if (budget < 1) budget = 1;
-  uint32_t first = 0;
+  uint32_t t = most;
+  double t_cost = 1e300;
+  auto consider = [&](uint32_t cand) {
+    int64_t columns = 0, blocks = 0;  // blocks of sums that a reduction pass moves
+    for (int i = 0; i < n; ++i) {
+      const uint32_t w = epochs[i] <= (uint32_t)kDirectEpochs ? (epochs[i] > 0) : (epochs[i] + cand - 1) / cand;
+      columns += w;
+      if (w > 1) blocks += 2 * w + 1;
+    }
+    if (columns > budget + n_live) return;  // (the bound that the scratch is sized by)
+    double cost = (double)cand + kBatchColumnEpochs;
+    if (columns > budget) {
+      const double dealt =
+          ((double)total_epochs + kBatchColumnEpochs * (double)columns) / (double)budget + 0.5 * (double)cand;
+      if (dealt > cost) cost = dealt;
+    }
+    if (blocks) cost += kBatchMergeLaunchEpochs + kBatchMergeEpochs * (double)blocks / (double)budget;
+    if (cost < t_cost) {
+      t_cost = cost;
+      t = cand;
+    }
+  };
+  consider(most);
+  const double average = (double)total_epochs / (double)budget;
+  for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
+    const double cand = std::ceil(average * factor);
+    if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
+  }
+  int order[kBatchLeaves], wgs[kBatchLeaves], unit[kBatchLeaves];
   for (int i = 0; i < n; ++i) {
-    const int64_t rows = leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i];
-    const int64_t n_epochs = (rows + kEpochRows - 1) / kEpochRows;
-    int wgs = 0, unit_epochs = 1;
     bool one_each = false;
-    if (n_epochs > 0) plan_leaf_units(n_epochs, budget * n_epochs / total_epochs, &wgs, &unit_epochs, &one_each);
-    b.leaf[i].row_off = (uint32_t)(leaf_offsets[l0 + i] - leaf_offsets[l0]);
-    b.leaf[i].n = (uint32_t)rows;
-    b.leaf[i].first_wg = first;
-    b.leaf[i].wgs_unit = (uint32_t)wgs | ((uint32_t)unit_epochs << 16);
-    first += (uint32_t)wgs;
+    wgs[i] = 0;
+    unit[i] = 1;
+    order[i] = i;
+    if (epochs[i] > 0) plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
+  }
+  std::stable_sort(order, order + n, [&](int x, int y) {
+    return (int64_t)epochs[x] * (wgs[y] > 0 ? wgs[y] : 1) > (int64_t)epochs[y] * (wgs[x] > 0 ? wgs[x] : 1);
+  });
+  uint32_t first = 0;
+  for (int k = 0; k < n; ++k) {
+    const int i = order[k];
+    b.leaf[k].row_off =
+        seg_off ? seg_off[l0 + i] : (uint32_t)(leaf_offsets[l0 + i] - leaf_offsets[l0]);
+    b.leaf[k].n = (uint32_t)(leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i]);
+    b.leaf[k].first_wg = first;
+    b.leaf[k].packed = batch_leaf_pack((uint32_t)wgs[i], (uint32_t)unit[i], (uint32_t)i);
+    first += (uint32_t)wgs[i];
   }
   b.total_wgs = first;
   return b;
@@ -812,6 +877,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   if (plan_n_tiles(p) > 65535) return GBDT_EUNSUPPORTED;
   // byte offsets inside a tile (slack included) are formed in 32 bits
   if ((n_rows + kEpochRows) * (int64_t)p.wm >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
+  const int32_t line_tiles = fused ? 1 : plan_line_tiles(p, n_rows);  // (a fused copy has a region per tile)
   void* ws = nullptr;
   uint32_t* counters = nullptr;
   bool counters_zero = false;
@@ -862,9 +928,23 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.n_leaf = n_leaf_rows;
   a.n_main = p.n_main;
   a.wr = p.wr;
+  a.line_tiles = line_tiles;
   a.wgs = g.wgs;
   a.chunks = g.wgs * g.blocks_per_wg;
   a.unit_epochs = g.unit_epochs;
+  a.first_epochs = 0;
+  if (!g.one_unit_each) {
+    const int64_t n_epochs = (n_leaf_rows + kEpochRows - 1) / kEpochRows;
+    if (g_deterministic.load()) {  // an even split: the same sums in every run, and rows stay together
+      a.unit_epochs = (int32_t)((n_epochs + g.wgs - 1) / g.wgs);
+    } else {
+      const int32_t first = (int32_t)(n_epochs * kFirstUnitPercent / 100 / g.wgs);
+      if (first >= kUnitEpochs) {
+        a.first_epochs = first;
+        a.unit_epochs = kTailUnitEpochs;
+      }
+    }
+  }
   // no counter when every workgroup has one unit anyway, or when the split must be fixed
   a.fixed_stride = (g.one_unit_each || g_deterministic.load()) ? g.wgs : 0;
   a.direct_out = (g.wgs == 1 && !fused) ? hist_out : nullptr;  // (joint histograms always take the reduction pass)
@@ -924,11 +1004,11 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   m.counters = uses_counters ? counters : nullptr;
   const int max_slots = plan_slots(p, p.wm);
   const int mx = (n_bins * max_slots + kMergeCells - 1) / kMergeCells;
-  if (merge_lanes((int64_t)mx * plan_n_tiles(p), a.chunks) == kMergeLanesWide) {
-    hipLaunchKernelGGL(hist_merge_kernel<kMergeLanesWide>, dim3(mx, plan_n_tiles(p)),
-                       dim3(kMergeCells * kMergeLanesWide), 0, s, m);
+  if (merge_parts((int64_t)mx * plan_n_tiles(p), a.chunks) == kMergePartsWide) {
+    hipLaunchKernelGGL(hist_merge_kernel<kMergePartsWide>, dim3(mx, plan_n_tiles(p)),
+                       dim3(kMergeQuads * kMergePartsWide), 0, s, m);
   } else {
-    hipLaunchKernelGGL(hist_merge_kernel<kMergeLanes>, dim3(mx, plan_n_tiles(p)), dim3(kMergeCells * kMergeLanes),
+    hipLaunchKernelGGL(hist_merge_kernel<kMergeParts>, dim3(mx, plan_n_tiles(p)), dim3(kMergeQuads * kMergeParts),
                        0, s, m);
   }
   HIP_TRY(hipGetLastError());
@@ -1183,9 +1263,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   }
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;
-    BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles);
-    if (seg_off)
-      for (int32_t i = 0; i < n; ++i) b.leaf[i].row_off = seg_off[l0 + i];
+    const BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
     BatchMergeArgs m;
     m.m.partials = (const uint32_t*)ws;
     m.m.out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -1197,7 +1275,10 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     m.m.counters = nullptr;
     m.column_words = col;
     m.blocks_per_wg = wide ? 2 : 1;
-    memcpy(m.leaf, b.leaf, sizeof m.leaf);
+    // the leaves the pass has work for: empty ones (zeros) and those of several workgroups per tile
+    int n_merge = 0;
+    for (int32_t i = 0; i < n; ++i)
+      if (batch_wgs(b.leaf[i]) != 1u) m.leaf[n_merge++] = b.leaf[i];
     if (b.total_wgs > 0) {
       BatchArgs a;
       a.packed = (const uint8_t*)bin_matrix;
@@ -1209,7 +1290,9 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_rows = n_rows;
       a.n_main = p.n_main;
       a.wr = p.wr;
+      a.line_tiles = plan_line_tiles(p, n_rows);
       a.n_leaves = n;
+      a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
       a.n_features = n_features;
       a.n_bins = n_bins;
@@ -1232,22 +1315,20 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       }
       if (rc != GBDT_OK) return rc;
     }
-    bool any_to_merge = false;  // empty leaves (zeros) or leaves of several workgroups per tile
-    for (int32_t i = 0; i < n; ++i) any_to_merge |= (b.leaf[i].wgs_unit & 0xffffu) != 1u;
-    if (!any_to_merge) continue;
+    if (n_merge == 0) continue;
     const int max_slots = plan_slots(p, p.wm);
     const int mx = (n_bins * max_slots + kMergeCells - 1) / kMergeCells;
     int32_t most_chunks = 0;
-    for (int32_t i = 0; i < n; ++i) {
-      const int32_t c = (int32_t)(b.leaf[i].wgs_unit & 0xffffu) * (wide ? 2 : 1);
+    for (int i = 0; i < n_merge; ++i) {
+      const int32_t c = (int32_t)batch_wgs(m.leaf[i]) * (wide ? 2 : 1);
       most_chunks = c > most_chunks ? c : most_chunks;
     }
-    if (merge_lanes((int64_t)mx * n_tiles * n, most_chunks) == kMergeLanesWide) {
-      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergeLanesWide>, dim3(mx, n_tiles, n),
-                         dim3(kMergeCells * kMergeLanesWide), 0, s, m);
+    if (merge_parts((int64_t)mx * n_tiles * n_merge, most_chunks) == kMergePartsWide) {
+      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergePartsWide>, dim3(mx, n_tiles, n_merge),
+                         dim3(kMergeQuads * kMergePartsWide), 0, s, m);
     } else {
-      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergeLanes>, dim3(mx, n_tiles, n),
-                         dim3(kMergeCells * kMergeLanes), 0, s, m);
+      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergeParts>, dim3(mx, n_tiles, n_merge),
+                         dim3(kMergeQuads * kMergeParts), 0, s, m);
     }
     HIP_TRY(hipGetLastError());
   }
@@ -2019,13 +2100,14 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
   const int n_tiles = plan_n_tiles(p);
   const BatchPlan b = plan_batch(leaf_offsets, 0, n_leaves, (int64_t)n_cus * wg_per_cu, n_tiles);
   for (int32_t l = 0; l < n_leaves; ++l) {
-    leaf_wgs_out[l] = (int32_t)(b.leaf[l].wgs_unit & 0xffffu);
-    leaf_unit_epochs_out[l] = (int32_t)(b.leaf[l].wgs_unit >> 16);
+    leaf_wgs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_wgs(b.leaf[l]);
+    leaf_unit_epochs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_unit_epochs(b.leaf[l]);
   }
   const int64_t blocks = (int64_t)b.total_wgs * n_tiles;
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
-    const BatchBlock k = batch_block(b.leaf, n_leaves, p.n_main, p.wr, (uint32_t)i);
-    block_out[3 * i] = k.leaf;
+    const BatchBlock k = batch_block(b.leaf, n_leaves, p.n_main, p.wr,
+                                     plan_line_tiles(p, kPlanLinesMinRows), b.total_wgs, (uint32_t)i);
+    block_out[3 * i] = (int32_t)batch_leaf_no(b.leaf[k.leaf]);
     block_out[3 * i + 1] = k.tile;
     block_out[3 * i + 2] = k.wg;
   }

@@ -31,7 +31,7 @@ pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features,
   if (q >= n_rows * lpr) return;
   const int64_t r = q / lpr;
   const int32_t j = (int32_t)(q - r * lpr);
-  const int64_t tile_off = n_rows * ((int64_t)t * plan.wm);  // t <= n_main, all earlier tiles are main
+  const TileAt at = plan_tile_at(plan.wm, plan.n_main, plan.wr, n_rows, plan_line_tiles(plan, n_rows), t);
   const uint8_t* row = src + r * (int64_t)n_features;
   uint32_t word = 0;
 #pragma unroll
@@ -48,7 +48,7 @@ pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features,
     }
     word |= v << (8 * i);
   }
-  *reinterpret_cast<uint32_t*>(dst + tile_off + r * w + 4 * j) = word;
+  *reinterpret_cast<uint32_t*>(dst + at.off + r * at.stride + 4 * j) = word;
 }
 
 // The column-major copy behind the tiles: a 64 x 64 block of the row-major matrix is read a
@@ -170,8 +170,10 @@ struct BuildArgs {
   int64_t n_leaf;
   int32_t n_main;       // main tiles
   int32_t wr;           // remainder tile width, 0 if none
+  int32_t line_tiles;   // main tiles that share a region of the matrix (tile_plan.h)
   int32_t wgs;          // workgroups per tile
   int32_t chunks;       // partial blocks per tile: wgs, or 2 * wgs with wide accumulation
+  int32_t first_epochs; // 0, or the length of every workgroup's first unit
   int32_t unit_epochs;  // consecutive epochs a workgroup takes at a time
   int32_t fixed_stride; // 0: units from the tile's counter; else unit u is followed by u + this
   gbdt_bin_t* direct_out;  // wgs == 1 only: the histogram itself, written by the build kernel
@@ -180,8 +182,13 @@ struct BuildArgs {
 };
 
 // A histogram cell is ONE 64-bit integer that carries, from the low bits up, the
-// count (10 bits), the quantised gradient sum (27 bits, signed) and the quantised
-// hessian sum (27 bits, signed).  A workgroup drains its cells after every epoch
+// quantised gradient sum (27 bits, signed, stored with a bias of 2^26 that an empty cell holds
+// already), the count (10 bits) and the quantised hessian sum (27 bits, signed).  With the bias no
+// field ever borrows from the one above it, and in this order the gradient sum is one shift-and-add
+// away from a signed word, the hessian sum one mask: 9 vector instructions a cell from the drained
+// word to the accumulators, two of them the fused multiply-adds.  (Count, gradient, hessian
+// without a bias took 11, and the 256-bin variants are bound by vector instructions as much as by
+// local memory.)  A workgroup drains its cells after every epoch
 // of kEpochRows rows, so a cell receives at most 512 additions between drains.
 constexpr int kEpochRows = 512;
 constexpr int kUnitEpochs = 4;  // consecutive epochs a workgroup takes from its group's counter (>= 3)
@@ -189,6 +196,8 @@ constexpr int kCountBits = 10;
 constexpr int kSumBits = 27;
 static_assert(kEpochRows < (1 << kCountBits), "an epoch's count must fit its field");
 static_assert(kCountBits + 2 * kSumBits == 64, "the three fields fill the cell");
+constexpr int kSumPad = 32 - kSumBits;  // a sum in the upper bits of a signed word is 2^kSumPad times itself
+constexpr unsigned long long kEmptyCell = 1ull << (kSumBits - 1);
 
 // Power-of-two scale 2^k for quantising the values of one epoch to integers: the
 // largest k with 2^k * m + kEpochRows / 2 (rounding slack) < 2^26, so that no cell's
@@ -327,14 +336,14 @@ struct TileShape {
 //
 // All wavefronts of a workgroup share ONE histogram; no replica has to be reduced.
 template <int CAP, int W, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE = false>
-__device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
+__device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uint32_t row_stride,
                                            const int32_t* __restrict__ idx,
                                            const float* __restrict__ grad,
-                                           const float* __restrict__ hess, bool stats_by_pos,
+                                           const float* __restrict__ hess, bool stats_by_pos, bool paced,
                                            uint32_t end,
-                                           uint32_t first_unit, uint32_t unit_epochs,
+                                           uint32_t first_unit, uint32_t first_epochs, uint32_t unit_epochs,
                                            uint32_t fixed_stride, uint32_t* counter,
-                                           uint32_t counter_base, unsigned long long* lds,
+                                           uint32_t counter_base, uint32_t n_firsts, unsigned long long* lds,
                                            uint32_t* __restrict__ out, const DirectOut& direct,
                                            uint32_t* __restrict__ out_lo = nullptr) {
   static_assert(!WIDE || sizeof(ACC) == 8, "wide cells are drained into fp64 accumulators");
@@ -344,6 +353,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   constexpr int NTBL = LPR == 8 ? 1 : 2;  // LPR 4: two byte-words share a page of 32 slots
 
   char* cells = reinterpret_cast<char*>(lds);
+  constexpr unsigned long long kEmpty = WIDE ? 0ull : kEmptyCell;
   constexpr int NCELLARR = WIDE ? 2 : 1;  // wide: gradient cells, then hessian cells
   float* red = reinterpret_cast<float*>(lds + NCELLARR * CELLS);  // [2 parities][2 stats][NW]
   uint32_t* unit_box = reinterpret_cast<uint32_t*>(red + 4 * NW);  // the unit just taken from the counter
@@ -371,7 +381,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   }
 
 #pragma unroll
-  for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = 0ull;
+  for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = kEmpty;
   ACC acc_g[PP], acc_h[PP];
   uint32_t acc_c[PP];
 #pragma unroll
@@ -392,8 +402,8 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   };
   // lanes 0..7 fetch the wave sums of |g|, lanes 8..15 those of |h|; the two totals are
   // moved to scalar registers and turned into exponents there
-  auto read_scales = [&](int parity, int& kg, int& kh) {
-    float v = red[parity * 2 * NW + (lane & (2 * NW - 1))];
+  auto request_scales = [&](int parity) { return red[parity * 2 * NW + (lane & (2 * NW - 1))]; };
+  auto scales_from = [&](float v, int& kg, int& kh) {
     v = sum_in_8(v) * 1.001953125f;
     kg = epoch_scale_exp(__builtin_amdgcn_readlane(__float_as_uint(v), 0));
     kh = epoch_scale_exp(__builtin_amdgcn_readlane(__float_as_uint(v), 8));
@@ -435,27 +445,29 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   };
 
   // Bins of one row group.  Without an index list the rows of an epoch are
-  // consecutive, so group gi sits gi * RPW * W bytes behind group 0 (an immediate
-  // offset of the load) and rows past the chunk end are simply read: they lie inside
-  // the matrix or its slack and their addend is zero.  With an index list the row id
-  // comes from the row's owner.
+  // consecutive, so group gi sits gi * RPW rows behind group 0 (added to the uniform
+  // base) and rows past the chunk end are simply read: they lie inside
+  // the matrix, its slack or the columns behind it, and their addend is zero.  With an index list the
+  // row's byte offset (`rows`) comes from the row's owner.
   constexpr int GPE = S::GPE;
   auto load_group = [&](uint4& w, uint32_t rows, uint32_t off0, auto gi_tag) {
     constexpr int gi = decltype(gi_tag)::value;
-    uint32_t off;  // 32-bit byte offsets ((n_rows + slack) * W < 2^32)
+    uint32_t off;  // 32-bit byte offsets ((n_rows + slack) * row_stride < 2^32)
+    const uint8_t* base = tile;
     if (INDEXED) {
-      off = from_owner(rows, gi_tag) * (uint32_t)W + (uint32_t)(VEC * j);
+      off = from_owner(rows, gi_tag) + (uint32_t)(VEC * j);
     } else {
-      off = off0 + (uint32_t)(gi * RPW * W);
+      off = off0;
+      base += (uint32_t)(gi * RPW) * row_stride;
     }
     if (NWORD == 4) {
-      w = *reinterpret_cast<const uint4*>(tile + off);
+      w = *reinterpret_cast<const uint4*>(base + off);
     } else if (NWORD == 2) {
-      const uint2 v = *reinterpret_cast<const uint2*>(tile + off);
+      const uint2 v = *reinterpret_cast<const uint2*>(base + off);
       w.x = v.x;
       w.y = v.y;
     } else {
-      w.x = *reinterpret_cast<const uint32_t*>(tile + off);
+      w.x = *reinterpret_cast<const uint32_t*>(base + off);
     }
   };
   // lo, hi: the addend of the row this lane owns (zero for a row past the chunk end); wide:
@@ -498,9 +510,10 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   // (an epoch past the leaf is read at the leaf's last epoch: in range, and ignored)
   const uint32_t n_epochs_leaf = (end + kEpochRows - 1) / kEpochRows;
   const uint32_t past = n_epochs_leaf * (uint32_t)kEpochRows;  // position of "no epoch"
+  const uint32_t lane_offset = (uint32_t)rho * row_stride + (uint32_t)(VEC * j);
   auto group_offset0 = [&](uint32_t e0) {
     const uint32_t e = e0 < past ? e0 : past - (uint32_t)kEpochRows;
-    return (e + (uint32_t)wave * 64u + (uint32_t)rho) * (uint32_t)W + (uint32_t)(VEC * j);
+    return (e + (uint32_t)wave * 64u) * row_stride + lane_offset;
   };
   // The bins of all row groups of one epoch, requested in group order.  (The scheduling
   // barriers keep that order: the epoch loop waits for group gi with "at most GPE + 1
@@ -508,9 +521,10 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   // issued in the order the loop re-issues them.)
   auto load_epoch = [&](uint4 (&w)[GPE], uint32_t rows, uint32_t e0) {
     const uint32_t off0 = group_offset0(e0);
+    const uint32_t row_off = rows * row_stride;
     auto step = [&](auto gi_tag) {
       constexpr int gi = decltype(gi_tag)::value;
-      load_group(w[gi], rows, off0, gi_tag);
+      load_group(w[gi], row_off, off0, gi_tag);
       __builtin_amdgcn_sched_barrier(0);
     };
     step(std::integral_constant<int, 0>{});
@@ -524,29 +538,25 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
       step(std::integral_constant<int, 7>{});
     }
   };
-  // Moves the sums of cell m into this thread's accumulators and clears it.
-  auto drain_cell = [&](int m, float inv_g, float inv_h, double inv_gw, double inv_hw) {
+  // Takes the sums of a cell out of local memory (read and clear in one operation) ...
+  auto request_cell = [&](int i) {
+    return __hip_atomic_exchange(&lds[i], kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  // ... and adds them to this thread's accumulators of its cell m (wide: th = the hessian cell).
+  auto drain_cell = [&](int m, unsigned long long t, unsigned long long th, float inv_g, float inv_h,
+                        double inv_gw, double inv_hw) {
     if constexpr (WIDE) {
-      const unsigned long long tg = __hip_atomic_exchange(&lds[tid + m * NT], 0ull, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_WORKGROUP);
-      const unsigned long long th = __hip_atomic_exchange(&lds[CELLS + tid + m * NT], 0ull, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_WORKGROUP);
       // the count sits below the gradient sum; an arithmetic shift drops it whatever the sign
-      acc_c[m] += (uint32_t)tg & ((1u << kCountBits) - 1u);
-      acc_g[m] = (ACC)fma((double)((long long)tg >> kCountBits), inv_gw, (double)acc_g[m]);
+      acc_c[m] += (uint32_t)t & ((1u << kCountBits) - 1u);
+      acc_g[m] = (ACC)fma((double)((long long)t >> kCountBits), inv_gw, (double)acc_g[m]);
       acc_h[m] = (ACC)fma((double)((long long)th >> kCountBits), inv_hw, (double)acc_h[m]);
       return;
     }
-    // read and clear in one LDS operation
-    const unsigned long long t = __hip_atomic_exchange(&lds[tid + m * NT], 0ull, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
     const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
-    const uint32_t c = tlo & ((1u << kCountBits) - 1u);
-    // bits 10..36: the gradient sum, sign-extended; the hessian sum sits above a
-    // borrow of one when the gradient sum is negative
-    const uint32_t mid = (thi << (32 - kCountBits)) | (tlo >> kCountBits);
-    const int32_t gs = (int32_t)(mid << (32 - kSumBits)) >> (32 - kSumBits);
-    const int32_t hs = ((int32_t)thi >> (kCountBits + kSumBits - 32)) + (int32_t)((mid >> (kSumBits - 1)) & 1u);
+    // both sums in the upper bits of a word, times 2^kSumPad (the scales inv_g, inv_h allow for it)
+    const int32_t gs = (int32_t)((tlo << kSumPad) + 0x80000000u);
+    const int32_t hs = (int32_t)(thi & ~((1u << kSumPad) - 1u));
+    const uint32_t c = (uint32_t)(t >> kSumBits) & ((1u << kCountBits) - 1u);
     // integer * power of two + accumulator, rounded once
     if (sizeof(ACC) == 8) {
       acc_g[m] = (ACC)fma((double)gs, (double)inv_g, (double)acc_g[m]);
@@ -564,10 +574,11 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   auto add_and_reload = [&](uint4 (&w)[GPE], uint32_t lo, uint32_t hi, uint32_t lo2, uint32_t hi2,
                             uint32_t rows_nxt, uint32_t e0_nxt) {
     const uint32_t off0 = group_offset0(e0_nxt);
+    const uint32_t row_off = rows_nxt * row_stride;
     auto step = [&](auto gi_tag) {
       constexpr int gi = decltype(gi_tag)::value;
       add_group(w[gi], lo, hi, lo2, hi2, gi_tag);
-      load_group(w[gi], rows_nxt, off0, gi_tag);
+      load_group(w[gi], row_off, off0, gi_tag);
     };
     step(std::integral_constant<int, 0>{});
     step(std::integral_constant<int, 1>{});
@@ -598,27 +609,33 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
   // u + fixed_stride.  The grouping of epochs into partial sums is then the same in
   // every run, and so is every bit of the result.
   struct Pos {
-    uint32_t row;  // first leaf position of the epoch; `past`: no epoch
-    uint32_t idx;  // its number inside its unit
+    uint32_t row;   // first leaf position of the epoch; `past`: no epoch
+    uint32_t left;  // epochs of its unit from here on
+    uint32_t unit;
   };
-  const uint32_t n_units = (n_epochs_leaf + unit_epochs - 1) / unit_epochs;
+  const uint32_t n_first = n_firsts * first_epochs;  // epochs in the long first units
+  const uint32_t n_units = n_first >= n_epochs_leaf
+                               ? n_firsts : n_firsts + (n_epochs_leaf - n_first + unit_epochs - 1) / unit_epochs;
   uint32_t next_unit = n_units;  // the unit taken from the counter (n_units or more: none)
   auto unit_first = [&](uint32_t u) {
     Pos r;
-    r.row = u < n_units ? u * unit_epochs * (uint32_t)kEpochRows : past;
-    r.idx = 0;
+    const uint32_t e = u < n_firsts ? u * first_epochs : n_first + (u - n_firsts) * unit_epochs;
+    r.row = u < n_units && e < n_epochs_leaf ? e * (uint32_t)kEpochRows : past;
+    r.left = u < n_firsts ? first_epochs : unit_epochs;
+    r.unit = u;
     return r;
   };
   auto after = [&](Pos x) {  // the epoch after x in this workgroup's sequence
     if (x.row >= past) return x;
     Pos r;
     r.row = x.row + kEpochRows;
-    r.idx = x.idx + 1;
+    r.left = x.left - 1;
+    r.unit = x.unit;
     // the leaf may end inside its last unit
-    if (r.idx == unit_epochs || r.row >= past) {
+    if (r.left == 0 || r.row >= past) {
       // The taken unit is used up: until the next take arrives there is no further unit
       // (only the leaf's short last unit can end before that, and nothing follows it).
-      r = unit_first(next_unit);
+      r = unit_first(fixed_stride ? x.unit + fixed_stride : next_unit);
       next_unit = n_units;
     }
     return r;
@@ -640,25 +657,20 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
     reduce_abs(ok ? fabsf(g_cur) : 0.0f, ok ? fabsf(h_cur) : 0.0f, 0);
   }
   __syncthreads();  // also orders the LDS clearing before the first atomics
-  read_scales(0, kg, kh);
+  scales_from(request_scales(0), kg, kh);
 
   uint32_t parity = 0;
   while (p0.row < end) {  // uniform over the workgroup
-    const bool enters_unit = p0.idx == 0;
+    const bool takes = !fixed_stride && p0.left == 3;
     uint32_t taken = 0;
-    if (enters_unit) {
-      if (fixed_stride) {
-        taken = p0.row / (unit_epochs * (uint32_t)kEpochRows) + fixed_stride;
-      } else if (tid == 0) {
-        taken = counter_base + __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    if (takes && tid == 0)
+      taken = counter_base + __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // ---- requests for later epochs
     const uint32_t row_nn = load_row_id(p2.row);
     const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
     const float g_nxt = load_stat(grad, stat_nxt);
     const float h_nxt = load_stat(hess, stat_nxt);
-    // ---- this lane's row -> 64-bit addend 1 + gq * 2^10 + hq * 2^37 (two's complement)
+    // ---- this lane's row -> 64-bit addend gq + 2^27 + hq * 2^37 (two's complement)
     //      (wide: 1 + gq * 2^10 into the gradient cell, hq * 2^10 into the hessian cell)
     uint32_t lo, hi, lo2 = 0u, hi2 = 0u;
     if constexpr (WIDE) {
@@ -674,8 +686,8 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
     } else {
       const int32_t gq = __float2int_rn(g_cur * pow2f(kg));
       const int32_t hq = __float2int_rn(h_cur * pow2f(kh));
-      lo = ((uint32_t)gq << kCountBits) + 1u;
-      hi = (uint32_t)(gq >> (32 - kCountBits)) + ((uint32_t)hq << (kCountBits + kSumBits - 32));
+      lo = (uint32_t)gq + (1u << kSumBits);  // (|gq| < 2^26: the sum is positive)
+      hi = (uint32_t)hq << (kCountBits + kSumBits - 32);
       const bool ok = own_valid(p0.row);
       lo = ok ? lo : 0u;
       hi = ok ? hi : 0u;
@@ -692,19 +704,33 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile,
       const bool ok = own_valid(p1.row);
       reduce_abs(ok ? fabsf(g_nxt) : 0.0f, ok ? fabsf(h_nxt) : 0.0f, (int)parity);
     }
-    if (enters_unit && !fixed_stride && tid == 0) unit_box[0] = taken;
+    if (takes && tid == 0) unit_box[0] = taken;
+    // Workgroups that share cache lines (tile_plan.h) drift apart if nothing holds them together, and a
+    // line is then fetched twice.  Waiting here for half of the next epoch's bins lets a workgroup that runs
+    // ahead, whose requests miss, be caught up by the one whose requests hit.
+    if (paced) __builtin_amdgcn_s_waitcnt(GPE == 8 ? 0x0f74 : 0x0f72);  // vmcnt(GPE / 2)
     __syncthreads();  // all atomics of the epoch have landed
 
     // ---- drain: integer sums -> registers, clear the cells for the next epoch
-    const float inv_g = pow2f(-kg), inv_h = pow2f(-kh);
+    const float inv_g = pow2f(-kg) * (1.0f / (1 << kSumPad)), inv_h = pow2f(-kh) * (1.0f / (1 << kSumPad));
     const double inv_gw = pow2d(-kg - kWideShift), inv_hw = pow2d(-kh - kWideShift);
-    // The next epoch's scales are requested from local memory BEFORE the cells: results come
-    // back in order, so the cells can then be decoded one by one as they arrive, instead of
-    // all of them being waited for because the youngest request is needed first.
-    read_scales((int)parity, kg, kh);
-    if (enters_unit) next_unit = __builtin_amdgcn_readfirstlane(fixed_stride ? taken : unit_box[0]);
+    // All requests leave before the first answer is waited for, the next epoch's scales and the taken
+    // unit first: answers come back in order, so the cells are then decoded one by one as they
+    // arrive.  (The scheduling barrier keeps the scales' arithmetic, which the next phase needs, from
+    // being waited for between the requests.)
+    const float next_sums = request_scales((int)parity);
+    const uint32_t box = unit_box[0];
+    unsigned long long cell[PP], cell_h[WIDE ? PP : 1];
 #pragma unroll
-    for (int m = 0; m < PP; ++m) drain_cell(m, inv_g, inv_h, inv_gw, inv_hw);
+    for (int m = 0; m < PP; ++m) {
+      cell[m] = request_cell(tid + m * NT);
+      if constexpr (WIDE) cell_h[m] = request_cell(CELLS + tid + m * NT);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    scales_from(next_sums, kg, kh);
+    if (takes) next_unit = __builtin_amdgcn_readfirstlane(box);
+#pragma unroll
+    for (int m = 0; m < PP; ++m) drain_cell(m, cell[m], cell_h[WIDE ? m : 0], inv_g, inv_h, inv_gw, inv_hw);
     p0 = p1;
     p1 = p2;
     p2 = after(p2);
@@ -779,21 +805,25 @@ hist_build_kernel(BuildArgs a) {
   // reduction scratch and the unit box
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const int32_t main_blocks = a.n_main * a.wgs;
-  const int32_t b = blockIdx.x;
   const uint32_t n_leaf = (uint32_t)a.n_leaf;
-  const int32_t t = b < main_blocks ? b % a.n_main : a.n_main;         // tile
-  const int32_t c = b < main_blocks ? b / a.n_main : b - main_blocks;  // workgroup of the tile
+  const LineBlock lb = line_block(a.n_main, a.wr, a.line_tiles, (uint32_t)a.wgs, false, blockIdx.x);
+  const int32_t t = lb.tile;
+  const int32_t c = (int32_t)lb.col;  // workgroup of the tile
   uint32_t* counter = a.counters + plan_counter_slot(t);
-  const uint8_t* tile = a.packed + a.n_rows * ((int64_t)t * WM);
+  const TileAt at = plan_tile_at(WM, a.n_main, a.wr, a.n_rows, a.line_tiles, t);
+  const uint8_t* tile = a.packed + at.off;
+  const uint32_t stride = (uint32_t)at.stride;
+  const uint32_t n_firsts = a.first_epochs ? (uint32_t)a.wgs : 0u;
+  const bool paced = WM == 64 && a.line_tiles > 1;
   const DirectOut direct = {a.direct_out, t, WM, a.n_main, a.wr, a.n_features, a.n_bins};
   // wide accumulation: the workgroup's second block lies a.wgs blocks behind its first
-  if (b < main_blocks) {
+  if (t < a.n_main) {
     constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
     uint32_t* out = a.partials + ((size_t)t * a.chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, INDEXED, WIDE>(tile, a.idx, a.grad, a.hess, a.stats_by_pos != 0, n_leaf,
-                                                     (uint32_t)c, (uint32_t)a.unit_epochs,
-                                                     (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, lds,
+    build_tile<CAP, WM, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf,
+                                                     (uint32_t)c, (uint32_t)a.first_epochs,
+                                                     (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter,
+                                                     (uint32_t)a.wgs, n_firsts, lds,
                                                      out, direct, out + (size_t)a.wgs * kBlock);
   } else {
     uint32_t* rem_base =
@@ -801,14 +831,14 @@ hist_build_kernel(BuildArgs a) {
     if (a.wr == 16) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
       build_tile<CAP, 16, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, a.idx, a.grad, a.hess, a.stats_by_pos != 0, n_leaf, (uint32_t)c, (uint32_t)a.unit_epochs,
-          (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, lds, rem_base + (size_t)c * kBlock, direct,
+          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
+          (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
           rem_base + (size_t)(a.wgs + c) * kBlock);
     } else if constexpr (WM > 32) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
       build_tile<CAP, 32, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, a.idx, a.grad, a.hess, a.stats_by_pos != 0, n_leaf, (uint32_t)c, (uint32_t)a.unit_epochs,
-          (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, lds, rem_base + (size_t)c * kBlock, direct,
+          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
+          (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
           rem_base + (size_t)(a.wgs + c) * kBlock);
     }
   }
@@ -857,7 +887,9 @@ struct BatchArgs {
   int64_t n_rows;
   int32_t n_main;
   int32_t wr;
+  int32_t line_tiles;
   int32_t n_leaves;
+  uint32_t n_cols;       // workgroup columns of all leaves
   gbdt_bin_t* hist_out;  // [n_leaves][n_features][n_bins]: written directly by leaves of one workgroup per tile
   int32_t n_features;
   int32_t n_bins;
@@ -878,41 +910,44 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WP
 hist_build_batch_kernel(BatchArgs a) {
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, a.n_main, a.wr, blockIdx.x);
+  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, a.n_main, a.wr, a.line_tiles, a.n_cols, blockIdx.x);
   const BatchLeaf lf = a.leaf[blk.leaf];
-  const int32_t wgs = (int32_t)(lf.wgs_unit & 0xffffu);
-  const uint32_t unit_epochs = lf.wgs_unit >> 16;
+  const int32_t wgs = (int32_t)batch_wgs(lf);
+  const uint32_t unit_epochs = batch_unit_epochs(lf);
   constexpr int kPerWg = WIDE ? 2 : 1;  // partial blocks per workgroup
   const int32_t chunks = kPerWg * wgs;
   const int32_t t = blk.tile, c = blk.wg;
   const bool is_main = t < a.n_main;
-  const uint8_t* tile = a.packed + a.n_rows * ((int64_t)t * WM);
+  const TileAt at = plan_tile_at(WM, a.n_main, a.wr, a.n_rows, a.line_tiles, t);
+  const uint8_t* tile = a.packed + at.off;
+  const uint32_t stride = (uint32_t)at.stride;
   const int32_t* idx = a.idx + lf.row_off;
+  const bool paced = WM == 64 && a.line_tiles > 1;
   const bool by_pos = a.stats_by_pos != 0;  // then grad / hess follow the concatenated row lists
   const float* grad = by_pos ? a.grad + lf.row_off : a.grad;
   const float* hess = by_pos ? a.hess + lf.row_off : a.hess;
   uint32_t* leaf_out =
       a.partials + (size_t)lf.first_wg * kPerWg * column_words<CAP, WM, NIB, NT>(a.n_main, a.wr);
   const DirectOut direct = {
-      wgs == 1 ? a.hist_out + (size_t)blk.leaf * a.n_features * a.n_bins : nullptr,
+      wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr,
       t, WM, a.n_main, a.wr, a.n_features, a.n_bins};
   if (is_main) {
     constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
     uint32_t* out = leaf_out + ((size_t)t * chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, true, WIDE>(tile, idx, grad, hess, by_pos, lf.n, (uint32_t)c, unit_epochs,
-                                                  (uint32_t)wgs, nullptr, 0u, lds, out, direct,
+    build_tile<CAP, WM, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+                                                  (uint32_t)wgs, nullptr, 0u, 0u, lds, out, direct,
                                                   out + (size_t)wgs * kBlock);
   } else {
     uint32_t* rem_base = leaf_out + (size_t)a.n_main * chunks * (size_t)block_words<CAP, WM, NIB, NT>();
     if (a.wr == 16) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
-      build_tile<CAP, 16, NIB, NT, ACC, true, WIDE>(tile, idx, grad, hess, by_pos, lf.n, (uint32_t)c, unit_epochs,
-                                                    (uint32_t)wgs, nullptr, 0u, lds, rem_base + (size_t)c * kBlock,
+      build_tile<CAP, 16, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+                                                    (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
                                                     direct, rem_base + (size_t)(wgs + c) * kBlock);
     } else if constexpr (WM > 32) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
-      build_tile<CAP, 32, NIB, NT, ACC, true, WIDE>(tile, idx, grad, hess, by_pos, lf.n, (uint32_t)c, unit_epochs,
-                                                    (uint32_t)wgs, nullptr, 0u, lds, rem_base + (size_t)c * kBlock,
+      build_tile<CAP, 32, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+                                                    (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
                                                     direct, rem_base + (size_t)(wgs + c) * kBlock);
     }
   }

@@ -28,34 +28,29 @@ struct MergeArgs {
   uint32_t* counters;  // the tiles' unit counters, set back to zero here; NULL: not used by the build
 };
 
-constexpr int kMergeCells = 64;   // histogram cells per workgroup
-constexpr int kMergeLanes = 4;    // threads that share the chunks of one cell ...
-constexpr int kMergeLanesWide = 16;  // ... and when there are few cells and many chunks (one or two tiles built
-                                     // by hundreds of workgroups): 4 lanes would leave most of the machine idle
+constexpr int kMergeCells = 64;      // histogram cells per workgroup
+constexpr int kMergeParts = 8;       // threads that share the chunks of a cell ...
+constexpr int kMergePartsWide = 32;  // ... and when there are few cells and many chunks (one or two tiles built
+                                     // by hundreds of workgroups): 8 would leave most of the machine idle
+constexpr int kMergeQuads = kMergeCells / 4;  // a thread takes 4 neighbouring slots of a bin: 16-byte loads
 
 // The "final reduction program" of Sec. 4: sums the partial histograms of the
 // workgroups that shared a feature tile.  A workgroup takes 64 consecutive (bin,
 // slot) pairs of one tile (slot fastest, so reads of a partial block are coalesced
-// in runs of 32); 4 threads per pair each sum every 4th chunk in fp64, in chunk
-// order, and the 4 sub-sums are added in a fixed order: the result does not depend
-// on scheduling.  Counts are summed as integers.  grid.y = tile.  (LANES = 4 or 16 threads per
-// pair; which one is a function of the launch's shape only.)
-template <int LANES>
+// in runs of 32); PARTS threads per 4 pairs each sum every PARTS-th chunk in fp64, in chunk
+// order, and the sub-sums are added in a fixed order: the result does not depend
+// on scheduling.  Counts are summed as integers.  grid.y = tile.  (PARTS = 8 or 32;
+// which one is a function of the launch's shape only.)  Bound by the latency of its loads: four chunks are
+// requested together.
+template <int PARTS>
 __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
-  constexpr int kMergeLanes = LANES;
   if (a.counters && blockIdx.x == 0 && threadIdx.x == 0) a.counters[plan_counter_slot((int32_t)blockIdx.y)] = 0u;
-  __shared__ double s_g[kMergeLanes][kMergeCells];
-  __shared__ double s_h[kMergeLanes][kMergeCells];
-  __shared__ uint32_t s_n[kMergeLanes][kMergeCells];
+  __shared__ double s_g[PARTS][kMergeCells];
+  __shared__ double s_h[PARTS][kMergeCells];
+  __shared__ uint32_t s_n[PARTS][kMergeCells];
   const int32_t t = blockIdx.y;
   const int32_t w = plan_tile_width(a.plan, t);
   const int32_t slots = plan_slots(a.plan, w);
-  const int cell = threadIdx.x % kMergeCells;
-  const int part = threadIdx.x / kMergeCells;
-  const int32_t e = blockIdx.x * kMergeCells + cell;
-  const bool live = e < a.n_bins * slots;
-  const int32_t bin = live ? e / slots : 0;
-  const int32_t slot = live ? e - bin * slots : 0;
   const size_t hw = (size_t)plan_cells(a.plan, w);
   const size_t main_block = (size_t)3 * plan_cells(a.plan, a.plan.wm);
   const uint32_t* p;
@@ -67,46 +62,64 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
     p = a.partials + (size_t)a.plan.n_main * a.chunks_main * main_block;
     chunks = a.chunks_rem;
   }
-  p += (size_t)plan_cell(a.plan, bin, slot) + (size_t)part * 3 * hw;
-  double g = 0.0, h = 0.0;
-  uint32_t n = 0;
-  if (live) {
-    // Same order of additions as a plain loop over the thread's chunks; the loads of 8
-    // chunks are issued together (the loop is bound by memory latency, not by bandwidth).
-    const size_t step = (size_t)kMergeLanes * 3 * hw;
-    int32_t c = part;
-    for (; c + 7 * kMergeLanes < chunks; c += 8 * kMergeLanes) {
-      uint32_t vg[8], vh[8], vn[8];
+  const int quad = threadIdx.x % kMergeQuads;
+  const int part = threadIdx.x / kMergeQuads;
+  const int32_t e0 = blockIdx.x * kMergeCells + 4 * quad;
+  // (a bin has a multiple of 16 slots, so the four cells are one bin's, and all live or none)
+  if (e0 < a.n_bins * slots) {
+    const int32_t bin = e0 / slots;
+    const int32_t slot = e0 - bin * slots;
+    p += (size_t)plan_cell(a.plan, bin, slot) + (size_t)part * 3 * hw;
+    double g[4] = {0.0, 0.0, 0.0, 0.0}, h[4] = {0.0, 0.0, 0.0, 0.0};
+    uint32_t n[4] = {0u, 0u, 0u, 0u};
+    const size_t step = (size_t)PARTS * 3 * hw;
+    constexpr int kFlight = 4;
+    for (int32_t c = part; c < chunks; c += kFlight * PARTS) {
+      uint4 vg[kFlight], vh[kFlight], vn[kFlight];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        vg[i] = p[i * step];
-        vh[i] = p[i * step + hw];
-        vn[i] = p[i * step + 2 * hw];
+      for (int i = 0; i < kFlight; ++i) {
+        const size_t at = c + i * PARTS < chunks ? i * step : 0;  // (past the end: the first one again)
+        vg[i] = *reinterpret_cast<const uint4*>(p + at);
+        vh[i] = *reinterpret_cast<const uint4*>(p + at + hw);
+        vn[i] = *reinterpret_cast<const uint4*>(p + at + 2 * hw);
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        g += (double)__uint_as_float(vg[i]);
-        h += (double)__uint_as_float(vh[i]);
-        n += vn[i];
+      for (int i = 0; i < kFlight; ++i) {
+        if (c + i * PARTS < chunks) {
+          g[0] += (double)__uint_as_float(vg[i].x);
+          g[1] += (double)__uint_as_float(vg[i].y);
+          g[2] += (double)__uint_as_float(vg[i].z);
+          g[3] += (double)__uint_as_float(vg[i].w);
+          h[0] += (double)__uint_as_float(vh[i].x);
+          h[1] += (double)__uint_as_float(vh[i].y);
+          h[2] += (double)__uint_as_float(vh[i].z);
+          h[3] += (double)__uint_as_float(vh[i].w);
+          n[0] += vn[i].x;
+          n[1] += vn[i].y;
+          n[2] += vn[i].z;
+          n[3] += vn[i].w;
+        }
       }
-      p += 8 * step;
+      p += kFlight * step;
     }
-    for (; c < chunks; c += kMergeLanes) {
-      g += (double)__uint_as_float(p[0]);
-      h += (double)__uint_as_float(p[hw]);
-      n += p[2 * hw];
-      p += step;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s_g[part][4 * quad + k] = g[k];
+      s_h[part][4 * quad + k] = h[k];
+      s_n[part][4 * quad + k] = n[k];
     }
   }
-  s_g[part][cell] = g;
-  s_h[part][cell] = h;
-  s_n[part][cell] = n;
   __syncthreads();
-  if (part == 0 && live) {
-    const int32_t f = plan_feature_of(a.plan, t, slot);
+  const int cell = threadIdx.x;
+  const int32_t e = blockIdx.x * kMergeCells + cell;
+  if (cell < kMergeCells && e < a.n_bins * slots) {
+    const int32_t bin = e / slots;
+    const int32_t f = plan_feature_of(a.plan, t, e - bin * slots);
     if (f < a.n_features) {  // else: padding slot
+      double g = 0.0, h = 0.0;
+      uint32_t n = 0;
 #pragma unroll
-      for (int q = 1; q < kMergeLanes; ++q) {
+      for (int q = 0; q < PARTS; ++q) {
         g += s_g[q][cell];
         h += s_h[q][cell];
         n += s_n[q][cell];
@@ -120,15 +133,15 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
   }
 }
 
-template <int LANES>
-__global__ void __launch_bounds__(kMergeCells * LANES) hist_merge_kernel(MergeArgs a) {
-  merge_cells<LANES>(a);
+template <int PARTS>
+__global__ void __launch_bounds__(kMergeQuads * PARTS) hist_merge_kernel(MergeArgs a) {
+  merge_cells<PARTS>(a);
 }
 
-// Threads per (bin, slot) pair for a reduction over `blocks` workgroups of 4-lane pairs and up to
-// `chunks` partial blocks per pair.
-inline int merge_lanes(int64_t blocks, int32_t chunks) {
-  return (blocks < 512 && chunks >= 64) ? kMergeLanesWide : kMergeLanes;
+// Threads per cell for a reduction over `blocks` workgroups of 8 of them and up to
+// `chunks` partial blocks per cell.
+inline int merge_parts(int64_t blocks, int32_t chunks) {
+  return (blocks < 512 && chunks >= 64) ? kMergePartsWide : kMergeParts;
 }
 
 // The same reduction for a batched launch: grid.z = leaf of the launch; its partial
@@ -142,16 +155,16 @@ struct BatchMergeArgs {
   BatchLeaf leaf[kBatchLeaves];
 };
 
-template <int LANES>
-__global__ void __launch_bounds__(kMergeCells * LANES) hist_merge_batch_kernel(BatchMergeArgs a) {
+template <int PARTS>
+__global__ void __launch_bounds__(kMergeQuads * PARTS) hist_merge_batch_kernel(BatchMergeArgs a) {
   const BatchLeaf lf = a.leaf[blockIdx.z];
-  if ((lf.wgs_unit & 0xffffu) == 1u) return;  // written by the build kernel itself
+  if (batch_wgs(lf) == 1u) return;  // written by the build kernel itself
   MergeArgs m = a.m;
   m.partials += (size_t)lf.first_wg * a.column_words;
-  m.out += (size_t)blockIdx.z * m.n_features * m.n_bins;
-  m.chunks_main = (int32_t)(lf.wgs_unit & 0xffffu) * a.blocks_per_wg;
+  m.out += (size_t)batch_leaf_no(lf) * m.n_features * m.n_bins;
+  m.chunks_main = (int32_t)batch_wgs(lf) * a.blocks_per_wg;
   m.chunks_rem = m.plan.wr ? m.chunks_main : 0;
-  merge_cells<LANES>(m);
+  merge_cells<PARTS>(m);
 }
 
 // ----------------------------------------------------------------- unfuse kernel

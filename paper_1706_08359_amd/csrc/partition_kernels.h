@@ -65,7 +65,7 @@ struct SplitColumn {
   bool from_tiles;
   int64_t col_off;   // byte offset of the feature's column
   int64_t tile_off;  // byte offset of the feature's tile
-  int32_t w, col;    // tile width; byte of the tile row
+  int32_t w, col;    // bytes from a tile row to the next; byte of the tile row
   int32_t shift;     // 4-bit bins: the nibble
   uint32_t mask;
   int32_t thr;
@@ -90,9 +90,10 @@ __device__ __forceinline__ SplitColumn split_column(const gbdt_split_t* __restri
     const int32_t fb = plan.nib ? (f >> 1) : f;
     int32_t t = fb / plan.wm;
     if (t > plan.n_main) t = plan.n_main;
-    c.w = plan_tile_width(plan, t);
+    const TileAt at = plan_tile_at(plan.wm, plan.n_main, plan.wr, n_rows, plan_line_tiles(plan, n_rows), t);
+    c.w = at.stride;
     c.col = fb - t * plan.wm;
-    c.tile_off = n_rows * ((int64_t)t * plan.wm);
+    c.tile_off = at.off;
     if (plan.nib) {
       c.shift = (f & 1) ? 4 : 0;
       c.mask = 15u;

@@ -87,6 +87,51 @@ GBDT_HD int64_t plan_packed_bytes(const TilePlan& p, int64_t n_rows, int32_t n_f
   return plan_columns_base(p, n_rows) + (int64_t)n_features * plan_column_stride(n_rows);
 }
 
+// Lines.  Memory is fetched in lines of 128 bytes, and a tile row has 64 or 32: a leaf that is a
+// small part of the matrix fetches two or four times the bytes it uses when every tile has a region
+// of its own.  (Measured with a plain gather of listed rows: 5.8 TB/s of whole lines at any density, whether
+// 32, 64 or 128 bytes of them are used.)  So two neighbouring main tiles share a region, one after
+// the other inside a row of 128 or 64 bytes, and the build kernels run the workgroups that need the
+// same line on the same XCD at the same time (batch_plan.h): one of them fetches it, the others find it in
+// that XCD's L2.  The tiles left over (an odd main tile, the remainder tile) share a region too.
+// Build kernel, before -> now: 8,000,000 x 500 x 64 bins, 50 / 25 / 12.5 % of the rows 657 / 368 / 202 ->
+// 467 / 243 / 136 us; 2,000,000 x 500 x 255 bins, 25 / 5 % 147 / 43 -> 122 / 32 us; 400,000 x 2,000 x 63
+// bins, half of the rows 123 -> 101 us, all rows 176 -> 179 us.  (Four 32-byte tiles a line were
+// better still for sparse leaves, 107 / 32 us, but the root then fetches its lines up to four times:
+// 362 -> 413 us.)
+// Small matrices keep one region per tile: they fit the caches anyway, and the build may
+// read up to kEpochRows - 1 rows past the last one, which have to lie inside the buffer: with 128-byte
+// rows that is more than the slack, but with kPlanLinesMinRows rows and the features of two
+// tiles the columns behind it are longer still.  So do the largest, whose byte offsets in a
+// region of 128-byte rows would not fit 32 bits.
+constexpr int64_t kPlanLinesMinRows = 4096;
+constexpr int64_t kPlanLinesMaxRows = ((int64_t)1 << 25) - 1024;
+GBDT_HD int32_t plan_line_tiles(const TilePlan& p, int64_t n_rows) {  // main tiles per row of a region: 1 or 2
+  (void)p;
+  return n_rows >= kPlanLinesMinRows && n_rows <= kPlanLinesMaxRows ? 2 : 1;
+}
+struct TileAt {
+  int64_t off;     // byte offset of the tile's first row
+  int32_t stride;  // bytes from a row to the next
+};
+GBDT_HD TileAt plan_tile_at(int32_t wm, int32_t n_main, int32_t wr, int64_t n_rows, int32_t line_tiles, int32_t t) {
+  TileAt a;
+  if (line_tiles == 1) {
+    a.off = n_rows * ((int64_t)t * wm);
+    a.stride = t < n_main ? wm : wr;
+    return a;
+  }
+  const int32_t paired = n_main & ~1;  // main tiles that share a region with another main tile
+  if (t < paired) {
+    a.off = n_rows * ((int64_t)(t & ~1) * wm) + (int64_t)(t & 1) * wm;
+    a.stride = 2 * wm;
+  } else {
+    a.off = n_rows * ((int64_t)paired * wm) + (int64_t)(t - paired) * wm;
+    a.stride = (n_main - paired) * wm + wr;
+  }
+  return a;
+}
+
 GBDT_HD int32_t plan_n_tiles(const TilePlan& p) { return p.n_main + (p.wr ? 1 : 0); }
 GBDT_HD int32_t plan_tile_width(const TilePlan& p, int32_t t) { return t < p.n_main ? p.wm : p.wr; }
 // features (= slots) held by a tile of width w

@@ -1,0 +1,83 @@
+"""Feature tiles that share the rows of one region (two 64-byte or two 32-byte tiles a row, and the
+tiles that are left over together): every combination of whole lines, a lone main tile and a remainder
+tile, on both sides of the row count from which tiles share rows, built as a root, as an index list, in a
+batch with empty, short and long leaves, and partitioned by a feature of every tile.
+
+The gradients are multiples of 1/2 and the hessians of 1/4, so every sum is exact and has to agree
+with the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gbdt_oracle as orc
+from paper_1706_08359_amd import binding as B
+from tests.gpu_util import GpuProblem
+
+pytestmark = pytest.mark.gpu
+
+# features: 64 bins 1 main + remainder, 2 main, 3 main, 3 main + remainder; 255 bins the same with
+# 32-byte tiles, and one short of a whole line; 16 bins with two features a byte
+SHAPES = [(70, 64), (128, 63), (190, 64), (210, 40), (40, 255), (64, 256), (96, 200), (63, 255), (137, 255),
+          (270, 16), (385, 7)]
+ROWS = [4095, 4096, 9001]
+
+
+def problem(n_rows, n_features, n_bins, seed=5):
+    rng = np.random.default_rng(seed + n_rows + n_features)
+    bins = rng.integers(0, n_bins, size=(n_rows, n_features)).astype(np.uint8)
+    grad = (rng.integers(-2, 3, size=n_rows) * 0.5).astype(np.float32)
+    hess = (rng.integers(1, 4, size=n_rows) * 0.25).astype(np.float32)
+    return GpuProblem(bins, n_bins, grad, hess), rng
+
+
+def same(got_t, ref, what):
+    got = B.hist_to_numpy(got_t)
+    for k in ("grad", "hess", "count"):
+        assert np.array_equal(got[k].astype(np.float64), ref[k].astype(np.float64)), (what, k)
+
+
+@pytest.mark.parametrize("n_features,n_bins", SHAPES)
+@pytest.mark.parametrize("n_rows", ROWS)
+def test_lines_of_tiles(n_rows, n_features, n_bins):
+    print(f"lines {n_rows} x {n_features}, {n_bins} bins", flush=True)
+    p, rng = problem(n_rows, n_features, n_bins)
+    same(p.build(), p.oracle(), "root")
+    same(p.build(n_leaf=n_rows - 511), p.oracle(n_leaf=n_rows - 511), "first rows")
+    idx = np.sort(rng.choice(n_rows, size=n_rows // 3, replace=False)).astype(np.int32)
+    same(p.build(idx), p.oracle(idx), "list")
+    sizes = [0, 1, 513, n_rows // 2, 0, 2100]
+    perm = np.concatenate([np.sort(rng.choice(n_rows, size=s, replace=False)) for s in sizes]).astype(np.int32)
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    hists = B.gbdt_hist_build_batch(p.packed, n_rows, n_features, n_bins, torch.from_numpy(perm).to(p.dev), offs,
+                                    p.grad, p.hess)
+    for l in range(len(sizes)):
+        same(hists[l], p.oracle(perm[offs[l]:offs[l + 1]]), f"leaf {l}")
+    # the short-list partition reads the tiles: one feature of the first and last tile, one in between
+    bins = p.bins_cpu.numpy()
+    for f in (0, n_features // 2, n_features - 1):
+        rec = B.split_record(f, n_bins // 2, p.dev)
+        kids, n_left = B.gbdt_partition_rows(p.packed, n_rows, n_features, n_bins, torch.from_numpy(idx).to(p.dev),
+                                             idx.size, rec)
+        left, right = orc.partition_rows(bins, f, n_bins // 2, idx)
+        assert int(n_left.item()) == left.size
+        assert np.array_equal(kids.cpu().numpy()[:idx.size], np.concatenate([left, right])), f
+
+
+@pytest.mark.parametrize("n_features,n_bins", [(210, 63), (137, 255), (270, 16)])
+def test_long_leaf_starts_with_long_units(n_features, n_bins):
+    """Enough epochs that every workgroup starts with one long unit and takes short ones after it, with
+    rows at the very end of the leaf, in the default and in the bit-reproducible mode."""
+    n_rows = 1_200_001
+    print(f"long leaf {n_rows} x {n_features}, {n_bins} bins", flush=True)
+    p, rng = problem(n_rows, n_features, n_bins)
+    feats = [0, n_features // 2, n_features - 1]
+    ref = p.oracle(features=feats)
+    for det in (False, True):
+        B.gbdt_set_deterministic(det)
+        try:
+            got = B.hist_to_numpy(p.build())
+        finally:
+            B.gbdt_set_deterministic(False)
+        for j, f in enumerate(feats):
+            for k in ("grad", "hess", "count"):
+                assert np.array_equal(got[k][f].astype(np.float64), ref[k][j].astype(np.float64)), (det, f, k)
