@@ -223,6 +223,7 @@ constexpr int64_t kFusedMinLeafRows = 8192;
 constexpr int64_t kFusedMinLeafFraction = 3;
 // A fused copy is made when it has at most this fraction of the features as columns.
 constexpr double kFusedMaxColumnRatio = 0.85;
+constexpr int64_t kFuseSampleRows = 4096;  // rows gbdt_bins_fuse looks at before it reads them all
 
 // Packs features into columns of at most kFusedCap joint levels: features in descending order
 // of their level counts, each into the fullest column that still takes it (best fit).
@@ -1049,16 +1050,12 @@ int gbdt_bins_pack(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   const int64_t max_words = n_rows * (p.wm / 4);
   const int64_t bx = (max_words + 255) / 256;
   if (bx >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
-  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)bx, (unsigned)tiles), dim3(256), 0,
-                     (hipStream_t)stream, bins_rowmajor, n_rows, n_features, p,
-                     (uint8_t*)packed_out);
-  HIP_TRY(hipGetLastError());
-  // the column-major copy behind the tiles
-  const int64_t rb = (n_rows + 63) / 64;
-  const int32_t fb = (n_features + 63) / 64;
-  if (fb > 65535) return GBDT_EUNSUPPORTED;
-  hipLaunchKernelGGL(pack_columns_kernel, dim3((unsigned)rb, (unsigned)fb), dim3(256), 0, (hipStream_t)stream,
-                     bins_rowmajor, n_rows, n_features, p.nib ? 15u : (uint32_t)(p.cap - 1),
+  if ((n_features + 63) / 64 > 65535) return GBDT_EUNSUPPORTED;
+  const dim3 grid((unsigned)((n_rows + kPackRows - 1) / kPackRows),
+                  (unsigned)((n_features + kPackFeatures - 1) / kPackFeatures));
+  hipLaunchKernelGGL(p.nib ? pack_kernel<true> : pack_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream,
+                     bins_rowmajor, n_rows, n_features, p, plan_line_tiles(p, n_rows),
+                     (uint32_t)(p.cap - 1) * 0x01010101u, (uint8_t*)packed_out,
                      (uint8_t*)packed_out + plan_columns_base(p, n_rows), plan_column_stride(n_rows));
   HIP_TRY(hipGetLastError());
   return GBDT_OK;
@@ -1091,22 +1088,39 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   if (n_rows >= ((int64_t)1 << 30)) return GBDT_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   if (stream_is_capturing(s)) return GBDT_EUNSUPPORTED;  // this call reads results on the host
-  // 1. the largest bin value of every feature (the head of fused_out serves as scratch)
+  // 1. the largest bin value of every feature (the head of fused_out serves as scratch).  First over the
+  // first kFuseSampleRows rows: columns hold at most log2(kFusedCap) bits, so features that need more
+  // bits than kFusedMaxColumnRatio of that many columns have -- with the levels seen so far, which can
+  // only grow -- are never fused, and the rest of the matrix need not be read to know it.
   uint32_t* max_dev = (uint32_t*)fused_out;
   hipLaunchKernelGGL(counters_zero_kernel, dim3((n_features + 255) / 256), dim3(256), 0, s, max_dev, n_features);
   HIP_TRY(hipGetLastError());
-  const int64_t row_blocks = (n_rows + 255) / 256;
-  if (row_blocks >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
-  hipLaunchKernelGGL(feature_max_kernel, dim3((unsigned)row_blocks), dim3(256), 0, s, bins_rowmajor, n_rows,
-                     n_features, max_dev);
-  HIP_TRY(hipGetLastError());
+  if ((n_rows + 255) / 256 >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
   std::vector<uint32_t> levels((size_t)n_features);
-  HIP_TRY(hipMemcpyAsync(levels.data(), max_dev, levels.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  for (uint32_t& l : levels) {
-    l = l + 1;                       // bins 0 .. max occur (at most)
-    if (l > (uint32_t)n_bins) l = (uint32_t)n_bins;  // the build masks stray values to the capacity anyway
+  auto find_levels = [&](int64_t rows) -> int {
+    const int64_t stripes = (rows + 4 * 32 - 1) / (4 * 32);  // (32 rows a thread: every wavefront ends with atomics)
+    const dim3 grid((unsigned)(stripes < 1024 ? stripes : 1024),
+                    (unsigned)((n_features + kMaxFeatures - 1) / kMaxFeatures));
+    hipLaunchKernelGGL(feature_max_kernel, grid, dim3(256), 0, s, bins_rowmajor, rows, n_rows, n_features, max_dev);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(levels.data(), max_dev, levels.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    for (uint32_t& l : levels) {
+      l = l + 1;                       // bins 0 .. max occur (at most)
+      if (l > (uint32_t)n_bins) l = (uint32_t)n_bins;  // the build masks stray values to the capacity anyway
+    }
+    return GBDT_OK;
+  };
+  if (n_rows > kFuseSampleRows) {
+    const int rc = find_levels(kFuseSampleRows);
+    if (rc != GBDT_OK) return rc;
+    double bits = 0.0;
+    for (const uint32_t l : levels) bits += std::log2((double)l);
+    // (a thousandth of a bit a feature to spare for the rounding of the logarithms)
+    if (bits - 1e-3 * n_features > kFusedMaxColumnRatio * n_features * std::log2((double)kFusedCap)) return GBDT_OK;
   }
+  const int rc_levels = find_levels(n_rows);
+  if (rc_levels != GBDT_OK) return rc_levels;
   // 2. the plan; does it pay?
   std::vector<FusedCol> cols;
   std::vector<FusedFeat> feats;
