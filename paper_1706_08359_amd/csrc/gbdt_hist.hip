@@ -1155,8 +1155,15 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   const int64_t max_words = n_rows * (lay.plan.wm / 4);
   const int64_t bx = (max_words + 255) / 256;
   if (bx >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
-  hipLaunchKernelGGL(pack_fused_kernel, dim3((unsigned)bx, (unsigned)tiles), dim3(256), 0, s, bins_rowmajor, n_rows,
-                     n_features, lay.plan, (const FusedCol*)(base + lay.cols_off), n_cols, (uint8_t*)base);
+  const FusedCol* cols_dev = (const FusedCol*)(base + lay.cols_off);
+  if (n_features <= kFuseStageFeatures) {
+    hipLaunchKernelGGL(pack_fused_staged_kernel, dim3((unsigned)((n_rows + kFuseStageRows - 1) / kFuseStageRows)),
+                       dim3(256), (size_t)kFuseStageRows * n_features, s, bins_rowmajor, n_rows, n_features, lay.plan,
+                       cols_dev, n_cols, (uint8_t*)base);
+  } else {
+    hipLaunchKernelGGL(pack_fused_kernel, dim3((unsigned)bx, (unsigned)tiles), dim3(256), 0, s, bins_rowmajor, n_rows,
+                       n_features, lay.plan, cols_dev, n_cols, (uint8_t*)base);
+  }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(s));  // the host tables must outlive their copies
   FusedEntry e;

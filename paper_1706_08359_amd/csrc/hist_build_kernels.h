@@ -240,6 +240,65 @@ pack_fused_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_fea
   *reinterpret_cast<uint32_t*>(dst + tile_off + r * w + 4 * j) = word;
 }
 
+// The same for matrices of up to kFuseStageFeatures features: a workgroup stages kFuseStageRows whole rows in
+// local memory and gathers the parts of its columns from there, every thread one word of the packed row
+// for 8 rows at a time, so that a column's description is read once for them.  (Gathered byte by byte
+// from memory, 3,000,000 x 700 took 7.2 ms; staged 1.7.)
+constexpr int kFuseStageRows = 16;
+constexpr int kFuseStageFeatures = 4096;
+__global__ void __launch_bounds__(256)
+pack_fused_staged_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features, TilePlan plan,
+                         const FusedCol* __restrict__ cols, int32_t n_cols, uint8_t* __restrict__ dst) {
+  extern __shared__ __align__(16) uint8_t rows[];  // [kFuseStageRows][n_features]
+  const int64_t r0 = (int64_t)blockIdx.x * kFuseStageRows;
+  const int32_t nr = n_rows - r0 < kFuseStageRows ? (int32_t)(n_rows - r0) : kFuseStageRows;
+  const int32_t bytes = nr * n_features;
+  const uint8_t* from = src + r0 * n_features;
+  for (int32_t at = 16 * (int32_t)threadIdx.x; at < bytes; at += 16 * 256) {
+    if (at + 16 <= bytes) {
+      uint4 v;
+      __builtin_memcpy(&v, from + at, 16);
+      *reinterpret_cast<uint4*>(rows + at) = v;
+    } else {
+      for (int32_t i = at; i < bytes; ++i) rows[i] = from[i];
+    }
+  }
+  __syncthreads();
+  constexpr int kRows = 8;  // rows a thread takes at a time
+  const int32_t n_words = plan.row_bytes >> 2;
+  for (int32_t item = (int32_t)threadIdx.x; item < n_words * (kFuseStageRows / kRows); item += 256) {
+    const int32_t part = item / n_words, wd = item - part * n_words;
+    if (part * kRows >= nr) break;
+    uint32_t word[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) word[r] = 0u;
+    for (int i = 0; i < 4; ++i) {
+      const int32_t c = 4 * wd + i;
+      if (c >= n_cols) break;
+      const FusedCol col = cols[c];
+      uint32_t v[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) v[r] = 0u;
+#pragma unroll
+      for (int k = 0; k < kFusedMaxParts; ++k) {
+        if (k < col.n_parts) {
+          const int32_t f = col.feature[k] + part * kRows * n_features;
+#pragma unroll
+          for (int r = 0; r < kRows; ++r)  // (rows past the last one: any staged byte, never stored)
+            v[r] += (uint32_t)rows[part * kRows + r < nr ? f + r * n_features : 0] * col.stride[k];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) word[r] |= (v[r] & (uint32_t)(kFusedCap - 1)) << (8 * i);
+    }
+    const TileAt at = plan_tile_at(plan.wm, plan.n_main, plan.wr, n_rows, 1, 4 * wd / plan.wm);
+    uint8_t* out = dst + at.off + (4 * wd) % plan.wm + (r0 + part * kRows) * at.stride;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+      if (part * kRows + r < nr) *reinterpret_cast<uint32_t*>(out + (int64_t)r * at.stride) = word[r];
+  }
+}
+
 // ----------------------------------------------------------- histogram build kernel
 
 struct BuildArgs {
