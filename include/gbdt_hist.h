@@ -87,7 +87,8 @@ typedef struct {
  * (App. C.4: n_bins <= 16 stores two 4-bit values per byte, otherwise one byte
  * per value; Sec. 4 "Data Structure": features are bundled so that one thread
  * loads a 4-byte group of one sample).  Rows are kept contiguous inside
- * feature tiles of 16, 32 or 64 bytes; 32 KiB of slack follow the last tile (the
+ * feature tiles of 16, 32 or 64 bytes, two of which share a row from 4,096 rows on; 32 KiB
+ * of slack follow the last tile (the
  * build kernel may read, and ignore, whole row groups past the last row).  Behind
  * them the matrix is stored once more column by column, one byte per value
  * (columns padded to a multiple of 256 rows): the row partition after a split reads

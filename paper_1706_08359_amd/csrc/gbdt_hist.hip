@@ -223,7 +223,8 @@ constexpr int64_t kFusedMinLeafRows = 8192;
 constexpr int64_t kFusedMinLeafFraction = 3;
 // A fused copy is made when it has at most this fraction of the features as columns.
 constexpr double kFusedMaxColumnRatio = 0.85;
-constexpr int64_t kFuseSampleRows = 4096;  // rows gbdt_bins_fuse looks at before it reads them all
+constexpr int64_t kFuseSampleRows = 4096;  // rows gbdt_bins_fuse looks at before it reads them all ...
+constexpr int64_t kFuseSampleMinRows = 65536;  // ... of a matrix that takes longer to read than a round trip to the host
 
 // Packs features into columns of at most kFusedCap joint levels: features in descending order
 // of their level counts, each into the fullest column that still takes it (best fit).
@@ -659,7 +660,8 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
   };
   consider(most);
   const double average = (double)total_epochs / (double)budget;
-  for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
+  if (most <= (uint32_t)kDirectEpochs) t = most;  // (every leaf has one column whatever T is)
+  else for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
     const double cand = std::ceil(average * factor);
     if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
   }
@@ -671,8 +673,9 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
     order[i] = i;
     if (epochs[i] > 0) plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
   }
-  std::stable_sort(order, order + n, [&](int x, int y) {
-    return (int64_t)epochs[x] * (wgs[y] > 0 ? wgs[y] : 1) > (int64_t)epochs[y] * (wgs[x] > 0 ? wgs[x] : 1);
+  std::sort(order, order + n, [&](int x, int y) {  // (equal ones in the call's order)
+    const int64_t a = (int64_t)epochs[x] * (wgs[y] > 0 ? wgs[y] : 1), b2 = (int64_t)epochs[y] * (wgs[x] > 0 ? wgs[x] : 1);
+    return a != b2 ? a > b2 : x < y;
   });
   uint32_t first = 0;
   for (int k = 0; k < n; ++k) {
@@ -1125,7 +1128,7 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
     }
     return GBDT_OK;
   };
-  if (n_rows > kFuseSampleRows) {
+  if (n_rows >= kFuseSampleMinRows) {
     const int rc = find_levels(kFuseSampleRows);
     if (rc != GBDT_OK) return rc;
     double bits = 0.0;
@@ -1264,12 +1267,14 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
                      (wide ? 2 : 1);
   // one scratch buffer serves the launches one after the other: size it for the largest
   size_t need_words = 0;
+  BatchPlan first_plan;  // (of the first launch: nearly always the only one)
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;
     for (int32_t i = 0; i < n; ++i)
       if (leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     if (leaf_offsets[l0 + n] - leaf_offsets[l0] >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
-    const BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles);
+    const BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
+    if (l0 == 0) first_plan = b;
     if ((int64_t)b.total_wgs * n_tiles >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     const size_t w = (size_t)b.total_wgs * col;
     if (w > need_words) need_words = w;
@@ -1299,7 +1304,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   }
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;
-    const BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
+    const BatchPlan b = l0 == 0 ? first_plan : plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
     BatchMergeArgs m;
     m.m.partials = (const uint32_t*)ws;
     m.m.out = hist_out + (size_t)l0 * n_features * n_bins;

@@ -44,7 +44,7 @@ def test_pack_block_edges(n_rows, n_features, n_bins):
 @pytest.mark.parametrize("n_features,late", [(40, 16), (1500, 5), (37, 64), (4096, 3), (4097, 4)])
 def test_fuse_sees_levels_of_late_rows(n_features, late):
     """Only bins 0 and 1 at first; in the last rows some features reach `late` levels."""
-    n_rows, nb = 20_001, 64
+    n_rows, nb = 70_001, 64                    # (past the size from which a part is looked at first)
     print(f"fuse {n_features} features, late levels {late}", flush=True)
     rng = np.random.default_rng(n_features)
     bins = rng.integers(0, 2, size=(n_rows, n_features)).astype(np.uint8)
