@@ -1115,10 +1115,15 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   if ((n_rows + 255) / 256 >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
   std::vector<uint32_t> levels((size_t)n_features);
   auto find_levels = [&](int64_t rows) -> int {
-    const int64_t stripes = (rows + 4 * 32 - 1) / (4 * 32);  // (32 rows a thread: every wavefront ends with atomics)
-    const dim3 grid((unsigned)(stripes < 1024 ? stripes : 1024),
-                    (unsigned)((n_features + kMaxFeatures - 1) / kMaxFeatures));
-    hipLaunchKernelGGL(feature_max_kernel, grid, dim3(256), 0, s, bins_rowmajor, rows, n_rows, n_features, max_dev);
+    int32_t lane_bits = 0;  // threads across a row, 16 features each
+    while (lane_bits < 6 && (16 << lane_bits) < n_features) ++lane_bits;
+    const int64_t block_rows = (int64_t)(256 >> lane_bits) * kMaxFlight;
+    const int64_t stripes = (rows + block_rows - 1) / block_rows;
+    const int64_t most = rows >= kFuseSampleMinRows ? 1024 : 64;  // (every workgroup ends with atomics)
+    hipLaunchKernelGGL(feature_max_kernel,
+                       dim3((unsigned)(stripes < most ? stripes : most),
+                            (unsigned)((n_features + kMaxFeatures - 1) / kMaxFeatures)),
+                       dim3(256), 0, s, bins_rowmajor, rows, n_rows, n_features, lane_bits, max_dev);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(levels.data(), max_dev, levels.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));

@@ -156,58 +156,64 @@ struct FusedFeat {  // where a feature went
 };
 
 // Largest bin value of every feature over the rows [0, n_rows) of a row-major matrix of total_rows rows (maxima
-// start at zero).  A thread takes 16 consecutive features and every stripe-th row, 8 rows at a time in
-// flight; maxima are kept per byte in pairs of 16-bit halves, and only one that exceeds what is known
-// already is sent out with an atomic.
-// grid = (row stripes, blocks of 1024 features); block = 64 threads across x 4 rows.
+// start at zero).  A thread takes 16 consecutive features; 1 << lane_bits of them cover a row (up to 1024
+// features; wider matrices take more blocks in y) and the others of the workgroup take other rows,
+// 8 in flight each; maxima are kept per byte in pairs of 16-bit halves, combined in local memory, and only one that
+// exceeds what is known already is sent out with an atomic.  grid = (row stripes, blocks of 1024 features).
 constexpr int kMaxFeatures = 1024;
+constexpr int kMaxFlight = 8;
 __global__ void __launch_bounds__(256)
 feature_max_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int64_t total_rows, int32_t n_features,
-                   uint32_t* __restrict__ max_out) {
+                   int32_t lane_bits, uint32_t* __restrict__ max_out) {
   typedef unsigned short half2u __attribute__((ext_vector_type(2)));
-  const int32_t f = (int32_t)blockIdx.y * kMaxFeatures + 16 * (threadIdx.x & 63);
-  if (f >= n_features) return;
-  const int64_t total = total_rows * n_features;
-  const int64_t stripe = (int64_t)gridDim.x * 4;
-  uint32_t even[4] = {0u, 0u, 0u, 0u}, odd[4] = {0u, 0u, 0u, 0u};  // bytes 0, 2 and 1, 3 of every word
-  auto larger = [](uint32_t x, uint32_t y) {
-    half2u a, b;
-    __builtin_memcpy(&a, &x, 4);
-    __builtin_memcpy(&b, &y, 4);
-    const half2u m = __builtin_elementwise_max(a, b);
-    uint32_t r;
-    __builtin_memcpy(&r, &m, 4);
-    return r;
-  };
-  constexpr int kFlight = 8;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < n_rows; r += kFlight * stripe) {
-    uint4 v[kFlight];
+  __shared__ uint32_t s_max[kMaxFeatures];
+  const int32_t f_block = (int32_t)blockIdx.y * kMaxFeatures;
+  const int32_t fl = 16 * (int32_t)(threadIdx.x & ((1u << lane_bits) - 1u));  // first feature, in the block
+  const int32_t f = f_block + fl;
+  const int32_t rows_per_block = 256 >> lane_bits;
+  for (int i = threadIdx.x; i < kMaxFeatures; i += 256) s_max[i] = 0u;
+  __syncthreads();
+  if (f < n_features) {
+    const int64_t total = total_rows * n_features;
+    const int64_t stripe = (int64_t)gridDim.x * rows_per_block;
+    uint32_t even[4] = {0u, 0u, 0u, 0u}, odd[4] = {0u, 0u, 0u, 0u};  // bytes 0, 2 and 1, 3 of every word
+    auto larger = [](uint32_t x, uint32_t y) {
+      half2u p, q;
+      __builtin_memcpy(&p, &x, 4);
+      __builtin_memcpy(&q, &y, 4);
+      const half2u m = __builtin_elementwise_max(p, q);
+      uint32_t r;
+      __builtin_memcpy(&r, &m, 4);
+      return r;
+    };
+    for (int64_t r = (int64_t)blockIdx.x * rows_per_block + (threadIdx.x >> lane_bits); r < n_rows;
+         r += kMaxFlight * stripe) {
+      uint4 v[kMaxFlight];
 #pragma unroll
-    for (int i = 0; i < kFlight; ++i) {
-      const int64_t ri = r + i * stripe < n_rows ? r + i * stripe : r;
-      v[i] = pack_load16(src, ri * n_features + f, total, n_features - f, ~0u);
-    }
+      for (int i = 0; i < kMaxFlight; ++i) {
+        const int64_t ri = r + i * stripe < n_rows ? r + i * stripe : r;
+        v[i] = pack_load16(src, ri * n_features + f, total, n_features - f, ~0u);
+      }
 #pragma unroll
-    for (int i = 0; i < kFlight; ++i) {
-      const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+      for (int i = 0; i < kMaxFlight; ++i) {
+        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        even[k] = larger(even[k], w[k] & 0x00ff00ffu);
-        odd[k] = larger(odd[k], (w[k] >> 8) & 0x00ff00ffu);
+        for (int k = 0; k < 4; ++k) {
+          even[k] = larger(even[k], w[k] & 0x00ff00ffu);
+          odd[k] = larger(odd[k], (w[k] >> 8) & 0x00ff00ffu);
+        }
       }
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int k = i >> 2, b = i & 3;
+      atomicMax(&s_max[fl + i], ((b & 1 ? odd[k] : even[k]) >> (b & 2 ? 16 : 0)) & 0xffffu);
+    }
   }
-  // what is known of the 16 features (requested together), then atomics for those this thread exceeds
-  uint32_t known[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i)
-    known[i] = f + i < n_features
-                   ? __hip_atomic_load(max_out + f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0u;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int k = i >> 2, b = i & 3;
-    const uint32_t m = ((b & 1 ? odd[k] : even[k]) >> (b & 2 ? 16 : 0)) & 0xffffu;
-    if (m > known[i]) atomicMax(max_out + f + i, m);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kMaxFeatures && f_block + i < n_features; i += 256) {
+    uint32_t* known = max_out + f_block + i;
+    if (s_max[i] > __hip_atomic_load(known, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(known, s_max[i]);
   }
 }
 
