@@ -526,6 +526,10 @@ int gbdt_debug_split_plan(int32_t n_features, int32_t n_bins, int32_t n_hists, i
  * 256 positions a workgroup takes (positions per chunk / 256), out[1] = chunks, out[2] = bytes of
  * scratch (flag words and chunk counts).  Host only. */
 int gbdt_debug_partition_plan(int64_t n_leaf_rows, int64_t* out, int32_t n_out);
+/* What a local-memory cell of the (narrow) build holds after the n <= 512 additions of an epoch,
+ * whose quantised gradients and hessians are given: out[0] = sum of the gradients, out[1] = sum of the
+ * hessians, out[2] = count.  Computed by the functions the kernel uses.  Host only. */
+int gbdt_debug_cell_sums(const int32_t* grad_q, const int32_t* hess_q, int32_t n, int64_t* out);
 int gbdt_debug_locate(int32_t n_features, int32_t n_bins, int32_t feature, int32_t* tile_out,
                       int32_t* slot_out);
 

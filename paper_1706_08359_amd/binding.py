@@ -23,7 +23,7 @@ EXPORTS = [
     "gbdt_best_split", "gbdt_workspace_bytes", "gbdt_set_workspace", "gbdt_strerror",
     "gbdt_last_hip_error", "gbdt_debug_geometry", "gbdt_debug_locate",
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
-    "gbdt_debug_partition_plan",
+    "gbdt_debug_partition_plan", "gbdt_debug_cell_sums",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -553,6 +553,17 @@ def gbdt_debug_locate(n_features: int, n_bins: int, feature: int):
     _check(load().gbdt_debug_locate(n_features, n_bins, feature, ctypes.byref(t), ctypes.byref(s)),
            "gbdt_debug_locate")
     return t.value, s.value
+
+
+def gbdt_debug_cell_sums(grad_q, hess_q):
+    """(gradient sum, hessian sum, count) that a cell of the build reports after these additions."""
+    lib = load()
+    g, h = (np.ascontiguousarray(a, dtype=np.int32) for a in (grad_q, hess_q))
+    out = (ctypes.c_int64 * 3)()
+    lib.gbdt_debug_cell_sums.restype = ctypes.c_int
+    lib.gbdt_debug_cell_sums.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
+    _check(lib.gbdt_debug_cell_sums(g.ctypes.data, h.ctypes.data, g.size, out), "gbdt_debug_cell_sums")
+    return out[0], out[1], out[2]
 
 
 def gbdt_set_deterministic(enable: bool) -> None:

@@ -2211,6 +2211,20 @@ int gbdt_debug_partition_plan(int64_t n_leaf_rows, int64_t* out, int32_t n_out) 
   return GBDT_OK;
 }
 
+int gbdt_debug_cell_sums(const int32_t* grad_q, const int32_t* hess_q, int32_t n, int64_t* out) {
+  if (n < 0 || n > kEpochRows || !out || (n > 0 && (!grad_q || !hess_q))) return GBDT_EINVAL;
+  uint64_t cell = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    const CellWords w = cell_addend(grad_q[i], hess_q[i]);
+    cell += ((uint64_t)w.hi << 32) | w.lo;
+  }
+  const CellSums s = cell_sums((uint32_t)cell, (uint32_t)(cell >> 32));
+  out[0] = (int64_t)s.grad >> kSumPad;
+  out[1] = (int64_t)s.hess >> kSumPad;
+  out[2] = s.count;
+  return GBDT_OK;
+}
+
 int gbdt_debug_locate(int32_t n_features, int32_t n_bins, int32_t feature, int32_t* tile_out,
                       int32_t* slot_out) {
   if (!tile_out || !slot_out || n_features <= 0 || n_bins < 2 || n_bins > 256 || feature < 0 ||

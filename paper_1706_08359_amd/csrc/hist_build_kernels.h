@@ -14,6 +14,7 @@
 #include "../../include/gbdt_hist.h"
 #include "tile_plan.h"
 #include "batch_plan.h"
+#include "cell_format.h"
 
 namespace {
 
@@ -330,23 +331,7 @@ struct BuildArgs {
   int32_t n_bins;
 };
 
-// A histogram cell is ONE 64-bit integer that carries, from the low bits up, the
-// quantised gradient sum (27 bits, signed, stored with a bias of 2^26 that an empty cell holds
-// already), the count (10 bits) and the quantised hessian sum (27 bits, signed).  With the bias no
-// field ever borrows from the one above it, and in this order the gradient sum is one shift-and-add
-// away from a signed word, the hessian sum one mask: 9 vector instructions a cell from the drained
-// word to the accumulators, two of them the fused multiply-adds.  (Count, gradient, hessian
-// without a bias took 11, and the 256-bin variants are bound by vector instructions as much as by
-// local memory.)  A workgroup drains its cells after every epoch
-// of kEpochRows rows, so a cell receives at most 512 additions between drains.
-constexpr int kEpochRows = 512;
 constexpr int kUnitEpochs = 4;  // consecutive epochs a workgroup takes from its group's counter (>= 3)
-constexpr int kCountBits = 10;
-constexpr int kSumBits = 27;
-static_assert(kEpochRows < (1 << kCountBits), "an epoch's count must fit its field");
-static_assert(kCountBits + 2 * kSumBits == 64, "the three fields fill the cell");
-constexpr int kSumPad = 32 - kSumBits;  // a sum in the upper bits of a signed word is 2^kSumPad times itself
-constexpr unsigned long long kEmptyCell = 1ull << (kSumBits - 1);
 
 // Power-of-two scale 2^k for quantising the values of one epoch to integers: the
 // largest k with 2^k * m + kEpochRows / 2 (rounding slack) < 2^26, so that no cell's
@@ -354,7 +339,8 @@ constexpr unsigned long long kEmptyCell = 1ull << (kSumBits - 1);
 // m = 1.002 * (fp32 sum of |v| over the epoch) (the factor covers the rounding of the
 // sum itself).  Integer arithmetic only: on a wave-uniform value it runs on the
 // scalar unit.  A zero (or denormal) sum gives k = 0; k is kept in [-126, 126] so
-// that 2^k and 2^-k are normal floats.
+// that 2^k and 2^-k are normal floats.  (The drain's 2^-(k + kSumPad) is a denormal from k = 122 on,
+// which the multiply-adds take as it is.)
 __device__ __forceinline__ int epoch_scale_exp(uint32_t m_bits) {
   const int e = (int)((m_bits >> 23) & 0xffu);
   const uint32_t mant = m_bits & 0x7fffffu;
@@ -503,7 +489,6 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   constexpr int NTBL = LPR == 8 ? 1 : 2;  // LPR 4: two byte-words share a page of 32 slots
 
   char* cells = reinterpret_cast<char*>(lds);
-  constexpr unsigned long long kEmpty = WIDE ? 0ull : kEmptyCell;
   constexpr int NCELLARR = WIDE ? 2 : 1;  // wide: gradient cells, then hessian cells
   float* red = reinterpret_cast<float*>(lds + NCELLARR * CELLS);  // [2 parities][2 stats][NW]
   uint32_t* unit_box = reinterpret_cast<uint32_t*>(red + 4 * NW);  // the unit just taken from the counter
@@ -531,7 +516,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   }
 
 #pragma unroll
-  for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = kEmpty;
+  for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = 0ull;
   ACC acc_g[PP], acc_h[PP];
   uint32_t acc_c[PP];
 #pragma unroll
@@ -690,7 +675,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   };
   // Takes the sums of a cell out of local memory (read and clear in one operation) ...
   auto request_cell = [&](int i) {
-    return __hip_atomic_exchange(&lds[i], kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __hip_atomic_exchange(&lds[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
   // ... and adds them to this thread's accumulators of its cell m (wide: th = the hessian cell).
   auto drain_cell = [&](int m, unsigned long long t, unsigned long long th, float inv_g, float inv_h,
@@ -702,11 +687,10 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       acc_h[m] = (ACC)fma((double)((long long)th >> kCountBits), inv_hw, (double)acc_h[m]);
       return;
     }
-    const uint32_t tlo = (uint32_t)t, thi = (uint32_t)(t >> 32);
-    // both sums in the upper bits of a word, times 2^kSumPad (the scales inv_g, inv_h allow for it)
-    const int32_t gs = (int32_t)((tlo << kSumPad) + 0x80000000u);
-    const int32_t hs = (int32_t)(thi & ~((1u << kSumPad) - 1u));
-    const uint32_t c = (uint32_t)(t >> kSumBits) & ((1u << kCountBits) - 1u);
+    // both sums times 2^kSumPad (the scales inv_g, inv_h allow for it)
+    const CellSums sums = cell_sums((uint32_t)t, (uint32_t)(t >> 32));
+    const int32_t gs = sums.grad, hs = sums.hess;
+    const uint32_t c = sums.count;
     // integer * power of two + accumulator, rounded once
     if (sizeof(ACC) == 8) {
       acc_g[m] = (ACC)fma((double)gs, (double)inv_g, (double)acc_g[m]);
@@ -819,7 +803,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
     const float g_nxt = load_stat(grad, stat_nxt);
     const float h_nxt = load_stat(hess, stat_nxt);
-    // ---- this lane's row -> 64-bit addend gq + 2^27 + hq * 2^37 (two's complement)
+    // ---- this lane's row -> 64-bit addend (cell_format.h)
     //      (wide: 1 + gq * 2^10 into the gradient cell, hq * 2^10 into the hessian cell)
     uint32_t lo, hi, lo2 = 0u, hi2 = 0u;
     if constexpr (WIDE) {
@@ -833,10 +817,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       lo2 = ok ? (uint32_t)ah : 0u;
       hi2 = ok ? (uint32_t)(ah >> 32) : 0u;
     } else {
-      const int32_t gq = __float2int_rn(g_cur * pow2f(kg));
-      const int32_t hq = __float2int_rn(h_cur * pow2f(kh));
-      lo = (uint32_t)gq + (1u << kSumBits);  // (|gq| < 2^26: the sum is positive)
-      hi = (uint32_t)hq << (kCountBits + kSumBits - 32);
+      const CellWords add = cell_addend(__float2int_rn(g_cur * pow2f(kg)), __float2int_rn(h_cur * pow2f(kh)));
+      lo = add.lo;
+      hi = add.hi;
       const bool ok = own_valid(p0.row);
       lo = ok ? lo : 0u;
       hi = ok ? hi : 0u;

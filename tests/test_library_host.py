@@ -271,6 +271,28 @@ def test_split_search_plan_covers_every_feature_within_the_lds_budget(n_bins):
             assert 3 * p["group"] <= 256
 
 
+def test_cell_counts_are_exact_whatever_the_sums_do():
+    """A cell's count and sums share 64 bits.  Sums of magnitudes below 2^26 (what the scale of an epoch
+    guarantees when the epoch's sum of magnitudes is a finite fp32 number) come back exactly; beyond that, with
+    values that a conversion has saturated too, the sums wrap but the count stays exact: tree
+    growth finds the rows of a node by its counts."""
+    rng = np.random.default_rng(8)
+    for trial in range(200):
+        n = int(rng.integers(0, 513))
+        g, h = (rng.normal(size=n) * (2.0 ** 26 - 257) / max(1, n) / 5 for _ in range(2))
+        g, h = np.rint(g).astype(np.int64), np.rint(h).astype(np.int64)
+        assert np.abs(g).sum() < 2 ** 26 and np.abs(h).sum() < 2 ** 26
+        assert B.gbdt_debug_cell_sums(g, h) == (g.sum(), h.sum(), n)
+    top = 2 ** 26 - 257
+    for g, h in ((top, -top), (-top, top), (-top, -top), (top, top)):
+        assert B.gbdt_debug_cell_sums([g, 0], [0, h]) == (g, h, 2)
+    big, small = 2 ** 31 - 1, -2 ** 31
+    for g, h in (([big] * 3, [1] * 3), ([small] * 512, [small] * 512), ([big, small, 5], [big, 0, 0]),
+                 ([9_860_761] * 7, [0] * 7),        # 1e38 at the smallest scale there is, 2^-103
+                 ([0] * 512, [big] * 512), ([-9_860_761] * 100, [9_860_761] * 100)):
+        assert B.gbdt_debug_cell_sums(g, h)[2] == len(g), (g[0], h[0])
+
+
 def test_partition_plan_chunks_cover_the_list():
     """Chunks of 256 * rows_per_thread positions: 8 steps, or a multiple of 16 (the kernels take
     8 or 16 steps at a time), at most 2048 chunks, every position in exactly one chunk."""
