@@ -88,8 +88,7 @@ typedef struct {
  * per value; Sec. 4 "Data Structure": features are bundled so that one thread
  * loads a 4-byte group of one sample).  Rows are kept contiguous inside
  * feature tiles of 16, 32 or 64 bytes, two of which share a row from 4,096 rows on; 32 KiB
- * of slack follow the last tile (the
- * build kernel may read, and ignore, whole row groups past the last row).  Behind
+ * of slack follow the last tile (the build kernel may read, and ignore, whole row groups past the last row).  Behind
  * them the matrix is stored once more column by column, one byte per value
  * (columns padded to a multiple of 256 rows): the row partition after a split reads
  * one feature of every leaf row from there, a byte instead of a tile row.  The layout
@@ -508,6 +507,13 @@ int gbdt_debug_geometry(int32_t n_features, int32_t n_bins, int64_t n_leaf_rows,
 int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* leaf_offsets,
                           int32_t n_leaves, int32_t n_cus, int32_t wg_per_cu, int32_t* leaf_wgs_out,
                           int32_t* leaf_unit_epochs_out, int32_t* block_out, int32_t max_blocks);
+/* Where the tiles of a packed matrix lie and how the blocks of a build launch with `cols` workgroups per
+ * tile are dealt out: tile_out[2 t], tile_out[2 t + 1] = byte offset of tile t's first row and bytes from
+ * a row to the next; block_out[2 i], block_out[2 i + 1] = (tile, workgroup of the tile) of block
+ * i < max_blocks, for a batched launch (by_column != 0) or a single leaf's.  Computed by the functions the
+ * kernels use.  Returns the number of blocks, or a negative gbdt_status.  Host only. */
+int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int32_t cols, int32_t by_column,
+                         int64_t* tile_out, int32_t* block_out, int32_t max_blocks);
 /* The column plan gbdt_bins_fuse makes for features with the given numbers of levels (1..64
  * each): col_out[f] / stride_out[f] = the column of feature f and the weight of its bin in the
  * column's joint value; *n_cols_out the number of columns.  Host only. */

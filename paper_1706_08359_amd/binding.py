@@ -23,7 +23,7 @@ EXPORTS = [
     "gbdt_best_split", "gbdt_workspace_bytes", "gbdt_set_workspace", "gbdt_strerror",
     "gbdt_last_hip_error", "gbdt_debug_geometry", "gbdt_debug_locate",
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
-    "gbdt_debug_partition_plan", "gbdt_debug_cell_sums",
+    "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -553,6 +553,24 @@ def gbdt_debug_locate(n_features: int, n_bins: int, feature: int):
     _check(load().gbdt_debug_locate(n_features, n_bins, feature, ctypes.byref(t), ctypes.byref(s)),
            "gbdt_debug_locate")
     return t.value, s.value
+
+
+def gbdt_debug_block_map(n_features: int, n_bins: int, n_rows: int, cols: int, by_column: bool):
+    """(tiles [n_tiles, 2] = (offset, row stride), blocks [n, 2] = (tile, workgroup)) of a build launch."""
+    lib = load()
+    g = gbdt_debug_geometry(n_features, n_bins, 1)
+    n_tiles = g["n_main"] + (1 if g["wr"] else 0)
+    tiles = np.zeros((n_tiles, 2), np.int64)
+    blocks = np.zeros((n_tiles * cols, 2), np.int32)
+    lib.gbdt_debug_block_map.restype = ctypes.c_int
+    lib.gbdt_debug_block_map.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                         ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32]
+    rc = lib.gbdt_debug_block_map(n_features, n_bins, n_rows, cols, 1 if by_column else 0, tiles.ctypes.data,
+                                  blocks.ctypes.data, blocks.shape[0])
+    if rc < 0:
+        _check(rc, "gbdt_debug_block_map")
+    assert rc == blocks.shape[0]
+    return tiles, blocks
 
 
 def gbdt_debug_cell_sums(grad_q, hess_q):

@@ -28,7 +28,10 @@ static_assert(kBatchLeaves <= 256, "a leaf's number has 8 bits");
 // matrix, same column and so the same rows at the same time -- are kept on one XCD, whose L2 then
 // fetches the line once.  Consecutive blocks go to the 8 XCDs in turn, so eight (line, column)
 // pairs are dealt out at a time and their tiles follow one another 8 blocks apart; the
-// pairs left over (fewer than 8) come last.  In a batched launch pairs are numbered column after
+// pairs left over (fewer than 8) come last.  Tiles that make no whole line follow, the remainder tile
+// last of all unless it shares a region: its blocks have the least work, and where the grid does not fill
+// the machine evenly they are what the last CUs should get (300,000 x 193 x 63, 588 blocks on 256 CUs:
+// dealt out with the lone main tile's the root took 34.7 us, behind them 30.6).  In a batched launch pairs are numbered column after
 // column, so that blocks start in the order of the columns, the longest first; a single leaf's blocks
 // all start at once, and there a line's columns are numbered through, so that (with a multiple
 // of 8 columns) the lines of a column, which read the same gradients and hessians, share an XCD too.
@@ -49,8 +52,8 @@ GBDT_HD void line_deal(uint32_t b, uint32_t n_pairs, uint32_t tiles, uint32_t* p
     *tile = r / rest;
   }
 }
-GBDT_HD LineBlock line_block(int32_t n_main, int32_t wr, int32_t line_tiles, uint32_t cols, bool by_column,
-                             uint32_t b) {
+GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, int32_t line_tiles, uint32_t cols,
+                             bool by_column, uint32_t b) {
   LineBlock r;
   if (n_main + (wr ? 1 : 0) == 1) {
     r.tile = 0;
@@ -73,8 +76,14 @@ GBDT_HD LineBlock line_block(int32_t n_main, int32_t wr, int32_t line_tiles, uin
     r.col = by_column ? pair / lines : pair % cols;
     return r;
   }
+  b -= line_blocks;
   const uint32_t first = lines * (uint32_t)line_tiles;  // the tiles that make no whole line
-  line_deal(b - line_blocks, cols, (uint32_t)n_main - first + (wr ? 1u : 0u), &pair, &tile);
+  if (plan_leftover_shared(wm, n_main, wr)) {
+    line_deal(b, cols, 2u, &pair, &tile);
+  } else {
+    tile = b / cols;
+    pair = b % cols;
+  }
   r.tile = (int32_t)(first + tile);
   r.col = pair;
   return r;
@@ -101,9 +110,9 @@ GBDT_HD int32_t batch_leaf_of(const BatchLeaf* leaf, int32_t n_leaves, uint32_t 
   return lo;
 }
 
-GBDT_HD BatchBlock batch_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t n_main, int32_t wr,
+GBDT_HD BatchBlock batch_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t wm, int32_t n_main, int32_t wr,
                                int32_t line_tiles, uint32_t cols, uint32_t b) {
-  const LineBlock lb = line_block(n_main, wr, line_tiles, cols, true, b);
+  const LineBlock lb = line_block(wm, n_main, wr, line_tiles, cols, true, b);
   BatchBlock r;
   r.leaf = batch_leaf_of(leaf, n_leaves, lb.col);
   r.tile = lb.tile;

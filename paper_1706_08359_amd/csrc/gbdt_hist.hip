@@ -895,7 +895,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   if (plan_n_tiles(p) > 65535) return GBDT_EUNSUPPORTED;
   // byte offsets inside a tile (slack included) are formed in 32 bits
   if ((n_rows + kEpochRows) * (int64_t)p.wm >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
-  const int32_t line_tiles = fused ? 1 : plan_line_tiles(p, n_rows);  // (a fused copy has a region per tile)
+  const int32_t line_tiles = fused ? 1 : plan_line_tiles(n_rows);  // (a fused copy has a region per tile)
   void* ws = nullptr;
   uint32_t* counters = nullptr;
   bool counters_zero = false;
@@ -1071,7 +1071,7 @@ int gbdt_bins_pack(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   const dim3 grid((unsigned)((n_rows + kPackRows - 1) / kPackRows),
                   (unsigned)((n_features + kPackFeatures - 1) / kPackFeatures));
   hipLaunchKernelGGL(p.nib ? pack_kernel<true> : pack_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream,
-                     bins_rowmajor, n_rows, n_features, p, plan_line_tiles(p, n_rows),
+                     bins_rowmajor, n_rows, n_features, p, plan_line_tiles(n_rows),
                      (uint32_t)(p.cap - 1) * 0x01010101u, (uint8_t*)packed_out,
                      (uint8_t*)packed_out + plan_columns_base(p, n_rows), plan_column_stride(n_rows));
   HIP_TRY(hipGetLastError());
@@ -1342,7 +1342,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_rows = n_rows;
       a.n_main = p.n_main;
       a.wr = p.wr;
-      a.line_tiles = plan_line_tiles(p, n_rows);
+      a.line_tiles = plan_line_tiles(n_rows);
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -2161,11 +2161,33 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
   }
   const int64_t blocks = (int64_t)b.total_wgs * n_tiles;
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
-    const BatchBlock k = batch_block(b.leaf, n_leaves, p.n_main, p.wr,
-                                     plan_line_tiles(p, kPlanLinesMinRows), b.total_wgs, (uint32_t)i);
+    const BatchBlock k = batch_block(b.leaf, n_leaves, p.wm, p.n_main, p.wr,
+                                     plan_line_tiles(kPlanLinesMinRows), b.total_wgs, (uint32_t)i);
     block_out[3 * i] = (int32_t)batch_leaf_no(b.leaf[k.leaf]);
     block_out[3 * i + 1] = k.tile;
     block_out[3 * i + 2] = k.wg;
+  }
+  return (int)blocks;
+}
+
+int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int32_t cols, int32_t by_column,
+                         int64_t* tile_out, int32_t* block_out, int32_t max_blocks) {
+  if (n_rows < 0 || n_features <= 0 || n_bins < 2 || n_bins > 256 || cols < 1 || !tile_out || (!block_out && max_blocks > 0))
+    return GBDT_EINVAL;
+  const TilePlan p = make_tile_plan(n_features, n_bins);
+  const int n_tiles = plan_n_tiles(p);
+  const int32_t line_tiles = plan_line_tiles(n_rows);
+  for (int32_t t = 0; t < n_tiles; ++t) {
+    const TileAt at = plan_tile_at(p.wm, p.n_main, p.wr, n_rows, line_tiles, t);
+    tile_out[2 * t] = at.off;
+    tile_out[2 * t + 1] = at.stride;
+  }
+  const int64_t blocks = (int64_t)n_tiles * cols;
+  if (blocks >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
+  for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
+    const LineBlock b = line_block(p.wm, p.n_main, p.wr, line_tiles, (uint32_t)cols, by_column != 0, (uint32_t)i);
+    block_out[2 * i] = b.tile;
+    block_out[2 * i + 1] = (int32_t)b.col;
   }
   return (int)blocks;
 }

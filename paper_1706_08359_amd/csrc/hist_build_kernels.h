@@ -938,7 +938,7 @@ hist_build_kernel(BuildArgs a) {
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
   const uint32_t n_leaf = (uint32_t)a.n_leaf;
-  const LineBlock lb = line_block(a.n_main, a.wr, a.line_tiles, (uint32_t)a.wgs, false, blockIdx.x);
+  const LineBlock lb = line_block(WM, a.n_main, a.wr, a.line_tiles, (uint32_t)a.wgs, false, blockIdx.x);
   const int32_t t = lb.tile;
   const int32_t c = (int32_t)lb.col;  // workgroup of the tile
   uint32_t* counter = a.counters + plan_counter_slot(t);
@@ -946,7 +946,7 @@ hist_build_kernel(BuildArgs a) {
   const uint8_t* tile = a.packed + at.off;
   const uint32_t stride = (uint32_t)at.stride;
   const uint32_t n_firsts = a.first_epochs ? (uint32_t)a.wgs : 0u;
-  const bool paced = WM == 64 && a.line_tiles > 1;
+  const bool paced = WM == 64 && at.shared;
   const DirectOut direct = {a.direct_out, t, WM, a.n_main, a.wr, a.n_features, a.n_bins};
   // wide accumulation: the workgroup's second block lies a.wgs blocks behind its first
   if (t < a.n_main) {
@@ -1052,7 +1052,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WP
 hist_build_batch_kernel(BatchArgs a) {
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, a.n_main, a.wr, a.line_tiles, a.n_cols, blockIdx.x);
+  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, WM, a.n_main, a.wr, a.line_tiles, a.n_cols, blockIdx.x);
   const BatchLeaf lf = a.leaf[blk.leaf];
   const int32_t wgs = (int32_t)batch_wgs(lf);
   const uint32_t unit_epochs = batch_unit_epochs(lf);
@@ -1064,7 +1064,7 @@ hist_build_batch_kernel(BatchArgs a) {
   const uint8_t* tile = a.packed + at.off;
   const uint32_t stride = (uint32_t)at.stride;
   const int32_t* idx = a.idx + lf.row_off;
-  const bool paced = WM == 64 && a.line_tiles > 1;
+  const bool paced = WM == 64 && at.shared;
   const bool by_pos = a.stats_by_pos != 0;  // then grad / hess follow the concatenated row lists
   const float* grad = by_pos ? a.grad + lf.row_off : a.grad;
   const float* hess = by_pos ? a.hess + lf.row_off : a.hess;

@@ -90,7 +90,7 @@ __device__ __forceinline__ SplitColumn split_column(const gbdt_split_t* __restri
     const int32_t fb = plan.nib ? (f >> 1) : f;
     int32_t t = fb / plan.wm;
     if (t > plan.n_main) t = plan.n_main;
-    const TileAt at = plan_tile_at(plan.wm, plan.n_main, plan.wr, n_rows, plan_line_tiles(plan, n_rows), t);
+    const TileAt at = plan_tile_at(plan.wm, plan.n_main, plan.wr, n_rows, plan_line_tiles(n_rows), t);
     c.w = at.stride;
     c.col = fb - t * plan.wm;
     c.tile_off = at.off;

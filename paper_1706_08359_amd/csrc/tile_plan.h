@@ -10,6 +10,7 @@
 //
 //   packed = [tile 0: n_rows x W_0 bytes][tile 1: n_rows x W_1 bytes] ...
 //
+// (from 4,096 rows on two tiles share such a region, row by row: "Lines" below).
 // All tiles have the "main" width WM except possibly the last one, which is 16
 // or 32 bytes wide when few feature bytes remain (so that padding stays small).
 //
@@ -93,12 +94,17 @@ GBDT_HD int64_t plan_packed_bytes(const TilePlan& p, int64_t n_rows, int32_t n_f
 // 32, 64 or 128 bytes of them are used.)  So two neighbouring main tiles share a region, one after
 // the other inside a row of 128 or 64 bytes, and the build kernels run the workgroups that need the
 // same line on the same XCD at the same time (batch_plan.h): one of them fetches it, the others find it in
-// that XCD's L2.  The tiles left over (an odd main tile, the remainder tile) share a region too.
-// Build kernel, before -> now: 8,000,000 x 500 x 64 bins, 50 / 25 / 12.5 % of the rows 657 / 368 / 202 ->
-// 467 / 243 / 136 us; 2,000,000 x 500 x 255 bins, 25 / 5 % 147 / 43 -> 122 / 32 us; 400,000 x 2,000 x 63
+// that XCD's L2.
+// Build kernel, a region per tile -> shared: 8,000,000 x 500 x 64 bins, 50 / 25 / 12.5 % of the rows 657 / 368 / 202
+// -> 467 / 243 / 136 us; 2,000,000 x 500 x 255 bins, 25 / 5 % 147 / 43 -> 122 / 32 us; 400,000 x 2,000 x 63
 // bins, half of the rows 123 -> 101 us, all rows 176 -> 179 us.  (Four 32-byte tiles a line were
 // better still for sparse leaves, 107 / 32 us, but the root then fetches its lines up to four times:
 // 362 -> 413 us.)
+// What is left over, a main tile without a partner and the remainder tile, shares a region only with 32-byte tiles:
+// rows of 48 bytes (1,000,000 x 40 x 255: 32 leaves of a call 57 -> 46 us, the root 38 either way).  With
+// 64-byte tiles the rows would have 80 or 96 bytes and two or three of eight would lie across two lines:
+// 1,000,000 x 150 x 16 bins, root 47 us with a region each and 62 with one, 32 leaves 53 and 52;
+// 300,000 x 70 x 64, root 24.1 and 26.4, 32 leaves 29.7 and 30.1.
 // Small matrices keep one region per tile: they fit the caches anyway, and the build may
 // read up to kEpochRows - 1 rows past the last one, which have to lie inside the buffer: with 128-byte
 // rows that is more than the slack, but with kPlanLinesMinRows rows and the features of two
@@ -106,29 +112,32 @@ GBDT_HD int64_t plan_packed_bytes(const TilePlan& p, int64_t n_rows, int32_t n_f
 // region of 128-byte rows would not fit 32 bits.
 constexpr int64_t kPlanLinesMinRows = 4096;
 constexpr int64_t kPlanLinesMaxRows = ((int64_t)1 << 25) - 1024;
-GBDT_HD int32_t plan_line_tiles(const TilePlan& p, int64_t n_rows) {  // main tiles per row of a region: 1 or 2
-  (void)p;
+GBDT_HD int32_t plan_line_tiles(int64_t n_rows) {  // main tiles per row of a region: 1 or 2
   return n_rows >= kPlanLinesMinRows && n_rows <= kPlanLinesMaxRows ? 2 : 1;
+}
+// ... and whether a main tile left over alone shares its region with the remainder tile.
+GBDT_HD bool plan_leftover_shared(int32_t wm, int32_t n_main, int32_t wr) {
+  return (n_main & 1) != 0 && wr != 0 && wm == 32;
 }
 struct TileAt {
   int64_t off;     // byte offset of the tile's first row
   int32_t stride;  // bytes from a row to the next
+  bool shared;     // the region holds another tile too
 };
 GBDT_HD TileAt plan_tile_at(int32_t wm, int32_t n_main, int32_t wr, int64_t n_rows, int32_t line_tiles, int32_t t) {
   TileAt a;
-  if (line_tiles == 1) {
-    a.off = n_rows * ((int64_t)t * wm);
-    a.stride = t < n_main ? wm : wr;
-    return a;
-  }
   const int32_t paired = n_main & ~1;  // main tiles that share a region with another main tile
-  if (t < paired) {
-    a.off = n_rows * ((int64_t)(t & ~1) * wm) + (int64_t)(t & 1) * wm;
+  int32_t first = t;                   // the region's first tile; the tiles in front of it are main tiles
+  a.stride = t < n_main ? wm : wr;
+  if (line_tiles > 1 && t < paired) {
+    first = t & ~1;
     a.stride = 2 * wm;
-  } else {
-    a.off = n_rows * ((int64_t)paired * wm) + (int64_t)(t - paired) * wm;
-    a.stride = (n_main - paired) * wm + wr;
+  } else if (line_tiles > 1 && plan_leftover_shared(wm, n_main, wr)) {
+    first = paired;
+    a.stride = wm + wr;
   }
+  a.off = n_rows * ((int64_t)first * wm) + (int64_t)(t - first) * wm;
+  a.shared = a.stride > (t < n_main ? wm : wr);
   return a;
 }
 

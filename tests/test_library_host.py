@@ -271,6 +271,63 @@ def test_split_search_plan_covers_every_feature_within_the_lds_budget(n_bins):
             assert 3 * p["group"] <= 256
 
 
+LINE_SHAPES = [(1, 64), (40, 255), (32, 255), (64, 256), (96, 200), (100, 255), (137, 255), (64, 63), (70, 64), (100, 64),
+               (128, 63), (129, 63), (150, 16), (193, 63), (220, 63), (270, 16), (400, 16), (2000, 63)]
+LINE_ROWS = [1, 511, 4095, 4096, 9001, 300_000, 2 ** 25 - 1024, 2 ** 25 - 1023, 40_000_000]
+
+
+@pytest.mark.parametrize("n_features,n_bins", LINE_SHAPES)
+def test_regions_of_tiles(n_features, n_bins):
+    """Where the tiles lie: no byte belongs to two of them and all of them to the row bytes, rows of shared regions
+    are 128 or 64 bytes of whole lines or the 48 of a lone 32-byte tile and its remainder, and what the build
+    reads past the last row is inside the buffer and at 32-bit offsets."""
+    g = B.gbdt_debug_geometry(n_features, n_bins, 1)
+    widths = [g["wm"]] * g["n_main"] + ([g["wr"]] if g["wr"] else [])
+    for n_rows in LINE_ROWS:
+        tiles, _ = B.gbdt_debug_block_map(n_features, n_bins, n_rows, 1, False)
+        total = B.gbdt_bins_packed_bytes(n_rows, n_features, n_bins)
+        regions = {}
+        for t, (off, stride) in enumerate(tiles.tolist()):
+            assert stride in (widths[t], 128, 64, 48) and off % 16 == 0 and stride % 16 == 0
+            base = min(o for o, s in tiles.tolist() if s == stride and o <= off < o + stride)
+            regions.setdefault((base, stride), []).append((off - base, widths[t]))
+            past = -(-n_rows // 512) * 512          # rows up to the end of the last epoch
+            assert past * stride + (off - base) <= 2 ** 32
+            assert off + (past - 1) * stride + widths[t] <= total, (n_rows, t)
+        at = 0
+        for (base, stride), parts in sorted(regions.items()):
+            assert base == at                        # regions back to back, their rows filled by their tiles
+            assert sorted(parts) == [(sum(w for _, w in sorted(parts)[:i]), sorted(parts)[i][1])
+                                     for i in range(len(parts))]
+            assert sum(w for _, w in parts) == stride
+            at += n_rows * stride
+        assert at == n_rows * g["row_bytes"]
+        shared = [len(p) > 1 for p in regions.values()]
+        assert any(shared) == (4096 <= n_rows <= 2 ** 25 - 1024 and
+                               (g["n_main"] >= 2 or (g["wm"] == 32 and len(widths) == 2)))
+
+
+@pytest.mark.parametrize("n_features,n_bins", LINE_SHAPES)
+@pytest.mark.parametrize("by_column", [False, True])
+def test_blocks_of_a_launch(n_features, n_bins, by_column):
+    """Every (tile, workgroup) is one block's, whatever the layout; the two tiles of a region get their workgroups of a
+    column to the same XCD (blocks 8 apart, except in the last few); a remainder tile of its own comes last."""
+    g = B.gbdt_debug_geometry(n_features, n_bins, 1)
+    n_tiles = g["n_main"] + (1 if g["wr"] else 0)
+    for n_rows in (1000, 9001, 2 ** 25):
+        for cols in (1, 3, 7, 8, 9, 100, 147, 512):
+            tiles, blocks = B.gbdt_debug_block_map(n_features, n_bins, n_rows, cols, by_column)
+            at = {tuple(tc): i for i, tc in enumerate(blocks.tolist())}
+            assert set(at) == {(t, c) for t in range(n_tiles) for c in range(cols)}
+            strides = tiles[:, 1].tolist()
+            for t in range(0, n_tiles - 1, 2):
+                if strides[t] > g["wm"]:             # (t, t + 1) share a region
+                    same = [at[t + 1, c] - at[t, c] for c in range(cols)]
+                    assert sum(d != 8 for d in same) <= 7
+            if g["wr"] and strides[-1] == g["wr"]:
+                assert [at[n_tiles - 1, c] for c in range(cols)] == list(range((n_tiles - 1) * cols, n_tiles * cols))
+
+
 def test_cell_counts_are_exact_whatever_the_sums_do():
     """A cell's count and sums share 64 bits.  Sums of magnitudes below 2^26 (what the scale of an epoch
     guarantees when the epoch's sum of magnitudes is a finite fp32 number) come back exactly; beyond that, with
