@@ -341,7 +341,12 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
         }
       }
     }
-    // (the sums were written by this wavefront's own lanes: 3 * group <= 64)
+    // The parent terms need sums that other lanes of the first wavefront wrote, and only those: the fences keep
+    // the compiler from moving the reads up, and no other wavefront has to be waited for.
+    static_assert(3 * kSplitMaxGroup <= 64, "the running sums of a group are the work of one wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (tid < nf) {
       const double G = pg[tid * S + B - 1], H = ph[tid * S + B - 1];
       parent[tid] = __ddiv_rn(__dmul_rn(G, G), H + lambda);
