@@ -519,6 +519,8 @@ int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int
  * column's joint value; *n_cols_out the number of columns.  Host only. */
 int gbdt_debug_fusion_plan(const uint32_t* levels, int32_t n_features, int32_t* col_out, int32_t* stride_out,
                            int32_t* n_cols_out);
+/* Rows gbdt_bins_fuse looks at before it reads the whole matrix, 0: none.  Host only. */
+int64_t gbdt_debug_fuse_sample_rows(int64_t n_rows, int32_t n_features);
 /* Resident workgroups per compute unit of the build kernel variant that serves
  * n_bins (indexed != 0: the variant that gathers through leaf_row_idx), as the HIP
  * runtime reports it on the current device; 0 if the query is not possible. */

@@ -23,7 +23,7 @@ EXPORTS = [
     "gbdt_best_split", "gbdt_workspace_bytes", "gbdt_set_workspace", "gbdt_strerror",
     "gbdt_last_hip_error", "gbdt_debug_geometry", "gbdt_debug_locate",
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
-    "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map",
+    "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -553,6 +553,14 @@ def gbdt_debug_locate(n_features: int, n_bins: int, feature: int):
     _check(load().gbdt_debug_locate(n_features, n_bins, feature, ctypes.byref(t), ctypes.byref(s)),
            "gbdt_debug_locate")
     return t.value, s.value
+
+
+def gbdt_debug_fuse_sample_rows(n_rows: int, n_features: int) -> int:
+    """Rows gbdt_bins_fuse looks at before it reads the whole matrix, 0: none."""
+    lib = load()
+    lib.gbdt_debug_fuse_sample_rows.restype = ctypes.c_int64
+    lib.gbdt_debug_fuse_sample_rows.argtypes = [ctypes.c_int64, ctypes.c_int32]
+    return int(lib.gbdt_debug_fuse_sample_rows(n_rows, n_features))
 
 
 def gbdt_debug_block_map(n_features: int, n_bins: int, n_rows: int, cols: int, by_column: bool):

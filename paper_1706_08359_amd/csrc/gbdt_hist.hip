@@ -224,7 +224,15 @@ constexpr int64_t kFusedMinLeafFraction = 3;
 // A fused copy is made when it has at most this fraction of the features as columns.
 constexpr double kFusedMaxColumnRatio = 0.85;
 constexpr int64_t kFuseSampleRows = 4096;  // rows gbdt_bins_fuse looks at before it reads them all ...
-constexpr int64_t kFuseSampleMinRows = 65536;  // ... of a matrix that takes longer to read than a round trip to the host
+constexpr int64_t kFuseSampleMinRows = 65536;  // ... of a matrix of so many rows ...
+constexpr int64_t kFuseSampleMinBytes = (int64_t)1 << 25;  // ... and bytes
+// (A look is a launch and a round trip to the host more, 24 us where it proves nothing; where it does, the
+// second launch is saved, and the reading.  Looking first from 65,536 rows on, whatever the bytes: 66,000 x 8 x 16, not
+// fused, 48 -> 61 us, and 36 without the look; 1,000,000 x 10 x 16 65 and 40 us.  Provably full: 800,000 x 40 x 64
+// 34 us with and 41 without, 2,000,000 x 40 x 64 34 and about 60.)
+int64_t fuse_sample_rows(int64_t n_rows, int32_t n_features) {
+  return n_rows >= kFuseSampleMinRows && n_rows * n_features >= kFuseSampleMinBytes ? kFuseSampleRows : 0;
+}
 
 // Packs features into columns of at most kFusedCap joint levels: features in descending order
 // of their level counts, each into the fullest column that still takes it (best fit).
@@ -1133,8 +1141,8 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
     }
     return GBDT_OK;
   };
-  if (n_rows >= kFuseSampleMinRows) {
-    const int rc = find_levels(kFuseSampleRows);
+  if (const int64_t sample = fuse_sample_rows(n_rows, n_features)) {
+    const int rc = find_levels(sample);
     if (rc != GBDT_OK) return rc;
     double bits = 0.0;
     for (const uint32_t l : levels) bits += std::log2((double)l);
@@ -2207,6 +2215,10 @@ int gbdt_debug_fusion_plan(const uint32_t* levels, int32_t n_features, int32_t* 
   }
   *n_cols_out = (int32_t)cols.size();
   return GBDT_OK;
+}
+
+int64_t gbdt_debug_fuse_sample_rows(int64_t n_rows, int32_t n_features) {
+  return n_rows > 0 && n_features > 0 ? fuse_sample_rows(n_rows, n_features) : 0;
 }
 
 int gbdt_debug_occupancy(int32_t n_bins, int32_t indexed) {

@@ -44,7 +44,8 @@ def test_pack_block_edges(n_rows, n_features, n_bins):
 @pytest.mark.parametrize("n_features,late", [(40, 16), (1500, 5), (37, 64), (4096, 3), (4097, 4)])
 def test_fuse_sees_levels_of_late_rows(n_features, late):
     """Only bins 0 and 1 at first; in the last rows some features reach `late` levels."""
-    n_rows, nb = 70_001, 64                    # (past the size from which a part is looked at first)
+    n_rows, nb = max(70_001, (1 << 25) // n_features + 1), 64
+    assert 0 < B.gbdt_debug_fuse_sample_rows(n_rows, n_features) < n_rows - 3   # (a part is looked at first)
     print(f"fuse {n_features} features, late levels {late}", flush=True)
     rng = np.random.default_rng(n_features)
     bins = rng.integers(0, 2, size=(n_rows, n_features)).astype(np.uint8)
@@ -57,9 +58,20 @@ def test_fuse_sees_levels_of_late_rows(n_features, late):
     same_root(packed, bins, nb, *exact_stats(rng, n_rows))
 
 
-def test_fuse_gives_up_on_full_features():
-    """63 levels everywhere: no two features fit a column, and none are fused."""
+@pytest.mark.parametrize("n_rows,looks_first", [(9000, False), ((1 << 25) // 50, False), ((1 << 25) // 50 + 1, True)])
+def test_fuse_gives_up_on_full_features(n_rows, looks_first):
+    """63 levels everywhere: no two features fit a column, and none are fused, whether the first rows already prove
+    it or the whole matrix is read; levels that only late rows show are no reason to give up early."""
+    assert (B.gbdt_debug_fuse_sample_rows(n_rows, 50) > 0) == looks_first
     rng = np.random.default_rng(1)
-    bins = torch.from_numpy(rng.integers(0, 63, size=(9000, 50)).astype(np.uint8)).to(DEV)
+    bins = torch.from_numpy(rng.integers(0, 63, size=(n_rows, 50)).astype(np.uint8)).to(DEV)
     packed = B.gbdt_bins_pack(bins, 63, fuse=False)
     assert B.gbdt_bins_fuse(bins, 63, packed) == (0, None)
+    bins %= 4
+    bins[-1] = 62                              # (one row, the last: read only with the whole matrix)
+    packed = B.gbdt_bins_pack(bins, 63, fuse=False)
+    assert B.gbdt_bins_fuse(bins, 63, packed) == (0, None)
+    bins[-1] = 3
+    packed = B.gbdt_bins_pack(bins, 63, fuse=False)
+    n_cols, fused = B.gbdt_bins_fuse(bins, 63, packed)
+    assert n_cols == B.gbdt_debug_fusion_plan(np.full(50, 4, np.uint32))[2] and fused is not None

@@ -251,6 +251,14 @@ def test_fusion_plan_is_a_valid_mixed_radix_packing():
     assert n_cols == 9
 
 
+def test_fuse_reads_small_matrices_once():
+    """Looking at some rows first costs a round trip to the host: not for a matrix that is read in less."""
+    assert B.gbdt_debug_fuse_sample_rows(66_000, 8) == 0 and B.gbdt_debug_fuse_sample_rows(1_000_000, 10) == 0
+    assert B.gbdt_debug_fuse_sample_rows(60_000, 4000) == 0
+    for n_rows, n_features in ((400_000, 2000), (3_000_000, 700), (65_536, 512)):
+        assert 0 < B.gbdt_debug_fuse_sample_rows(n_rows, n_features) <= n_rows // 16
+
+
 @pytest.mark.parametrize("n_bins", [2, 16, 63, 64, 100, 255, 256])
 def test_split_search_plan_covers_every_feature_within_the_lds_budget(n_bins):
     """The work split of the split search follows the number of histograms of the launch; whatever
