@@ -24,6 +24,7 @@ EXPORTS = [
     "gbdt_last_hip_error", "gbdt_debug_geometry", "gbdt_debug_locate",
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
     "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
+    "gbdt_debug_leaf_plan",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -553,6 +554,18 @@ def gbdt_debug_locate(n_features: int, n_bins: int, feature: int):
     _check(load().gbdt_debug_locate(n_features, n_bins, feature, ctypes.byref(t), ctypes.byref(s)),
            "gbdt_debug_locate")
     return t.value, s.value
+
+
+def gbdt_debug_leaf_plan(n_rows: int, n_features: int, n_bins: int, n_leaf_rows: int, indexed: bool) -> dict:
+    """How gbdt_hist_build shares out a leaf on the current device, in the modes set."""
+    lib = load()
+    out = (ctypes.c_int64 * 6)()
+    lib.gbdt_debug_leaf_plan.restype = ctypes.c_int
+    lib.gbdt_debug_leaf_plan.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
+                                         ctypes.c_void_p, ctypes.c_int32]
+    _check(lib.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf_rows, 1 if indexed else 0, out, 6),
+           "gbdt_debug_leaf_plan")
+    return dict(zip(("wgs", "unit_epochs", "first_epochs", "fixed_stride", "deal_lines", "one_unit_each"), out))
 
 
 def gbdt_debug_fuse_sample_rows(n_rows: int, n_features: int) -> int:

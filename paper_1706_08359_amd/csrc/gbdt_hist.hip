@@ -438,6 +438,35 @@ BuildGeom make_geom(int32_t n_features, int32_t n_bins, int64_t n_leaf, int cus,
   return g;
 }
 
+// How the workgroups of a tile share out a leaf's epochs, and how the launch's blocks are dealt out.
+struct UnitPlan {
+  int32_t unit_epochs;
+  int32_t first_epochs;  // 0, or the length of every workgroup's first unit
+  int32_t fixed_stride;  // 0: units from the tile's counter
+  int32_t deal_lines;    // by lines (batch_plan.h)
+};
+UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool deterministic) {
+  UnitPlan u;
+  u.unit_epochs = g.unit_epochs;
+  u.first_epochs = 0;
+  if (!g.one_unit_each) {
+    const int64_t n_epochs = (n_leaf + kEpochRows - 1) / kEpochRows;
+    if (deterministic) {  // an even split: the same sums in every run, and rows stay together
+      u.unit_epochs = (int32_t)((n_epochs + g.wgs - 1) / g.wgs);
+    } else {
+      const int32_t first = (int32_t)(n_epochs * kFirstUnitPercent / 100 / g.wgs);
+      if (first >= kUnitEpochs) {
+        u.first_epochs = first;
+        u.unit_epochs = kTailUnitEpochs;
+      }
+    }
+  }
+  // no counter when every workgroup has one unit anyway, or when the split must be fixed
+  u.fixed_stride = (g.one_unit_each || deterministic) ? g.wgs : 0;
+  u.deal_lines = line_tiles > 1 && u.unit_epochs > 1;
+  return u;
+}
+
 // Kernel variants: bin capacity -> (main tile width, 4-bit, waves per SIMD the
 // register budget is set for).
 #define GBDT_VARIANT_16 16, 64, true, kBuildThreads, 8, double
@@ -624,6 +653,7 @@ struct BatchPlan {
   BatchLeaf leaf[kBatchLeaves];  // most epochs per workgroup first
   int n = 0;
   uint32_t total_wgs = 0;  // workgroups per tile over all leaves
+  int most_unit_epochs = 1;
 };
 constexpr double kBatchColumnEpochs = 3.0;
 constexpr double kBatchMergeEpochs = 2.0;
@@ -680,6 +710,7 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
     unit[i] = 1;
     order[i] = i;
     if (epochs[i] > 0) plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
+    if (unit[i] > b.most_unit_epochs) b.most_unit_epochs = unit[i];
   }
   std::sort(order, order + n, [&](int x, int y) {  // (equal ones in the call's order)
     const int64_t a = (int64_t)epochs[x] * (wgs[y] > 0 ? wgs[y] : 1), b2 = (int64_t)epochs[y] * (wgs[x] > 0 ? wgs[x] : 1);
@@ -957,22 +988,11 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.line_tiles = line_tiles;
   a.wgs = g.wgs;
   a.chunks = g.wgs * g.blocks_per_wg;
-  a.unit_epochs = g.unit_epochs;
-  a.first_epochs = 0;
-  if (!g.one_unit_each) {
-    const int64_t n_epochs = (n_leaf_rows + kEpochRows - 1) / kEpochRows;
-    if (g_deterministic.load()) {  // an even split: the same sums in every run, and rows stay together
-      a.unit_epochs = (int32_t)((n_epochs + g.wgs - 1) / g.wgs);
-    } else {
-      const int32_t first = (int32_t)(n_epochs * kFirstUnitPercent / 100 / g.wgs);
-      if (first >= kUnitEpochs) {
-        a.first_epochs = first;
-        a.unit_epochs = kTailUnitEpochs;
-      }
-    }
-  }
-  // no counter when every workgroup has one unit anyway, or when the split must be fixed
-  a.fixed_stride = (g.one_unit_each || g_deterministic.load()) ? g.wgs : 0;
+  const UnitPlan u = plan_units(g, n_leaf_rows, line_tiles, g_deterministic.load());
+  a.unit_epochs = u.unit_epochs;
+  a.first_epochs = u.first_epochs;
+  a.fixed_stride = u.fixed_stride;
+  a.deal_lines = u.deal_lines;
   a.direct_out = (g.wgs == 1 && !fused) ? hist_out : nullptr;  // (joint histograms always take the reduction pass)
   a.n_features = n_features;
   a.n_bins = n_bins;
@@ -1351,6 +1371,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_main = p.n_main;
       a.wr = p.wr;
       a.line_tiles = plan_line_tiles(n_rows);
+      a.deal_lines = a.line_tiles > 1 && b.most_unit_epochs > 1;
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -2151,6 +2172,18 @@ int gbdt_debug_geometry(int32_t n_features, int32_t n_bins, int64_t n_leaf_rows,
   return GBDT_OK;
 }
 
+int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int64_t n_leaf_rows, int32_t indexed,
+                         int64_t* out, int32_t n_out) {
+  if (!valid_shape(n_rows, n_features, n_bins) || n_leaf_rows < 0 || !out || n_out < 6) return GBDT_EINVAL;
+  const bool wide = g_wide.load() != 0;
+  const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
+                                build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, indexed != 0, wide), wide);
+  const UnitPlan u = plan_units(g, n_leaf_rows, plan_line_tiles(n_rows), g_deterministic.load());
+  const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal_lines, g.one_unit_each};
+  for (int i = 0; i < 6; ++i) out[i] = v[i];
+  return GBDT_OK;
+}
+
 int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* leaf_offsets,
                           int32_t n_leaves, int32_t n_cus, int32_t wg_per_cu, int32_t* leaf_wgs_out,
                           int32_t* leaf_unit_epochs_out, int32_t* block_out, int32_t max_blocks) {
@@ -2170,7 +2203,8 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
   const int64_t blocks = (int64_t)b.total_wgs * n_tiles;
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
     const BatchBlock k = batch_block(b.leaf, n_leaves, p.wm, p.n_main, p.wr,
-                                     plan_line_tiles(kPlanLinesMinRows), b.total_wgs, (uint32_t)i);
+                                     plan_line_tiles(kPlanLinesMinRows) > 1 && b.most_unit_epochs > 1, b.total_wgs,
+                                     (uint32_t)i);
     block_out[3 * i] = (int32_t)batch_leaf_no(b.leaf[k.leaf]);
     block_out[3 * i + 1] = k.tile;
     block_out[3 * i + 2] = k.wg;
@@ -2193,7 +2227,7 @@ int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int
   const int64_t blocks = (int64_t)n_tiles * cols;
   if (blocks >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
-    const LineBlock b = line_block(p.wm, p.n_main, p.wr, line_tiles, (uint32_t)cols, by_column != 0, (uint32_t)i);
+    const LineBlock b = line_block(p.wm, p.n_main, p.wr, line_tiles > 1, (uint32_t)cols, by_column != 0, (uint32_t)i);
     block_out[2 * i] = b.tile;
     block_out[2 * i + 1] = (int32_t)b.col;
   }

@@ -1,7 +1,8 @@
 """Feature tiles that share the rows of one region (two 64-byte or two 32-byte tiles a row, and the
 tiles that are left over together): every combination of whole lines, a lone main tile and a remainder
 tile, on both sides of the row count from which tiles share rows, built as a root, as an index list, in a
-batch with empty, short and long leaves, and partitioned by a feature of every tile.
+batch with empty, short and long leaves, and partitioned by a feature of every tile; dealt out by lines and not;
+long leaves whose workgroups start with a long unit.
 
 The gradients are multiples of 1/2 and the hessians of 1/4, so every sum is exact and has to agree
 with the oracle bit for bit."""
@@ -61,6 +62,49 @@ def test_lines_of_tiles(n_rows, n_features, n_bins):
         left, right = orc.partition_rows(bins, f, n_bins // 2, idx)
         assert int(n_left.item()) == left.size
         assert np.array_equal(kids.cpu().numpy()[:idx.size], np.concatenate([left, right])), f
+
+
+def rows_for(n_features, n_bins, epochs_each):
+    """Rows of a root that gives every workgroup `epochs_each` epochs on this device, wide accumulation or not."""
+    tiles, _ = B.gbdt_debug_block_map(n_features, n_bins, 1, 1, False)
+    g = B.gbdt_debug_geometry(n_features, n_bins, 1)
+    most = max(B.gbdt_debug_occupancy(g["cap"], i) for i in (False, True))
+    n_cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return int(most * n_cus // len(tiles) * epochs_each * 512) + 1
+
+
+def check_features(p, got_t, feats, idx, what):
+    got = B.hist_to_numpy(got_t)
+    ref = p.oracle(idx, features=feats)
+    for j, f in enumerate(feats):
+        for k in ("grad", "hess", "count"):
+            assert np.array_equal(got[k][f].astype(np.float64), ref[k][j].astype(np.float64)), (what, f, k)
+
+
+@pytest.mark.parametrize("n_features,n_bins", SHAPES)
+def test_lines_of_tiles_dealt_out(n_features, n_bins):
+    """Leaves of two or three epochs a workgroup: the blocks are dealt out by shared lines (shorter leaves, as above, are
+    not), the first and last feature of every tile checked."""
+    n_rows = rows_for(n_features, n_bins, 2.5)
+    print(f"dealt {n_rows} x {n_features}, {n_bins} bins", flush=True)
+    plan = B.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_rows, False)
+    assert plan["deal_lines"] == 1 and plan["unit_epochs"] in (2, 3)
+    p, rng = problem(n_rows, n_features, n_bins)
+    first = {}
+    for f in range(n_features):
+        first.setdefault(B.gbdt_debug_locate(n_features, n_bins, f)[0], []).append(f)
+    feats = sorted({f for fs in first.values() for f in (fs[0], fs[-1])})
+    check_features(p, p.build(), feats, None, "root")
+    idx = np.sort(rng.choice(n_rows, size=n_rows - n_rows // 8, replace=False)).astype(np.int32)
+    check_features(p, p.build(idx), feats, idx, "list")
+    offs = np.array([0, n_rows // 3, n_rows // 3, n_rows // 3 + 5, idx.size])
+    perm = np.concatenate([np.sort(part) for part in np.split(rng.permutation(idx), offs[1:-1])]).astype(np.int32)
+    wgs, ue, _ = B.gbdt_debug_batch_plan(n_features, n_bins, offs, 256, B.gbdt_debug_occupancy(n_bins, True))
+    assert ue.max() > 1
+    hists = B.gbdt_hist_build_batch(p.packed, n_rows, n_features, n_bins, torch.from_numpy(perm).to(p.dev), offs,
+                                    p.grad, p.hess)
+    for l in range(len(offs) - 1):
+        check_features(p, hists[l], feats, perm[offs[l]:offs[l + 1]], f"leaf {l}")
 
 
 @pytest.mark.parametrize("n_features,n_bins", [(210, 63), (137, 255), (270, 16)])
