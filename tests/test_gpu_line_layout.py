@@ -110,18 +110,30 @@ def test_lines_of_tiles_dealt_out(n_features, n_bins):
 @pytest.mark.parametrize("n_features,n_bins", [(210, 63), (137, 255), (270, 16)])
 def test_long_leaf_starts_with_long_units(n_features, n_bins):
     """Enough epochs that every workgroup starts with one long unit and takes short ones after it, with
-    rows at the very end of the leaf, in the default and in the bit-reproducible mode."""
-    n_rows = 1_200_001
+    rows at the very end of the leaf, as a root and as a list, in the default mode, in the bit-reproducible one (one
+    even unit each) and with wide accumulation."""
+    n_rows = rows_for(n_features, n_bins, 16)
     print(f"long leaf {n_rows} x {n_features}, {n_bins} bins", flush=True)
     p, rng = problem(n_rows, n_features, n_bins)
     feats = [0, n_features // 2, n_features - 1]
-    ref = p.oracle(features=feats)
-    for det in (False, True):
+    idx = np.nonzero(rng.random(n_rows) < 0.9)[0].astype(np.int32)
+    idx[-1] = n_rows - 1
+    for det, wide in ((False, False), (True, False), (False, True), (True, True)):
         B.gbdt_set_deterministic(det)
+        B.gbdt_set_wide_accumulation(wide)
         try:
-            got = B.hist_to_numpy(p.build())
+            for rows in (None, idx):
+                n_leaf = n_rows if rows is None else rows.size
+                plan = B.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf, rows is not None)
+                n_epochs = -(-n_leaf // 512)
+                assert plan["one_unit_each"] == 0 and plan["deal_lines"] == 1
+                if det:
+                    assert plan["first_epochs"] == 0 and plan["fixed_stride"] == plan["wgs"]
+                    assert plan["unit_epochs"] == -(-n_epochs // plan["wgs"])
+                else:
+                    assert plan["first_epochs"] >= 4 and plan["fixed_stride"] == 0 and plan["unit_epochs"] >= 3
+                    assert plan["first_epochs"] * plan["wgs"] < n_epochs
+                check_features(p, p.build(rows), feats, rows, (det, wide, rows is None))
         finally:
             B.gbdt_set_deterministic(False)
-        for j, f in enumerate(feats):
-            for k in ("grad", "hess", "count"):
-                assert np.array_equal(got[k][f].astype(np.float64), ref[k][j].astype(np.float64)), (det, f, k)
+            B.gbdt_set_wide_accumulation(False)
