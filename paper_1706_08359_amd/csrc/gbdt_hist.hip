@@ -664,28 +664,33 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
   BatchPlan b;
   b.n = n;
   uint32_t epochs[kBatchLeaves], most = 1;  // (leaves hold fewer than 2^31 rows)
+  uint32_t longer[kBatchLeaves];  // the leaves whose columns depend on T: those of more than kDirectEpochs epochs
   int64_t total_epochs = 0;
-  int n_live = 0;
+  int n_live = 0, n_long = 0;
   for (int i = 0; i < n; ++i) {
     epochs[i] = (uint32_t)((leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] + kEpochRows - 1) / kEpochRows);
     total_epochs += epochs[i];
     if (epochs[i] > most) most = epochs[i];
     n_live += epochs[i] > 0;
+    if (epochs[i] > (uint32_t)kDirectEpochs) longer[n_long++] = epochs[i];
   }
   int64_t budget = resident / n_tiles;
   if (budget < 1) budget = 1;
   uint32_t t = most;
   double t_cost = 1e300;
   auto consider = [&](uint32_t cand) {
-    int64_t columns = 0, blocks = 0;  // blocks of sums that a reduction pass moves
-    for (int i = 0; i < n; ++i) {
-      const uint32_t w = epochs[i] <= (uint32_t)kDirectEpochs ? (epochs[i] > 0) : (epochs[i] + cand - 1) / cand;
+    // ceil(e / cand) by a multiplication: e and cand are below 2^22, so quotients that are no whole numbers are
+    // at least 2^-22 away from one, and 2^-24 covers the rounding of those that are
+    const double inv = 1.0 / (double)cand;
+    uint32_t columns = (uint32_t)(n_live - n_long), blocks = 0;  // blocks: of sums that a reduction pass moves
+    for (int i = 0; i < n_long; ++i) {
+      const uint32_t w = (uint32_t)((int32_t)((double)(int32_t)(longer[i] + cand - 1) * inv + 0x1p-24));
       columns += w;
-      if (w > 1) blocks += 2 * w + 1;
+      blocks += w > 1 ? 2 * w + 1 : 0;
     }
-    if (columns > budget + n_live) return;  // (the bound that the scratch is sized by)
+    if ((int64_t)columns > budget + n_live) return;  // (the bound that the scratch is sized by)
     double cost = (double)cand + kBatchColumnEpochs;
-    if (columns > budget) {
+    if ((int64_t)columns > budget) {
       const double dealt =
           ((double)total_epochs + kBatchColumnEpochs * (double)columns) / (double)budget + 0.5 * (double)cand;
       if (dealt > cost) cost = dealt;
@@ -696,26 +701,38 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
       t = cand;
     }
   };
-  consider(most);
-  const double average = (double)total_epochs / (double)budget;
-  if (most <= (uint32_t)kDirectEpochs) t = most;  // (every leaf has one column whatever T is)
-  else for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
-    const double cand = std::ceil(average * factor);
-    if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
+  if (n_long > 0) {  // (else every leaf has one column whatever T is)
+    consider(most);
+    const double average = (double)total_epochs / (double)budget;
+    for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
+      const double cand = std::ceil(average * factor);
+      if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
+    }
   }
-  int order[kBatchLeaves], wgs[kBatchLeaves], unit[kBatchLeaves];
+  int wgs[kBatchLeaves], unit[kBatchLeaves];
+  uint32_t each[kBatchLeaves], most_each = 0;  // epochs of a leaf's busiest workgroup
   for (int i = 0; i < n; ++i) {
-    bool one_each = false;
-    wgs[i] = 0;
-    unit[i] = 1;
-    order[i] = i;
-    if (epochs[i] > 0) plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
+    if (epochs[i] <= (uint32_t)kDirectEpochs) {  // (as plan_leaf_units has it)
+      wgs[i] = epochs[i] > 0;
+      unit[i] = epochs[i] > 0 ? (int)epochs[i] : 1;
+      each[i] = epochs[i];
+    } else {
+      bool one_each = false;
+      plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
+      each[i] = one_each ? (uint32_t)unit[i] : (epochs[i] + (uint32_t)wgs[i] - 1) / (uint32_t)wgs[i];
+    }
+    if (each[i] > most_each) most_each = each[i];
     if (unit[i] > b.most_unit_epochs) b.most_unit_epochs = unit[i];
   }
-  std::sort(order, order + n, [&](int x, int y) {  // (equal ones in the call's order)
-    const int64_t a = (int64_t)epochs[x] * (wgs[y] > 0 ? wgs[y] : 1), b2 = (int64_t)epochs[y] * (wgs[x] > 0 ? wgs[x] : 1);
-    return a != b2 ? a > b2 : x < y;
-  });
+  // the longest first, to within 1/128 of the longest (equal ones in the call's order): a counting sort,
+  // because a call of many short leaves takes about as long on the host as on the device
+  int shift = 0;
+  while ((most_each >> shift) > 255u) ++shift;
+  uint16_t place[257] = {0};  // place[k + 1] ends as the first place of key k, keys descending
+  for (int i = 0; i < n; ++i) ++place[256 - (each[i] >> shift)];
+  for (int k = 1; k <= 256; ++k) place[k] = (uint16_t)(place[k] + place[k - 1]);
+  int order[kBatchLeaves];
+  for (int i = 0; i < n; ++i) order[place[255 - (each[i] >> shift)]++] = i;
   uint32_t first = 0;
   for (int k = 0; k < n; ++k) {
     const int i = order[k];

@@ -195,6 +195,10 @@ def test_batched_launch_plan_covers_every_leaf_exactly(n_features, n_bins, wg_pe
             # workgroup c takes units c, c + wgs, ...: together all units, each once
             taken = sorted(u for c in range(wgs[l]) for u in range(c, n_units, int(wgs[l])))
             assert taken == list(range(n_units))
+        # the longest workgroups start first, to within 1/128 of the longest
+        each = [-(-int(sizes[l]) // 512) / wgs[l] if wgs[l] else 0.0 for l in range(n_leaves)]
+        starts = list(dict.fromkeys(blocks[blocks[:, 1] == 0][:, 0].tolist()))
+        assert all(each[b] <= each[a] + 1 + max(each) / 128 for a, b in zip(starts, starts[1:]))
         # the leaves share the machine: about one machine-full of workgroup columns, plus the
         # at-least-one of every leaf
         assert int(wgs.sum()) <= 256 * wg_per_cu // n_tiles + n_leaves
