@@ -39,8 +39,13 @@ static_assert(kBatchLeaves <= 256, "a leaf's number has 8 bits");
 // behind the other then and find its line there, both wait for the same one at the same time, and the
 // tiles are better spread over the XCDs: 50,000 x 500 x 64, two leaves of half the rows together 21.5 us dealt
 // by lines, 20.1 so; 30,000 x 1,000 x 64, half of the rows 21.1 and 19.9.  With two epochs each it is the other way round
-// (30,000 x 1,000 x 64, all rows: 21.4 us dealt by lines, 24.4 so).
+// (30,000 x 1,000 x 64, all rows: 21.4 us dealt by lines, 24.4 so) unless the launch leaves CUs without a workgroup, as
+// only those with one workgroup a CU do: latency counts there, not traffic (256 bins, wide accumulation, 172 blocks: 700,000 x
+// 50, an eighth of the rows 20.3 us dealt by lines, 17.7 so; 144 blocks, 300,000 x 500, a 32nd 37.9 and 35.3).
 constexpr uint32_t kXcds = 8;
+GBDT_HD bool lines_pay(int32_t unit_epochs, int64_t blocks, int32_t cus) {
+  return unit_epochs > 2 || (unit_epochs == 2 && blocks >= cus);
+}
 struct LineBlock {
   int32_t tile;
   uint32_t col;

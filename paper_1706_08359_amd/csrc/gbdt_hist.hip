@@ -445,7 +445,7 @@ struct UnitPlan {
   int32_t fixed_stride;  // 0: units from the tile's counter
   int32_t deal_lines;    // by lines (batch_plan.h)
 };
-UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool deterministic) {
+UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool deterministic, int cus) {
   UnitPlan u;
   u.unit_epochs = g.unit_epochs;
   u.first_epochs = 0;
@@ -463,7 +463,7 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool
   }
   // no counter when every workgroup has one unit anyway, or when the split must be fixed
   u.fixed_stride = (g.one_unit_each || deterministic) ? g.wgs : 0;
-  u.deal_lines = line_tiles > 1 && u.unit_epochs > 1;
+  u.deal_lines = line_tiles > 1 && lines_pay(g.unit_epochs, (int64_t)g.wgs * plan_n_tiles(g.plan), cus);
   return u;
 }
 
@@ -1005,7 +1005,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.line_tiles = line_tiles;
   a.wgs = g.wgs;
   a.chunks = g.wgs * g.blocks_per_wg;
-  const UnitPlan u = plan_units(g, n_leaf_rows, line_tiles, g_deterministic.load());
+  const UnitPlan u = plan_units(g, n_leaf_rows, line_tiles, g_deterministic.load(), device_cu_count());
   a.unit_epochs = u.unit_epochs;
   a.first_epochs = u.first_epochs;
   a.fixed_stride = u.fixed_stride;
@@ -1388,7 +1388,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_main = p.n_main;
       a.wr = p.wr;
       a.line_tiles = plan_line_tiles(n_rows);
-      a.deal_lines = a.line_tiles > 1 && b.most_unit_epochs > 1;
+      a.deal_lines = a.line_tiles > 1 && lines_pay(b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, device_cu_count());
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -2195,7 +2195,7 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
   const bool wide = g_wide.load() != 0;
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
                                 build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, indexed != 0, wide), wide);
-  const UnitPlan u = plan_units(g, n_leaf_rows, plan_line_tiles(n_rows), g_deterministic.load());
+  const UnitPlan u = plan_units(g, n_leaf_rows, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
   const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal_lines, g.one_unit_each};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
   return GBDT_OK;
@@ -2218,10 +2218,10 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
     leaf_unit_epochs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_unit_epochs(b.leaf[l]);
   }
   const int64_t blocks = (int64_t)b.total_wgs * n_tiles;
+  const bool deal = plan_line_tiles(kPlanLinesMinRows) > 1 && lines_pay(b.most_unit_epochs, blocks, n_cus);
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
     const BatchBlock k = batch_block(b.leaf, n_leaves, p.wm, p.n_main, p.wr,
-                                     plan_line_tiles(kPlanLinesMinRows) > 1 && b.most_unit_epochs > 1, b.total_wgs,
-                                     (uint32_t)i);
+                                     deal, b.total_wgs, (uint32_t)i);
     block_out[3 * i] = (int32_t)batch_leaf_no(b.leaf[k.leaf]);
     block_out[3 * i + 1] = k.tile;
     block_out[3 * i + 2] = k.wg;
