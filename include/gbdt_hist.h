@@ -390,8 +390,10 @@ typedef struct {
  *   max_leaves       >= 1; growth also stops when no open leaf has an admissible split
  *   scratch          DEVICE, 256-byte aligned, gbdt_grow_tree_scratch_bytes(...) bytes
  *                    (two row lists, half a row list for the smaller children of a round,
- *                    about 3 x max_leaves histograms, the split records); the calls inside
- *                    also use the library's scratch workspace
+ *                    about 3 x max_leaves histograms, the split records, and for large matrices of few
+ *                    features 8 bytes per row for gradient and hessian side by side; a buffer without
+ *                    room for those last still serves, slower); the calls inside also use the
+ *                    library's scratch workspace
  *   nodes_out        HOST gbdt_tree_node_t [2 * max_leaves - 1]
  *   n_nodes_out      HOST, receives the number of nodes written (always odd)
  *   row_order_out    DEVICE int32 [n_rows] or NULL: all row ids, grouped by leaf, ascending
@@ -399,7 +401,8 @@ typedef struct {
  * Unlike the other calls this one WAITS for `stream` (once per round, to read the new split
  * records) and allocates a few KB of page-locked host memory on first use.  The histograms
  * of a round are built by gbdt_hist_build_batch, whose split of rows among workgroups is
- * fixed: the same call gives the same tree, bit for bit, every time.
+ * fixed; the root's is built by gbdt_hist_build, so that with gbdt_set_deterministic the same call
+ * gives the same tree, bit for bit, every time.
  */
 int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, int32_t n_bins,
                    const float* grad, const float* hess, int32_t max_leaves, float lambda,
@@ -414,9 +417,9 @@ size_t gbdt_grow_tree_scratch_bytes(int64_t n_rows, int32_t n_features, int32_t 
  * number of leaves (Sec. 5 runs its comparison trainers with a maximum depth of 8): every
  * node of the current level whose best split is admissible and gains more than
  * min_split_gain is split.  A whole level costs a handful of launches whatever its width:
- * one batched split search and one read-back of the level's records, one batched
- * partition, one batched histogram build of all the smaller children, one subtraction
- * kernel for their siblings.  Nodes are numbered level by level, the children of a level
+ * one batched split search, which first forms the siblings of the level (levels of more than
+ * 1,024 nodes: a subtraction kernel of its own), and one read-back of the level's records, one batched
+ * partition, one batched histogram build of all the smaller children.  Nodes are numbered level by level, the children of a level
  * in the order of their parents, left first (parents precede children).
  *   max_depth        0 .. 16; at most 2^max_depth leaves
  *   scratch          DEVICE, 256-byte aligned, gbdt_grow_tree_depthwise_scratch_bytes(...)

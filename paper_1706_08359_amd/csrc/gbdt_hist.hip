@@ -764,6 +764,9 @@ int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, 
                        const_cast<gbdt_bin_t*>(hists), hist_stride, n_features, n_bins, sg.group, sg.passes,
                        (double)lambda, (double)min_child_hess, (SplitCand*)ws, splits_out, host_mirror, sib);
   };
+  // The short prefix loop of launches of many workgroups also serves all groups of more than four steps: these are only
+  // formed by launches of about 450 workgroups and more (split_grouping), where it is as fast as the one that reads ahead
+  // or a little faster (200 features x 256 bins, 13 histograms 12.6 and 12.8 us, 32 histograms 23.8 and 24.1).
   const bool many = (int64_t)sg.n_wg * n_hists > kSplitManyWgs;
   if (siblings) {
     launch(few_steps ? (many ? split_gain_kernel<4, true, SplitSiblings> : split_gain_kernel<4, false, SplitSiblings>)
@@ -1109,9 +1112,6 @@ int gbdt_bins_pack(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   const TilePlan p = make_tile_plan(n_features, n_bins);
   const int tiles = plan_n_tiles(p);
   if (tiles > 65535) return GBDT_EUNSUPPORTED;
-  const int64_t max_words = n_rows * (p.wm / 4);
-  const int64_t bx = (max_words + 255) / 256;
-  if (bx >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
   if ((n_features + 63) / 64 > 65535) return GBDT_EUNSUPPORTED;
   const dim3 grid((unsigned)((n_rows + kPackRows - 1) / kPackRows),
                   (unsigned)((n_features + kPackFeatures - 1) / kPackFeatures));
@@ -1451,8 +1451,8 @@ size_t gbdt_hist_build_batch_workspace_bytes(int32_t n_features, int32_t n_bins,
                                   : (p.cap == 64 ? variant_column_words<GBDT_VARIANT_64>(p)
                                                  : variant_column_words<GBDT_VARIANT_256>(p))) *
                      (wide ? 2 : 1);
-  // every leaf of a launch gets its share of the resident workgroups, rounded down, but
-  // at least one workgroup per tile
+  // the leaves of a launch share the resident workgroups, and each has at least one per tile: plan_batch takes
+  // no plan of more columns than that
   int64_t budget = resident / n_tiles;
   if (budget < 1) budget = 1;
   const int64_t per_launch = n_leaves < kBatchLeaves ? n_leaves : kBatchLeaves;
