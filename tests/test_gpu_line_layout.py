@@ -137,3 +137,39 @@ def test_long_leaf_starts_with_long_units(n_features, n_bins):
         finally:
             B.gbdt_set_deterministic(False)
             B.gbdt_set_wide_accumulation(False)
+
+
+@pytest.mark.parametrize("n_rows", [2 ** 25 - 1024, 2 ** 25 - 1023])
+def test_largest_shared_regions(n_rows):
+    """The last row count whose byte offsets in a region of 128-byte rows fit 32 bits, and the first with a region per
+    tile: the root, a list with the last rows, and the short-list partition by a feature of the second tile.
+    (97 features of one byte are two tiles of 64; the reference is computed on the device, from exact sums.)"""
+    F, nb, dev = 97, 64, torch.device("cuda:0")
+    print(f"largest regions {n_rows} x {F}", flush=True)
+    tiles, _ = B.gbdt_debug_block_map(F, nb, n_rows, 1, False)
+    assert tiles[:, 1].tolist() == ([128, 128] if n_rows == 2 ** 25 - 1024 else [64, 64])
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(4)
+    bins = torch.randint(0, nb, (n_rows, F), generator=gen, device=dev, dtype=torch.uint8)
+    grad = torch.randint(-2, 3, (n_rows,), generator=gen, device=dev).float() * 0.5
+    hess = torch.randint(1, 4, (n_rows,), generator=gen, device=dev).float() * 0.25
+    packed = B.gbdt_bins_pack(bins, nb, fuse=False)
+    idx = torch.cat([torch.randperm(n_rows - 3000, generator=gen, device=dev)[:150_000].sort().values,
+                     torch.arange(n_rows - 3000, n_rows, device=dev)]).to(torch.int32)
+    for rows in (None, idx):
+        n_leaf = n_rows if rows is None else rows.numel()
+        got = B.gbdt_hist_build(packed, n_rows, F, nb, rows, n_leaf, grad, hess)
+        for f in (0, 63, 64, 96):
+            col = bins[:, f] if rows is None else bins[rows.long(), f]
+            g, h = (grad, hess) if rows is None else (grad[rows.long()], hess[rows.long()])
+            for b in range(nb):
+                at = col == b
+                assert int(got.view(torch.int32)[f, b, 2]) == int(at.sum()), (f, b)
+                assert float(got[f, b, 0]) == float(g[at].sum(dtype=torch.float64)), (f, b)
+                assert float(got[f, b, 1]) == float(h[at].sum(dtype=torch.float64)), (f, b)
+    short = idx[-6000:].contiguous()
+    for f in (63, 64, 96):
+        kids, n_left = B.gbdt_partition_rows(packed, n_rows, F, nb, short, short.numel(), B.split_record(f, 30, dev))
+        left = bins[short.long(), f] <= 30
+        assert int(n_left) == int(left.sum())
+        assert torch.equal(kids[:short.numel()], torch.cat([short[left], short[~left]]))
