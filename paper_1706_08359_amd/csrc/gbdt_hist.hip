@@ -400,6 +400,10 @@ void plan_leaf_units(int64_t n_epochs, int64_t budget, int* wgs_out, int* unit_e
 // epochs handed out from the start: categorical root (fused columns) 289 -> 258 us, dense_wide root with a
 // region per tile 176 -> 170 us, dense_tall root 129 -> 124 us; 85 to 98 % are within 2 % of each other, and
 // tiles that share lines want the most (dense_wide root 181 us at 85 %, 179 at 95).
+// Not so a list whose tiles share no lines (a lone tile, fused columns, the largest matrices): hundreds of
+// stretches of scattered rows at once are a little slower than one front of small units that goes through the list.
+// 40,000,000 x 60 x 64, a list of half the rows: 439 us with long first units, 415 with units of 4 epochs (and 498 /
+// 466 on a first pass); the fused columns of 3,000,000 x 700 x 16, half of the rows: 222 / 214 and 269 / 256.
 constexpr int kFirstUnitPercent = 95;
 constexpr int kTailUnitEpochs = 3;  // the fewest the pipeline's look-ahead allows
 static_assert(kTailUnitEpochs >= 3, "a unit's successor is taken in its third-last epoch");
@@ -445,7 +449,7 @@ struct UnitPlan {
   int32_t fixed_stride;  // 0: units from the tile's counter
   int32_t deal_lines;    // by lines (batch_plan.h)
 };
-UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool deterministic, int cus) {
+UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t line_tiles, bool deterministic, int cus) {
   UnitPlan u;
   u.unit_epochs = g.unit_epochs;
   u.first_epochs = 0;
@@ -455,7 +459,8 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, int32_t line_tiles, bool
       u.unit_epochs = (int32_t)((n_epochs + g.wgs - 1) / g.wgs);
     } else {
       const int32_t first = (int32_t)(n_epochs * kFirstUnitPercent / 100 / g.wgs);
-      if (first >= kUnitEpochs) {
+      const bool lines = line_tiles > 1 && g.plan.n_main > 1;
+      if (first >= kUnitEpochs && (!indexed || lines)) {
         u.first_epochs = first;
         u.unit_epochs = kTailUnitEpochs;
       }
@@ -1008,7 +1013,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.line_tiles = line_tiles;
   a.wgs = g.wgs;
   a.chunks = g.wgs * g.blocks_per_wg;
-  const UnitPlan u = plan_units(g, n_leaf_rows, line_tiles, g_deterministic.load(), device_cu_count());
+  const UnitPlan u = plan_units(g, n_leaf_rows, leaf_row_idx != nullptr, line_tiles, g_deterministic.load(), device_cu_count());
   a.unit_epochs = u.unit_epochs;
   a.first_epochs = u.first_epochs;
   a.fixed_stride = u.fixed_stride;
@@ -2195,7 +2200,7 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
   const bool wide = g_wide.load() != 0;
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
                                 build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, indexed != 0, wide), wide);
-  const UnitPlan u = plan_units(g, n_leaf_rows, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
+  const UnitPlan u = plan_units(g, n_leaf_rows, indexed != 0, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
   const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal_lines, g.one_unit_each};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
   return GBDT_OK;

@@ -173,3 +173,18 @@ def test_largest_shared_regions(n_rows):
         left = bins[short.long(), f] <= 30
         assert int(n_left) == int(left.sum())
         assert torch.equal(kids[:short.numel()], torch.cat([short[left], short[~left]]))
+
+
+def test_long_list_of_a_lone_tile():
+    """A list whose tiles share no lines takes units of four epochs from the start, a root of the same rows does not."""
+    n_features, n_bins = 20, 64
+    n_rows = rows_for(n_features, n_bins, 15)
+    print(f"long list {n_rows} x {n_features}", flush=True)
+    p, rng = problem(n_rows, n_features, n_bins)
+    idx = np.nonzero(rng.random(n_rows) < 0.95)[0].astype(np.int32)
+    for rows in (None, idx):
+        n_leaf = n_rows if rows is None else rows.size
+        plan = B.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf, rows is not None)
+        assert plan["one_unit_each"] == 0 and plan["fixed_stride"] == 0
+        assert (plan["first_epochs"], plan["unit_epochs"]) == (0, 4) if rows is not None else plan["first_epochs"] >= 4
+        check_features(p, p.build(rows), [0, 7, 19], rows, rows is None)
