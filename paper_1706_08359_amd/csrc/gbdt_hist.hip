@@ -26,6 +26,7 @@
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <initializer_list>
 #include <mutex>
 #include <type_traits>
 #include <unordered_map>
@@ -663,9 +664,20 @@ struct BatchPlan {
 constexpr double kBatchColumnEpochs = 3.0;
 constexpr double kBatchMergeEpochs = 2.0;
 constexpr double kBatchMergeLaunchEpochs = 1.5;
+// An epoch takes as long as the other workgroups of its CU let it: with k of the w that fit a CU at once it
+// takes about 0.2 + 0.8 k / w of the time with all of them; the 256-bin variant, of which two fit and which is
+// bound by vector work as much as by what they share, 0.4 + 0.6 k / w (5,050 cycles alone, 7,090 together).  A plan of
+// fewer columns can so be as fast, and it has fewer sums to reduce and fewer rows of the matrix in flight.
+// What counts is the fullest CU, so counts of workgroups just at or under a multiple of the CUs are tried too.
+// (8,000,000 x 500 x 64, 64 equal leaves: one column each, two workgroups a CU, 1,290 us, two columns each, which a
+// plan prefers that takes an epoch to last the same always, 1,650; 11,000,000 x 300 x 16, 64 equal leaves: four columns
+// each, exactly three workgroups a CU, 810 us, five 1,270.)
+constexpr double kBatchAloneShare = 0.2, kBatchAloneShareOfTwo = 0.4;
+constexpr int kBatchMaxPerCu = 8;
 
-BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t resident,
+BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus, int wg_per_cu,
                      int n_tiles, const uint32_t* seg_off = nullptr) {
+  const int64_t resident = (int64_t)cus * wg_per_cu;
   BatchPlan b;
   b.n = n;
   uint32_t epochs[kBatchLeaves], most = 1;  // (leaves hold fewer than 2^31 rows)
@@ -683,6 +695,8 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
   if (budget < 1) budget = 1;
   uint32_t t = most;
   double t_cost = 1e300;
+  double share[kBatchMaxPerCu] = {0};
+  if (wg_per_cu > kBatchMaxPerCu) wg_per_cu = kBatchMaxPerCu;
   auto consider = [&](uint32_t cand) {
     // ceil(e / cand) by a multiplication: e and cand are below 2^22, so quotients that are no whole numbers are
     // at least 2^-22 away from one, and 2^-24 covers the rounding of those that are
@@ -694,7 +708,8 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
       blocks += w > 1 ? 2 * w + 1 : 0;
     }
     if ((int64_t)columns > budget + n_live) return;  // (the bound that the scratch is sized by)
-    double cost = (double)cand + kBatchColumnEpochs;
+    const int64_t per_cu = ((int64_t)columns * n_tiles + cus - 1) / cus;  // workgroups of the fullest CU
+    double cost = (double)cand * (per_cu < wg_per_cu ? share[per_cu] : 1.0) + kBatchColumnEpochs;
     if ((int64_t)columns > budget) {
       const double dealt =
           ((double)total_epochs + kBatchColumnEpochs * (double)columns) / (double)budget + 0.5 * (double)cand;
@@ -707,12 +722,20 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int64_t
     }
   };
   if (n_long > 0) {  // (else every leaf has one column whatever T is)
+    const double alone = wg_per_cu <= 2 ? kBatchAloneShareOfTwo : kBatchAloneShare;
+    for (int k = 1; k < wg_per_cu && k < kBatchMaxPerCu; ++k)
+      share[k] = alone + (1.0 - alone) * (double)k / (double)wg_per_cu;
     consider(most);
-    const double average = (double)total_epochs / (double)budget;
-    for (const double factor : {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0}) {
-      const double cand = std::ceil(average * factor);
-      if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
-    }
+    auto consider_around = [&](int64_t columns, std::initializer_list<double> factors) {
+      const double average = (double)total_epochs / (double)columns;
+      for (const double factor : factors) {
+        const double cand = std::ceil(average * factor);
+        if (cand < (double)most) consider(cand < 1.0 ? 1u : (uint32_t)cand);
+      }
+    };
+    consider_around(budget, {0.4, 0.45, 0.5, 0.55, 0.65, 0.8, 1.0, 1.03, 1.1, 1.25, 1.5, 2.0, 4.0});
+    for (int k = 1; k < wg_per_cu && k < kBatchMaxPerCu; ++k)
+      if ((int64_t)k * cus >= n_tiles) consider_around((int64_t)k * cus / n_tiles, {1.0, 1.03, 1.1, 1.25});
   }
   int wgs[kBatchLeaves], unit[kBatchLeaves];
   uint32_t each[kBatchLeaves], most_each = 0;  // epochs of a leaf's busiest workgroup
@@ -1314,7 +1337,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   if (n_tiles > 65535) return GBDT_EUNSUPPORTED;
   if ((n_rows + kEpochRows) * (int64_t)p.wm >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
   const bool wide = g_wide.load() != 0;
-  const int64_t resident = (int64_t)device_cu_count() * build_wg_per_cu(p.cap, true, wide);
+  const int cus = device_cu_count(), wg_per_cu = build_wg_per_cu(p.cap, true, wide);
   // words of the partial blocks of one workgroup column (two blocks each with wide accumulation)
   const size_t col = (p.cap == 16 ? variant_column_words<GBDT_VARIANT_16>(p)
                                   : (p.cap == 64 ? variant_column_words<GBDT_VARIANT_64>(p)
@@ -1328,7 +1351,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     for (int32_t i = 0; i < n; ++i)
       if (leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     if (leaf_offsets[l0 + n] - leaf_offsets[l0] >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
-    const BatchPlan b = plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
+    const BatchPlan b = plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_tiles, seg_off);
     if (l0 == 0) first_plan = b;
     if ((int64_t)b.total_wgs * n_tiles >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     const size_t w = (size_t)b.total_wgs * col;
@@ -1359,7 +1382,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   }
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;
-    const BatchPlan b = l0 == 0 ? first_plan : plan_batch(leaf_offsets, l0, n, resident, n_tiles, seg_off);
+    const BatchPlan b = l0 == 0 ? first_plan : plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_tiles, seg_off);
     BatchMergeArgs m;
     m.m.partials = (const uint32_t*)ws;
     m.m.out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -1393,7 +1416,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_main = p.n_main;
       a.wr = p.wr;
       a.line_tiles = plan_line_tiles(n_rows);
-      a.deal_lines = a.line_tiles > 1 && lines_pay(b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, device_cu_count());
+      a.deal_lines = a.line_tiles > 1 && lines_pay(b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, cus);
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -2217,7 +2240,7 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
     if (leaf_offsets[l + 1] < leaf_offsets[l]) return GBDT_EINVAL;
   const TilePlan p = make_tile_plan(n_features, n_bins);
   const int n_tiles = plan_n_tiles(p);
-  const BatchPlan b = plan_batch(leaf_offsets, 0, n_leaves, (int64_t)n_cus * wg_per_cu, n_tiles);
+  const BatchPlan b = plan_batch(leaf_offsets, 0, n_leaves, n_cus, wg_per_cu, n_tiles);
   for (int32_t l = 0; l < n_leaves; ++l) {
     leaf_wgs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_wgs(b.leaf[l]);
     leaf_unit_epochs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_unit_epochs(b.leaf[l]);

@@ -204,6 +204,17 @@ def test_batched_launch_plan_covers_every_leaf_exactly(n_features, n_bins, wg_pe
         assert int(wgs.sum()) <= 256 * wg_per_cu // n_tiles + n_leaves
 
 
+@pytest.mark.parametrize("n_rows,n_features,n_bins,wg_per_cu,columns",
+                         [(8_000_000, 500, 64, 3, 64), (11_000_000, 300, 16, 4, 256), (8_000_000, 500, 256, 2, 64)])
+def test_batched_plan_of_equal_leaves_fills_the_cus_evenly(n_rows, n_features, n_bins, wg_per_cu, columns):
+    """64 equal leaves: rather one column each, or four, with the same number of workgroups on every CU than a
+    second round of columns, or some CUs with one workgroup more than the others."""
+    offs = [i * (n_rows // 64) for i in range(65)]
+    wgs, _, blocks = B.gbdt_debug_batch_plan(n_features, n_bins, offs, 256, wg_per_cu)
+    assert int(wgs.sum()) == columns and len(set(wgs.tolist())) == 1
+    assert blocks.shape[0] % 256 == 0
+
+
 @pytest.mark.parametrize("n_features,n_bins", [(28, 64), (2000, 63), (137, 255), (700, 16)])
 def test_wide_accumulation_doubles_the_partial_blocks(n_features, n_bins):
     """The wide mode writes two partial blocks per workgroup; the sizes the library reports for
