@@ -405,7 +405,11 @@ void plan_leaf_units(int64_t n_epochs, int64_t budget, int* wgs_out, int* unit_e
 // stretches of scattered rows at once are a little slower than one front of small units that goes through the list.
 // 40,000,000 x 60 x 64, a list of half the rows: 439 us with long first units, 415 with units of 4 epochs (and 498 /
 // 466 on a first pass); the fused columns of 3,000,000 x 700 x 16, half of the rows: 222 / 214 and 269 / 256.
+// 4-bit tiles with a narrower last one: of the four workgroups of a CU one may be of the narrow tile, done in half
+// the time, and those beside it then run ahead, so more is left to even out (11,000,000 x 700 x 16, root 1,500 us at 95 %,
+// 1,444 at 85, 1,410 at 75 and at 60, 1,411 with units of 4 from the start).
 constexpr int kFirstUnitPercent = 95;
+constexpr int kFirstUnitPercentUneven = 75;
 constexpr int kTailUnitEpochs = 3;  // the fewest the pipeline's look-ahead allows
 static_assert(kTailUnitEpochs >= 3, "a unit's successor is taken in its third-last epoch");
 
@@ -459,7 +463,8 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
     if (deterministic) {  // an even split: the same sums in every run, and rows stay together
       u.unit_epochs = (int32_t)((n_epochs + g.wgs - 1) / g.wgs);
     } else {
-      const int32_t first = (int32_t)(n_epochs * kFirstUnitPercent / 100 / g.wgs);
+      const int percent = g.plan.nib && g.plan.wr ? kFirstUnitPercentUneven : kFirstUnitPercent;
+      const int32_t first = (int32_t)(n_epochs * percent / 100 / g.wgs);
       const bool lines = line_tiles > 1 && g.plan.n_main > 1;
       if (first >= kUnitEpochs && (!indexed || lines)) {
         u.first_epochs = first;
