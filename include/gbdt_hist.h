@@ -505,7 +505,7 @@ int gbdt_debug_geometry(int32_t n_features, int32_t n_bins, int64_t n_leaf_rows,
 /* How gbdt_hist_build shares out a leaf of n_leaf_rows rows on the current device (without one: 256 compute
  * units), in the modes set: out[0] = workgroups per tile, out[1] = epochs per unit, out[2] = epochs of every
  * workgroup's first unit (0: no longer than the others), out[3] = 0 when units are handed out at run time, else the
- * fixed stride between a workgroup's units, out[4] = 1 when blocks are dealt out by shared lines,
+ * fixed stride between a workgroup's units, out[4] = 1 or 2 when blocks are dealt out by shared lines,
  * out[5] = 1 when every workgroup has one unit.  (A fused copy of the matrix has its own plan.) */
 int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int64_t n_leaf_rows, int32_t indexed,
                          int64_t* out, int32_t n_out);
@@ -520,7 +520,8 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
 /* Where the tiles of a packed matrix lie and how the blocks of a build launch with `cols` workgroups per
  * tile are dealt out: tile_out[2 t], tile_out[2 t + 1] = byte offset of tile t's first row and bytes from
  * a row to the next; block_out[2 i], block_out[2 i + 1] = (tile, workgroup of the tile) of block
- * i < max_blocks, for a batched launch (by_column != 0) or a single leaf's.  Computed by the functions the
+ * i < max_blocks, for a batched launch (by_column != 0) or a single leaf's, of long leaves, in the accumulation mode
+ * set.  Computed by the functions the
  * kernels use.  Returns the number of blocks, or a negative gbdt_status.  Host only. */
 int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int32_t cols, int32_t by_column,
                          int64_t* tile_out, int32_t* block_out, int32_t max_blocks);

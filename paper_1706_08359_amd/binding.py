@@ -565,7 +565,7 @@ def gbdt_debug_leaf_plan(n_rows: int, n_features: int, n_bins: int, n_leaf_rows:
                                          ctypes.c_void_p, ctypes.c_int32]
     _check(lib.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf_rows, 1 if indexed else 0, out, 6),
            "gbdt_debug_leaf_plan")
-    return dict(zip(("wgs", "unit_epochs", "first_epochs", "fixed_stride", "deal_lines", "one_unit_each"), out))
+    return dict(zip(("wgs", "unit_epochs", "first_epochs", "fixed_stride", "deal", "one_unit_each"), out))
 
 
 def gbdt_debug_fuse_sample_rows(n_rows: int, n_features: int) -> int:

@@ -43,8 +43,17 @@ static_assert(kBatchLeaves <= 256, "a leaf's number has 8 bits");
 // only those with one workgroup a CU do: latency counts there, not traffic (256 bins, wide accumulation, 172 blocks: 700,000 x
 // 50, an eighth of the rows 20.3 us dealt by lines, 17.7 so; 144 blocks, 300,000 x 500, a 32nd 37.9 and 35.3).
 constexpr uint32_t kXcds = 8;
-GBDT_HD bool lines_pay(int32_t unit_epochs, int64_t blocks, int32_t cus) {
-  return unit_epochs > 2 || (unit_epochs == 2 && blocks >= cus);
+// With wide accumulation a workgroup is as fast as its CU lets it, and one beside a workgroup of the remainder tile is faster.
+// The hand-out of units evens that out within a tile, so every tile has to have workgroups on both kinds of CU: a lone main
+// tile between the pairs and the remainder tile has them all where no remainder is.  There its blocks are dealt
+// out with the pairs', eight columns at a time (tile after tile of them: pairs stay 8 blocks apart).  3,000,000 x 400 x 16,
+// root 522 us behind the pairs, 479 so (467 with a region per tile); 1,500,000 x 330 x 64 238 and 222.  (Without wide
+// accumulation memory evens the CUs out, and the order by lines is the better one: 11,000,000 x 700 x 16, root 1,410 us, 1,450
+// so.)
+enum DealOrder : int32_t { kDealTiles = 0, kDealLines = 1, kDealColumns = 2 };
+GBDT_HD int32_t deal_order(int32_t line_tiles, int32_t unit_epochs, int64_t blocks, int32_t cus, bool wide) {
+  if (line_tiles == 1 || unit_epochs < 2 || (unit_epochs == 2 && blocks < cus)) return kDealTiles;
+  return wide ? kDealColumns : kDealLines;
 }
 struct LineBlock {
   int32_t tile;
@@ -62,7 +71,7 @@ GBDT_HD void line_deal(uint32_t b, uint32_t n_pairs, uint32_t* pair, uint32_t* t
     *pair = dealt + r - *tile * rest;
   }
 }
-GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, bool deal_lines, uint32_t cols, bool by_column,
+GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, int32_t deal, uint32_t cols, bool by_column,
                              uint32_t b) {
   LineBlock r;
   if (n_main + (wr ? 1 : 0) == 1) {
@@ -70,7 +79,7 @@ GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, bool deal_l
     r.col = b;
     return r;
   }
-  if (!deal_lines) {  // neighbouring blocks take different tiles
+  if (deal == kDealTiles) {  // neighbouring blocks take different tiles
     const uint32_t main_blocks = (uint32_t)n_main * cols;
     r.tile = b < main_blocks ? (int32_t)(b % (uint32_t)n_main) : n_main;
     r.col = b < main_blocks ? b / (uint32_t)n_main : b - main_blocks;
@@ -78,6 +87,33 @@ GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, bool deal_l
   }
   const uint32_t lines = (uint32_t)n_main / 2u;
   uint32_t pair = 0, tile = 0;
+  if (deal == kDealColumns && (n_main & 1) && lines && !plan_leftover_shared(wm, n_main, wr)) {
+    const uint32_t chunk = kXcds * (uint32_t)n_main, in_chunks = cols / kXcds * chunk;
+    if (b < in_chunks) {
+      const uint32_t k = b / chunk, i = b - k * chunk;
+      r.tile = (int32_t)(i / kXcds);
+      r.col = k * kXcds + i % kXcds;
+      return r;
+    }
+    // the last few columns, as below
+    LineBlock rest = {0, 0};
+    const uint32_t n = cols % kXcds;
+    b -= in_chunks;
+    if (b < lines * n * 2u) {
+      line_deal(b, lines * n, &pair, &tile);
+      rest.tile = (int32_t)(pair % lines * 2u + tile);
+      rest.col = pair / lines;
+    } else if (b < (uint32_t)n_main * n) {
+      rest.tile = n_main - 1;
+      rest.col = b - lines * n * 2u;
+    } else {  // the remainder tile, every column of it
+      r.tile = n_main;
+      r.col = b - (uint32_t)n_main * n;
+      return r;
+    }
+    rest.col += cols - n;
+    return rest;
+  }
   const uint32_t line_blocks = lines * cols * 2u;
   if (b < line_blocks) {
     line_deal(b, lines * cols, &pair, &tile);
@@ -121,8 +157,8 @@ GBDT_HD int32_t batch_leaf_of(const BatchLeaf* leaf, int32_t n_leaves, uint32_t 
 }
 
 GBDT_HD BatchBlock batch_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t wm, int32_t n_main, int32_t wr,
-                               bool deal_lines, uint32_t cols, uint32_t b) {
-  const LineBlock lb = line_block(wm, n_main, wr, deal_lines, cols, true, b);
+                               int32_t deal, uint32_t cols, uint32_t b) {
+  const LineBlock lb = line_block(wm, n_main, wr, deal, cols, true, b);
   BatchBlock r;
   r.leaf = batch_leaf_of(leaf, n_leaves, lb.col);
   r.tile = lb.tile;

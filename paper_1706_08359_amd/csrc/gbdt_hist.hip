@@ -452,7 +452,7 @@ struct UnitPlan {
   int32_t unit_epochs;
   int32_t first_epochs;  // 0, or the length of every workgroup's first unit
   int32_t fixed_stride;  // 0: units from the tile's counter
-  int32_t deal_lines;    // by lines (batch_plan.h)
+  int32_t deal;          // order of the launch's blocks (batch_plan.h)
 };
 UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t line_tiles, bool deterministic, int cus) {
   UnitPlan u;
@@ -474,7 +474,7 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
   }
   // no counter when every workgroup has one unit anyway, or when the split must be fixed
   u.fixed_stride = (g.one_unit_each || deterministic) ? g.wgs : 0;
-  u.deal_lines = line_tiles > 1 && lines_pay(g.unit_epochs, (int64_t)g.wgs * plan_n_tiles(g.plan), cus);
+  u.deal = deal_order(line_tiles, g.unit_epochs, (int64_t)g.wgs * plan_n_tiles(g.plan), cus, g.blocks_per_wg > 1);
   return u;
 }
 
@@ -1045,7 +1045,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.unit_epochs = u.unit_epochs;
   a.first_epochs = u.first_epochs;
   a.fixed_stride = u.fixed_stride;
-  a.deal_lines = u.deal_lines;
+  a.deal = u.deal;
   a.direct_out = (g.wgs == 1 && !fused) ? hist_out : nullptr;  // (joint histograms always take the reduction pass)
   a.n_features = n_features;
   a.n_bins = n_bins;
@@ -1421,7 +1421,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_main = p.n_main;
       a.wr = p.wr;
       a.line_tiles = plan_line_tiles(n_rows);
-      a.deal_lines = a.line_tiles > 1 && lines_pay(b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, cus);
+      a.deal = deal_order(a.line_tiles, b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, cus, wide);
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -2229,7 +2229,7 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
                                 build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, indexed != 0, wide), wide);
   const UnitPlan u = plan_units(g, n_leaf_rows, indexed != 0, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
-  const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal_lines, g.one_unit_each};
+  const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal, g.one_unit_each};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
   return GBDT_OK;
 }
@@ -2251,7 +2251,8 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
     leaf_unit_epochs_out[batch_leaf_no(b.leaf[l])] = (int32_t)batch_unit_epochs(b.leaf[l]);
   }
   const int64_t blocks = (int64_t)b.total_wgs * n_tiles;
-  const bool deal = plan_line_tiles(kPlanLinesMinRows) > 1 && lines_pay(b.most_unit_epochs, blocks, n_cus);
+  const int32_t deal =
+      deal_order(plan_line_tiles(kPlanLinesMinRows), b.most_unit_epochs, blocks, n_cus, g_wide.load() != 0);
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
     const BatchBlock k = batch_block(b.leaf, n_leaves, p.wm, p.n_main, p.wr,
                                      deal, b.total_wgs, (uint32_t)i);
@@ -2276,8 +2277,9 @@ int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int
   }
   const int64_t blocks = (int64_t)n_tiles * cols;
   if (blocks >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
+  const int32_t deal = deal_order(line_tiles, kUnitEpochs, blocks, 1, g_wide.load() != 0);
   for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
-    const LineBlock b = line_block(p.wm, p.n_main, p.wr, line_tiles > 1, (uint32_t)cols, by_column != 0, (uint32_t)i);
+    const LineBlock b = line_block(p.wm, p.n_main, p.wr, deal, (uint32_t)cols, by_column != 0, (uint32_t)i);
     block_out[2 * i] = b.tile;
     block_out[2 * i + 1] = (int32_t)b.col;
   }

@@ -321,7 +321,7 @@ struct BuildArgs {
   int32_t n_main;       // main tiles
   int32_t wr;           // remainder tile width, 0 if none
   int32_t line_tiles;   // main tiles that share a region of the matrix (tile_plan.h)
-  int32_t deal_lines;   // the launch's blocks are dealt out by lines (batch_plan.h)
+  int32_t deal;         // order of the launch's blocks (batch_plan.h)
   int32_t wgs;          // workgroups per tile
   int32_t chunks;       // partial blocks per tile: wgs, or 2 * wgs with wide accumulation
   int32_t first_epochs; // 0, or the length of every workgroup's first unit
@@ -944,7 +944,7 @@ hist_build_kernel(BuildArgs a) {
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
   const uint32_t n_leaf = (uint32_t)a.n_leaf;
-  const LineBlock lb = line_block(WM, a.n_main, a.wr, a.deal_lines != 0, (uint32_t)a.wgs, false, blockIdx.x);
+  const LineBlock lb = line_block(WM, a.n_main, a.wr, a.deal, (uint32_t)a.wgs, false, blockIdx.x);
   const int32_t t = lb.tile;
   const int32_t c = (int32_t)lb.col;  // workgroup of the tile
   uint32_t* counter = a.counters + plan_counter_slot(t);
@@ -1036,7 +1036,7 @@ struct BatchArgs {
   int32_t n_main;
   int32_t wr;
   int32_t line_tiles;
-  int32_t deal_lines;
+  int32_t deal;
   int32_t n_leaves;
   uint32_t n_cols;       // workgroup columns of all leaves
   gbdt_bin_t* hist_out;  // [n_leaves][n_features][n_bins]: written directly by leaves of one workgroup per tile
@@ -1059,7 +1059,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WP
 hist_build_batch_kernel(BatchArgs a) {
   constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
   __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, WM, a.n_main, a.wr, a.deal_lines != 0, a.n_cols, blockIdx.x);
+  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, WM, a.n_main, a.wr, a.deal, a.n_cols, blockIdx.x);
   const BatchLeaf lf = a.leaf[blk.leaf];
   const int32_t wgs = (int32_t)batch_wgs(lf);
   const uint32_t unit_epochs = batch_unit_epochs(lf);

@@ -88,7 +88,7 @@ def test_lines_of_tiles_dealt_out(n_features, n_bins):
     n_rows = rows_for(n_features, n_bins, 2.5)
     print(f"dealt {n_rows} x {n_features}, {n_bins} bins", flush=True)
     plan = B.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_rows, False)
-    assert plan["deal_lines"] == 1 and plan["unit_epochs"] in (2, 3)
+    assert plan["deal"] == 1 and plan["unit_epochs"] in (2, 3)
     p, rng = problem(n_rows, n_features, n_bins)
     first = {}
     for f in range(n_features):
@@ -126,7 +126,7 @@ def test_long_leaf_starts_with_long_units(n_features, n_bins):
                 n_leaf = n_rows if rows is None else rows.size
                 plan = B.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf, rows is not None)
                 n_epochs = -(-n_leaf // 512)
-                assert plan["one_unit_each"] == 0 and plan["deal_lines"] == 1
+                assert plan["one_unit_each"] == 0 and plan["deal"] == (2 if wide else 1)
                 if det:
                     assert plan["first_epochs"] == 0 and plan["fixed_stride"] == plan["wgs"]
                     assert plan["unit_epochs"] == -(-n_epochs // plan["wgs"])

@@ -333,9 +333,19 @@ def test_regions_of_tiles(n_features, n_bins):
 
 @pytest.mark.parametrize("n_features,n_bins", LINE_SHAPES)
 @pytest.mark.parametrize("by_column", [False, True])
-def test_blocks_of_a_launch(n_features, n_bins, by_column):
+@pytest.mark.parametrize("wide", [False, True])
+def test_blocks_of_a_launch(n_features, n_bins, by_column, wide):
+    B.gbdt_set_wide_accumulation(wide)
+    try:
+        check_blocks_of_a_launch(n_features, n_bins, by_column, wide)
+    finally:
+        B.gbdt_set_wide_accumulation(False)
+
+
+def check_blocks_of_a_launch(n_features, n_bins, by_column, wide):
     """Every (tile, workgroup) is one block's, whatever the layout; the two tiles of a region get their workgroups of a
-    column to the same XCD (blocks 8 apart, except in the last few); a remainder tile of its own comes last."""
+    column to the same XCD (blocks 8 apart, except in the last few); a remainder tile of its own comes last; with wide
+    accumulation a lone main tile has workgroups all through the launch."""
     g = B.gbdt_debug_geometry(n_features, n_bins, 1)
     n_tiles = g["n_main"] + (1 if g["wr"] else 0)
     for n_rows in (1000, 9001, 2 ** 25):
@@ -348,6 +358,10 @@ def test_blocks_of_a_launch(n_features, n_bins, by_column):
                 if strides[t] > g["wm"]:             # (t, t + 1) share a region
                     same = [at[t + 1, c] - at[t, c] for c in range(cols)]
                     assert sum(d != 8 for d in same) <= 7
+            lone = g["n_main"] - 1
+            if wide and n_rows == 9001 and g["n_main"] % 2 and lone and strides[lone] == g["wm"] and cols >= 16:
+                where = np.array(sorted(at[lone, c] for c in range(cols)))
+                assert np.diff(where).max() <= 8 * g["n_main"] and where[0] < 8 * g["n_main"]
             if g["wr"] and strides[-1] == g["wr"]:
                 assert [at[n_tiles - 1, c] for c in range(cols)] == list(range((n_tiles - 1) * cols, n_tiles * cols))
 
