@@ -524,36 +524,39 @@ int build_wg_per_cu(int cap, bool indexed, bool wide = false) {
   return c;
 }
 
-// Work split of split_gain_kernel over the n_hists histograms of a launch.  group: features a
-// workgroup holds in local memory at a time; passes: groups it takes one after the other; n_wg:
-// workgroups, and candidates, per histogram.  A workgroup's time is a chain of latencies (loads,
-// the serial fp64 prefix, the candidate's hand-off) that hardly depends on the group, so a lone
-// histogram is spread over about 256 workgroups, and a launch with many histograms gets larger
-// groups (up to 16 features: more leave too few workgroups per CU to hide those latencies), then
-// up to 4 passes, aiming at 500-1000 workgroups in all.  (2,000 features x 63 bins, 64
-// histograms: 188 us with 8 features per workgroup as for a lone histogram, 85 us with 16 x 4;
-// 137 x 255, 64 histograms: 113 us with one feature per workgroup, 40 us with 7 x 2.)
-constexpr int64_t kSplitManyWgs = 1024;  // workgroups of a launch from which residency counts
+// Work split of split_gain_kernel over the n_hists histograms of a launch.  group: features of a wavefront's
+// step; passes: steps a workgroup takes; waves: its wavefronts; n_wg: workgroups, and candidates, per histogram.
+// A wavefront takes one step while all of them fit the machine at once (four a SIMD: the kernel needs 122
+// registers), then several.  Up to kSplitMaxWaves steps are one workgroup's, and nothing is handed
+// over (28 x 64: 3.8 us, in two workgroups 4.9).  Beyond, workgroups are small -- 28 x 255 takes 5.4 us with four wavefronts
+// each, 5.8 with 8 and 6.6 with 16 -- until the hand-off queues at the ticket: 2,000 x 63 6.5 us in 125 workgroups, 6.2 in
+// 63; 2,000 x 255 12.7 in 500, 8.7 in 125.
+constexpr int kSplitFitWaves = 4096;  // 256 CUs x 4 SIMDs x 4
+constexpr int kSplitFewWgs = 64;
 struct SplitGrouping {
-  int group, passes, n_wg;
+  int group, passes, waves, n_wg;
 };
 SplitGrouping split_grouping(int32_t n_features, int32_t n_bins, int32_t n_hists) {
   SplitGrouping g;
-  const int cap = split_max_group(n_bins);
-  const int spread = (n_features + 255) / 256;  // a lone histogram: about 256 groups
-  const int64_t total = (int64_t)n_features * (n_hists > 0 ? n_hists : 1);
-  const int64_t shared = (total + 511) / 512;   // many histograms: about 512 groups in all
-  g.group = (int)(shared > spread ? shared : spread);
-  if (g.group > cap) g.group = cap;
-  if (g.group < 1) g.group = 1;
-  const int n_groups = (n_features + g.group - 1) / g.group;
-  const int64_t wgs = (int64_t)n_groups * (n_hists > 0 ? n_hists : 1);
-  g.passes = (int)((wgs + 1023) / 1024);
-  if (g.passes > 4) g.passes = 4;
-  if (g.passes > n_groups) g.passes = n_groups;
-  if (g.passes < 1) g.passes = 1;
-  g.n_wg = (n_groups + g.passes - 1) / g.passes;
-  return g;
+  g.group = 64 >> split_lane_bits(n_bins);
+  const int64_t n_steps = ((int64_t)n_features + g.group - 1) / g.group;
+  int64_t each = (n_steps * (n_hists > 0 ? n_hists : 1) + kSplitFitWaves - 1) / kSplitFitWaves;  // steps of a wavefront
+  if (n_steps <= kSplitMaxWaves) {
+    if (each > 4) each = 4;
+    g.waves = (int)((n_steps + each - 1) / each);
+    g.passes = (int)n_steps;
+    g.n_wg = 1;
+    return g;
+  }
+  // never more workgroups than a lone histogram gets: the scratch is sized by that
+  const int64_t most = n_hists > 1 ? split_grouping(n_features, n_bins, 1).n_wg : n_steps;
+  g.waves = 4;
+  if (each > (n_steps + g.waves - 1) / g.waves) each = (n_steps + g.waves - 1) / g.waves;
+  for (;; g.waves *= 2) {
+    g.passes = (int)(each * g.waves);
+    g.n_wg = (int)((n_steps + g.passes - 1) / g.passes);
+    if (g.waves >= kSplitMaxWaves || (g.n_wg <= kSplitFewWgs && g.n_wg <= most)) return g;
+  }
 }
 
 // GBDT_HIST_CHECK_INPUTS=1 (debugging): every call that takes a row list first counts its
@@ -789,24 +792,27 @@ int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, 
   void* ws = nullptr;
   int rc = get_workspace((size_t)n_hists * sg.n_wg * sizeof(SplitCand), s, &ws);
   if (rc != GBDT_OK) return rc;
-  const size_t lds = (size_t)sg.group * split_feature_bytes(n_bins);
   // (only with siblings does the kernel write to the histograms)
-  const bool few_steps = split_steps(n_bins, sg.group) <= 4;
   auto launch = [&](auto kernel, const auto& sib) {
-    hipLaunchKernelGGL(kernel, dim3(sg.n_wg, n_hists), dim3(kSplitThreads), lds, s,
-                       const_cast<gbdt_bin_t*>(hists), hist_stride, n_features, n_bins, sg.group, sg.passes,
-                       (double)lambda, (double)min_child_hess, (SplitCand*)ws, splits_out, host_mirror, sib);
+    hipLaunchKernelGGL(kernel, dim3(sg.n_wg, n_hists), dim3(64 * sg.waves), 0, s, const_cast<gbdt_bin_t*>(hists),
+                       hist_stride, n_features, n_bins, sg.passes, (double)lambda, (double)min_child_hess,
+                       (SplitCand*)ws, splits_out, host_mirror, sib);
   };
-  // The short prefix loop of launches of many workgroups also serves all groups of more than four steps: these are only
-  // formed by launches of about 450 workgroups and more (split_grouping), where it is as fast as the one that reads ahead
-  // or a little faster (200 features x 256 bins, 13 histograms 12.6 and 12.8 us, 32 histograms 23.8 and 24.1).
-  const bool many = (int64_t)sg.n_wg * n_hists > kSplitManyWgs;
+  auto launch_of = [&](const auto& sib) {
+    using SIB = std::decay_t<decltype(sib)>;
+    switch (n_bins < kSplitBins ? 0 : split_lane_bits(n_bins)) {
+      case 0: launch(split_gain_kernel<2, true, SIB>, sib); break;
+      case 2: launch(split_gain_kernel<2, false, SIB>, sib); break;
+      case 3: launch(split_gain_kernel<3, false, SIB>, sib); break;
+      case 4: launch(split_gain_kernel<4, false, SIB>, sib); break;
+      case 5: launch(split_gain_kernel<5, false, SIB>, sib); break;
+      default: launch(split_gain_kernel<6, false, SIB>, sib); break;
+    }
+  };
   if (siblings) {
-    launch(few_steps ? (many ? split_gain_kernel<4, true, SplitSiblings> : split_gain_kernel<4, false, SplitSiblings>)
-                     : split_gain_kernel<kSplitSteps, true, SplitSiblings>, *siblings);
+    launch_of(*siblings);
   } else {
-    launch(few_steps ? (many ? split_gain_kernel<4, true, NoSiblings> : split_gain_kernel<4, false, NoSiblings>)
-                     : split_gain_kernel<kSplitSteps, true, NoSiblings>, NoSiblings{});
+    launch_of(NoSiblings{});
   }
   HIP_TRY(hipGetLastError());
   return GBDT_OK;
@@ -1911,6 +1917,7 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
       sib.pool = pool;
       sib.first = k;
       sib.n = k;
+      sib.keep = 1;
       for (int j = 0; j < kSplitSiblings; ++j) sib.parent_slot[j] = j < k ? cands[batch[j]].slot : 0;
       rc = launch_split(h_small, (int64_t)hist_elems, 2 * k, lambda, min_child_hess, recs + next_slot, n_features,
                         n_bins, s, pinned_dev, &sib);
@@ -2188,6 +2195,7 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     level_sib.pool = hist_buf[cur];
     level_sib.first = k;
     level_sib.n = k <= kSplitSiblings && 2 * k <= kSplitMaxHists ? k : 0;
+    level_sib.keep = depth + 1 < max_depth;  // (nobody reads the last level's)
     for (int j = 0; j < level_sib.n; ++j) level_sib.parent_slot[j] = parent_slot[j];
     for (int j0 = 0; j0 < k && level_sib.n == 0; j0 += kSiblingTable) {
       SiblingTable t;
@@ -2318,7 +2326,7 @@ int gbdt_debug_split_plan(int32_t n_features, int32_t n_bins, int32_t n_hists, i
   out[0] = g.group;
   out[1] = g.passes;
   out[2] = g.n_wg;
-  out[3] = (int64_t)g.group * split_feature_bytes(n_bins);
+  out[3] = (int64_t)kSplitMaxWaves * (sizeof(SplitCand) + sizeof(int32_t));
   return GBDT_OK;
 }
 

@@ -25,8 +25,7 @@ struct SplitCand {
 
 static_assert(sizeof(SplitCand) == 7 * 8, "a candidate is moved as 7 64-bit words");
 
-constexpr int kSplitThreads = 256;
-constexpr int kSplitLdsBudget = 48 * 1024;
+constexpr int kSplitMaxWaves = 16;  // wavefronts of a workgroup at most
 constexpr int kSplitMaxHists = 32768;  // histograms per launch (grid.y)
 
 // One ticket counter per histogram of a launch: the workgroups of a histogram count
@@ -77,105 +76,160 @@ __device__ __forceinline__ SplitCand load_cand(const SplitCand* src) {
   memcpy(&c, w, sizeof c);
   return c;
 }
-// LDS bytes one feature needs in split_gain_kernel: fp64 running sums of gradient,
-// hessian and count per bin (bins padded to a multiple of kSplitBlock), + the feature's parent term.
-// A row is two doubles longer than that: the prefix pass walks down all rows of a group at once,
-// 16 bytes per lane, and with rows an odd multiple of 16 bytes apart the lanes fall on different banks
-// (with rows a multiple of 128 bytes apart, as they were, all of them fell on the same: 16 features
-// x 64 bins took 6,100 cycles there).
-constexpr int kSplitBlock = 16;  // bins the prefix loop adds per register block
-__host__ __device__ inline int split_padded_bins(int n_bins) { return (n_bins + kSplitBlock - 1) & ~(kSplitBlock - 1); }
-__host__ __device__ inline int split_row(int n_bins) { return split_padded_bins(n_bins) + 2; }
-__host__ __device__ inline int split_feature_bytes(int n_bins) { return 24 * split_row(n_bins) + 8; }
+// How a wavefront holds histogram rows: a lane has kSplitBins consecutive bins of a feature, so a row takes
+// 1 << lane_bits lanes (4, 8, .. 64) and a wavefront 64 >> lane_bits rows at a time, a STEP.
+constexpr int kSplitBins = 4;
+__host__ __device__ inline int split_lane_bits(int n_bins) {
+  int b = 2;
+  while ((kSplitBins << b) < n_bins) ++b;
+  return b;
+}
 
-// How the workgroup's wavefronts walk over the (feature, bin) pairs of a group, in steps of 64: up to 64 bins
-// a step is 64 / lanes rows side by side (lanes = the bins rounded up to a power of two), beyond that a
-// row takes `chunks` steps.  No division per thread, and a step's loads are whole rows.
-constexpr int kSplitSteps = 8;  // steps a wavefront takes of a group at most: 32 steps a group
-struct SplitWalk {
-  int lane_bits;  // log2 of the lanes per row
-  int rows;       // rows per step
-  int chunks;     // steps per row
-  int per_chunk;  // (s * per_chunk) >> 16 == s / chunks for the few steps s there are
+// Data of another lane of the wavefront, by DPP; lanes without a source, and rows of 16 lanes that ROW_MASK
+// leaves out, get 0.
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ double dpp_or_zero(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)((unsigned long long)b >> 32), CTRL, ROW_MASK, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+__device__ __forceinline__ double and_mask(double v, uint32_t m) {  // v, or 0 where m is 0 (else m is all ones)
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  return __longlong_as_double(
+      (long long)(((unsigned long long)((uint32_t)(b >> 32) & m) << 32) | ((uint32_t)b & m)));
+}
+
+// The lanes of a row: shifts and sums over them.  (Rows of 16 lanes and more are what DPP shifts keep apart by
+// themselves; shorter ones mask what comes from the row before.)
+template <int LB>
+struct RowLanes {
+  uint32_t from1, from2, from4;  // all ones where the lane 1, 2, 4 places before is of the same row
+  __device__ __forceinline__ explicit RowLanes(int lane) {
+    const int l = lane & ((1 << LB) - 1);
+    from1 = l >= 1 ? ~0u : 0u;
+    from2 = l >= 2 ? ~0u : 0u;
+    from4 = l >= 4 ? ~0u : 0u;
+  }
+  // sum over the row's lanes up to and with this one
+  __device__ __forceinline__ double prefix(double t) const {
+    if constexpr (LB >= 4) {
+      t += dpp_or_zero<0x111>(t);  // row_shr:1, 2, 4, 8
+      t += dpp_or_zero<0x112>(t);
+      t += dpp_or_zero<0x114>(t);
+      t += dpp_or_zero<0x118>(t);
+      if constexpr (LB >= 5) t += dpp_or_zero<0x142, 0xa>(t);  // row_bcast15
+      if constexpr (LB >= 6) t += dpp_or_zero<0x143, 0xc>(t);  // row_bcast31
+    } else {
+      t += and_mask(dpp_or_zero<0x111>(t), from1);
+      t += and_mask(dpp_or_zero<0x112>(t), from2);
+      if constexpr (LB >= 3) t += and_mask(dpp_or_zero<0x114>(t), from4);
+    }
+    return t;
+  }
+  // the value of the lane before, 0 in a row's first lane
+  __device__ __forceinline__ double before(double t) const {
+    if constexpr (LB == 4) return dpp_or_zero<0x111>(t);  // row_shr:1
+    if constexpr (LB == 6) return dpp_or_zero<0x138>(t);  // wave_shr:1
+    return and_mask(dpp_or_zero<0x138>(t), from1);
+  }
+  // the value of the row's last lane
+  __device__ __forceinline__ double last(double t, int lane) const {
+    const long long b = __double_as_longlong(t);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)((unsigned long long)b >> 32);
+    int rl, rh;
+    if constexpr (LB == 6) {
+      rl = __builtin_amdgcn_readlane(lo, 63);
+      rh = __builtin_amdgcn_readlane(hi, 63);
+    } else if constexpr (LB == 5) {
+      const int l0 = __builtin_amdgcn_readlane(lo, 31), l1 = __builtin_amdgcn_readlane(lo, 63);
+      const int h0 = __builtin_amdgcn_readlane(hi, 31), h1 = __builtin_amdgcn_readlane(hi, 63);
+      rl = lane < 32 ? l0 : l1;
+      rh = lane < 32 ? h0 : h1;
+    } else if constexpr (LB == 4) {
+      rl = __builtin_amdgcn_update_dpp(0, lo, 0x15f, 0xf, 0xf, false);  // row_newbcast:15
+      rh = __builtin_amdgcn_update_dpp(0, hi, 0x15f, 0xf, 0xf, false);
+    } else if constexpr (LB == 3) {  // lanes 0..7 of a row of 16 take lane 7, the others lane 15
+      rl = __builtin_amdgcn_update_dpp(0, lo, 0x157, 0xf, 0x3, false);
+      rl = __builtin_amdgcn_update_dpp(rl, lo, 0x15f, 0xf, 0xc, false);
+      rh = __builtin_amdgcn_update_dpp(0, hi, 0x157, 0xf, 0x3, false);
+      rh = __builtin_amdgcn_update_dpp(rh, hi, 0x15f, 0xf, 0xc, false);
+    } else {
+      rl = __builtin_amdgcn_update_dpp(0, lo, 0xff, 0xf, 0xf, false);  // quad_perm [3,3,3,3]
+      rh = __builtin_amdgcn_update_dpp(0, hi, 0xff, 0xf, 0xf, false);
+    }
+    return __longlong_as_double((long long)(((unsigned long long)(uint32_t)rh << 32) | (uint32_t)rl));
+  }
 };
-__host__ __device__ inline SplitWalk split_walk(int n_bins) {
-  SplitWalk w;
-  w.lane_bits = n_bins <= 16 ? 4 : (n_bins <= 32 ? 5 : 6);
-  w.rows = 64 >> w.lane_bits;
-  w.chunks = (n_bins + 63) / 64;
-  w.per_chunk = 65536 / w.chunks + 1;
-  return w;
+
+// Largest value / smallest index over the wavefront, in every lane.  (NaN is passed over.)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_max(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)((unsigned long long)b >> 32);
+  const int l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROW_MASK, 0xf, false);
+  const int h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROW_MASK, 0xf, false);
+  return fmax(v, __longlong_as_double((long long)(((unsigned long long)(uint32_t)h2 << 32) | (uint32_t)l2)));
 }
-// features per group at most: what fits the local memory budget
-constexpr int kSplitMaxGroup = 16;
-inline int split_max_group(int n_bins) {
-  int cap = kSplitLdsBudget / split_feature_bytes(n_bins);
-  if (cap > kSplitMaxGroup) cap = kSplitMaxGroup;
-  const SplitWalk w = split_walk(n_bins);
-  constexpr int most = kSplitSteps * (kSplitThreads / 64);
-  if (cap > most / w.chunks * w.rows) cap = most / w.chunks * w.rows;
-  return cap < 1 ? 1 : cap;
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max<0xb1, 0xf>(v);   // quad_perm [1,0,3,2]
+  v = dpp_max<0x4e, 0xf>(v);   // quad_perm [2,3,0,1]
+  v = dpp_max<0x141, 0xf>(v);  // row_half_mirror
+  v = dpp_max<0x140, 0xf>(v);  // row_mirror
+  v = dpp_max<0x142, 0xa>(v);  // row_bcast15
+  v = dpp_max<0x143, 0xc>(v);  // row_bcast31
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)b >> 32), 63);
+  return __longlong_as_double((long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo));
 }
-// steps a wavefront takes of a group
-inline int split_steps(int n_bins, int group) {
-  const SplitWalk w = split_walk(n_bins);
-  return ((group + w.rows - 1) / w.rows * w.chunks + kSplitThreads / 64 - 1) / (kSplitThreads / 64);
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_min(int v) {
+  const int o = __builtin_amdgcn_update_dpp(v, v, CTRL, ROW_MASK, 0xf, false);
+  return o < v ? o : v;
+}
+__device__ __forceinline__ int wave_min(int v) {
+  v = dpp_min<0xb1, 0xf>(v);
+  v = dpp_min<0x4e, 0xf>(v);
+  v = dpp_min<0x141, 0xf>(v);
+  v = dpp_min<0x140, 0xf>(v);
+  v = dpp_min<0x142, 0xa>(v);
+  v = dpp_min<0x143, 0xc>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+// The index of the wavefront's best (gain, index) under the order "larger gain, then smaller index"
+// (index < 0: no candidate); -1 if no lane has one.  A gain that is no number loses against every number.
+__device__ __forceinline__ int32_t wave_argmax(double gain, int32_t idx) {
+  const double top = wave_max(idx >= 0 ? gain : -INFINITY);
+  bool mine = idx >= 0 && gain == top;
+  if (__ballot(mine) == 0ull) mine = idx >= 0;
+  const int32_t best = wave_min(mine ? idx : 0x7fffffff);
+  return best == 0x7fffffff ? -1 : best;
 }
 
-// Arg-max over the threads of a workgroup under the order "larger gain, then smaller index"
-// (index < 0: no candidate): exchanges inside each wavefront, then the four wavefront
-// results through local memory.  The order is total, so the result does not depend on how
-// the comparisons are arranged.  Every thread returns with the winner in (gain, idx).
-__device__ __forceinline__ void block_argmax(double& gain, int32_t& idx, double* s_gain, int32_t* s_idx) {
-  auto better = [](double g2, int32_t i2, double g1, int32_t i1) {
-    return i2 >= 0 && (i1 < 0 || g2 > g1 || (g2 == g1 && i2 < i1));
-  };
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double g2 = __shfl_xor(gain, o);
-    const int32_t i2 = __shfl_xor(idx, o);
-    if (better(g2, i2, gain, idx)) {
-      gain = g2;
-      idx = i2;
-    }
-  }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    s_gain[wave] = gain;
-    s_idx[wave] = idx;
-  }
-  __syncthreads();
-  gain = s_gain[0];
-  idx = s_idx[0];
-#pragma unroll
-  for (int w = 1; w < kSplitThreads / 64; ++w) {
-    const double g2 = s_gain[w];
-    const int32_t i2 = s_idx[w];
-    if (better(g2, i2, gain, idx)) {
-      gain = g2;
-      idx = i2;
-    }
-  }
-  __syncthreads();  // the scratch may be reused
-}
-
-// Gain scan of Sec. 3.3.  A workgroup takes `passes` groups of `group` consecutive features, one
-// group at a time:
-//  1. Their histogram rows are copied into local memory as doubles.
-//  2. One lane per (feature, statistic) runs the left-to-right prefix sum of grad, hess
-//     or count in fp64, bins ascending (this fixes the rounding order).
-//  3. All lanes then evaluate the gain of every (feature, threshold) pair from those
-//     prefixes -- the divisions, the expensive part -- and keep the best pair under
-//     the order "larger gain, then smaller feature, then smaller bin".
+// Gain scan of Sec. 3.3.  A wavefront takes a step of rows at a time, all in registers, no local memory and no barriers:
+//  1. Lanes fetch their kSplitBins bins.
+//  2. Running sums of gradient, hessian and count in fp64.  The result has to be that of the sum strictly from left
+//     to right (it decides which thresholds tie exactly), so the sums are formed in parallel -- within a lane,
+//     then over the row's lanes -- and CHECKED: if p[i] == p[i - 1] + v[i] holds in fp64 for every bin, then
+//     p is that sum, by induction.  It holds whenever no addition rounds, i.e. unless the row's
+//     values span more than some 20 binary orders of magnitude; then the lanes repeat the sum from
+//     left to right, a lane's turn at a time.  (Counts never round.)
+//  3. The gains.  Divisions are the expensive part, and nearly all of them lose: an approximation by one reciprocal with
+//     a bound of its error rules out what cannot beat the best gain the wavefront knows, and only
+//     the rest is divided out.
 // Feature totals are the prefix at the last bin, right = total - left, a threshold is
-// admissible when both sides hold >= 1 sample and >= min_child_hess of hessian.
-// and keeps the best pair over its groups in registers.  (Requesting the rows of the next group before
-// the prefix sums of the present one costs more registers than the wait is worth: 165 instead of 95, two
-// workgroups per CU fewer, 64 histograms of 2,000 x 63 bins in 66 us instead of 50.)
-//  4. The workgroup that finishes last for its histogram (a ticket taken after its own
-//     candidate is written and fenced; nobody waits) reduces the candidates of all
-//     workgroups to the histogram's split record: workgroups hold ascending feature
-//     groups, so "smaller candidate index" is "smaller feature".
+// admissible when both sides hold >= 1 sample and >= min_child_hess of hessian (so the last bin never is).
+//  4. Arg-max over the wavefront, then over the workgroup's wavefronts, and where a histogram has several workgroups, over
+//     those: the one that finishes last (a ticket taken after its own candidate is written; nobody waits) reduces
+//     the candidates of all to the histogram's split record: workgroups hold ascending features,
+//     so "smaller candidate index" is "smaller feature".
+// Bound by vector work (about 240 instructions a step) and, with many histograms, by reading them: 64 histograms of 2,000 x 63
+// take 23.6 us, 4.1 TB/s, 256 of them 75 (5.2 TB/s); a lone one 6.2.  (A workgroup used to stage up to 16
+// features in local memory, one wavefront ran their sums one bin after the other while the others waited, and
+// every threshold was divided out: 50.6, 156 and 9.8 us.)  Lanes of four bins, not one, because the sums over lanes are most of the
+// work: 2 vector instructions a bin and statistic for them so, 6 with 64 lanes a row.  The next step's rows
+// are requested before the present ones are used: 25.8 us without.
 // grid.y = histogram of the call; histogram y starts hist_stride bins after histogram
 // y - 1 (the stride may be negative: any two histograms of a pool can be searched in
 // one launch).  mirror (may be NULL): a second place for the records, page-locked host
@@ -184,32 +238,30 @@ __device__ __forceinline__ void block_argmax(double& gain, int32_t& idx, double*
 // sib (sib.n may be 0): histograms sib.first .. sib.first + sib.n - 1 of the call are siblings
 // by subtraction that do not exist yet: histogram sib.first + j is first formed, element by
 // element as hist_subtract_kernel does it, as (pool histogram parent_slot[j]) - (histogram j of
-// the call, the built child), written to its place and searched in the same pass: every
-// (feature, bin) is read by exactly one workgroup, which also writes the difference.
+// the call, the built child), written to its place (unless nobody will read it: keep == 0) and searched in the
+// same pass: every (feature, bin) is read by exactly one workgroup, which also writes the difference.
 constexpr int kSplitSiblings = 512;
 struct SplitSiblings {
   const gbdt_bin_t* pool;  // histograms of hist_elems bins each
   int32_t first, n;
+  int32_t keep;
   int32_t parent_slot[kSplitSiblings];
 };
 struct NoSiblings {};  // (a launch without siblings does not carry the table)
 
-// STEPS: register rows for the steps of a wavefront (4 or kSplitSteps; groups of few steps leave more
-// workgroups room on a CU).  MANY: a launch of more workgroups than the machine holds at once, where
-// workgroups per CU count more than one workgroup's time.  SIB: SplitSiblings or NoSiblings.
-template <int STEPS, bool MANY, typename SIB>
-__global__ void __launch_bounds__(kSplitThreads)
+template <int LB, bool SHORT, typename SIB>
+__global__ void __launch_bounds__(64 * kSplitMaxWaves)
 split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
-                  int32_t n_bins, int32_t group, int32_t passes, double lambda, double min_child_hess,
+                  int32_t n_bins, int32_t wg_steps, double lambda, double min_child_hess,
                   SplitCand* __restrict__ cand, gbdt_split_t* __restrict__ out,
                   gbdt_split_t* __restrict__ mirror, SIB sib) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double s_gain[kSplitThreads / 64];
-  __shared__ int32_t s_pair[kSplitThreads / 64];
-  __shared__ int s_last;
-  constexpr int kWaves = kSplitThreads / 64;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kRows = 64 >> LB;
+  constexpr int K = kSplitBins;
+  __shared__ SplitCand s_cand[kSplitMaxWaves];
+  __shared__ int32_t s_pair[kSplitMaxWaves];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int n_waves = (int)blockDim.x >> 6;
   bool is_sib = false;
   const gbdt_bin_t *built = nullptr, *sib_parent = nullptr;  // the sibling's built twin, and their parent
   if constexpr (std::is_same_v<SIB, SplitSiblings>) {
@@ -221,204 +273,221 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
     }
   }
   hist += (int64_t)blockIdx.y * hist_stride;
-  cand += (size_t)blockIdx.y * gridDim.x;
-  out += blockIdx.y;
   const int B = n_bins;
-  const int Bp = split_padded_bins(B);
-  const int S = split_row(B);
-  // layout (doubles): pg[group][S] | ph[group][S] | pn[group][S] | parent[group]
-  double* pg = reinterpret_cast<double*>(smem);
-  double* ph = pg + (size_t)group * S;
-  double* pn = ph + (size_t)group * S;
-  double* parent = pn + (size_t)group * S;
+  const RowLanes<LB> row_lanes(lane);
+  const int bin0 = K * (lane & ((1 << LB) - 1));  // this lane's first bin
+  const int row = lane >> LB;
+  // Of a row that ends inside its K bins a lane fetches the row's last K, so that no load leaves the row, and the
+  // first `skip` of them, which the lane before has, count as zero.  Lanes past the row's end skip all.
+  const int past = bin0 + K - B;
+  const int skip = past < 0 ? 0 : (past < K ? past : K);
+  const bool whole = B == (K << LB);  // (then no lane skips anything)
+  const int first_bin = SHORT ? 0 : (bin0 - skip < B - K ? bin0 - skip : B - K);
 
-  const SplitWalk walk = split_walk(B);
-  const int row_lane = lane >> walk.lane_bits;               // row of the step
-  const int bin_lane = lane & ((1 << walk.lane_bits) - 1);   // bin inside the step's chunk
-  // step i of this wavefront: (first row, first bin); rows are dealt over the wavefronts step by step
-  auto step_at = [&](int i, int& row0, int& bin0) {
-    const int s = i * kWaves + wave;
-    const int r = (s * walk.per_chunk) >> 16;
-    row0 = r * walk.rows;
-    bin0 = (s - r * walk.chunks) * 64;
+  const int32_t n_steps = (n_features + kRows - 1) / kRows;
+  const int32_t step0 = (int32_t)blockIdx.x * wg_steps;
+  const int32_t f_first = step0 * kRows;
+  const int32_t step_end = n_steps - step0 < wg_steps ? n_steps : step0 + wg_steps;
+
+  auto row_of = [&](int32_t step) {  // (rows past the last feature: the last one again, counted as zeros)
+    const int32_t f = step * kRows + row;
+    return (size_t)(f < n_features ? f : n_features - 1) * B + first_bin;
   };
-  // this lane's place relative to its step's first row and bin (the rest is uniform): in a histogram, in LDS
-  const uint32_t lane_bin = (uint32_t)(row_lane * B + bin_lane);
-  const int lane_cell = row_lane * S + bin_lane;
-
-  // The workgroup takes `passes` groups of `group` consecutive features one after the other and
-  // keeps, per thread, the best pair seen so far with everything the record needs: one
-  // candidate and one ticket per workgroup, however many features it looked at.
-  const int32_t f_first = (int32_t)blockIdx.x * passes * group;
-  gbdt_bin_t held[STEPS], held_parent[STEPS];
-  auto request = [&](int32_t f0, int32_t nf) {
-    const gbdt_bin_t* src = (is_sib ? built : hist) + (size_t)f0 * B;
-    const gbdt_bin_t* src_parent = is_sib ? sib_parent + (size_t)f0 * B : nullptr;
+  auto fetch = [&](const gbdt_bin_t* from, size_t at, gbdt_bin_t (&v)[K]) {
+    if constexpr (!SHORT) {
+      __builtin_memcpy(v, from + at, sizeof v);
+    } else {  // two or three bins: the one lane of a row that has any keeps them in its last places
 #pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
-      int row0, bin0;
-      step_at(i, row0, bin0);
-      gbdt_bin_t v = {0.0f, 0.0f, 0u}, q = {0.0f, 0.0f, 0u};
-      if (row0 + row_lane < nf && bin0 + bin_lane < B) {
-        v = (src + (row0 * B + bin0))[lane_bin];
-        if (is_sib) q = (src_parent + (row0 * B + bin0))[lane_bin];
-      }
-      held[i] = v;
-      held_parent[i] = q;
+      for (int k = 0; k < K; ++k) v[k] = from[at + (k < K - B ? 0 : k - (K - B))];
     }
   };
-  auto features_of = [&](int32_t f0) { return n_features - f0 < group ? n_features - f0 : group; };
 
-  double best_gain = 0.0;
+  // The approximation takes both quotients as one, good to about 2^-48 of their sum while the denominators are
+  // positive -- as they are where a side's hessian has to be.
+  constexpr double kSlack = 0x1p-40;
+  const bool positive = min_child_hess > 0.0;
+  double bound = -INFINITY;  // some threshold the wavefront has seen gains at least this
+  // this lane's best pair with everything the record needs
+  double best_gain = 0.0, best_gl = 0.0, best_hl = 0.0, best_nl = 0.0, best_g = 0.0, best_h = 0.0, best_n = 0.0;
   int32_t best_pair = -1;  // (feature - f_first) * (B - 1) + bin, ascending in (feature, bin)
-  double best_gl = 0.0, best_hl = 0.0, best_nl = 0.0, best_g = 0.0, best_h = 0.0, best_n = 0.0;
-  for (int32_t pass = 0; pass < passes; ++pass) {
-    const int32_t f0 = f_first + pass * group;
-    if (f0 >= n_features) break;  // (the same for every thread)
-    const int32_t nf = features_of(f0);
-    if (pass > 0) __syncthreads();  // the sums of the group before are no longer needed
-
-    // 1. every bin's (gradient, hessian, count) as doubles (all exact), zeros in the padding
-    request(f0, nf);
+  gbdt_bin_t next[K];  // the next step's
+  fetch(is_sib ? built : hist, row_of(step0 + wave), next);
+  for (int32_t step = step0 + wave; step < step_end; step += n_waves) {
+    gbdt_bin_t v[K];
+    const size_t at = row_of(step);
 #pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
-      int row0, bin0;
-      step_at(i, row0, bin0);
-      if (row0 + row_lane < nf && bin0 + bin_lane < Bp) {
-        gbdt_bin_t v = held[i];
-        if (is_sib) {
-          v.grad = held_parent[i].grad - v.grad;
-          v.hess = held_parent[i].hess - v.hess;
-          v.count = held_parent[i].count - v.count;
-          if (bin0 + bin_lane < B) (hist + ((size_t)f0 * B + row0 * B + bin0))[lane_bin] = v;
-        }
-        const int e = row0 * S + bin0 + lane_cell;
-        pg[e] = (double)v.grad;
-        ph[e] = (double)v.hess;
-        pn[e] = (double)v.count;
+    for (int k = 0; k < K; ++k) v[k] = next[k];
+    fetch(is_sib ? built : hist, row_of(step + n_waves), next);
+    // places of this lane that hold no bin of their own
+    const int none = (step + 1) * kRows <= n_features || step * kRows + row < n_features ? skip : K;
+    if (is_sib) {
+      gbdt_bin_t q[K];
+      fetch(sib_parent, at, q);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        v[k].grad = q[k].grad - v[k].grad;
+        v[k].hess = q[k].hess - v[k].hess;
+        v[k].count = q[k].count - v[k].count;
       }
-    }
-    __syncthreads();
-
-    // 2. running sums in place, strictly left to right, one lane per (statistic, feature).
-    // The chain of dependent fp64 adds is the critical path of a lone histogram: there two
-    // register blocks of kSplitBlock bins are used in turn, without copies: while one is added
-    // and written back, the other one's values are on their way from local memory.
-    if (tid < 3 * nf) {
-      const int st = tid / nf;
-      const int fl = tid - st * nf;
-      double2* p = reinterpret_cast<double2*>(pg + ((size_t)st * group + fl) * S);
-      constexpr int kPairs = kSplitBlock / 2;
-      const int n_blocks = Bp / kSplitBlock;
-      double2 va[kPairs];
+      if constexpr (std::is_same_v<SIB, SplitSiblings>) {
+        if (sib.keep && none < K) {  // (where lanes overlap they write the same)
+          if constexpr (!SHORT) {
+            __builtin_memcpy(hist + at, v, sizeof v);
+          } else {
 #pragma unroll
-      for (int i = 0; i < kPairs; ++i) va[i] = p[i];
-      double acc = 0.0;
-      auto add_block = [&](double2 (&v)[kPairs], int block) {
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-          v[i].x = acc + v[i].x;
-          v[i].y = v[i].x + v[i].y;
-          acc = v[i].y;
-        }
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) p[block * kPairs + i] = v[i];
-      };
-      if constexpr (MANY) {
-        for (int k = 0; k < n_blocks; ++k) {
-          if (k > 0) {
-#pragma unroll
-            for (int i = 0; i < kPairs; ++i) va[i] = p[k * kPairs + i];
+            for (int k = 0; k < K; ++k) hist[at + (k < K - B ? 0 : k - (K - B))] = v[k];
           }
-          add_block(va, k);
-        }
-      } else {
-        double2 vb[kPairs];
-        for (int k = 0; k < n_blocks; k += 2) {
-          const bool has_b = k + 1 < n_blocks;
-          if (has_b) {
-#pragma unroll
-            for (int i = 0; i < kPairs; ++i) vb[i] = p[(k + 1) * kPairs + i];
-          }
-          add_block(va, k);
-          if (k + 2 < n_blocks) {
-#pragma unroll
-            for (int i = 0; i < kPairs; ++i) va[i] = p[(k + 2) * kPairs + i];
-          }
-          if (has_b) add_block(vb, k + 1);
         }
       }
     }
-    // The parent terms need sums that other lanes of the first wavefront wrote, and only those: the fences keep
-    // the compiler from moving the reads up, and no other wavefront has to be waited for.
-    static_assert(3 * kSplitMaxGroup <= 64, "the running sums of a group are the work of one wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (tid < nf) {
-      const double G = pg[tid * S + B - 1], H = ph[tid * S + B - 1];
-      parent[tid] = __ddiv_rn(__dmul_rn(G, G), H + lambda);
+    if (!whole || (step + 1) * kRows > n_features) {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (k < none) v[k] = gbdt_bin_t{0.0f, 0.0f, 0u};
     }
-    __syncthreads();
-
-    // 3. the gains of this group's (feature, threshold) pairs
+    // running sums
+    double pg[K], ph[K], pn[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      pg[k] = (k ? pg[k - 1] : 0.0) + (double)v[k].grad;
+      ph[k] = (k ? ph[k - 1] : 0.0) + (double)v[k].hess;
+      pn[k] = (k ? pn[k - 1] : 0.0) + (double)v[k].count;
+    }
+    const double bg = row_lanes.before(row_lanes.prefix(pg[K - 1]));
+    const double bh = row_lanes.before(row_lanes.prefix(ph[K - 1]));
+    const double bn = row_lanes.before(row_lanes.prefix(pn[K - 1]));
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      pg[k] += bg;
+      ph[k] += bh;
+      pn[k] += bn;
+    }
+    bool same = (row_lanes.before(pg[K - 1]) == bg) & (row_lanes.before(ph[K - 1]) == bh);
+#pragma unroll
+    for (int k = 1; k < K; ++k) {
+      same &= pg[k - 1] + (double)v[k].grad == pg[k];
+      same &= ph[k - 1] + (double)v[k].hess == ph[k];
+    }
+    if (__ballot(!same) != 0ull) {
 #pragma unroll 1
-    for (int i = 0; i < STEPS; ++i) {
-      int row0, bin0;
-      step_at(i, row0, bin0);
-      if (row0 >= nf) break;  // (the same for the whole wavefront)
-      const int fl = row0 + row_lane, t = bin0 + bin_lane;
-      if (fl >= nf || t >= B - 1) continue;
-      const int e = row0 * S + bin0 + lane_cell, last = fl * S + B - 1;
-      const double GL = pg[e], HL = ph[e], NL = pn[e];
-      const double G = pg[last], H = ph[last], N = pn[last];
-      const double GR = G - GL, HR = H - HL;
-      const double NR = N - NL;  // counts are exact in fp64
-      const bool ok = NL >= 1.0 && NR >= 1.0 && HL >= min_child_hess && HR >= min_child_hess;
-      if (ok) {
-        const double lt = __ddiv_rn(__dmul_rn(GL, GL), HL + lambda);
-        const double rt = __ddiv_rn(__dmul_rn(GR, GR), HR + lambda);
-        const double gain = __dsub_rn(__dadd_rn(lt, rt), parent[fl]);
-        if (best_pair < 0 || gain > best_gain) {  // pairs ascend: ties keep the earlier pair
-          best_gain = gain;
-          best_pair = (f0 - f_first + fl) * (B - 1) + t;
-          best_gl = GL;
-          best_hl = HL;
-          best_nl = NL;
-          best_g = G;
-          best_h = H;
-          best_n = N;
+      for (int turn = 0; turn < (1 << LB); ++turn) {  // after turn i the row's lanes 0 .. i are right
+        double g = turn ? row_lanes.before(pg[K - 1]) : 0.0, h = turn ? row_lanes.before(ph[K - 1]) : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          g += (double)v[k].grad;
+          h += (double)v[k].hess;
+          pg[k] = g;
+          ph[k] = h;
+        }
+      }
+    }
+    const double G = row_lanes.last(pg[K - 1], lane), H = row_lanes.last(ph[K - 1], lane);
+    const double N = row_lanes.last(pn[K - 1], lane);
+
+    // what a threshold gains at most
+    const double hp = H + lambda;
+    double rp = __builtin_amdgcn_rcp(hp);
+    rp = fma(rp, fma(-hp, rp, 1.0), rp);
+    const double parent_about = G * G * rp, parent_least = parent_about * (1.0 - kSlack);
+    double most[K];
+    bool ok[K], any = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double GL = pg[k], HL = ph[k], GR = G - GL, HR = H - HL;
+      ok[k] = pn[k] >= 1.0 && N - pn[k] >= 1.0 && HL >= min_child_hess && HR >= min_child_hess && k >= none;
+      const double a = HL + lambda, b = HR + lambda, ab = a * b;
+      double r = __builtin_amdgcn_rcp(ab);
+      r = fma(r, fma(-ab, r, 1.0), r);
+      most[k] = fma(fma(GL * GL, b, GR * GR * a) * r, 1.0 + kSlack, -parent_least);
+      any = any || (ok[k] && (!positive || !(most[k] < bound)));
+    }
+    if (__ballot(any) != 0ull) {
+      if (positive) {  // what some threshold gains for certain
+        double top = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < K; ++k) top = ok[k] ? fmax(top, most[k]) : top;
+        bound = fmax(bound, wave_max(top - 8.0 * kSlack * (fabs(top) + parent_about)));
+      }
+      const double parent = __ddiv_rn(__dmul_rn(G, G), hp);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const bool divide = ok[k] && (!positive || !(most[k] < bound));  // (true where most[k] is no number)
+        if (__ballot(divide) == 0ull) continue;
+        if (divide) {
+          const double GL = pg[k], HL = ph[k], GR = G - GL, HR = H - HL;
+          const double lt = __ddiv_rn(__dmul_rn(GL, GL), HL + lambda);
+          const double rt = __ddiv_rn(__dmul_rn(GR, GR), HR + lambda);
+          const double gain = __dsub_rn(__dadd_rn(lt, rt), parent);
+          if (best_pair < 0 || gain > best_gain) {  // pairs ascend: ties keep the earlier pair
+            best_gain = gain;
+            best_pair = (step * kRows + row - f_first) * (B - 1) + bin0 - skip + k;
+            best_gl = GL;
+            best_hl = HL;
+            best_nl = pn[k];
+            best_g = G;
+            best_h = H;
+            best_n = N;
+          }
         }
       }
     }
   }
-  const int32_t my_pair = best_pair;
-  block_argmax(best_gain, best_pair, s_gain, s_pair);
-  // the thread that holds the winning pair (thread 0 when there is none) hands the candidate over
-  const bool writer = best_pair < 0 ? tid == 0 : my_pair == best_pair;
-  if (writer) {
-    SplitCand c;
-    const int32_t e = best_pair;
-    if (e < 0) {
-      c.gain = 0.0;
-      c.gl = c.hl = c.gr = c.hr = 0.0;
-      c.nl = c.nr = 0;
-      c.feature = -1;
-      c.bin = -1;
-    } else {
-      const int fl = e / (B - 1);
-      const int t = e - fl * (B - 1);
-      c.gain = best_gain;
-      c.gl = best_gl;
-      c.hl = best_hl;
-      c.nl = (uint32_t)best_nl;
-      c.gr = best_g - best_gl;
-      c.hr = best_h - best_hl;
-      c.nr = (uint32_t)(best_n - best_nl);
-      c.feature = f_first + fl;
-      c.bin = t;
+
+  // the wavefront's best pair, then the workgroup's
+  {
+    const int32_t top = wave_argmax(best_gain, best_pair);
+    if (top < 0 ? lane == 0 : best_pair == top) {
+      SplitCand c;
+      if (top < 0) {
+        c.gain = 0.0;
+        c.gl = c.hl = c.gr = c.hr = 0.0;
+        c.nl = c.nr = 0;
+        c.feature = -1;
+        c.bin = -1;
+      } else {
+        const int fl = top / (B - 1);
+        c.gain = best_gain;
+        c.gl = best_gl;
+        c.hl = best_hl;
+        c.nl = (uint32_t)best_nl;
+        c.gr = best_g - best_gl;
+        c.hr = best_h - best_hl;
+        c.nr = (uint32_t)(best_n - best_nl);
+        c.feature = f_first + fl;
+        c.bin = top - fl * (B - 1);
+      }
+      s_cand[wave] = c;
+      s_pair[wave] = top;
     }
-    store_cand(cand + blockIdx.x, c);
+  }
+  __syncthreads();
+  if (wave != 0) return;  // the first wavefront does the rest
+  const int32_t my_pair = lane < n_waves ? s_pair[lane] : -1;
+  const int32_t top = wave_argmax(lane < n_waves ? s_cand[lane & (kSplitMaxWaves - 1)].gain : 0.0, my_pair);
+  const bool writer = top < 0 ? lane == 0 : my_pair == top;
+  auto write_record = [&](const SplitCand& c) {
+    gbdt_split_t r;
+    r.feature = c.feature;
+    r.bin = c.bin;
+    r.gain = (float)c.gain;
+    r.left_grad = (float)c.gl;
+    r.left_hess = (float)c.hl;
+    r.left_count = c.nl;
+    r.right_grad = (float)c.gr;
+    r.right_hess = (float)c.hr;
+    r.right_count = c.nr;
+    out[blockIdx.y] = r;
+    if (mirror) mirror[blockIdx.y] = r;
+  };
+  const int32_t n_cand = (int32_t)gridDim.x;
+  if (n_cand == 1) {  // the histogram's only workgroup
+    if (writer) write_record(s_cand[lane]);
+    return;
+  }
+  cand += (size_t)blockIdx.y * gridDim.x;
+  bool last = false;
+  if (writer) {
+    store_cand(cand + blockIdx.x, s_cand[lane]);
     // HARDWARE ASSUMPTION (gfx942 / gfx950, not the language's memory model): a device-scope
     // atomic store is written through to the point where the other XCDs' device-scope atomic
     // loads read it, and is acknowledged (vmcnt) only then.  Waiting for the candidate's
@@ -426,32 +495,26 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
     // needs, and the reader needs no acquire because it reads the candidates with device-scope
     // atomic loads only.  A release / acquire pair in the language's sense would also write back
     // and invalidate every line of the L2, which costs tens of microseconds here -- several
-    // times the whole kernel.  tests/test_gpu_robustness.py runs 64 x 250 workgroups of this
-    // hand-off 20 times and every split test goes through it; on a part where the assumption
+    // times the whole kernel.  tests/test_gpu_robustness.py runs 20 launches of 64 histograms whose workgroups hand
+    // off so, and every split test of more than one workgroup goes through it; on a part where the assumption
     // did not hold those tests would show stale candidates.
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0); expcnt, lgkmcnt untouched
     unsigned int* ticket = split_ticket(blockIdx.y);
     const unsigned int old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = old == gridDim.x - 1;
+    last = old == gridDim.x - 1;
     if (last)  // back to zero for the next launch
       __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = last;
   }
-  __syncthreads();
-  if (!s_last) return;
+  if (__ballot(last) == 0ull) return;
   // The ticket's value has arrived, so every other workgroup's candidate was acknowledged
   // before its ticket; the loads below are device-scope atomics and bypass stale caches.
 
-  // ---- the histogram's last workgroup: arg-max over all candidates.  Each thread folds
-  // a strided subset in ascending order, then a tree reduction.
-  // (Two round trips to the other workgroups' results: the keys of all candidates, then the winner's record,
-  // which its owner fetches and writes.  Fetching whole candidates at once saves the second, but 56 bytes
-  // apart seven words of each take longer than that: a lone histogram of 500 x 64, 250 candidates, 9.9 us so
-  // and 9.5 with keys first; 28 candidates 6.9 either way.)
-  const int32_t n_cand = (int32_t)gridDim.x;
+  // ---- the histogram's last workgroup: arg-max over all candidates.  (Two round trips to the other workgroups'
+  // results: the keys of all candidates, then the winner's record, which its owner fetches and writes.
+  // Fetching whole candidates at once saves the second, but 56 bytes apart seven words of each take longer than that.)
   double bg = 0.0;
   int32_t bi = -1;
-  for (int32_t i = tid; i < n_cand; i += kSplitThreads) {
+  for (int32_t i = lane; i < n_cand; i += 64) {
     double gain;
     int32_t feature;
     load_cand_key(cand + i, &gain, &feature);
@@ -460,30 +523,13 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
       bi = i;
     }
   }
-  const int32_t my_cand = bi;
-  block_argmax(bg, bi, s_gain, s_pair);
-  if (bi < 0 ? tid == 0 : my_cand == bi) {
-    gbdt_split_t r;
-    if (bi < 0) {
-      r.feature = -1;
-      r.bin = -1;
-      r.gain = 0.0f;
-      r.left_grad = r.left_hess = r.right_grad = r.right_hess = 0.0f;
-      r.left_count = r.right_count = 0;
+  const int32_t won = wave_argmax(bg, bi);
+  if (won < 0 ? lane == 0 : bi == won) {
+    if (won < 0) {
+      write_record(s_cand[0]);  // (no workgroup has an admissible threshold, this one included)
     } else {
-      const SplitCand mine = load_cand(cand + bi);
-      r.feature = mine.feature;
-      r.bin = mine.bin;
-      r.gain = (float)mine.gain;
-      r.left_grad = (float)mine.gl;
-      r.left_hess = (float)mine.hl;
-      r.left_count = mine.nl;
-      r.right_grad = (float)mine.gr;
-      r.right_hess = (float)mine.hr;
-      r.right_count = mine.nr;
+      write_record(load_cand(cand + won));
     }
-    *out = r;
-    if (mirror) mirror[blockIdx.y] = r;
   }
 }
 
