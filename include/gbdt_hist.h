@@ -525,6 +525,10 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
  * kernels use.  Returns the number of blocks, or a negative gbdt_status.  Host only. */
 int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int32_t cols, int32_t by_column,
                          int64_t* tile_out, int32_t* block_out, int32_t max_blocks);
+/* The same for a launch with wide accumulation whose 256-bin main tiles are built in halves: block_out[3 * i] = tile,
+ * [3 * i + 1] = half, [3 * i + 2] = workgroup of block i.  Returns the blocks of the launch. */
+int gbdt_debug_half_blocks(int32_t n_features, int64_t n_rows, int32_t cols, int32_t by_column, int32_t* block_out,
+                           int32_t max_blocks);
 /* The column plan gbdt_bins_fuse makes for features with the given numbers of levels (1..64
  * each): col_out[f] / stride_out[f] = the column of feature f and the weight of its bin in the
  * column's joint value; *n_cols_out the number of columns.  Host only. */

@@ -135,9 +135,42 @@ GBDT_HD LineBlock line_block(int32_t wm, int32_t n_main, int32_t wr, int32_t dea
   return r;
 }
 
+// The same for a launch whose main tiles are built in halves (plan_halves): the two halves of a (tile, column) follow
+// one another 8 blocks apart, as the tiles of a line do, because they read the same bytes; the remainder tile, which has no
+// halves, comes last.
+struct HalfBlock {
+  int32_t tile, half;
+  uint32_t col;
+};
+GBDT_HD HalfBlock half_block(int32_t wm, int32_t n_main, int32_t deal, uint32_t cols, bool by_column, uint32_t b) {
+  const uint32_t main_blocks = (uint32_t)n_main * cols, dealt = main_blocks / kXcds * kXcds;
+  HalfBlock r;
+  if (b >= 2u * main_blocks) {
+    r.tile = n_main;
+    r.half = 0;
+    r.col = b - 2u * main_blocks;
+    return r;
+  }
+  uint32_t of;
+  if (b < 2u * dealt) {
+    const uint32_t i = b / kXcds;
+    r.half = (int32_t)(i % 2u);
+    of = i / 2u * kXcds + b % kXcds;
+  } else {
+    const uint32_t i = b - 2u * dealt, rest = main_blocks - dealt;
+    r.half = i < rest ? 0 : 1;
+    of = dealt + i - (uint32_t)r.half * rest;
+  }
+  const LineBlock lb = line_block(wm, n_main, 0, deal, cols, by_column, of);
+  r.tile = lb.tile;
+  r.col = lb.col;
+  return r;
+}
+
 struct BatchBlock {
   int32_t leaf;  // its place in the table
   int32_t tile;  // feature tile
+  int32_t half;  // of the tile, where main tiles are built in halves
   int32_t wg;    // workgroup of (leaf, tile)
 };
 
@@ -162,7 +195,18 @@ GBDT_HD BatchBlock batch_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t 
   BatchBlock r;
   r.leaf = batch_leaf_of(leaf, n_leaves, lb.col);
   r.tile = lb.tile;
+  r.half = 0;
   r.wg = (int32_t)(lb.col - leaf[r.leaf].first_wg);
+  return r;
+}
+GBDT_HD BatchBlock batch_half_block(const BatchLeaf* leaf, int32_t n_leaves, int32_t wm, int32_t n_main,
+                                    int32_t deal, uint32_t cols, uint32_t b) {
+  const HalfBlock hb = half_block(wm, n_main, deal, cols, true, b);
+  BatchBlock r;
+  r.leaf = batch_leaf_of(leaf, n_leaves, hb.col);
+  r.tile = hb.tile;
+  r.half = hb.half;
+  r.wg = (int32_t)(hb.col - leaf[r.leaf].first_wg);
   return r;
 }
 

@@ -333,6 +333,8 @@ struct BuildGeom {
   int unit_epochs;      // epochs per unit
   bool one_unit_each;   // short leaf: every workgroup has exactly one unit, no counter
   int blocks_per_wg;    // partial blocks a workgroup writes: 1, or 2 with wide accumulation
+  bool halves;          // main tiles are built in halves (plan_halves)
+  int parts;            // tiles, or halves and the remainder tile
   size_t partial_words;  // total words of all partial blocks
 };
 
@@ -418,14 +420,17 @@ static_assert(kTailUnitEpochs >= 3, "a unit's successor is taken in its third-la
 // workgroups per CU of the kernel variant as reported by the runtime (<= 0: estimate
 // from the LDS footprint alone).
 BuildGeom make_geom(int32_t n_features, int32_t n_bins, int64_t n_leaf, int cus,
-                    int wg_per_cu_hint, bool wide = false, int64_t max_wgs = (int64_t)1 << 40) {
+                    int wg_per_cu_hint, bool wide = false, bool halves = false, int64_t max_wgs = (int64_t)1 << 40) {
   BuildGeom g;
   g.plan = make_tile_plan(n_features, n_bins);
+  g.halves = halves;
+  g.parts = plan_n_parts(g.plan, halves);
   const TilePlan& p = g.plan;
   g.nt = kBuildThreads;
   g.blocks_per_wg = wide ? 2 : 1;
-  const size_t main_block = (size_t)3 * plan_cells(p, p.wm);
-  g.lds_bytes = (size_t)plan_cells(p, p.wm) * 8 * g.blocks_per_wg + 4 * (g.nt / 64) * sizeof(float) + 8;
+  const size_t main_block = (size_t)3 * plan_cells(p, p.wm);  // (of both halves where tiles are built so)
+  const size_t wg_cells = plan_cells(p, halves ? 16 : p.wm);
+  g.lds_bytes = wg_cells * 8 * g.blocks_per_wg + 4 * (g.nt / 64) * sizeof(float) + 8;
   int wg_per_cu = wg_per_cu_hint;
   if (wg_per_cu <= 0) {
     wg_per_cu = (int)(kLdsPerCu / g.lds_bytes);
@@ -434,15 +439,15 @@ BuildGeom make_geom(int32_t n_features, int32_t n_bins, int64_t n_leaf, int cus,
   }
   if (wg_per_cu < 1) wg_per_cu = 1;
   const int64_t resident = (int64_t)cus * wg_per_cu;
-  const int n_tiles = plan_n_tiles(p);
   const int64_t n_epochs = (n_leaf + kEpochRows - 1) / kEpochRows;
   // (A narrow tile's epochs are cheaper, but not by much: the per-epoch overhead does
   // not shrink with the tile.  It gets as many workgroups as a main tile.)
-  int64_t budget = resident / n_tiles;
+  int64_t budget = resident / g.parts;
   if (budget > max_wgs) budget = max_wgs;
   plan_leaf_units(n_epochs, budget, &g.wgs, &g.unit_epochs, &g.one_unit_each);
+  // (a 16-byte tile of 256 bins needs half of what is set aside for it)
   g.partial_words = ((size_t)p.n_main * g.wgs * main_block +
-                     (size_t)(p.wr ? g.wgs : 0) * 3 * (p.wr ? plan_cells(p, p.wr) : 0)) *
+                     (size_t)(p.wr ? g.wgs : 0) * 3 * (p.wr ? (size_t)plan_pages(p, p.wr) * p.cap * 32 : 0)) *
                     g.blocks_per_wg;
   return g;
 }
@@ -465,7 +470,7 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
     } else {
       const int percent = g.plan.nib && g.plan.wr ? kFirstUnitPercentUneven : kFirstUnitPercent;
       const int32_t first = (int32_t)(n_epochs * percent / 100 / g.wgs);
-      const bool lines = line_tiles > 1 && g.plan.n_main > 1;
+      const bool lines = (line_tiles > 1 && g.plan.n_main > 1) || g.halves;
       if (first >= kUnitEpochs && (!indexed || lines)) {
         u.first_epochs = first;
         u.unit_epochs = kTailUnitEpochs;
@@ -473,10 +478,14 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
     }
   }
   // no counter when every workgroup has one unit anyway, or when the split must be fixed
-  u.fixed_stride = (g.one_unit_each || deterministic) ? g.wgs : 0;
-  u.deal = deal_order(line_tiles, g.unit_epochs, (int64_t)g.wgs * plan_n_tiles(g.plan), cus, g.blocks_per_wg > 1);
+  // (... or when there are more parts than counters)
+  u.fixed_stride = (g.one_unit_each || deterministic || g.parts > kCounterSlots) ? g.wgs : 0;
+  u.deal = deal_order(line_tiles, g.unit_epochs, (int64_t)g.wgs * g.parts, cus, g.blocks_per_wg > 1);
   return u;
 }
+
+// A leaf that a build takes as sparse in the matrix (plan_halves): a list of at most a fifth of the rows.
+bool leaf_is_sparse(bool indexed, int64_t n_leaf, int64_t n_rows) { return indexed && n_leaf <= n_rows / 5; }
 
 // Kernel variants: bin capacity -> (main tile width, 4-bit, waves per SIMD the
 // register budget is set for).
@@ -487,12 +496,13 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
 #define GBDT_VARIANT_16W 16, 64, true, kBuildThreads, 6, double
 #define GBDT_VARIANT_64W 64, 64, false, kBuildThreads, 4, double
 #define GBDT_VARIANT_256W 256, 32, false, kBuildThreads, 2, double
+#define GBDT_VARIANT_256W_HALVES 256, 32, false, kBuildThreads, 4, double
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false>
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false>
 int query_occupancy() {
   int n = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &n, reinterpret_cast<const void*>(hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, INDEXED, WIDE>), NT, 0);
+      &n, reinterpret_cast<const void*>(hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, INDEXED, WIDE, HALVES>), NT, 0);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return 0;
@@ -502,19 +512,23 @@ int query_occupancy() {
 
 // Resident workgroups per CU of the build kernel variant for this bin capacity
 // (registers, LDS and wave slots taken into account by the runtime); cached.
-int build_wg_per_cu(int cap, bool indexed, bool wide = false) {
+int build_wg_per_cu(int cap, bool indexed, bool wide = false, bool halves = false) {
   // GBDT_HIST_WG_PER_CU overrides the runtime's answer (tuning experiments only)
   if (const char* e = getenv("GBDT_HIST_WG_PER_CU")) {
     const int v = atoi(e);
     if (v > 0) return v;
   }
-  static int cache[6][2] = {{-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}};
+  static int cache[7][2] = {{-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}, {-1, -1}};
   const int ci = cap == 16 ? 0 : (cap == 64 ? 1 : 2);
-  int& c = cache[ci + (wide ? 3 : 0)][indexed ? 1 : 0];
+  int& c = cache[halves ? 6 : ci + (wide ? 3 : 0)][indexed ? 1 : 0];
+  if (c < 0 && halves) {
+    c = indexed ? query_occupancy<GBDT_VARIANT_256W_HALVES, true, true, true>()
+                : query_occupancy<GBDT_VARIANT_256W_HALVES, false, true, true>();
+  }
   if (c < 0 && wide) {
     if (cap == 16) c = indexed ? query_occupancy<GBDT_VARIANT_16W, true, true>() : query_occupancy<GBDT_VARIANT_16W, false, true>();
     else if (cap == 64) c = indexed ? query_occupancy<GBDT_VARIANT_64W, true, true>() : query_occupancy<GBDT_VARIANT_64W, false, true>();
-    else c = indexed ? query_occupancy<GBDT_VARIANT_256W, true, true>() : query_occupancy<GBDT_VARIANT_256W, false, true>();
+    else c = query_occupancy<GBDT_VARIANT_256W, true, true>();  // (only lists are built so)
   }
   if (c < 0) {
     if (cap == 16) c = indexed ? query_occupancy<GBDT_VARIANT_16, true>() : query_occupancy<GBDT_VARIANT_16, false>();
@@ -622,28 +636,28 @@ struct BuildTimer {
   }
 };
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false>
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false, bool LISTS_ONLY = false>
 int launch_build(const BuildArgs& a, int blocks, hipStream_t s, bool timed = true) {
   BuildTimer timer;
   int rc = timed ? timer.begin(s) : GBDT_OK;
   if (rc != GBDT_OK) return rc;
   if (a.idx) {
-    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, true, WIDE>), dim3(blocks), dim3(NT), 0, s,
+    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, true, WIDE, HALVES>), dim3(blocks), dim3(NT), 0, s,
                        a);
-  } else {
-    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, false, WIDE>), dim3(blocks), dim3(NT), 0, s,
+  } else if constexpr (!LISTS_ONLY) {
+    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, false, WIDE, HALVES>), dim3(blocks), dim3(NT), 0, s,
                        a);
   }
   HIP_TRY(hipGetLastError());
   return timer.end(s);
 }
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false>
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false>
 int launch_build_batch(const BatchArgs& a, int blocks, hipStream_t s) {
   BuildTimer timer;
   int rc = timer.begin(s);
   if (rc != GBDT_OK) return rc;
-  hipLaunchKernelGGL((hist_build_batch_kernel<CAP, WM, NIB, NT, WPE, ACC, WIDE>), dim3(blocks), dim3(NT), 0, s, a);
+  hipLaunchKernelGGL((hist_build_batch_kernel<CAP, WM, NIB, NT, WPE, ACC, WIDE, HALVES>), dim3(blocks), dim3(NT), 0, s, a);
   HIP_TRY(hipGetLastError());
   return timer.end(s);
 }
@@ -971,8 +985,10 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
     n_bins = kFusedCap;
   }
   const size_t joint_words = fused ? (size_t)n_features * n_bins * 3 : 0;
-  const int wg_per_cu = build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, leaf_row_idx != nullptr, wide);
-  BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(), wg_per_cu, wide);
+  const TilePlan plan0 = make_tile_plan(n_features, n_bins);
+  const bool halves = plan_halves(plan0, wide, leaf_is_sparse(leaf_row_idx != nullptr, n_leaf_rows, n_rows));
+  const int wg_per_cu = build_wg_per_cu(plan0.cap, leaf_row_idx != nullptr, wide, halves);
+  BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(), wg_per_cu, wide, halves);
   if (fixed_base) {
     // fewer workgroups per tile until the partial blocks fit the fixed buffer
     size_t avail_words = fixed_bytes > kWsHeadBytes ? (fixed_bytes - kWsHeadBytes) / 4 : 0;
@@ -986,7 +1002,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
                  n_features, n_bins, per_wg * 4, avail_words * 4);
         return GBDT_EUNSUPPORTED;
       }
-      g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(), wg_per_cu, wide, fit);
+      g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(), wg_per_cu, wide, halves, fit);
     }
   }
   const TilePlan& p = g.plan;
@@ -1055,8 +1071,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   a.direct_out = (g.wgs == 1 && !fused) ? hist_out : nullptr;  // (joint histograms always take the reduction pass)
   a.n_features = n_features;
   a.n_bins = n_bins;
-  const int n_tiles = plan_n_tiles(p);
-  const int blocks = n_tiles * g.wgs;
+  const int blocks = g.parts * g.wgs;
   const bool uses_counters = a.fixed_stride == 0;
   // While the stream is being captured nothing runs now, so what is known about the
   // counters must not change: the captured sequence zeroes them itself, before and (if
@@ -1082,8 +1097,10 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
       rc = launch_build<GBDT_VARIANT_16W, true>(a, blocks, s, timed);
     } else if (p.cap == 64) {
       rc = launch_build<GBDT_VARIANT_64W, true>(a, blocks, s, timed);
+    } else if (halves) {
+      rc = launch_build<GBDT_VARIANT_256W_HALVES, true, true>(a, blocks, s, timed);
     } else {
-      rc = launch_build<GBDT_VARIANT_256W, true>(a, blocks, s, timed);
+      rc = launch_build<GBDT_VARIANT_256W, true, false, true>(a, blocks, s, timed);
     }
   } else if (p.cap == 16) {
     rc = launch_build<GBDT_VARIANT_16>(a, blocks, s, timed);
@@ -1106,6 +1123,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   m.n_bins = n_bins;
   m.chunks_main = a.chunks;
   m.chunks_rem = p.wr ? a.chunks : 0;
+  m.halves = halves ? 1 : 0;
   m.counters = uses_counters ? counters : nullptr;
   const int max_slots = plan_slots(p, p.wm);
   const int mx = (n_bins * max_slots + kMergeCells - 1) / kMergeCells;
@@ -1277,10 +1295,12 @@ size_t gbdt_workspace_bytes(int64_t n_rows, int32_t n_features, int32_t n_bins) 
   if (!valid_shape(n_rows, n_features, n_bins)) return 0;
   const int cap = make_tile_plan(n_features, n_bins).cap;
   const bool wide = g_wide.load() != 0;
-  const BuildGeom g0 =
-      make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, false, wide), wide);
-  const BuildGeom g1 =
-      make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, true, wide), wide);
+  // (a list that is built from whole tiles has half the resident workgroups and needs as much)
+  const bool halves = plan_halves(make_tile_plan(n_features, n_bins), wide, false);
+  const BuildGeom g0 = make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, false, wide, halves),
+                                 wide, halves);
+  const BuildGeom g1 = make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, true, wide, halves),
+                                 wide, halves);
   size_t b = (g0.partial_words > g1.partial_words ? g0.partial_words : g1.partial_words) * 4 +
              2 * (((size_t)n_rows + 63) / 64 * 64) * 4;  // + grad / hess of a leaf in leaf order
   // + the joint histograms of a fused copy (at most one column per feature)
@@ -1348,7 +1368,9 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   if (n_tiles > 65535) return GBDT_EUNSUPPORTED;
   if ((n_rows + kEpochRows) * (int64_t)p.wm >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
   const bool wide = g_wide.load() != 0;
-  const int cus = device_cu_count(), wg_per_cu = build_wg_per_cu(p.cap, true, wide);
+  const bool halves = plan_halves(p, wide, true);
+  const int cus = device_cu_count(), wg_per_cu = build_wg_per_cu(p.cap, true, wide, halves);
+  const int n_parts = plan_n_parts(p, halves);
   // words of the partial blocks of one workgroup column (two blocks each with wide accumulation)
   const size_t col = (p.cap == 16 ? variant_column_words<GBDT_VARIANT_16>(p)
                                   : (p.cap == 64 ? variant_column_words<GBDT_VARIANT_64>(p)
@@ -1362,9 +1384,9 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     for (int32_t i = 0; i < n; ++i)
       if (leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     if (leaf_offsets[l0 + n] - leaf_offsets[l0] >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
-    const BatchPlan b = plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_tiles, seg_off);
+    const BatchPlan b = plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_parts, seg_off);
     if (l0 == 0) first_plan = b;
-    if ((int64_t)b.total_wgs * n_tiles >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
+    if ((int64_t)b.total_wgs * n_parts >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
     const size_t w = (size_t)b.total_wgs * col;
     if (w > need_words) need_words = w;
   }
@@ -1393,7 +1415,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   }
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;
-    const BatchPlan b = l0 == 0 ? first_plan : plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_tiles, seg_off);
+    const BatchPlan b = l0 == 0 ? first_plan : plan_batch(leaf_offsets, l0, n, cus, wg_per_cu, n_parts, seg_off);
     BatchMergeArgs m;
     m.m.partials = (const uint32_t*)ws;
     m.m.out = hist_out + (size_t)l0 * n_features * n_bins;
@@ -1402,6 +1424,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     m.m.n_bins = n_bins;
     m.m.chunks_main = 0;
     m.m.chunks_rem = 0;
+    m.m.halves = halves ? 1 : 0;
     m.m.counters = nullptr;
     m.column_words = col;
     m.blocks_per_wg = wide ? 2 : 1;
@@ -1427,19 +1450,21 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_main = p.n_main;
       a.wr = p.wr;
       a.line_tiles = plan_line_tiles(n_rows);
-      a.deal = deal_order(a.line_tiles, b.most_unit_epochs, (int64_t)b.total_wgs * n_tiles, cus, wide);
+      a.deal = deal_order(a.line_tiles, b.most_unit_epochs, (int64_t)b.total_wgs * n_parts, cus, wide);
       a.n_leaves = n;
       a.n_cols = b.total_wgs;
       a.hist_out = hist_out + (size_t)l0 * n_features * n_bins;
       a.n_features = n_features;
       a.n_bins = n_bins;
       memcpy(a.leaf, b.leaf, sizeof a.leaf);
-      const int blocks = (int)b.total_wgs * n_tiles;
+      const int blocks = (int)b.total_wgs * n_parts;
       if (wide) {
         if (p.cap == 16) {
           rc = launch_build_batch<GBDT_VARIANT_16W, true>(a, blocks, s);
         } else if (p.cap == 64) {
           rc = launch_build_batch<GBDT_VARIANT_64W, true>(a, blocks, s);
+        } else if (halves) {
+          rc = launch_build_batch<GBDT_VARIANT_256W_HALVES, true, true>(a, blocks, s);
         } else {
           rc = launch_build_batch<GBDT_VARIANT_256W, true>(a, blocks, s);
         }
@@ -1483,16 +1508,17 @@ int gbdt_hist_build_batch(const void* bin_matrix, int64_t n_rows, int32_t n_feat
 size_t gbdt_hist_build_batch_workspace_bytes(int32_t n_features, int32_t n_bins, int32_t n_leaves) {
   if (n_features <= 0 || n_bins < 2 || n_bins > 256 || n_leaves < 0) return 0;
   const TilePlan p = make_tile_plan(n_features, n_bins);
-  const int n_tiles = plan_n_tiles(p);
   const bool wide = g_wide.load() != 0;
-  const int64_t resident = (int64_t)device_cu_count() * build_wg_per_cu(p.cap, true, wide);
+  const bool halves = plan_halves(p, wide, true);
+  const int n_parts = plan_n_parts(p, halves);
+  const int64_t resident = (int64_t)device_cu_count() * build_wg_per_cu(p.cap, true, wide, halves);
   const size_t col = (p.cap == 16 ? variant_column_words<GBDT_VARIANT_16>(p)
                                   : (p.cap == 64 ? variant_column_words<GBDT_VARIANT_64>(p)
                                                  : variant_column_words<GBDT_VARIANT_256>(p))) *
                      (wide ? 2 : 1);
   // the leaves of a launch share the resident workgroups, and each has at least one per tile: plan_batch takes
   // no plan of more columns than that
-  int64_t budget = resident / n_tiles;
+  int64_t budget = resident / n_parts;
   if (budget < 1) budget = 1;
   const int64_t per_launch = n_leaves < kBatchLeaves ? n_leaves : kBatchLeaves;
   // (the call gathers grad / hess into list order only when the scratch has 8 more bytes per listed
@@ -2234,8 +2260,10 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
                          int64_t* out, int32_t n_out) {
   if (!valid_shape(n_rows, n_features, n_bins) || n_leaf_rows < 0 || !out || n_out < 6) return GBDT_EINVAL;
   const bool wide = g_wide.load() != 0;
+  const TilePlan p = make_tile_plan(n_features, n_bins);
+  const bool halves = plan_halves(p, wide, leaf_is_sparse(indexed != 0, n_leaf_rows, n_rows));
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
-                                build_wg_per_cu(make_tile_plan(n_features, n_bins).cap, indexed != 0, wide), wide);
+                                build_wg_per_cu(p.cap, indexed != 0, wide, halves), wide, halves);
   const UnitPlan u = plan_units(g, n_leaf_rows, indexed != 0, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
   const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal, g.one_unit_each};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
@@ -2290,6 +2318,22 @@ int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int
     const LineBlock b = line_block(p.wm, p.n_main, p.wr, deal, (uint32_t)cols, by_column != 0, (uint32_t)i);
     block_out[2 * i] = b.tile;
     block_out[2 * i + 1] = (int32_t)b.col;
+  }
+  return (int)blocks;
+}
+
+int gbdt_debug_half_blocks(int32_t n_features, int64_t n_rows, int32_t cols, int32_t by_column, int32_t* block_out,
+                           int32_t max_blocks) {
+  if (n_rows < 0 || n_features <= 0 || cols < 1 || (!block_out && max_blocks > 0)) return GBDT_EINVAL;
+  const TilePlan p = make_tile_plan(n_features, 256);
+  const int64_t blocks = (int64_t)plan_n_parts(p, true) * cols;
+  if (blocks >= ((int64_t)1 << 31)) return GBDT_EUNSUPPORTED;
+  const int32_t deal = deal_order(plan_line_tiles(n_rows), kUnitEpochs, blocks, 1, true);
+  for (int64_t i = 0; i < blocks && i < max_blocks; ++i) {
+    const HalfBlock b = half_block(p.wm, p.n_main, deal, (uint32_t)cols, by_column != 0, (uint32_t)i);
+    block_out[3 * i] = b.tile;
+    block_out[3 * i + 1] = b.half;
+    block_out[3 * i + 2] = (int32_t)b.col;
   }
   return (int)blocks;
 }

@@ -371,6 +371,12 @@ __device__ __forceinline__ long long rint_to_i64(double v) {
   return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000LL;
 }
 
+// ... and back, exactly, for |i| < 2^51: an addition and a subtraction instead of two conversions, a scaling and an
+// addition.
+__device__ __forceinline__ double i64_to_f64(long long i) {
+  return __longlong_as_double(i + 0x4338000000000000LL) - 6755399441055744.0;
+}
+
 // Sum over the lanes of a wavefront with DPP moves (no LDS traffic); the total
 // arrives in lane 63.
 template <int CTRL, int ROW_MASK>
@@ -398,6 +404,7 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
 struct DirectOut {
   gbdt_bin_t* hist;  // [n_features][n_bins] of the leaf
   int32_t tile, wm, n_main, wr;
+  int32_t first_slot;  // of the tile, of the workgroup's histogram: 0, or 16 for a second half
   int32_t n_features, n_bins;
 };
 
@@ -411,7 +418,8 @@ struct TileShape {
   static constexpr int NBW = NWORD * (NIB ? 2 : 1); // byte-words (4 bin values each) per lane
   static constexpr int SLOTS = 4 * LPR * NBW;       // features of the tile
   static constexpr int PAGES = (SLOTS + 31) / 32;
-  static constexpr int CELLS = PAGES * CAP * 32;
+  static constexpr int PITCH = plan_pitch(CAP, SLOTS);  // cells from a bin to the next
+  static constexpr int CELLS = PAGES * CAP * PITCH;
   static constexpr int NW = NT / 64;
   static constexpr int PP = CELLS / NT;             // cells drained by one thread
   static constexpr int GPE = 64 / RPW;              // row groups per wavefront per epoch
@@ -445,7 +453,9 @@ struct TileShape {
 //
 // Addressing.  The byte address of a cell inside its page is (bin << 8) | (8 *
 // slot): one byte-permute builds it from the loaded bins and a per-lane table of
-// the four values 8 * slot; the page is an immediate offset of the instruction.
+// the four values 8 * slot; the page is an immediate offset of the instruction.  With rows of 16 cells it is
+// (bin >> 1) << 8 | (bin & 1) << 7 | (8 * slot): the lowest bits of a word's four bins first move into
+// the table's bytes, four instructions more for four values.
 //
 // Arithmetic.  The paper adds floats with a compare-and-swap loop in local memory
 // (App. B.3).  gfx950 has a native LDS float add, but it retires about 0.33
@@ -471,8 +481,11 @@ struct TileShape {
 // epoch barriers and across the hand-out of work.
 //
 // All wavefronts of a workgroup share ONE histogram; no replica has to be reduced.
+//
+// chunk_stride: bytes from a lane-chunk of a row to the next: VEC, or more where the workgroup takes a part of every
+// chunk only (plan_halves).
 template <int CAP, int W, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE = false>
-__device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uint32_t row_stride,
+__device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uint32_t row_stride, uint32_t chunk_stride,
                                            const int32_t* __restrict__ idx,
                                            const float* __restrict__ grad,
                                            const float* __restrict__ hess, bool stats_by_pos,
@@ -485,6 +498,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
                                            uint32_t* __restrict__ out_lo = nullptr) {
   static_assert(!WIDE || sizeof(ACC) == 8, "wide cells are drained into fp64 accumulators");
   using S = TileShape<CAP, W, NIB, NT>;
+  constexpr bool kShortRows = S::PITCH == 16;
   constexpr int VEC = S::VEC, NWORD = S::NWORD, LPR = S::LPR, RPW = S::RPW, NBW = S::NBW;
   constexpr int CELLS = S::CELLS, PP = S::PP, NW = S::NW;
   constexpr int NTBL = LPR == 8 ? 1 : 2;  // LPR 4: two byte-words share a page of 32 slots
@@ -573,10 +587,10 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   auto from_owner = [&](uint32_t v, auto gi_tag) -> uint32_t {
     constexpr int gi = decltype(gi_tag)::value;
     if (LPR == 4) {  // quad broadcast: every lane of a quad takes lane gi of the quad
-      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, gi * 0x55, 0xf, 0xf, false);
+      return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, gi * 0x55, 0xf, 0xf, false);
     }
     // LPR 8: lanes 0..7 of each row of 16 take lane gi, lanes 8..15 take lane 8 + gi
-    const int lo8 = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + gi, 0xf, 0x3, false);
+    const int lo8 = __builtin_amdgcn_mov_dpp((int)v, 0x150 + gi, 0xf, 0xf, false);
     return (uint32_t)__builtin_amdgcn_update_dpp(lo8, (int)v, 0x158 + gi, 0xf, 0xc, false);
   };
 
@@ -591,7 +605,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     uint32_t off;  // 32-bit byte offsets ((n_rows + slack) * row_stride < 2^32)
     const uint8_t* base = tile;
     if (INDEXED) {
-      off = from_owner(rows, gi_tag) + (uint32_t)(VEC * j);
+      off = from_owner(rows, gi_tag) + chunk_stride * (uint32_t)j;
     } else {
       off = off0;
       base += (uint32_t)(gi * RPW) * row_stride;
@@ -628,9 +642,11 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     for (int bw = 0; bw < NBW; ++bw) {
       const int page = LPR == 8 ? bw : (bw >> 1);
       const int tv = LPR == 8 ? 0 : (bw & 1);
+      const uint32_t upper = kShortRows ? (bword[bw] >> 1) & 0x7f7f7f7fu : bword[bw];
+      const uint32_t lower = kShortRows ? ((bword[bw] << 7) & 0x80808080u) | tbl[tv] : tbl[tv];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t a = __builtin_amdgcn_perm(bword[bw], tbl[tv], sel[k]);
+        const uint32_t a = __builtin_amdgcn_perm(upper, lower, sel[k]);
         __hip_atomic_fetch_add(
             reinterpret_cast<unsigned long long*>(cells + a + page * (CAP * 256)), add,
             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -646,7 +662,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // (an epoch past the leaf is read at the leaf's last epoch: in range, and ignored)
   const uint32_t n_epochs_leaf = (end + kEpochRows - 1) / kEpochRows;
   const uint32_t past = n_epochs_leaf * (uint32_t)kEpochRows;  // position of "no epoch"
-  const uint32_t lane_offset = (uint32_t)rho * row_stride + (uint32_t)(VEC * j);
+  const uint32_t lane_offset = (uint32_t)rho * row_stride + chunk_stride * (uint32_t)j;
   auto group_offset0 = [&](uint32_t e0) {
     const uint32_t e = e0 < past ? e0 : past - (uint32_t)kEpochRows;
     return (e + (uint32_t)wave * 64u) * row_stride + lane_offset;
@@ -684,8 +700,8 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     if constexpr (WIDE) {
       // the count sits below the gradient sum; an arithmetic shift drops it whatever the sign
       acc_c[m] += (uint32_t)t & ((1u << kCountBits) - 1u);
-      acc_g[m] = (ACC)fma((double)((long long)t >> kCountBits), inv_gw, (double)acc_g[m]);
-      acc_h[m] = (ACC)fma((double)((long long)th >> kCountBits), inv_hw, (double)acc_h[m]);
+      acc_g[m] = (ACC)fma(i64_to_f64((long long)t >> kCountBits), inv_gw, (double)acc_g[m]);
+      acc_h[m] = (ACC)fma(i64_to_f64((long long)th >> kCountBits), inv_hw, (double)acc_h[m]);
       return;
     }
     // both sums times 2^kSumPad (the scales inv_g, inv_h allow for it)
@@ -891,9 +907,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
 #pragma unroll
     for (int m = 0; m < PP; ++m) {
       const int cell = tid + m * NT;
-      const int bin = (cell >> 5) % CAP;
-      const int slot = (cell / (CAP * 32)) * 32 + (cell & 31);
-      const int32_t f = plan_feature_of(plan, direct.tile, slot);
+      const int bin = (cell / S::PITCH) % CAP;
+      const int slot = (cell / (CAP * S::PITCH)) * S::PITCH + cell % S::PITCH;
+      const int32_t f = plan_feature_of(plan, direct.tile, direct.first_slot + slot);
       if (slot < S::SLOTS && bin < direct.n_bins && f < direct.n_features) {
         gbdt_bin_t r;
         r.grad = (float)acc_g[m];
@@ -936,50 +952,78 @@ __device__ __host__ constexpr int block_words() {
 // matrix on one XCD, otherwise neighbouring blocks on different tiles; either way the workgroups of a column start
 // together, and the row ids / gradients / hessians of an epoch are fetched from HBM once and served to the
 // other tiles from cache.
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false>
+template <int CAP, int WM, bool NIB, int NT, bool WIDE, bool HALVES>
+struct BuildShape {
+  static_assert(!HALVES || (WIDE && CAP == 256), "see plan_halves");
+  static constexpr bool kHalves = HALVES;
+  static constexpr int kMainW = kHalves ? 16 : WM;        // width of the tile that a workgroup has the cells of
+  static constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, kMainW, NIB, NT>::CELLS;
+  // the cells (8 bytes each; two histograms with wide accumulation), the reduction scratch and the unit box
+  static constexpr int kLdsWords = kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1;
+};
+
+// One workgroup's work on (tile, half) of a leaf: build_tile with the tile's width.  leaf_out: the leaf's partial blocks,
+// `chunks` of every part (tile or half), parts back to back, wg the workgroup's among them; with wide accumulation its second
+// block lies wgs blocks behind its first.
+template <int CAP, int WM, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE, bool HALVES, typename... REST>
+__device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows, int32_t n_main, int32_t wr,
+                                           int32_t line_tiles, int32_t t, int32_t half, uint32_t* leaf_out, size_t chunks,
+                                           size_t wg, size_t wgs, gbdt_bin_t* direct_hist, int32_t n_features,
+                                           int32_t n_bins, unsigned long long* lds, const int32_t* idx, const float* grad,
+                                           const float* hess, bool by_pos, uint32_t stat_shift, REST... rest) {
+  using BS = BuildShape<CAP, WM, NIB, NT, WIDE, HALVES>;
+  const TileAt at = plan_tile_at(WM, n_main, wr, n_rows, line_tiles, t);
+  const uint8_t* tile = packed + at.off;
+  const uint32_t stride = (uint32_t)at.stride;
+  const bool paced = WM == 64 && at.shared;
+  const DirectOut direct = {direct_hist, t, WM, n_main, wr, 16 * half, n_features, n_bins};
+  constexpr size_t kMainBlock = (size_t)block_words<CAP, BS::kMainW, NIB, NT>();
+  if (t < n_main) {
+    constexpr uint32_t kVec = TileShape<CAP, WM, NIB, NT>::VEC;
+    const size_t part = BS::kHalves ? 2 * (size_t)t + (size_t)half : (size_t)t;
+    uint32_t* out = leaf_out + (part * chunks + wg) * kMainBlock;
+    build_tile<CAP, BS::kMainW, NIB, NT, ACC, INDEXED, WIDE>(tile + 4 * half, stride, kVec, idx, grad, hess, by_pos, stat_shift,
+                                                             paced, rest..., lds, out, direct, out + wgs * kMainBlock);
+    return;
+  }
+  uint32_t* rem_base = leaf_out + (size_t)(BS::kHalves ? 2 * n_main : n_main) * chunks * kMainBlock;
+  auto remainder = [&](auto width) {
+    constexpr int W = decltype(width)::value;
+    constexpr size_t kBlock = (size_t)block_words<CAP, W, NIB, NT>();
+    build_tile<CAP, W, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, TileShape<CAP, W, NIB, NT>::VEC, idx, grad, hess, by_pos,
+                                                    stat_shift, paced, rest..., lds, rem_base + wg * kBlock, direct,
+                                                    rem_base + (wgs + wg) * kBlock);
+  };
+  if (wr == 16) {
+    remainder(std::integral_constant<int, 16>{});
+  } else if constexpr (WM > 32) {
+    remainder(std::integral_constant<int, 32>{});
+  }
+}
+
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 hist_build_kernel(BuildArgs a) {
-  // one histogram of the main tile width (8 bytes per cell; two with wide accumulation), the
-  // reduction scratch and the unit box
-  constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
-  __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const uint32_t n_leaf = (uint32_t)a.n_leaf;
-  const LineBlock lb = line_block(WM, a.n_main, a.wr, a.deal, (uint32_t)a.wgs, false, blockIdx.x);
-  const int32_t t = lb.tile;
-  const int32_t c = (int32_t)lb.col;  // workgroup of the tile
-  uint32_t* counter = a.counters + plan_counter_slot(t);
-  const TileAt at = plan_tile_at(WM, a.n_main, a.wr, a.n_rows, a.line_tiles, t);
-  const uint8_t* tile = a.packed + at.off;
-  const uint32_t stride = (uint32_t)at.stride;
-  const uint32_t n_firsts = a.first_epochs ? (uint32_t)a.wgs : 0u;
-  const bool paced = WM == 64 && at.shared;
-  const DirectOut direct = {a.direct_out, t, WM, a.n_main, a.wr, a.n_features, a.n_bins};
-  // wide accumulation: the workgroup's second block lies a.wgs blocks behind its first
-  if (t < a.n_main) {
-    constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
-    uint32_t* out = a.partials + ((size_t)t * a.chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf,
-                                                     (uint32_t)c, (uint32_t)a.first_epochs,
-                                                     (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter,
-                                                     (uint32_t)a.wgs, n_firsts, lds,
-                                                     out, direct, out + (size_t)a.wgs * kBlock);
+  using BS = BuildShape<CAP, WM, NIB, NT, WIDE, HALVES>;
+  __shared__ __align__(16) unsigned long long lds[BS::kLdsWords];
+  int32_t t, half = 0, c;  // c: workgroup of the tile
+  if constexpr (BS::kHalves) {
+    const HalfBlock hb = half_block(WM, a.n_main, a.deal, (uint32_t)a.wgs, false, blockIdx.x);
+    t = hb.tile;
+    half = hb.half;
+    c = (int32_t)hb.col;
   } else {
-    uint32_t* rem_base =
-        a.partials + (size_t)a.n_main * a.chunks * (size_t)block_words<CAP, WM, NIB, NT>();
-    if (a.wr == 16) {
-      constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
-      build_tile<CAP, 16, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
-          (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
-          rem_base + (size_t)(a.wgs + c) * kBlock);
-    } else if constexpr (WM > 32) {
-      constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
-      build_tile<CAP, 32, NIB, NT, ACC, INDEXED, WIDE>(
-          tile, stride, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, paced, n_leaf, (uint32_t)c, (uint32_t)a.first_epochs,
-          (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs, n_firsts, lds, rem_base + (size_t)c * kBlock, direct,
-          rem_base + (size_t)(a.wgs + c) * kBlock);
-    }
+    const LineBlock lb = line_block(WM, a.n_main, a.wr, a.deal, (uint32_t)a.wgs, false, blockIdx.x);
+    t = lb.tile;
+    c = (int32_t)lb.col;
   }
+  uint32_t* counter = a.counters + plan_counter_slot(BS::kHalves ? 2 * t + half : t);
+  const uint32_t n_firsts = a.first_epochs ? (uint32_t)a.wgs : 0u;
+  build_part<CAP, WM, NIB, NT, ACC, INDEXED, WIDE, HALVES>(
+      a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, t, half, a.partials, (size_t)a.chunks, (size_t)c, (size_t)a.wgs,
+      a.direct_out, a.n_features, a.n_bins, lds, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, (uint32_t)a.n_leaf,
+      (uint32_t)c, (uint32_t)a.first_epochs, (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs,
+      n_firsts);
 }
 
 // Gradients and hessians of a row list, in list order: g_out[i] = grad[idx[i]].  The paper
@@ -1054,52 +1098,27 @@ __device__ __host__ inline size_t column_words(int32_t n_main, int32_t wr) {
   return w;
 }
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false>
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 hist_build_batch_kernel(BatchArgs a) {
-  constexpr int kCells = (WIDE ? 2 : 1) * TileShape<CAP, WM, NIB, NT>::CELLS;
-  __shared__ __align__(16) unsigned long long lds[kCells + (4 * (NT / 64) * 4 + 7) / 8 + 1];
-  const BatchBlock blk = batch_block(a.leaf, a.n_leaves, WM, a.n_main, a.wr, a.deal, a.n_cols, blockIdx.x);
+  using BS = BuildShape<CAP, WM, NIB, NT, WIDE, HALVES>;
+  __shared__ __align__(16) unsigned long long lds[BS::kLdsWords];
+  const BatchBlock blk = BS::kHalves
+                             ? batch_half_block(a.leaf, a.n_leaves, WM, a.n_main, a.deal, a.n_cols, blockIdx.x)
+                             : batch_block(a.leaf, a.n_leaves, WM, a.n_main, a.wr, a.deal, a.n_cols, blockIdx.x);
   const BatchLeaf lf = a.leaf[blk.leaf];
   const int32_t wgs = (int32_t)batch_wgs(lf);
   const uint32_t unit_epochs = batch_unit_epochs(lf);
   constexpr int kPerWg = WIDE ? 2 : 1;  // partial blocks per workgroup
-  const int32_t chunks = kPerWg * wgs;
-  const int32_t t = blk.tile, c = blk.wg;
-  const bool is_main = t < a.n_main;
-  const TileAt at = plan_tile_at(WM, a.n_main, a.wr, a.n_rows, a.line_tiles, t);
-  const uint8_t* tile = a.packed + at.off;
-  const uint32_t stride = (uint32_t)at.stride;
-  const int32_t* idx = a.idx + lf.row_off;
-  const bool paced = WM == 64 && at.shared;
   const bool by_pos = a.stats_by_pos != 0;  // then grad / hess follow the concatenated row lists
-  const float* grad = by_pos ? a.grad + lf.row_off : a.grad;
-  const float* hess = by_pos ? a.hess + lf.row_off : a.hess;
   uint32_t* leaf_out =
       a.partials + (size_t)lf.first_wg * kPerWg * column_words<CAP, WM, NIB, NT>(a.n_main, a.wr);
-  const DirectOut direct = {
-      wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr,
-      t, WM, a.n_main, a.wr, a.n_features, a.n_bins};
-  if (is_main) {
-    constexpr size_t kBlock = (size_t)block_words<CAP, WM, NIB, NT>();
-    uint32_t* out = leaf_out + ((size_t)t * chunks + c) * kBlock;
-    build_tile<CAP, WM, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
-                                                  (uint32_t)wgs, nullptr, 0u, 0u, lds, out, direct,
-                                                  out + (size_t)wgs * kBlock);
-  } else {
-    uint32_t* rem_base = leaf_out + (size_t)a.n_main * chunks * (size_t)block_words<CAP, WM, NIB, NT>();
-    if (a.wr == 16) {
-      constexpr size_t kBlock = (size_t)block_words<CAP, 16, NIB, NT>();
-      build_tile<CAP, 16, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
-                                                    (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
-                                                    direct, rem_base + (size_t)(wgs + c) * kBlock);
-    } else if constexpr (WM > 32) {
-      constexpr size_t kBlock = (size_t)block_words<CAP, 32, NIB, NT>();
-      build_tile<CAP, 32, NIB, NT, ACC, true, WIDE>(tile, stride, idx, grad, hess, by_pos, (uint32_t)a.stat_shift, paced, lf.n, (uint32_t)c, 0u, unit_epochs,
-                                                    (uint32_t)wgs, nullptr, 0u, 0u, lds, rem_base + (size_t)c * kBlock,
-                                                    direct, rem_base + (size_t)(wgs + c) * kBlock);
-    }
-  }
+  build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES>(
+      a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, blk.tile, blk.half, leaf_out, (size_t)(kPerWg * wgs),
+      (size_t)blk.wg, (size_t)wgs,
+      wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr, a.n_features, a.n_bins, lds,
+      a.idx + lf.row_off, by_pos ? a.grad + lf.row_off : a.grad, by_pos ? a.hess + lf.row_off : a.hess, by_pos,
+      (uint32_t)a.stat_shift, lf.n, (uint32_t)blk.wg, 0u, unit_epochs, (uint32_t)wgs, (uint32_t*)nullptr, 0u, 0u);
 }
 
 }  // namespace

@@ -25,6 +25,7 @@ struct MergeArgs {
   int32_t n_bins;
   int32_t chunks_main;
   int32_t chunks_rem;
+  int32_t halves;      // main tiles were built in halves (plan_halves)
   uint32_t* counters;  // the tiles' unit counters, set back to zero here; NULL: not used by the build
 };
 
@@ -44,14 +45,24 @@ constexpr int kMergeQuads = kMergeCells / 4;  // a thread takes 4 neighbouring s
 // requested together.
 template <int PARTS>
 __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
-  if (a.counters && blockIdx.x == 0 && threadIdx.x == 0) a.counters[plan_counter_slot((int32_t)blockIdx.y)] = 0u;
+  if (a.counters && blockIdx.x == 0 && threadIdx.x == 0) {
+    const int32_t y = (int32_t)blockIdx.y;
+    if (!a.halves) {
+      a.counters[plan_counter_slot(y)] = 0u;
+    } else {
+      a.counters[plan_counter_slot(2 * y)] = 0u;  // (2 * n_main: the remainder tile's)
+      if (y < a.plan.n_main) a.counters[plan_counter_slot(2 * y + 1)] = 0u;
+    }
+  }
   __shared__ double s_g[PARTS][kMergeCells];
   __shared__ double s_h[PARTS][kMergeCells];
   __shared__ uint32_t s_n[PARTS][kMergeCells];
   const int32_t t = blockIdx.y;
   const int32_t w = plan_tile_width(a.plan, t);
   const int32_t slots = plan_slots(a.plan, w);
-  const size_t hw = (size_t)plan_cells(a.plan, w);
+  const bool halved = a.halves && t < a.plan.n_main;
+  const int32_t wb = halved ? 16 : w;  // width of the tile that a partial block is of
+  const size_t hw = (size_t)plan_cells(a.plan, wb);
   const size_t main_block = (size_t)3 * plan_cells(a.plan, a.plan.wm);
   const uint32_t* p;
   int32_t chunks;
@@ -69,7 +80,8 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
   if (e0 < a.n_bins * slots) {
     const int32_t bin = e0 / slots;
     const int32_t slot = e0 - bin * slots;
-    p += (size_t)plan_cell(a.plan, bin, slot) + (size_t)part * 3 * hw;
+    if (halved) p += (size_t)(slot >> 4) * chunks * 3 * hw;  // (all blocks of the first half, then those of the second)
+    p += (size_t)plan_cell(a.plan, wb, bin, halved ? slot & 15 : slot) + (size_t)part * 3 * hw;
     double g[4] = {0.0, 0.0, 0.0, 0.0}, h[4] = {0.0, 0.0, 0.0, 0.0};
     uint32_t n[4] = {0u, 0u, 0u, 0u};
     const size_t step = (size_t)PARTS * 3 * hw;

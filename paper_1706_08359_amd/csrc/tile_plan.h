@@ -34,9 +34,10 @@
 // Histogram slot of a feature of the tile:  s = j + LPR * q + 4 * LPR * bw.
 // The local-memory histogram and each partial block in the workspace are cells
 // [page = s / 32][bin][s % 32]; one page row (32 cells of 8 bytes) spans all 32
-// banks exactly once.  With this slot order the lanes the LDS serves together,
+// banks twice.  With this slot order the lanes the LDS serves together,
 // which at any step work on pairwise different (j, q), fall into different
-// banks whatever the bin values are (see build_tile).
+// banks whatever the bin values are (see build_tile).  A tile of 16 slots with 256 bins has rows of 16 cells
+// (they span the banks once): half the cells to clear, drain and sum.
 #ifndef GBDT_TILE_PLAN_H_
 #define GBDT_TILE_PLAN_H_
 
@@ -142,6 +143,8 @@ GBDT_HD TileAt plan_tile_at(int32_t wm, int32_t n_main, int32_t wr, int64_t n_ro
 }
 
 GBDT_HD int32_t plan_n_tiles(const TilePlan& p) { return p.n_main + (p.wr ? 1 : 0); }
+// what workgroups of a build take one each of: tiles, or their halves
+GBDT_HD int32_t plan_n_parts(const TilePlan& p, bool halves) { return (halves ? 2 * p.n_main : p.n_main) + (p.wr ? 1 : 0); }
 GBDT_HD int32_t plan_tile_width(const TilePlan& p, int32_t t) { return t < p.n_main ? p.wm : p.wr; }
 // features (= slots) held by a tile of width w
 GBDT_HD int32_t plan_slots(const TilePlan& p, int32_t w) { return p.nib ? 2 * w : w; }
@@ -150,11 +153,27 @@ GBDT_HD int32_t plan_slots(const TilePlan& p, int32_t w) { return p.nib ? 2 * w 
 GBDT_HD int32_t plan_vec(const TilePlan& p, int32_t w) { return p.nib ? (w == 16 ? 4 : 8) : w / 4; }
 // pages of 32 slots in the histogram of a tile of width w
 GBDT_HD int32_t plan_pages(const TilePlan& p, int32_t w) { return (plan_slots(p, w) + 31) / 32; }
+// cells from a bin to the next in the histogram of a tile of width w
+GBDT_HD constexpr int32_t plan_pitch(int32_t cap, int32_t slots) { return cap == 256 && slots == 16 ? 16 : 32; }
 // cells ((bin, slot) pairs, padding included) of the histogram of a tile of width w
-GBDT_HD int32_t plan_cells(const TilePlan& p, int32_t w) { return plan_pages(p, w) * p.cap * 32; }
-// index of cell (bin, slot) inside a histogram / partial block
-GBDT_HD int32_t plan_cell(const TilePlan& p, int32_t bin, int32_t slot) {
-  return (slot >> 5) * p.cap * 32 + bin * 32 + (slot & 31);
+GBDT_HD int32_t plan_cells(const TilePlan& p, int32_t w) {
+  return plan_pages(p, w) * p.cap * plan_pitch(p.cap, plan_slots(p, w));
+}
+// index of cell (bin, slot) inside a histogram / partial block of a tile of width w
+GBDT_HD int32_t plan_cell(const TilePlan& p, int32_t w, int32_t bin, int32_t slot) {
+  const int32_t pitch = plan_pitch(p.cap, plan_slots(p, w));
+  return (slot >> 5) * p.cap * 32 + bin * pitch + (slot & 31);
+}
+
+// With wide accumulation a pair of cells is kept for every (bin, slot), and a 32-byte tile of 256 bins fills most of a
+// CU's local memory: one workgroup a CU.  Its main tiles are then built in HALVES, by different workgroups, two a CU: half h
+// takes the slots 16 h .. 16 h + 15, which are the byte-word h of every lane-chunk, and has the cells of a 16-byte tile.
+// (2,270,000 x 137 x 255, root 302 us with whole tiles, 217 in halves, 10 % of the rows 54 and 45; 10,500,000 x 28 x 255,
+// root 269 and 218, half of the rows 157 and 123.)  Not so sparse leaves of a matrix of one tile, which are bound by the
+// lines they fetch, bins and statistics, now twice: a tenth of 10,500,000 x 28 x 255 49.7 us whole, 53.5 in halves; 32 leaves
+// of 4,000,000 x 28 x 255, all its rows, in a call 217 and 225.
+GBDT_HD bool plan_halves(const TilePlan& p, bool wide, bool sparse) {
+  return wide && p.cap == 256 && !(sparse && p.n_main + (p.wr ? 1 : 0) == 1);
 }
 
 struct FeatureSlot {
