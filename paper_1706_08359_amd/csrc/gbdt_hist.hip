@@ -1125,15 +1125,12 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   m.chunks_rem = p.wr ? a.chunks : 0;
   m.halves = halves ? 1 : 0;
   m.counters = uses_counters ? counters : nullptr;
-  const int max_slots = plan_slots(p, p.wm);
-  const int mx = (n_bins * max_slots + kMergeCells - 1) / kMergeCells;
-  if (merge_parts((int64_t)mx * plan_n_tiles(p), a.chunks) == kMergePartsWide) {
-    hipLaunchKernelGGL(hist_merge_kernel<kMergePartsWide>, dim3(mx, plan_n_tiles(p)),
-                       dim3(kMergeQuads * kMergePartsWide), 0, s, m);
-  } else {
-    hipLaunchKernelGGL(hist_merge_kernel<kMergeParts>, dim3(mx, plan_n_tiles(p)), dim3(kMergeQuads * kMergeParts),
-                       0, s, m);
-  }
+  const int64_t tile_cells = (int64_t)n_bins * plan_slots(p, p.wm);
+  const int parts = merge_parts(tile_cells, plan_n_tiles(p), a.chunks);
+  const dim3 merge_grid((unsigned)((tile_cells + merge_wg_cells(parts) - 1) / merge_wg_cells(parts)), plan_n_tiles(p));
+  auto merge = [&](auto kernel) { hipLaunchKernelGGL(kernel, merge_grid, dim3(merge_wg_threads(parts)), 0, s, m); };
+  merge(parts == 1 ? hist_merge_kernel<1> : parts == 2 ? hist_merge_kernel<2> : parts == 4 ? hist_merge_kernel<4>
+        : parts == kMergePartsMost ? hist_merge_kernel<kMergePartsMost> : hist_merge_kernel<kMergePartsWide>);
   HIP_TRY(hipGetLastError());
   if (uses_counters && !capturing) set_counters_zero(counters, true);  // the reduction pass leaves them zero
   if (fused) {
@@ -1478,20 +1475,18 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       if (rc != GBDT_OK) return rc;
     }
     if (n_merge == 0) continue;
-    const int max_slots = plan_slots(p, p.wm);
-    const int mx = (n_bins * max_slots + kMergeCells - 1) / kMergeCells;
+    const int64_t tile_cells = (int64_t)n_bins * plan_slots(p, p.wm);
     int32_t most_chunks = 0;
     for (int i = 0; i < n_merge; ++i) {
       const int32_t c = (int32_t)batch_wgs(m.leaf[i]) * (wide ? 2 : 1);
       most_chunks = c > most_chunks ? c : most_chunks;
     }
-    if (merge_parts((int64_t)mx * n_tiles * n_merge, most_chunks) == kMergePartsWide) {
-      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergePartsWide>, dim3(mx, n_tiles, n_merge),
-                         dim3(kMergeQuads * kMergePartsWide), 0, s, m);
-    } else {
-      hipLaunchKernelGGL(hist_merge_batch_kernel<kMergeParts>, dim3(mx, n_tiles, n_merge),
-                         dim3(kMergeQuads * kMergeParts), 0, s, m);
-    }
+    const int parts = merge_parts(tile_cells, (int64_t)n_tiles * n_merge, most_chunks);
+    const dim3 merge_grid((unsigned)((tile_cells + merge_wg_cells(parts) - 1) / merge_wg_cells(parts)), n_tiles, n_merge);
+    auto merge = [&](auto kernel) { hipLaunchKernelGGL(kernel, merge_grid, dim3(merge_wg_threads(parts)), 0, s, m); };
+    merge(parts == 1 ? hist_merge_batch_kernel<1> : parts == 2 ? hist_merge_batch_kernel<2>
+          : parts == 4 ? hist_merge_batch_kernel<4>
+          : parts == kMergePartsMost ? hist_merge_batch_kernel<kMergePartsMost> : hist_merge_batch_kernel<kMergePartsWide>);
     HIP_TRY(hipGetLastError());
   }
   return GBDT_OK;
@@ -1663,6 +1658,7 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
     a.rows_per_thread = rpt;
     a.n_leaves = n;
     uint32_t chunks = 0;
+    bool any_empty = false;
     for (int32_t i = 0; i < kPartBatchLeaves; ++i) {
       PartLeaf& lf = a.leaf[i];
       if (i < n) {
@@ -1671,13 +1667,14 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
         lf.split_idx = (uint32_t)i;
         lf.first_chunk = chunks;
         chunks += (uint32_t)(((int64_t)lf.n + chunk_rows - 1) / chunk_rows);
+        any_empty = any_empty || lf.n == 0;
       } else {
         lf.row_off = lf.out_off = lf.n = lf.split_idx = 0;
         lf.first_chunk = chunks;
       }
     }
     a.n_chunks = chunks;
-    if (n_left_out) {
+    if (n_left_out && any_empty) {
       hipLaunchKernelGGL(partition_empty_counts_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
       HIP_TRY(hipGetLastError());
     }

@@ -29,22 +29,32 @@ struct MergeArgs {
   uint32_t* counters;  // the tiles' unit counters, set back to zero here; NULL: not used by the build
 };
 
-constexpr int kMergeCells = 64;      // histogram cells per workgroup
-constexpr int kMergeParts = 8;       // threads that share the chunks of a cell ...
-constexpr int kMergePartsWide = 32;  // ... and when there are few cells and many chunks (one or two tiles built
-                                     // by hundreds of workgroups): 8 would leave most of the machine idle
-constexpr int kMergeQuads = kMergeCells / 4;  // a thread takes 4 neighbouring slots of a bin: 16-byte loads
+// Threads that share the partial blocks (chunks) of a cell, PARTS: 1, 2 or 4 where a cell has few chunks, 8 otherwise, and 32
+// where there are few cells and many chunks (one or two tiles built by hundreds of workgroups: 8 would leave most of the machine
+// idle).  A thread takes 4 neighbouring slots of a bin, with 16-byte loads, and has four chunks in flight, so with fewer than
+// 4 * PARTS of them threads would wait for nothing.
+constexpr int kMergePartsMost = 8, kMergePartsWide = 32;
+template <int PARTS>
+struct MergeShape {
+  static constexpr int kQuads = PARTS < 8 ? 256 / PARTS : 16;  // groups of 4 slots of a workgroup
+  static constexpr int kThreads = kQuads * PARTS;
+  static constexpr int kCells = 4 * kQuads;
+  // whole bins of a tile, of which every feature's run is then written together (12 bytes at a time is what
+  // the others write)
+  static constexpr bool kStaged = PARTS < 8;
+};
 
 // The "final reduction program" of Sec. 4: sums the partial histograms of the
-// workgroups that shared a feature tile.  A workgroup takes 64 consecutive (bin,
+// workgroups that shared a feature tile.  A workgroup takes kCells consecutive (bin,
 // slot) pairs of one tile (slot fastest, so reads of a partial block are coalesced
 // in runs of 32); PARTS threads per 4 pairs each sum every PARTS-th chunk in fp64, in chunk
 // order, and the sub-sums are added in a fixed order: the result does not depend
-// on scheduling.  Counts are summed as integers.  grid.y = tile.  (PARTS = 8 or 32;
-// which one is a function of the launch's shape only.)  Bound by the latency of its loads: four chunks are
-// requested together.
+// on scheduling.  Counts are summed as integers.  grid.y = tile.  (PARTS is a function of the launch's shape only.)
+// Bound by the latency of its loads: four chunks are requested together.  (64 leaves of 1,500,000 x 500 x 255, 20 of them
+// in 2 to 4 chunks: 57 us with 8 threads a cell and 12-byte stores, 25.5 with one and whole runs.)
 template <int PARTS>
 __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
+  using M = MergeShape<PARTS>;
   if (a.counters && blockIdx.x == 0 && threadIdx.x == 0) {
     const int32_t y = (int32_t)blockIdx.y;
     if (!a.halves) {
@@ -54,9 +64,11 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
       if (y < a.plan.n_main) a.counters[plan_counter_slot(2 * y + 1)] = 0u;
     }
   }
-  __shared__ double s_g[PARTS][kMergeCells];
-  __shared__ double s_h[PARTS][kMergeCells];
-  __shared__ uint32_t s_n[PARTS][kMergeCells];
+  constexpr int kSums = PARTS > 1 ? M::kCells : 1;
+  __shared__ double s_g[PARTS][kSums];
+  __shared__ double s_h[PARTS][kSums];
+  __shared__ uint32_t s_n[PARTS][kSums];
+  __shared__ uint32_t s_run[M::kStaged ? 3 * M::kCells + 128 : 1];  // [slot][bin of the workgroup's][3], a word between slots
   const int32_t t = blockIdx.y;
   const int32_t w = plan_tile_width(a.plan, t);
   const int32_t slots = plan_slots(a.plan, w);
@@ -73,17 +85,19 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
     p = a.partials + (size_t)a.plan.n_main * a.chunks_main * main_block;
     chunks = a.chunks_rem;
   }
-  const int quad = threadIdx.x % kMergeQuads;
-  const int part = threadIdx.x / kMergeQuads;
-  const int32_t e0 = blockIdx.x * kMergeCells + 4 * quad;
+  const int quad = threadIdx.x % M::kQuads;
+  const int part = threadIdx.x / M::kQuads;
+  const int32_t e_first = blockIdx.x * M::kCells, e_end = a.n_bins * slots;
+  if (e_first >= e_end) return;  // (the same for the whole workgroup: a narrow tile has fewer cells)
+  const int32_t run_bins = M::kCells / slots;  // (staged: a multiple of the slots)
+  const int32_t e0 = e_first + 4 * quad;
   // (a bin has a multiple of 16 slots, so the four cells are one bin's, and all live or none)
-  if (e0 < a.n_bins * slots) {
-    const int32_t bin = e0 / slots;
-    const int32_t slot = e0 - bin * slots;
-    if (halved) p += (size_t)(slot >> 4) * chunks * 3 * hw;  // (all blocks of the first half, then those of the second)
-    p += (size_t)plan_cell(a.plan, wb, bin, halved ? slot & 15 : slot) + (size_t)part * 3 * hw;
-    double g[4] = {0.0, 0.0, 0.0, 0.0}, h[4] = {0.0, 0.0, 0.0, 0.0};
-    uint32_t n[4] = {0u, 0u, 0u, 0u};
+  const int32_t bin0 = e0 / slots, slot0 = e0 - bin0 * slots;
+  double g[4] = {0.0, 0.0, 0.0, 0.0}, h[4] = {0.0, 0.0, 0.0, 0.0};
+  uint32_t n[4] = {0u, 0u, 0u, 0u};
+  if (e0 < e_end) {
+    if (halved) p += (size_t)(slot0 >> 4) * chunks * 3 * hw;  // (all blocks of the first half, then those of the second)
+    p += (size_t)plan_cell(a.plan, wb, bin0, halved ? slot0 & 15 : slot0) + (size_t)part * 3 * hw;
     const size_t step = (size_t)PARTS * 3 * hw;
     constexpr int kFlight = 4;
     for (int32_t c = part; c < chunks; c += kFlight * PARTS) {
@@ -114,46 +128,85 @@ __device__ __forceinline__ void merge_cells(const MergeArgs& a) {
       }
       p += kFlight * step;
     }
+    if constexpr (PARTS > 1) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      s_g[part][4 * quad + k] = g[k];
-      s_h[part][4 * quad + k] = h[k];
-      s_n[part][4 * quad + k] = n[k];
+      for (int k = 0; k < 4; ++k) {
+        s_g[part][4 * quad + k] = g[k];
+        s_h[part][4 * quad + k] = h[k];
+        s_n[part][4 * quad + k] = n[k];
+      }
     }
   }
-  __syncthreads();
-  const int cell = threadIdx.x;
-  const int32_t e = blockIdx.x * kMergeCells + cell;
-  if (cell < kMergeCells && e < a.n_bins * slots) {
-    const int32_t bin = e / slots;
-    const int32_t f = plan_feature_of(a.plan, t, e - bin * slots);
-    if (f < a.n_features) {  // else: padding slot
-      double g = 0.0, h = 0.0;
-      uint32_t n = 0;
+  auto stage = [&](int32_t bin, int32_t slot, double sg, double sh, uint32_t sn) {
+    uint32_t* to = s_run + slot * (3 * run_bins + 1) + 3 * (bin - e_first / slots);
+    to[0] = __float_as_uint((float)sg);
+    to[1] = __float_as_uint((float)sh);
+    to[2] = sn;
+  };
+  if constexpr (PARTS == 1) {
+    if (e0 < e_end) {
 #pragma unroll
+      for (int k = 0; k < 4; ++k) stage(bin0, slot0 + k, g[k], h[k], n[k]);
+    }
+  } else {
+    __syncthreads();
+#pragma unroll 1
+    for (int cell = threadIdx.x; cell < M::kCells; cell += M::kThreads) {
+      const int32_t e = e_first + cell;
+      if (e >= e_end) break;
+      double sg = 0.0, sh = 0.0;
+      uint32_t sn = 0;
+#pragma unroll 8
       for (int q = 0; q < PARTS; ++q) {
-        g += s_g[q][cell];
-        h += s_h[q][cell];
-        n += s_n[q][cell];
+        sg += s_g[q][cell];
+        sh += s_h[q][cell];
+        sn += s_n[q][cell];
       }
-      gbdt_bin_t r;
-      r.grad = (float)g;
-      r.hess = (float)h;
-      r.count = n;
-      a.out[(size_t)f * a.n_bins + bin] = r;
+      const int32_t bin = e / slots, slot = e - bin * slots;
+      if constexpr (M::kStaged) {
+        stage(bin, slot, sg, sh, sn);
+      } else {
+        const int32_t f = plan_feature_of(a.plan, t, slot);
+        if (f < a.n_features) {  // else: padding slot
+          gbdt_bin_t r;
+          r.grad = (float)sg;
+          r.hess = (float)sh;
+          r.count = sn;
+          a.out[(size_t)f * a.n_bins + bin] = r;
+        }
+      }
+    }
+  }
+  if constexpr (M::kStaged) {
+    __syncthreads();
+    const int32_t b0 = e_first / slots;
+    const int32_t live = 3 * (a.n_bins - b0 < run_bins ? a.n_bins - b0 : run_bins);  // words of a feature's run
+    const int32_t per = M::kThreads / slots;  // threads of a run (a slot count is at most 128)
+    const int32_t slot = threadIdx.x / per, first = threadIdx.x % per;
+    const int32_t f = plan_feature_of(a.plan, t, slot);
+    if (f < a.n_features) {  // else: padding slot
+      uint32_t* to = reinterpret_cast<uint32_t*>(a.out + (size_t)f * a.n_bins + b0);
+      const uint32_t* from = s_run + slot * (3 * run_bins + 1);
+      for (int32_t i = first; i < live; i += per) to[i] = from[i];
     }
   }
 }
 
 template <int PARTS>
-__global__ void __launch_bounds__(kMergeQuads * PARTS) hist_merge_kernel(MergeArgs a) {
+__global__ void __launch_bounds__(MergeShape<PARTS>::kThreads) hist_merge_kernel(MergeArgs a) {
   merge_cells<PARTS>(a);
 }
 
-// Threads per cell for a reduction over `blocks` workgroups of 8 of them and up to
-// `chunks` partial blocks per cell.
-inline int merge_parts(int64_t blocks, int32_t chunks) {
-  return (blocks < 512 && chunks >= 64) ? kMergePartsWide : kMergeParts;
+// Cells of a workgroup with `parts` threads a cell, and its threads.
+inline int merge_wg_cells(int parts) { return parts < 8 ? 1024 / parts : 64; }
+inline int merge_wg_threads(int parts) { return parts < 8 ? 256 : 16 * parts; }
+// Threads per cell for a reduction over n_tiles tiles (of all leaves) of `cells` cells at most, up to `chunks` partial blocks each.
+inline int merge_parts(int64_t cells, int64_t n_tiles, int32_t chunks) {
+  auto blocks = [&](int parts) { return (cells + merge_wg_cells(parts) - 1) / merge_wg_cells(parts) * n_tiles; };
+  int parts = 1;
+  while (parts < kMergePartsMost && (chunks > 4 * parts || blocks(parts) < 512)) parts *= 2;
+  if (parts == kMergePartsMost && blocks(parts) < 512 && chunks >= 64) parts = kMergePartsWide;
+  return parts;
 }
 
 // The same reduction for a batched launch: grid.z = leaf of the launch; its partial
@@ -168,7 +221,7 @@ struct BatchMergeArgs {
 };
 
 template <int PARTS>
-__global__ void __launch_bounds__(kMergeQuads * PARTS) hist_merge_batch_kernel(BatchMergeArgs a) {
+__global__ void __launch_bounds__(MergeShape<PARTS>::kThreads) hist_merge_batch_kernel(BatchMergeArgs a) {
   const BatchLeaf lf = a.leaf[blockIdx.z];
   if (batch_wgs(lf) == 1u) return;  // written by the build kernel itself
   MergeArgs m = a.m;
