@@ -358,6 +358,10 @@ bool stats_gather_pays(int n_tiles, int64_t list_rows, int64_t rows_per_leaf, in
          rows_per_leaf * dense_limit <= n_rows;
 }
 
+// From this many rows on grad and hess do not fit an XCD's L2, and several lists are gathered by parts of the rows.  (Eight
+// leaves of 200,000 x 100 x 255, build and partition: 41.8 us in list order, 43.2 by parts.)
+constexpr int64_t kGatherListsMinRows = 1 << 19;
+
 // When a tree's leaves are not gathered that way (few tiles), gbdt_grow_tree lays gradient and hessian
 // of every row side by side once: a scattered row then costs one line of statistics instead of two, beside
 // its line of bins.  From the size on at which both arrays no longer fit an XCD's L2.
@@ -1406,9 +1410,28 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   float* g_list = (float*)ws + need_words;
   float* h_list = g_list + stats_words / 2;
   if (by_pos) {
-    hipLaunchKernelGGL(stats_gather_kernel, dim3((unsigned)((total_rows + 255) / 256)), dim3(256), 0, s,
-                       row_idx + leaf_offsets[0], grad, hess, total_rows, g_list, h_list);
-    HIP_TRY(hipGetLastError());
+    if (n_leaves == 1 || n_rows < kGatherListsMinRows) {
+      hipLaunchKernelGGL(stats_gather_kernel, dim3((unsigned)((total_rows + 255) / 256)), dim3(256), 0, s,
+                         row_idx + leaf_offsets[0], grad, hess, total_rows, g_list, h_list);
+      HIP_TRY(hipGetLastError());
+    }
+    for (int32_t l0 = 0; n_leaves > 1 && n_rows >= kGatherListsMinRows && l0 < n_leaves; l0 += kGatherLists) {
+      GatherTable t;
+      t.n_lists = n_leaves - l0 < kGatherLists ? n_leaves - l0 : kGatherLists;
+      const int64_t base = leaf_offsets[l0], before = base - leaf_offsets[0];
+      uint32_t blocks = 0;
+      for (int32_t i = 0; i < t.n_lists; ++i) {
+        const int64_t n = leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i];
+        t.first[i] = (uint32_t)(leaf_offsets[l0 + i] - base);
+        t.first_block[i] = blocks;
+        blocks += (uint32_t)(((n + kXcds - 1) / kXcds + kGatherRows - 1) / kGatherRows);
+      }
+      t.first[t.n_lists] = (uint32_t)(leaf_offsets[l0 + t.n_lists] - base);
+      if (blocks == 0) continue;
+      hipLaunchKernelGGL(stats_gather_lists_kernel, dim3(blocks * kXcds), dim3(256), 0, s, row_idx + base, grad, hess, t,
+                         g_list + before, h_list + before);
+      HIP_TRY(hipGetLastError());
+    }
   }
   for (int32_t l0 = 0; l0 < n_leaves; l0 += kBatchLeaves) {
     const int32_t n = n_leaves - l0 < kBatchLeaves ? n_leaves - l0 : kBatchLeaves;

@@ -1040,6 +1040,60 @@ stats_gather_kernel(const int32_t* __restrict__ idx, const float* __restrict__ g
   h_out[i] = hess[r];
 }
 
+// The same for several row lists back to back, dealt out to the XCDs by parts of the lists: an XCD takes the k-th eighth of every
+// list, one list after the other.  Lists of a tree's leaves ascend, so those are about the same rows of grad and hess, whose
+// lines the XCD's L2 then fetches once for all lists instead of once for each (64 leaves of 1,500,000 rows: 30 us in list
+// order, 18 so).  Any other lists are gathered as well.  A block takes kGatherRows positions of a part.
+constexpr int kGatherLists = 448;
+constexpr int kGatherRows = 1024;
+struct GatherTable {
+  uint32_t first[kGatherLists + 1];        // position of a list's first entry, and of the last list's end
+  uint32_t first_block[kGatherLists + 1];  // blocks of an eighth of all lists before it
+  int32_t n_lists;
+};
+__global__ void __launch_bounds__(256)
+stats_gather_lists_kernel(const int32_t* __restrict__ idx, const float* __restrict__ grad,
+                          const float* __restrict__ hess, GatherTable t, float* __restrict__ g_out,
+                          float* __restrict__ h_out) {
+  const uint32_t part = blockIdx.x % kXcds, b = blockIdx.x / kXcds;
+  int32_t lo = 0, hi = t.n_lists - 1;  // the list that block b of this part is of (an empty list has no block)
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (t.first_block[mid] <= b) {
+      lo = mid;
+    } else {
+      hi = mid - 1;
+    }
+  }
+  const uint32_t begin = t.first[lo], n = t.first[lo + 1] - begin, each = (n + kXcds - 1) / kXcds;
+  const uint32_t at = part * each + (b - t.first_block[lo]) * (uint32_t)kGatherRows;
+  const uint32_t part_end = (part + 1) * each < n ? (part + 1) * each : n;
+  constexpr int kSteps = kGatherRows / 256;
+  uint32_t row[kSteps];
+#pragma unroll
+  for (int i = 0; i < kSteps; ++i) {
+    const uint32_t k = at + 256u * (uint32_t)i + threadIdx.x;
+    row[i] = k < part_end ? (uint32_t)idx[begin + k] : 0u;
+  }
+  float g[kSteps], h[kSteps];
+#pragma unroll
+  for (int i = 0; i < kSteps; ++i) {
+    const uint32_t k = at + 256u * (uint32_t)i + threadIdx.x;
+    if (k < part_end) {
+      g[i] = grad[row[i]];
+      h[i] = hess[row[i]];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kSteps; ++i) {
+    const uint32_t k = at + 256u * (uint32_t)i + threadIdx.x;
+    if (k < part_end) {
+      g_out[begin + k] = g[i];
+      h_out[begin + k] = h[i];
+    }
+  }
+}
+
 // Gradient and hessian of every row side by side, for a tree's builds: a leaf's scattered rows then
 // fetch one line for both instead of two (see kStatsPairMinRows).
 __global__ void __launch_bounds__(256)
