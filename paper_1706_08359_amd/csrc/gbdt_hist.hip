@@ -321,6 +321,7 @@ int device_cu_count() {
 }
 
 constexpr size_t kLdsPerCu = 160 * 1024;
+constexpr int64_t kPackStreamBytes = (int64_t)256 << 20;  // the memory-side cache; see pack_kernel
 constexpr int kMinRowsPerChunk = kEpochRows;
 static_assert(kPlanSlackBytes == (int64_t)kEpochRows * 64, "slack behind the tiles: one epoch of the widest tile");
 constexpr int kBuildThreads = 512;  // threads per workgroup of every build kernel variant
@@ -1173,8 +1174,10 @@ int gbdt_bins_pack(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
   if ((n_features + 63) / 64 > 65535) return GBDT_EUNSUPPORTED;
   const dim3 grid((unsigned)((n_rows + kPackRows - 1) / kPackRows),
                   (unsigned)((n_features + kPackFeatures - 1) / kPackFeatures));
-  hipLaunchKernelGGL(p.nib ? pack_kernel<true> : pack_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream,
-                     bins_rowmajor, n_rows, n_features, p, plan_line_tiles(n_rows),
+  const bool big = plan_packed_bytes(p, n_rows, n_features) > kPackStreamBytes;
+  const auto kernel = p.nib ? (big ? pack_kernel<true, true> : pack_kernel<true, false>)
+                            : (big ? pack_kernel<false, true> : pack_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, bins_rowmajor, n_rows, n_features, p, plan_line_tiles(n_rows),
                      (uint32_t)(p.cap - 1) * 0x01010101u, (uint8_t*)packed_out,
                      (uint8_t*)packed_out + plan_columns_base(p, n_rows), plan_column_stride(n_rows));
   HIP_TRY(hipGetLastError());

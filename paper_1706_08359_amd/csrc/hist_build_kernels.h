@@ -28,6 +28,10 @@ namespace {
 // and writes 16 rows of a column, eight threads a whole line of 128 bytes.  Bound by memory:
 // 400,000 x 2,000 is 800 MB read and 1.6 GB written.  (Two kernels of 4-byte words put together from single
 // bytes took 0.80 ms for the tiles and 1.03 ms for the columns; this one takes 0.52, 4.6 TB/s.)
+// STREAM: what is written is marked as not needed soon.  Copies that the memory-side cache cannot hold are better not kept in
+// any cache: they would only be written back while the root is built (400,000 x 2,000 x 63: 575 -> 522 us, and the root build
+// right behind it 222 -> 192); smaller ones are found there by that build (4,000,000 x 28 x 255, 224 MB: 64 us, 67 with the
+// mark).
 // grid = (row blocks, feature blocks).
 constexpr int kPackRows = 128, kPackFeatures = 128;
 constexpr int kPackPitch = kPackFeatures / 4 + 1;  // 4-byte words from a row to the next in local memory
@@ -53,7 +57,18 @@ __device__ __forceinline__ uint4 pack_load16(const uint8_t* __restrict__ src, in
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-template <bool NIB>
+template <bool STREAM, typename WORDS>
+__device__ __forceinline__ void pack_store(uint8_t* to, const uint32_t (&v)[sizeof(WORDS) / 4]) {
+  WORDS w;
+  __builtin_memcpy(&w, v, sizeof w);
+  if constexpr (STREAM) {
+    __builtin_nontemporal_store(w, reinterpret_cast<WORDS*>(to));
+  } else {
+    *reinterpret_cast<WORDS*>(to) = w;
+  }
+}
+
+template <bool NIB, bool STREAM>
 __global__ void __launch_bounds__(256)
 pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features, TilePlan plan, int32_t line_tiles,
             uint32_t mask4, uint8_t* __restrict__ tiles, uint8_t* __restrict__ cols, int64_t col_stride) {
@@ -62,6 +77,8 @@ pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features,
   const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
   const int32_t f0 = (int32_t)blockIdx.y * kPackFeatures;
   const int64_t total = n_rows * n_features;
+  typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
   constexpr int kSteps = kPackRows / 32;  // 8 threads a row, 32 rows a step
   const int j = tid & 7;
   const int32_t f = f0 + 16 * j;
@@ -85,12 +102,11 @@ pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features,
       if (NIB) {  // features 2i, 2i + 1 -> low and high half of byte i
         const uint32_t x0 = v[i].x | (v[i].x >> 4), x1 = v[i].y | (v[i].y >> 4);
         const uint32_t x2 = v[i].z | (v[i].z >> 4), x3 = v[i].w | (v[i].w >> 4);
-        uint2 o;
-        o.x = __builtin_amdgcn_perm(x1, x0, 0x06040200u);
-        o.y = __builtin_amdgcn_perm(x3, x2, 0x06040200u);
-        *reinterpret_cast<uint2*>(dst + r * at.stride) = o;
+        const uint32_t o[2] = {__builtin_amdgcn_perm(x1, x0, 0x06040200u), __builtin_amdgcn_perm(x3, x2, 0x06040200u)};
+        pack_store<STREAM, Words2>(dst + r * at.stride, o);
       } else {
-        *reinterpret_cast<uint4*>(dst + r * at.stride) = v[i];
+        const uint32_t o[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+        pack_store<STREAM, Words4>(dst + r * at.stride, o);
       }
     }
   }
@@ -125,8 +141,7 @@ pack_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int32_t n_features,
 #pragma unroll
   for (int k = 0; k < 4; ++k)  // (rows past n_rows fall into the column's padding: its stride is a multiple of 256)
     if (fw + k < n_features)
-      *reinterpret_cast<uint4*>(cols + (int64_t)(fw + k) * col_stride + r0 + 16 * rg) =
-          make_uint4(out[k][0], out[k][1], out[k][2], out[k][3]);
+      pack_store<STREAM, Words4>(cols + (int64_t)(fw + k) * col_stride + r0 + 16 * rg, out[k]);
 }
 
 // ------------------------------------------------------------- fused columns
