@@ -389,8 +389,7 @@ typedef struct {
  *   grad, hess       DEVICE float [n_rows]
  *   max_leaves       >= 1; growth also stops when no open leaf has an admissible split
  *   scratch          DEVICE, 256-byte aligned, gbdt_grow_tree_scratch_bytes(...) bytes
- *                    (two row lists, half a row list for the smaller children of a round,
- *                    about 3 x max_leaves histograms, the split records, and for large matrices of few
+ *                    (two row lists, about 3 x max_leaves histograms, the split records, and for large matrices of few
  *                    features 8 bytes per row for gradient and hessian side by side; a buffer without
  *                    room for those last still serves, slower); the calls inside also use the
  *                    library's scratch workspace
@@ -418,7 +417,7 @@ size_t gbdt_grow_tree_scratch_bytes(int64_t n_rows, int32_t n_features, int32_t 
  * node of the current level whose best split is admissible and gains more than
  * min_split_gain is split.  A whole level costs a handful of launches whatever its width:
  * one batched split search, which first forms the siblings of the level (levels of more than
- * 1,024 nodes: a subtraction kernel of its own), and one read-back of the level's records, one batched
+ * 1,024 nodes: a subtraction kernel of its own), and one wait for the level's records, one batched
  * partition, one batched histogram build of all the smaller children.  Nodes are numbered level by level, the children of a level
  * in the order of their parents, left first (parents precede children).
  *   max_depth        0 .. 16; at most 2^max_depth leaves

@@ -806,7 +806,7 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
 // launch; splits_out[i] receives the record of histogram i.
 int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, float lambda,
                  float min_child_hess, gbdt_split_t* splits_out, int32_t n_features, int32_t n_bins,
-                 hipStream_t s, gbdt_split_t* host_mirror = nullptr, const SplitSiblings* siblings = nullptr) {
+                 hipStream_t s, gbdt_split_t* mirror = nullptr, const SplitSiblings* siblings = nullptr) {
   const SplitGrouping sg = split_grouping(n_features, n_bins, n_hists);
   void* ws = nullptr;
   int rc = get_workspace((size_t)n_hists * sg.n_wg * sizeof(SplitCand), s, &ws);
@@ -815,7 +815,7 @@ int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, 
   auto launch = [&](auto kernel, const auto& sib) {
     hipLaunchKernelGGL(kernel, dim3(sg.n_wg, n_hists), dim3(64 * sg.waves), 0, s, const_cast<gbdt_bin_t*>(hists),
                        hist_stride, n_features, n_bins, sg.passes, (double)lambda, (double)min_child_hess,
-                       (SplitCand*)ws, splits_out, host_mirror, sib);
+                       (SplitCand*)ws, splits_out, mirror, sib);
   };
   auto launch_of = [&](const auto& sib) {
     using SIB = std::decay_t<decltype(sib)>;
@@ -850,7 +850,7 @@ int32_t grow_speculative_budget(int32_t max_leaves) { return (max_leaves - 1) / 
 int32_t grow_max_expansions(int32_t max_leaves) { return (max_leaves - 1) + grow_speculative_budget(max_leaves); }
 
 struct TreeScratch {
-  size_t rows_a, rows_b, rows_small, hists, recs;  // byte offsets
+  size_t rows_a, rows_b, hists, recs;  // byte offsets
   size_t pairs;       // (gradient, hessian) of every row; only where they pay
   size_t least;       // bytes without the pairs: a caller's scratch of that size still serves
   size_t total;
@@ -865,8 +865,7 @@ TreeScratch tree_scratch_layout(int64_t n_rows, int32_t n_features, int32_t n_bi
   t.n_slots = 1 + 2 * grow_max_expansions(max_leaves);
   t.rows_a = 0;
   t.rows_b = rows;
-  t.rows_small = 2 * rows;  // the smaller children of a round: at most half of the rows
-  t.hists = t.rows_small + align256(((size_t)(n_rows > 0 ? n_rows : 1) / 2 + 1) * sizeof(int32_t));
+  t.hists = 2 * rows;
   t.recs = t.hists + align256((size_t)t.n_slots * n_features * n_bins * sizeof(gbdt_bin_t));
   t.pairs = t.least = t.recs + align256((size_t)t.n_slots * sizeof(gbdt_split_t));
   t.total = t.least + (stats_pair_pays(plan_n_tiles(make_tile_plan(n_features, n_bins)), n_rows)
@@ -874,41 +873,87 @@ TreeScratch tree_scratch_layout(int64_t n_rows, int32_t n_features, int32_t n_bi
   return t;
 }
 
-// Page-locked host memory of gbdt_grow_tree (one block per process, never freed): the split
-// records of a round, which the split search writes there as well as to device memory (the
-// host reads them after waiting for the stream, without a copy).  *dev_out: the address the
-// device uses for it.
-constexpr int kGrowPinnedRecs = 2 * kGrowRound;
-gbdt_split_t* pinned_records(gbdt_split_t** dev_out) {
-  static gbdt_split_t* p = nullptr;
-  static gbdt_split_t* d = nullptr;
-  static std::mutex mu;
-  std::lock_guard<std::mutex> lk(mu);
-  if (!p) {
-    void* q = nullptr;
-    if (hipHostMalloc(&q, kGrowPinnedRecs * sizeof(gbdt_split_t), hipHostMallocMapped) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
+// Page-locked host memory for the split records of a round or level, which the split search writes there as well as to device
+// memory: the host reads them after waiting for the stream, without a copy (20,000 x 30 x 64 to depth 5, which read them back
+// and sent the partition's copies of them: 258 us, 203 so).  A grower borrows a block for the length of its call, so growers of
+// several threads never share one; up to kIdleRecordBlocks are kept for later calls, until gbdt_reset.
+constexpr size_t kIdleRecordBlocks = 4;
+struct RecordBlock {
+  gbdt_split_t *host, *dev;  // the same memory, as the host and as the device addresses it
+  size_t n;
+  int device;
+};
+struct RecordBlocks {
+  std::mutex mu;
+  std::vector<RecordBlock> idle, lost;  // lost: a kernel that failed calls left behind may still write to it
+} g_rec_blocks;
+class HostRecords {
+ public:
+  explicit HostRecords(size_t n) {
+    b_ = RecordBlock{nullptr, nullptr, 512, 0};
+    if (hipGetDevice(&b_.device) != hipSuccess) return;
+    std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
+    auto& idle = g_rec_blocks.idle;
+    for (size_t i = 0; i < idle.size(); ++i) {
+      if (idle[i].device != b_.device || idle[i].n < n) continue;
+      b_ = idle[i];
+      idle.erase(idle.begin() + (ptrdiff_t)i);
+      return;
     }
-    void* dq = nullptr;
+    while (b_.n < n) b_.n *= 2;
+    void *q = nullptr, *dq = nullptr;
+    if (hipHostMalloc(&q, b_.n * sizeof(gbdt_split_t), hipHostMallocMapped) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
     if (hipHostGetDevicePointer(&dq, q, 0) != hipSuccess) {
       (void)hipGetLastError();
       (void)hipHostFree(q);
-      return nullptr;
+      return;
     }
-    p = (gbdt_split_t*)q;
-    d = (gbdt_split_t*)dq;
+    b_.host = (gbdt_split_t*)q;
+    b_.dev = (gbdt_split_t*)dq;
   }
-  *dev_out = d;
-  return p;
+  ~HostRecords() {
+    if (!b_.host) return;
+    std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
+    if (!in_flight_ && g_rec_blocks.idle.size() >= kIdleRecordBlocks) {
+      (void)hipHostFree(b_.host);
+      return;
+    }
+    try {
+      (in_flight_ ? g_rec_blocks.lost : g_rec_blocks.idle).push_back(b_);
+    } catch (...) {  // (no memory for the list: the block is not seen again)
+    }
+  }
+  HostRecords(const HostRecords&) = delete;
+  HostRecords& operator=(const HostRecords&) = delete;
+  bool ok() const { return b_.host != nullptr; }
+  const gbdt_split_t& operator[](size_t i) const { return b_.host[i]; }
+  gbdt_split_t* for_search() {  // the device address, for a search to be enqueued
+    in_flight_ = true;
+    return b_.dev;
+  }
+  hipError_t wait(hipStream_t s) {  // until the searches are done
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e == hipSuccess) in_flight_ = false;
+    return e;
+  }
+
+ private:
+  RecordBlock b_;
+  bool in_flight_ = false;
+};
+
+// A split that sends more rows to the children than the node has cannot be: the rows of the children would not be the node's.
+bool split_fits(const gbdt_split_t& r, uint64_t count) {
+  return r.feature < 0 || (uint64_t)r.left_count + r.right_count <= count;
 }
 
-
-// Scratch of gbdt_grow_tree_depthwise: two row buffers, the smaller children's rows, two
-// levels of histograms, the split records of a level and the records its partition uses.
+// Scratch of gbdt_grow_tree_depthwise: two row buffers, two levels of histograms and the split records of a level.
 constexpr int kMaxTreeDepth = 16;
 struct LevelScratch {
-  size_t rows_a, rows_b, rows_small, hists_a, hists_b, recs, part_recs, total;
+  size_t rows_a, rows_b, hists_a, hists_b, recs, total;
 };
 
 LevelScratch level_scratch_layout(int64_t n_rows, int32_t n_features, int32_t n_bins, int32_t max_depth) {
@@ -919,34 +964,11 @@ LevelScratch level_scratch_layout(int64_t n_rows, int32_t n_features, int32_t n_
   const size_t recs = align256(width * sizeof(gbdt_split_t));
   t.rows_a = 0;
   t.rows_b = rows;
-  t.rows_small = 2 * rows;
-  t.hists_a = 3 * rows;
+  t.hists_a = 2 * rows;
   t.hists_b = t.hists_a + hists;
   t.recs = t.hists_b + hists;
-  t.part_recs = t.recs + recs;
-  t.total = t.part_recs + recs;
+  t.total = t.recs + recs;
   return t;
-}
-
-// Page-locked host memory for the split records of a level (grows, never freed).
-gbdt_split_t* pinned_level_records(size_t n) {
-  static gbdt_split_t* p = nullptr;
-  static size_t cap = 0;
-  static std::mutex mu;
-  std::lock_guard<std::mutex> lk(mu);
-  if (cap < n) {
-    if (p) (void)hipHostFree(p);
-    p = nullptr;
-    cap = 0;
-    void* q = nullptr;
-    if (hipHostMalloc(&q, n * sizeof(gbdt_split_t), hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    p = (gbdt_split_t*)q;
-    cap = n;
-  }
-  return p;
 }
 
 // gbdt_hist_build, with the scratch either the library's workspace (fixed_base == NULL) or a
@@ -1348,12 +1370,13 @@ size_t gbdt_hist_build_noalloc_max_partial_bytes(void) { return kNoAllocPartialB
 
 // gbdt_hist_build_batch; with seg_off (gbdt_grow_tree: the leaves of a round are segments of its
 // row buffers, not one list back to back) leaf l's rows are row_idx[seg_off[l] .. seg_off[l] + its
-// length by leaf_offsets), and grad / hess are always read by row id -- from stat_pairs if given.
+// length by leaf_offsets), different leaves' positions being different also modulo seg_wrap and those below n_rows; grad / hess
+// read by row id are read from stat_pairs if given.
 static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features,
                           int32_t n_bins, const int32_t* row_idx, const int64_t* leaf_offsets,
                           int32_t n_leaves, const float* grad, const float* hess,
                           gbdt_bin_t* hist_out, void* stream, const uint32_t* seg_off,
-                          const float2* stat_pairs = nullptr) {
+                          uint32_t seg_wrap = ~0u, const float2* stat_pairs = nullptr) {
   if (!valid_shape(n_rows, n_features, n_bins)) return GBDT_EINVAL;
   if (n_leaves < 0) return GBDT_EINVAL;
   if (n_leaves == 0) return GBDT_OK;
@@ -1400,8 +1423,8 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     if (rc_ids != GBDT_OK) return rc_ids;
   }
   // grad / hess of the whole concatenated list in list order, gathered once (see stats_gather_pays)
-  bool by_pos = !seg_off && total_rows > 0 && stats_gather_pays(n_tiles, total_rows, total_rows / n_leaves, n_rows);
-  size_t stats_words = by_pos ? 2 * (((size_t)total_rows + 63) / 64 * 64) : 0;
+  bool by_pos = total_rows > 0 && stats_gather_pays(n_tiles, total_rows, total_rows / n_leaves, n_rows);
+  size_t stats_words = by_pos ? 2 * (((size_t)(seg_off ? n_rows : total_rows) + 63) / 64 * 64) : 0;
   void* ws = nullptr;
   int rc = get_workspace((need_words + stats_words) * 4 + 256, s, &ws);
   if (rc == GBDT_ENOMEM && by_pos) {  // a caller's workspace sized for the partial blocks alone: no gather
@@ -1413,26 +1436,27 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   float* g_list = (float*)ws + need_words;
   float* h_list = g_list + stats_words / 2;
   if (by_pos) {
-    if (n_leaves == 1 || n_rows < kGatherListsMinRows) {
+    const bool by_parts = seg_off || (n_leaves > 1 && n_rows >= kGatherListsMinRows);
+    if (!by_parts) {
       hipLaunchKernelGGL(stats_gather_kernel, dim3((unsigned)((total_rows + 255) / 256)), dim3(256), 0, s,
                          row_idx + leaf_offsets[0], grad, hess, total_rows, g_list, h_list);
       HIP_TRY(hipGetLastError());
     }
-    for (int32_t l0 = 0; n_leaves > 1 && n_rows >= kGatherListsMinRows && l0 < n_leaves; l0 += kGatherLists) {
+    for (int32_t l0 = 0; by_parts && l0 < n_leaves; l0 += kGatherLists) {
       GatherTable t;
       t.n_lists = n_leaves - l0 < kGatherLists ? n_leaves - l0 : kGatherLists;
-      const int64_t base = leaf_offsets[l0], before = base - leaf_offsets[0];
+      const int64_t base = seg_off ? 0 : leaf_offsets[l0], before = seg_off ? 0 : base - leaf_offsets[0];
       uint32_t blocks = 0;
       for (int32_t i = 0; i < t.n_lists; ++i) {
         const int64_t n = leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i];
-        t.first[i] = (uint32_t)(leaf_offsets[l0 + i] - base);
+        t.first[i] = seg_off ? seg_off[l0 + i] : (uint32_t)(leaf_offsets[l0 + i] - base);
+        t.n[i] = (uint32_t)n;
         t.first_block[i] = blocks;
         blocks += (uint32_t)(((n + kXcds - 1) / kXcds + kGatherRows - 1) / kGatherRows);
       }
-      t.first[t.n_lists] = (uint32_t)(leaf_offsets[l0 + t.n_lists] - base);
       if (blocks == 0) continue;
       hipLaunchKernelGGL(stats_gather_lists_kernel, dim3(blocks * kXcds), dim3(256), 0, s, row_idx + base, grad, hess, t,
-                         g_list + before, h_list + before);
+                         seg_wrap, g_list + before, h_list + before);
       HIP_TRY(hipGetLastError());
     }
   }
@@ -1459,8 +1483,10 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       BatchArgs a;
       a.packed = (const uint8_t*)bin_matrix;
       a.idx = seg_off ? row_idx : row_idx + leaf_offsets[l0];
-      a.grad = by_pos ? g_list + (leaf_offsets[l0] - leaf_offsets[0]) : grad;
-      a.hess = by_pos ? h_list + (leaf_offsets[l0] - leaf_offsets[0]) : hess;
+      const int64_t stats_at = seg_off ? 0 : leaf_offsets[l0] - leaf_offsets[0];
+      a.grad = by_pos ? g_list + stats_at : grad;
+      a.hess = by_pos ? h_list + stats_at : hess;
+      a.stat_wrap = seg_wrap;
       a.stats_by_pos = by_pos ? 1 : 0;
       a.stat_shift = 2;
       if (stat_pairs && !by_pos) {
@@ -1624,10 +1650,12 @@ int gbdt_partition_rows(const void* bin_matrix, int64_t n_rows, int32_t n_featur
   return GBDT_OK;
 }
 
-int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_features,
-                              int32_t n_bins, const int32_t* row_idx, const int64_t* leaf_offsets,
-                              int32_t n_leaves, const gbdt_split_t* splits, int32_t* children_out,
-                              int64_t* n_left_out, void* stream) {
+// gbdt_partition_rows_batch; with split_idx (gbdt_grow_tree_depthwise) leaf l's record is splits[split_idx[l]], kNoSplitRecord
+// for none, and a lone leaf of all rows may come without a list.
+static int partition_rows_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features,
+                                     int32_t n_bins, const int32_t* row_idx, const int64_t* leaf_offsets,
+                                     int32_t n_leaves, const gbdt_split_t* splits, const uint32_t* split_idx,
+                                     int32_t* children_out, int64_t* n_left_out, void* stream) {
   if (!valid_shape(n_rows, n_features, n_bins)) return GBDT_EINVAL;
   if (n_leaves < 0) return GBDT_EINVAL;
   if (n_leaves == 0) return GBDT_OK;
@@ -1641,11 +1669,11 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
     if (n > longest) longest = n;
   }
   const int64_t total_rows = leaf_offsets[n_leaves] - leaf_offsets[0];
-  if (total_rows > 0 && (!bin_matrix || !row_idx || !children_out)) return GBDT_EINVAL;
+  if (total_rows > 0 && (!bin_matrix || (!row_idx && !split_idx) || !children_out)) return GBDT_EINVAL;
   if (total_rows > 0 && n_rows == 0) return GBDT_EINVAL;
   if (n_rows >= ((int64_t)1 << 30)) return GBDT_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  if (total_rows > 0) {
+  if (total_rows > 0 && !split_idx) {
     const int rc_ids = check_row_ids(row_idx + leaf_offsets[0], total_rows, n_rows, s);
     if (rc_ids != GBDT_OK) return rc_ids;
   }
@@ -1672,8 +1700,8 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
     const int32_t n = n_leaves - l0 < kPartBatchLeaves ? n_leaves - l0 : kPartBatchLeaves;
     PartBatchArgs a;
     a.packed = (const uint8_t*)bin_matrix;
-    a.idx = row_idx + leaf_offsets[l0];
-    a.split = splits + l0;
+    a.idx = row_idx ? row_idx + leaf_offsets[l0] : nullptr;
+    a.split = split_idx ? splits : splits + l0;
     a.out = children_out + leaf_offsets[l0];
     a.n_left_out = n_left_out ? n_left_out + l0 : nullptr;
     a.flags = (uint64_t*)ws;
@@ -1690,7 +1718,7 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
       if (i < n) {
         lf.row_off = lf.out_off = (uint32_t)(leaf_offsets[l0 + i] - leaf_offsets[l0]);
         lf.n = (uint32_t)(leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i]);
-        lf.split_idx = (uint32_t)i;
+        lf.split_idx = split_idx ? split_idx[l0 + i] : (uint32_t)i;
         lf.first_chunk = chunks;
         chunks += (uint32_t)(((int64_t)lf.n + chunk_rows - 1) / chunk_rows);
         any_empty = any_empty || lf.n == 0;
@@ -1711,6 +1739,14 @@ int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_
     HIP_TRY(hipGetLastError());
   }
   return GBDT_OK;
+}
+
+int gbdt_partition_rows_batch(const void* bin_matrix, int64_t n_rows, int32_t n_features,
+                              int32_t n_bins, const int32_t* row_idx, const int64_t* leaf_offsets,
+                              int32_t n_leaves, const gbdt_split_t* splits, int32_t* children_out,
+                              int64_t* n_left_out, void* stream) {
+  return partition_rows_batch_impl(bin_matrix, n_rows, n_features, n_bins, row_idx, leaf_offsets, n_leaves, splits, nullptr,
+                                   children_out, n_left_out, stream);
 }
 
 // --- leaf-wise tree growth -------------------------------------------------------------
@@ -1734,13 +1770,11 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
   if (n_rows >= ((int64_t)1 << 30)) return GBDT_EUNSUPPORTED;
   const TreeScratch lay = tree_scratch_layout(n_rows, n_features, n_bins, max_leaves);
   if (scratch_bytes < lay.least) return GBDT_ENOMEM;
-  gbdt_split_t* pinned_dev = nullptr;
-  gbdt_split_t* pinned = pinned_records(&pinned_dev);
-  if (!pinned) return GBDT_ENOMEM;
+  HostRecords found(2 * kGrowRound);  // the records of the last search
+  if (!found.ok()) return GBDT_ENOMEM;
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)scratch;
   int32_t* rows_base = (int32_t*)(base + lay.rows_a);   // row buffer b starts b * row_elems entries in
-  int32_t* small_rows = (int32_t*)(base + lay.rows_small);
   gbdt_bin_t* pool = (gbdt_bin_t*)(base + lay.hists);
   gbdt_split_t* recs = (gbdt_split_t*)(base + lay.recs);            // record of the histogram in slot i
   const size_t hist_elems = (size_t)n_features * n_bins;
@@ -1783,7 +1817,7 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
   // root: histogram and first partition without an index list
   int rc = gbdt_hist_build(bin_matrix, n_rows, n_features, n_bins, nullptr, n_rows, grad, hess, pool, s);
   if (rc != GBDT_OK) return rc;
-  rc = launch_split(pool, 0, 1, lambda, min_child_hess, recs, n_features, n_bins, s, pinned_dev);
+  rc = launch_split(pool, 0, 1, lambda, min_child_hess, recs, n_features, n_bins, s, found.for_search());
   if (rc != GBDT_OK) return rc;
   const float2* stat_pairs = nullptr;
   if (lay.total > lay.least && scratch_bytes >= lay.total && max_leaves > 1) {
@@ -1792,14 +1826,15 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
     HIP_TRY(hipGetLastError());
     stat_pairs = pairs;
   }
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(found.wait(s));
   {
     Cand root;
     root.begin = 0;
     root.count = (uint32_t)n_rows;
     root.buf = 0;
     root.slot = 0;
-    root.rec = pinned[0];
+    root.rec = found[0];
+    if (!split_fits(root.rec, root.count)) return GBDT_EHIP;
     root.kid[0] = root.kid[1] = -1;
     root.id = 0;
     root.sum_grad = root.rec.left_grad + root.rec.right_grad;
@@ -1925,9 +1960,7 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
         HIP_TRY(hipGetLastError());
       }
     }
-    // ---- the smaller children's histograms in one batched build, straight from their segments of
-    // the row buffers -- or, where gathering grad / hess into list order pays (sparse leaves of a
-    // matrix of many tiles), from a copy of their rows back to back
+    // ---- the smaller children's histograms in one batched build, straight from their segments of the row buffers
     std::vector<int64_t> small_offs = {0};
     std::vector<uint32_t> small_seg((size_t)k);
     std::vector<int> left_small((size_t)k);
@@ -1940,27 +1973,11 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
       small_offs.push_back(small_offs.back() + (left_small[j] ? nl : nr));
     }
     gbdt_bin_t* h_small = pool + (size_t)next_slot * hist_elems;  // k slots: the built children; then k: their siblings
-    const int64_t small_total = small_offs.back();
-    if (small_total > 0 && stats_gather_pays(plan_n_tiles(plan), small_total, small_total / k, n_rows)) {
-      CompactTable t;
-      for (int j = 0; j < k; ++j) {
-        t.src_begin[j] = small_seg[j];
-        t.dst_begin[j] = (uint32_t)small_offs[j];
-      }
-      t.dst_begin[k] = (uint32_t)small_total;
-      t.n_seg = k;
-      hipLaunchKernelGGL(segments_compact_kernel, dim3((unsigned)((small_total + 255) / 256)), dim3(256), 0, s,
-                         (const int32_t*)rows_base, t, small_rows);
-      HIP_TRY(hipGetLastError());
-      rc = hist_build_batch_impl(bin_matrix, n_rows, n_features, n_bins, small_rows, small_offs.data(), k, grad,
-                                 hess, h_small, s, nullptr);
-    } else {
-      rc = hist_build_batch_impl(bin_matrix, n_rows, n_features, n_bins, rows_base, small_offs.data(), k, grad,
-                                 hess, h_small, s, small_seg.data(), stat_pairs);
-    }
+    rc = hist_build_batch_impl(bin_matrix, n_rows, n_features, n_bins, rows_base, small_offs.data(), k, grad,
+                               hess, h_small, s, small_seg.data(), (uint32_t)lay.row_elems, stat_pairs);
     if (rc != GBDT_OK) return rc;
     // ---- best splits of the 2k children, one launch, which first forms the k siblings as parent -
-    // built child; the records also land in `pinned`
+    // built child; the records also land in `found`
     {
       SplitSiblings sib;
       sib.pool = pool;
@@ -1969,12 +1986,12 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
       sib.keep = 1;
       for (int j = 0; j < kSplitSiblings; ++j) sib.parent_slot[j] = j < k ? cands[batch[j]].slot : 0;
       rc = launch_split(h_small, (int64_t)hist_elems, 2 * k, lambda, min_child_hess, recs + next_slot, n_features,
-                        n_bins, s, pinned_dev, &sib);
+                        n_bins, s, found.for_search(), &sib);
       if (rc != GBDT_OK) return rc;
     }
     {
       auto t0 = std::chrono::steady_clock::now();
-      HIP_TRY(hipStreamSynchronize(s));
+      HIP_TRY(found.wait(s));
       auto t1 = std::chrono::steady_clock::now();
       wait_us += std::chrono::duration<double, std::micro>(t1 - t0).count();
       rounds_us += std::chrono::duration<double, std::micro>(t1 - last_round_end).count();
@@ -1991,7 +2008,8 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
         c.count = side == 0 ? nl : nr;
         c.buf = 1 - pc.buf;
         c.slot = is_small ? next_slot + j : next_slot + k + j;
-        c.rec = pinned[is_small ? j : k + j];
+        c.rec = found[is_small ? j : k + j];
+        if (!split_fits(c.rec, c.count)) return GBDT_EHIP;
         c.sum_grad = side == 0 ? pc.rec.left_grad : pc.rec.right_grad;
         c.sum_hess = side == 0 ? pc.rec.left_hess : pc.rec.right_hess;
         c.kid[0] = c.kid[1] = -1;
@@ -2065,16 +2083,13 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
   const LevelScratch lay = level_scratch_layout(n_rows, n_features, n_bins, max_depth);
   if (scratch_bytes < lay.total) return GBDT_ENOMEM;
   const size_t width = (size_t)1 << max_depth;  // most nodes a level can hold
-  gbdt_split_t* pinned = pinned_level_records(2 * width);
-  if (!pinned) return GBDT_ENOMEM;
-  gbdt_split_t* pinned_part = pinned + width;  // records the partition of a level is driven by
+  HostRecords found(width);  // the records of the last search
+  if (!found.ok()) return GBDT_ENOMEM;
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)scratch;
   int32_t* rows_buf[2] = {(int32_t*)(base + lay.rows_a), (int32_t*)(base + lay.rows_b)};
-  int32_t* small_rows = (int32_t*)(base + lay.rows_small);
   gbdt_bin_t* hist_buf[2] = {(gbdt_bin_t*)(base + lay.hists_a), (gbdt_bin_t*)(base + lay.hists_b)};
   gbdt_split_t* recs = (gbdt_split_t*)(base + lay.recs);
-  gbdt_split_t* part_recs = (gbdt_split_t*)(base + lay.part_recs);
   const size_t hist_elems = (size_t)n_features * n_bins;
 
   auto fill_node = [&](int k, int parent, const gbdt_split_t& r, float sg, float sh, uint32_t cnt,
@@ -2092,15 +2107,11 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     nd.row_begin = begin;
   };
 
-  // root: its histogram without an index list; the row list 0..n-1 for the first partition
+  // root: its histogram, and the first partition, without an index list
   int cur = 0;  // row buffer and histogram buffer of the current level
   int rc = gbdt_hist_build(bin_matrix, n_rows, n_features, n_bins, nullptr, n_rows, grad, hess, hist_buf[cur], s);
   if (rc != GBDT_OK) return rc;
-  if (n_rows > 0) {
-    hipLaunchKernelGGL(row_iota_kernel, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, s, rows_buf[cur],
-                       n_rows);
-    HIP_TRY(hipGetLastError());
-  }
+  int32_t* rows_now = nullptr;  // the rows of the current level (NULL: 0, 1, 2, ...)
   // the level: its nodes in position order with their histogram slots; `frontier` also holds
   // the finished leaves, whose rows every later partition copies through unchanged
   struct Entry {
@@ -2120,17 +2131,15 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     std::sort(open.begin(), open.end(), [&](int a, int b) { return frontier[a].slot < frontier[b].slot; });
     const int n_open = (int)open.size();
     if (n_open == 0) break;
-    if (level_sib.n > 0) {
-      rc = launch_split(hist_buf[cur], (int64_t)hist_elems, n_open, lambda, min_child_hess, recs, n_features, n_bins,
-                        s, nullptr, &level_sib);
-    } else {
-      rc = gbdt_best_split_batch(hist_buf[cur], n_open, lambda, min_child_hess, recs, n_features, n_bins, s);
+    for (int h0 = 0; h0 < n_open; h0 += kSplitMaxHists) {
+      const int nh = n_open - h0 < kSplitMaxHists ? n_open - h0 : kSplitMaxHists;
+      rc = launch_split(hist_buf[cur] + (size_t)h0 * hist_elems, (int64_t)hist_elems, nh, lambda, min_child_hess, recs + h0,
+                        n_features, n_bins, s, found.for_search() + h0, level_sib.n > 0 ? &level_sib : nullptr);
+      if (rc != GBDT_OK) return rc;
     }
-    if (rc != GBDT_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(pinned, recs, (size_t)n_open * sizeof(gbdt_split_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(found.wait(s));
     if (!root_done) {
-      const gbdt_split_t r = pinned[0];
+      const gbdt_split_t r = found[0];
       float sg = r.left_grad + r.right_grad, sh = r.left_hess + r.right_hess;
       if (r.feature < 0 && n_rows > 0) {  // no record carries the totals: sum feature 0's bins here
         std::vector<gbdt_bin_t> row((size_t)n_bins);
@@ -2151,7 +2160,8 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     // the records of the level's nodes (slot order = order of `open`)
     std::vector<gbdt_split_t> rec_of(frontier.size());
     for (int j = 0; j < n_open; ++j) {
-      const gbdt_split_t& r = pinned[frontier[open[j]].slot];
+      const gbdt_split_t& r = found[frontier[open[j]].slot];
+      if (!split_fits(r, nodes_out[frontier[open[j]].node].count)) return GBDT_EHIP;
       rec_of[open[j]] = r;
       gbdt_tree_node_t& nd = nodes_out[frontier[open[j]].node];
       nd.feature = r.feature;
@@ -2159,30 +2169,29 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
       nd.gain = r.gain;
     }
     if (depth == max_depth) break;
-    // ---- which nodes split; the partition records of ALL entries (others: no split)
+    // ---- which nodes split, and where the partition finds their records
     std::vector<Entry> next;
     std::vector<int64_t> offs;          // positions of the entries of this level
     std::vector<int> splitting;         // indices into frontier
+    std::vector<uint32_t> split_idx;    // by entry: slot of its record, or that there is none
     for (size_t i = 0; i < frontier.size(); ++i) {
       const gbdt_tree_node_t& nd = nodes_out[frontier[i].node];
       offs.push_back(nd.row_begin);
-      gbdt_split_t pr;
-      memset(&pr, 0, sizeof pr);
-      pr.feature = pr.bin = -1;
+      split_idx.push_back(kNoSplitRecord);
       if (frontier[i].slot >= 0 && rec_of[i].feature >= 0 && rec_of[i].gain > min_split_gain) {
-        pr = rec_of[i];
+        split_idx.back() = (uint32_t)frontier[i].slot;
         splitting.push_back((int)i);
       }
-      pinned_part[i] = pr;
     }
     offs.push_back(n_rows);
     if (splitting.empty()) break;
-    HIP_TRY(hipMemcpyAsync(part_recs, pinned_part, frontier.size() * sizeof(gbdt_split_t),
-                           hipMemcpyHostToDevice, s));
     const int nxt = cur ^ 1;
-    rc = gbdt_partition_rows_batch(bin_matrix, n_rows, n_features, n_bins, rows_buf[cur], offs.data(),
-                                   (int32_t)frontier.size(), part_recs, rows_buf[nxt], nullptr, s);
+    // (the last level's rows go where the caller wants them)
+    int32_t* rows_next = depth + 1 == max_depth && row_order_out ? row_order_out : rows_buf[nxt];
+    rc = partition_rows_batch_impl(bin_matrix, n_rows, n_features, n_bins, rows_now, offs.data(),
+                                   (int32_t)frontier.size(), recs, split_idx.data(), rows_next, nullptr, s);
     if (rc != GBDT_OK) return rc;
+    rows_now = rows_next;
     // ---- children: node ids in the order of their parents' ids (the level's numbering),
     // histogram slots: the smaller children first (built), then the larger (by subtraction)
     std::vector<int> by_node = splitting;
@@ -2190,7 +2199,7 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     const int k = (int)by_node.size();
     std::vector<int64_t> small_offs = {0};
     std::vector<int> parent_slot((size_t)k);
-    std::vector<std::pair<uint32_t, uint32_t>> small_seg((size_t)k);  // (begin in the row buffer, length)
+    std::vector<uint32_t> small_seg((size_t)k);  // where a smaller child's rows begin
     std::vector<std::pair<Entry, Entry>> kids(frontier.size());
     for (int j = 0; j < k; ++j) {
       const int i = by_node[j];
@@ -2207,9 +2216,8 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
       fill_node(left, parent, none, r.left_grad, r.left_hess, r.left_count, begin);
       fill_node(right, parent, none, r.right_grad, r.right_hess, r.right_count, begin + r.left_count);
       const bool left_small = r.left_count <= r.right_count;
-      small_seg[j] = left_small ? std::make_pair((uint32_t)begin, r.left_count)
-                                : std::make_pair((uint32_t)(begin + r.left_count), r.right_count);
-      small_offs.push_back(small_offs.back() + small_seg[j].second);
+      small_seg[j] = (uint32_t)(left_small ? begin : begin + r.left_count);
+      small_offs.push_back(small_offs.back() + (left_small ? r.left_count : r.right_count));
       parent_slot[j] = frontier[i].slot;
       kids[i] = left_small ? std::make_pair(Entry{left, j}, Entry{right, k + j})
                            : std::make_pair(Entry{left, k + j}, Entry{right, j});
@@ -2222,24 +2230,9 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
         next.push_back(Entry{frontier[i].node, -1});  // a leaf from now on
       }
     }
-    // ---- the smaller children's rows back to back, their histograms in one batched build
-    for (int j0 = 0; j0 < k; j0 += kCompactSegs) {
-      CompactTable t;
-      const int ns = k - j0 < kCompactSegs ? k - j0 : kCompactSegs;
-      for (int j = 0; j < ns; ++j) {
-        t.src_begin[j] = small_seg[j0 + j].first;
-        t.dst_begin[j] = (uint32_t)small_offs[j0 + j];
-      }
-      t.dst_begin[ns] = (uint32_t)small_offs[j0 + ns];
-      t.n_seg = ns;
-      const uint32_t span = t.dst_begin[ns] - t.dst_begin[0];
-      if (span == 0) continue;
-      hipLaunchKernelGGL(segments_compact_kernel, dim3((span + 255) / 256), dim3(256), 0, s,
-                         (const int32_t*)rows_buf[nxt], t, small_rows);
-      HIP_TRY(hipGetLastError());
-    }
-    rc = gbdt_hist_build_batch(bin_matrix, n_rows, n_features, n_bins, small_rows, small_offs.data(), k, grad,
-                               hess, hist_buf[nxt], s);
+    // ---- the smaller children's histograms in one batched build, straight from their segments of the rows
+    rc = hist_build_batch_impl(bin_matrix, n_rows, n_features, n_bins, rows_now, small_offs.data(), k, grad,
+                               hess, hist_buf[nxt], s, small_seg.data());
     if (rc != GBDT_OK) return rc;
     level_sib.pool = hist_buf[cur];
     level_sib.first = k;
@@ -2259,9 +2252,12 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     cur = nxt;
   }
   *n_nodes_out = n_nodes;
-  if (row_order_out && n_rows > 0)
-    HIP_TRY(hipMemcpyAsync(row_order_out, rows_buf[cur], (size_t)n_rows * sizeof(int32_t),
-                           hipMemcpyDeviceToDevice, s));
+  if (row_order_out && n_rows > 0 && !rows_now) {  // never split: the rows in their own order
+    hipLaunchKernelGGL(row_iota_kernel, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, s, row_order_out, n_rows);
+    HIP_TRY(hipGetLastError());
+  } else if (row_order_out && n_rows > 0 && rows_now != row_order_out) {
+    HIP_TRY(hipMemcpyAsync(row_order_out, rows_now, (size_t)n_rows * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+  }
   return GBDT_OK;
 }
 
@@ -2523,6 +2519,17 @@ int gbdt_reset(void) {
       (void)hipEventDestroy(pr.second);
     }
     g_prof.pairs.clear();
+  }
+  {
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
+    auto& blocks = g_rec_blocks;
+    for (auto* list : {&g_rec_blocks.idle, &g_rec_blocks.lost}) {  // (of this device: no other has been waited for)
+      auto done = std::partition(list->begin(), list->end(), [&](const RecordBlock& b) { return b.device != dev; });
+      for (auto it = done; it != list->end(); ++it) (void)hipHostFree(it->host);
+      list->erase(done, list->end());
+    }
   }
   (void)hipGetLastError();
   // the split search's tickets: a launch that failed half-way may have left some counted

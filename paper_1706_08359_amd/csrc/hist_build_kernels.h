@@ -1055,20 +1055,23 @@ stats_gather_kernel(const int32_t* __restrict__ idx, const float* __restrict__ g
   h_out[i] = hess[r];
 }
 
-// The same for several row lists back to back, dealt out to the XCDs by parts of the lists: an XCD takes the k-th eighth of every
+// The same for several row lists, dealt out to the XCDs by parts of the lists: an XCD takes the k-th eighth of every
 // list, one list after the other.  Lists of a tree's leaves ascend, so those are about the same rows of grad and hess, whose
 // lines the XCD's L2 then fetches once for all lists instead of once for each (64 leaves of 1,500,000 rows: 30 us in list
-// order, 18 so).  Any other lists are gathered as well.  A block takes kGatherRows positions of a part.
-constexpr int kGatherLists = 448;
+// order, 18 so).  Any other lists are gathered as well.  A block takes kGatherRows positions of a part.  Lists are
+// segments of idx; what belongs to position i of idx goes to position i of the output, or i - wrap from `wrap` on (the two row
+// buffers of a tree share one set of positions).
+constexpr int kGatherLists = 300;
 constexpr int kGatherRows = 1024;
 struct GatherTable {
-  uint32_t first[kGatherLists + 1];        // position of a list's first entry, and of the last list's end
-  uint32_t first_block[kGatherLists + 1];  // blocks of an eighth of all lists before it
+  uint32_t first[kGatherLists];            // position of a list's first entry
+  uint32_t n[kGatherLists];
+  uint32_t first_block[kGatherLists];      // blocks of an eighth of all lists before it
   int32_t n_lists;
 };
 __global__ void __launch_bounds__(256)
 stats_gather_lists_kernel(const int32_t* __restrict__ idx, const float* __restrict__ grad,
-                          const float* __restrict__ hess, GatherTable t, float* __restrict__ g_out,
+                          const float* __restrict__ hess, GatherTable t, uint32_t wrap, float* __restrict__ g_out,
                           float* __restrict__ h_out) {
   const uint32_t part = blockIdx.x % kXcds, b = blockIdx.x / kXcds;
   int32_t lo = 0, hi = t.n_lists - 1;  // the list that block b of this part is of (an empty list has no block)
@@ -1080,7 +1083,8 @@ stats_gather_lists_kernel(const int32_t* __restrict__ idx, const float* __restri
       hi = mid - 1;
     }
   }
-  const uint32_t begin = t.first[lo], n = t.first[lo + 1] - begin, each = (n + kXcds - 1) / kXcds;
+  const uint32_t begin = t.first[lo], n = t.n[lo], each = (n + kXcds - 1) / kXcds;
+  const uint32_t out = begin >= wrap ? begin - wrap : begin;
   const uint32_t at = part * each + (b - t.first_block[lo]) * (uint32_t)kGatherRows;
   const uint32_t part_end = (part + 1) * each < n ? (part + 1) * each : n;
   constexpr int kSteps = kGatherRows / 256;
@@ -1103,8 +1107,8 @@ stats_gather_lists_kernel(const int32_t* __restrict__ idx, const float* __restri
   for (int i = 0; i < kSteps; ++i) {
     const uint32_t k = at + 256u * (uint32_t)i + threadIdx.x;
     if (k < part_end) {
-      g_out[begin + k] = g[i];
-      h_out[begin + k] = h[i];
+      g_out[out + k] = g[i];
+      h_out[out + k] = h[i];
     }
   }
 }
@@ -1152,6 +1156,7 @@ struct BatchArgs {
   int32_t deal;
   int32_t n_leaves;
   uint32_t n_cols;       // workgroup columns of all leaves
+  uint32_t stat_wrap;    // stats_by_pos: a list at idx position i has its statistics at i, or at i - this from this on
   gbdt_bin_t* hist_out;  // [n_leaves][n_features][n_bins]: written directly by leaves of one workgroup per tile
   int32_t n_features;
   int32_t n_bins;
@@ -1179,14 +1184,15 @@ hist_build_batch_kernel(BatchArgs a) {
   const int32_t wgs = (int32_t)batch_wgs(lf);
   const uint32_t unit_epochs = batch_unit_epochs(lf);
   constexpr int kPerWg = WIDE ? 2 : 1;  // partial blocks per workgroup
-  const bool by_pos = a.stats_by_pos != 0;  // then grad / hess follow the concatenated row lists
+  const bool by_pos = a.stats_by_pos != 0;  // then grad / hess follow the row lists
+  const uint32_t stat_off = !by_pos ? 0u : lf.row_off >= a.stat_wrap ? lf.row_off - a.stat_wrap : lf.row_off;
   uint32_t* leaf_out =
       a.partials + (size_t)lf.first_wg * kPerWg * column_words<CAP, WM, NIB, NT>(a.n_main, a.wr);
   build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES>(
       a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, blk.tile, blk.half, leaf_out, (size_t)(kPerWg * wgs),
       (size_t)blk.wg, (size_t)wgs,
       wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr, a.n_features, a.n_bins, lds,
-      a.idx + lf.row_off, by_pos ? a.grad + lf.row_off : a.grad, by_pos ? a.hess + lf.row_off : a.hess, by_pos,
+      a.idx + lf.row_off, a.grad + stat_off, a.hess + stat_off, by_pos,
       (uint32_t)a.stat_shift, lf.n, (uint32_t)blk.wg, 0u, unit_epochs, (uint32_t)wgs, (uint32_t*)nullptr, 0u, 0u);
 }
 

@@ -75,8 +75,8 @@ __device__ __forceinline__ SplitColumn split_column(const gbdt_split_t* __restri
                                                     const TilePlan& plan, int64_t n_rows,
                                                     int32_t n_features, bool from_tiles = false) {
   SplitColumn c;
-  const int32_t f = split->feature;
-  c.thr = split->bin;
+  const int32_t f = split ? split->feature : -1;
+  c.thr = split ? split->bin : 0;
   c.has_split = f >= 0 && f < n_features;
   c.from_tiles = from_tiles;
   c.col_off = 0;
@@ -350,6 +350,7 @@ partition_scatter_kernel(const int32_t* __restrict__ idx, int64_t n_leaf, int32_
 // launch's flag / count arrays, the split record split[split_idx], and writes its children to
 // out[out_off .. out_off + n).  The table travels as kernel arguments.
 constexpr int kPartBatchLeaves = 192;
+constexpr uint32_t kNoSplitRecord = ~0u;  // as split_idx: the leaf's rows are copied
 struct PartLeaf {
   uint32_t row_off, out_off, n, first_chunk, split_idx;
 };
@@ -387,7 +388,8 @@ __device__ __forceinline__ int32_t part_leaf_of(const PartLeaf* leaf, int32_t n_
 __global__ void __launch_bounds__(kPartThreads) partition_flag_batch_kernel(PartBatchArgs a) {
   const int32_t l = part_leaf_of(a.leaf, a.n_leaves, blockIdx.x);
   const PartLeaf lf = a.leaf[l];
-  const SplitColumn sc = split_column(a.split + lf.split_idx, a.plan, a.n_rows, a.n_features);
+  const SplitColumn sc =
+      split_column(lf.split_idx == kNoSplitRecord ? nullptr : a.split + lf.split_idx, a.plan, a.n_rows, a.n_features);
   GBDT_PART_DISPATCH(a.rows_per_thread,
                      partition_flag_chunk<S>(sc, a.packed, a.n_rows, a.idx + lf.row_off, lf.n,
                                              (int32_t)(blockIdx.x - lf.first_chunk), a.rows_per_thread,
@@ -458,33 +460,6 @@ partition_one_kernel(const uint8_t* __restrict__ packed, int64_t n_rows, int32_t
       out[left ? lefts_before_e : total + (e - lefts_before_e)] = r;
     }
   }
-}
-
-// Copies up to kCompactSegs segments of a row buffer back to back into another list:
-// segment j = src[src_begin[j] .. src_begin[j] + len_j) goes to dst[dst_begin[j] ..), the
-// dst_begin ascending with dst_begin[n_seg] = total.  (The smaller children of a tree
-// level, gathered for one batched histogram build.)
-constexpr int kCompactSegs = 448;
-struct CompactTable {
-  uint32_t src_begin[kCompactSegs];
-  uint32_t dst_begin[kCompactSegs + 1];
-  int32_t n_seg;
-};
-
-__global__ void __launch_bounds__(256)
-segments_compact_kernel(const int32_t* __restrict__ src, CompactTable t, int32_t* __restrict__ dst) {
-  const uint32_t i = t.dst_begin[0] + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= t.dst_begin[t.n_seg]) return;
-  int32_t lo = 0, hi = t.n_seg - 1;  // last segment that starts at or before i
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if (t.dst_begin[mid] <= i) {
-      lo = mid;
-    } else {
-      hi = mid - 1;
-    }
-  }
-  dst[i] = src[t.src_begin[lo] + (i - t.dst_begin[lo])];
 }
 
 // Debug aid: counts the entries of a row list that are not row ids of the matrix.
