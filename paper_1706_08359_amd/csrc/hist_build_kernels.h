@@ -381,6 +381,10 @@ constexpr int kWideShift = 24;
 __device__ __forceinline__ double pow2d(int k) {
   return __longlong_as_double((long long)(k + 1023) << 52);
 }
+// An epoch whose sum of magnitudes is past the largest fp32 number has no scale of its own: it is scaled as if the sum
+// were 2^128, and 2^kWidePast times smaller, so that sixteen rows of the largest number stay within the 2^51
+// that i64_to_f64 takes (its 54-bit field alone would take them at the larger scale).
+constexpr int kWidePast = 2;
 // round-to-nearest-even of |v| < 2^51 to a 64-bit integer (the sum's low mantissa bits)
 __device__ __forceinline__ long long rint_to_i64(double v) {
   return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000LL;
@@ -570,8 +574,14 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   auto request_scales = [&](int parity) { return red[parity * 2 * NW + (lane & (2 * NW - 1))]; };
   auto scales_from = [&](float v, int& kg, int& kh) {
     v = sum_in_8(v) * 1.001953125f;
-    kg = epoch_scale_exp(__builtin_amdgcn_readlane(__float_as_uint(v), 0));
-    kh = epoch_scale_exp(__builtin_amdgcn_readlane(__float_as_uint(v), 8));
+    const uint32_t bits_g = (uint32_t)__builtin_amdgcn_readlane(__float_as_uint(v), 0);
+    const uint32_t bits_h = (uint32_t)__builtin_amdgcn_readlane(__float_as_uint(v), 8);
+    kg = epoch_scale_exp(bits_g);
+    kh = epoch_scale_exp(bits_h);
+    if (WIDE) {  // sums past the largest fp32 number: kWidePast
+      if (bits_g >= 0x7f800000u) kg -= kWidePast;
+      if (bits_h >= 0x7f800000u) kh -= kWidePast;
+    }
   };
 
   // Row ownership.  In every epoch the wavefront takes 64 consecutive leaf positions,
