@@ -153,7 +153,9 @@ def _check(rc: int, what: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
-        return int(torch.cuda.current_stream().cuda_stream)
+        # torch.cuda.current_stream() makes a Stream object for the same handle: 2.7 us a call, this 0.3.  The smallest calls
+        # wait for the host (10,000 x 28 x 64, build and search: 18.4 us a pass with it, 14.4 so).
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return int(stream.cuda_stream)
     return int(stream)
