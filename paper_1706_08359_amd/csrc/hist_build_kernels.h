@@ -233,6 +233,13 @@ feature_max_kernel(const uint8_t* __restrict__ src, int64_t n_rows, int64_t tota
   }
 }
 
+// Copies words, also to page-locked host memory.
+__global__ void __launch_bounds__(256)
+words_copy_kernel(const uint32_t* __restrict__ from, int32_t n, uint32_t* __restrict__ to) {
+  const int32_t i = (int32_t)(blockIdx.x * 256 + threadIdx.x);
+  if (i < n) to[i] = from[i];
+}
+
 // The fused layout: feature tiles with a region each (whatever the rows: none are shared), as pack_kernel writes
 // those of a small matrix of n_cols one-byte features, a byte being the joint value of its column.  One thread per 4-byte word.
 __global__ void __launch_bounds__(256)
