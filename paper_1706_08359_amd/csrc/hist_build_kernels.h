@@ -389,9 +389,9 @@ __device__ __forceinline__ double pow2d(int k) {
   return __longlong_as_double((long long)(k + 1023) << 52);
 }
 // An epoch whose sum of magnitudes is past the largest fp32 number has no scale of its own: it is scaled as if the sum
-// were 2^128, and 2^kWidePast times smaller, so that sixteen rows of the largest number stay within the 2^51
-// that i64_to_f64 takes (its 54-bit field alone would take them at the larger scale).
-constexpr int kWidePast = 2;
+// were 2^128, with this exponent.  The 54-bit field of a cell then takes fifteen rows of the largest number, which is more than
+// the 2^51 that i64_to_f64 takes: epochs of this exponent are drained by a conversion of all 53 bits of a double.
+constexpr int kWidePastExp = (kSumBits - 2) + 127 - 255;
 // round-to-nearest-even of |v| < 2^51 to a 64-bit integer (the sum's low mantissa bits)
 __device__ __forceinline__ long long rint_to_i64(double v) {
   return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000LL;
@@ -585,10 +585,6 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     const uint32_t bits_h = (uint32_t)__builtin_amdgcn_readlane(__float_as_uint(v), 8);
     kg = epoch_scale_exp(bits_g);
     kh = epoch_scale_exp(bits_h);
-    if (WIDE) {  // sums past the largest fp32 number: kWidePast
-      if (bits_g >= 0x7f800000u) kg -= kWidePast;
-      if (bits_h >= 0x7f800000u) kh -= kWidePast;
-    }
   };
 
   // Row ownership.  In every epoch the wavefront takes 64 consecutive leaf positions,
@@ -903,6 +899,18 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     // unit first: answers come back in order, so the cells are then decoded one by one as they
     // arrive.  (The scheduling barrier keeps the scales' arithmetic, which the next phase needs, from
     // being waited for between the requests.)
+    if (WIDE && (kg <= kWidePastExp || kh <= kWidePastExp)) {
+      // kWidePastExp: rare, so here, cell by cell (the registers are taken), and what follows then finds empty cells.  (As the
+      // other branch of what follows it costs all wide kernels 10 to 40 registers.)
+#pragma unroll
+      for (int m = 0; m < PP; ++m) {
+        const unsigned long long t = request_cell(tid + m * NT), th = request_cell((WIDE ? CELLS : 0) + tid + m * NT);
+        acc_c[m] += (uint32_t)t & ((1u << kCountBits) - 1u);
+        acc_g[m] = (ACC)fma((double)((long long)t >> kCountBits), inv_gw, (double)acc_g[m]);
+        acc_h[m] = (ACC)fma((double)((long long)th >> kCountBits), inv_hw, (double)acc_h[m]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     const float next_sums = request_scales((int)parity);
     const uint32_t box = unit_box[0];
     unsigned long long cell[PP], cell_h[WIDE ? PP : 1];
