@@ -283,7 +283,8 @@ int gbdt_hist_subtract(const gbdt_bin_t* parent, const gbdt_bin_t* child, gbdt_b
  * bins <= t (running prefix), right = feature total - left.  A threshold is
  * admissible when both sides have count >= 1 and hessian sum >= min_child_hess.
  * The admissible threshold with the largest gain wins; equal gains go to the
- * smaller feature, then the smaller bin.  Prefix sums and gains are computed in
+ * smaller feature, then the smaller bin.  A gain that is no number (0 / 0: lambda = 0
+ * and a side without gradient and hessian) loses against every other.  Prefix sums and gains are computed in
  * fp64 from the fp32 histogram, bins in ascending order.
  *   hist        DEVICE gbdt_bin_t [n_features][n_bins]
  *   lambda      L2 regularisation added to each hessian sum, >= 0

@@ -197,8 +197,11 @@ __device__ __forceinline__ int wave_min(int v) {
   v = dpp_min<0x143, 0xc>(v);
   return __builtin_amdgcn_readlane(v, 63);
 }
+// A gain that is no number (0 / 0: lambda = 0 and a side without gradient and hessian) loses against every number, in a lane,
+// a wavefront, a workgroup and between them, so a search does not depend on how its steps are dealt out.
+__device__ __forceinline__ bool gain_beats(double gain, double best) { return gain > best || (best != best && gain == gain); }
 // The index of the wavefront's best (gain, index) under the order "larger gain, then smaller index"
-// (index < 0: no candidate); -1 if no lane has one.  A gain that is no number loses against every number.
+// (index < 0: no candidate); -1 if no lane has one.
 __device__ __forceinline__ int32_t wave_argmax(double gain, int32_t idx) {
   const double top = wave_max(idx >= 0 ? gain : -INFINITY);
   bool mine = idx >= 0 && gain == top;
@@ -418,7 +421,7 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
           const double lt = __ddiv_rn(__dmul_rn(GL, GL), HL + lambda);
           const double rt = __ddiv_rn(__dmul_rn(GR, GR), HR + lambda);
           const double gain = __dsub_rn(__dadd_rn(lt, rt), parent);
-          if (best_pair < 0 || gain > best_gain) {  // pairs ascend: ties keep the earlier pair
+          if (best_pair < 0 || gain_beats(gain, best_gain)) {  // pairs ascend: ties keep the earlier pair
             best_gain = gain;
             best_pair = (step * kRows + row - f_first) * (B - 1) + bin0 - skip + k;
             best_gl = GL;
@@ -518,7 +521,7 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
     double gain;
     int32_t feature;
     load_cand_key(cand + i, &gain, &feature);
-    if (feature >= 0 && (bi < 0 || gain > bg)) {  // i ascends, so ties keep the smaller feature
+    if (feature >= 0 && (bi < 0 || gain_beats(gain, bg))) {  // i ascends, so ties keep the smaller feature
       bg = gain;
       bi = i;
     }
