@@ -199,7 +199,7 @@ __device__ __forceinline__ int wave_min(int v) {
 }
 // A gain that is no number (0 / 0: lambda = 0 and a side without gradient and hessian) loses against every number, in a lane,
 // a wavefront, a workgroup and between them, so a search does not depend on how its steps are dealt out.
-__device__ __forceinline__ bool gain_beats(double gain, double best) { return gain > best || (best != best && gain == gain); }
+__device__ __forceinline__ bool gain_beats(double gain, double best) { return !(best >= gain) && gain == gain; }
 // The index of the wavefront's best (gain, index) under the order "larger gain, then smaller index"
 // (index < 0: no candidate); -1 if no lane has one.
 __device__ __forceinline__ int32_t wave_argmax(double gain, int32_t idx) {
@@ -216,8 +216,8 @@ __device__ __forceinline__ int32_t wave_argmax(double gain, int32_t idx) {
 //     to right (it decides which thresholds tie exactly), so the sums are formed in parallel -- within a lane,
 //     then over the row's lanes -- and CHECKED: if p[i] == p[i - 1] + v[i] holds in fp64 for every bin, then
 //     p is that sum, by induction.  It holds whenever no addition rounds, i.e. unless the row's
-//     values span more than some 20 binary orders of magnitude; then the lanes repeat the sum from
-//     left to right, a lane's turn at a time.  (Counts never round.)
+//     values span more than some 20 binary orders of magnitude; then the lanes correct their sums until it does, 2 to
+//     6 turns for most rows.  (Counts never round.)
 //  3. The gains.  Divisions are the expensive part, and nearly all of them lose: an approximation by one reciprocal with
 //     a bound of its error rules out what cannot beat the best gain the wavefront knows, and only
 //     the rest is divided out.
@@ -228,9 +228,11 @@ __device__ __forceinline__ int32_t wave_argmax(double gain, int32_t idx) {
 //     the candidates of all to the histogram's split record: workgroups hold ascending features,
 //     so "smaller candidate index" is "smaller feature".
 // Bound by vector work (about 240 instructions a step) and, with many histograms, by reading them: 64 histograms of 2,000 x 63
-// take 23.6 us, 4.1 TB/s, 256 of them 75 (5.2 TB/s); a lone one 6.2.  (A workgroup used to stage up to 16
+// take 23.6 us, 4.1 TB/s, 256 of them 75 (5.2 TB/s); a lone one 6.2.  Where the sums of every row round: 64 of 2,000 x 63 36 us, 64 of 500 x
+// 255 54 instead of 25 (41 and 93 with one lane after the other summing from left to right, 16 and 64 turns), a lone 28 x 255 6.8
+// instead of 5.2.  (A workgroup used to stage up to 16
 // features in local memory, one wavefront ran their sums one bin after the other while the others waited, and
-// every threshold was divided out: 50.6, 156 and 9.8 us.)  Lanes of four bins, not one, because the sums over lanes are most of the
+// every threshold was divided out: 50.6, 156 and 9.8 us, 79 for 500 x 255 and 8.9 for 28 x 255, whatever the sums.)  Lanes of four bins, not one, because the sums over lanes are most of the
 // work: 2 vector instructions a bin and statistic for them so, 6 with 64 lanes a row.  The next step's rows
 // are requested before the present ones are used: 25.8 us without.
 // grid.y = histogram of the call; histogram y starts hist_stride bins after histogram
@@ -309,6 +311,7 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
   // positive -- as they are where a side's hessian has to be.
   constexpr double kSlack = 0x1p-40;
   const bool positive = min_child_hess > 0.0;
+  auto arrives = [](double sum, double claim) { return (sum == claim) | ((sum != sum) & (claim != claim)); };
   double bound = -INFINITY;  // some threshold the wavefront has seen gains at least this
   // this lane's best pair with everything the record needs
   double best_gain = 0.0, best_gl = 0.0, best_hl = 0.0, best_nl = 0.0, best_g = 0.0, best_h = 0.0, best_n = 0.0;
@@ -372,16 +375,23 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
       same &= ph[k - 1] + (double)v[k].hess == ph[k];
     }
     if (__ballot(!same) != 0ull) {
+      // A lane's sums at its last bin are what it claims.  A turn sums every lane's bins onto the claim of the lane before; if
+      // all arrive at their claims, those are the sums from left to right.  Else claims move by what they and the claims
+      // before them were off.  (After turn i the row's lanes 0 .. i are right whatever the values are.)
 #pragma unroll 1
-      for (int turn = 0; turn < (1 << LB); ++turn) {  // after turn i the row's lanes 0 .. i are right
-        double g = turn ? row_lanes.before(pg[K - 1]) : 0.0, h = turn ? row_lanes.before(ph[K - 1]) : 0.0;
+      for (int turn = 0; turn < (1 << LB); ++turn) {
+        double g = row_lanes.before(pg[K - 1]), h = row_lanes.before(ph[K - 1]);
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          g += (double)v[k].grad;
-          h += (double)v[k].hess;
-          pg[k] = g;
-          ph[k] = h;
+        for (int k = 0; k < K - 1; ++k) {
+          pg[k] = g += (double)v[k].grad;
+          ph[k] = h += (double)v[k].hess;
         }
+        g += (double)v[K - 1].grad;
+        h += (double)v[K - 1].hess;
+        const double off_g = arrives(g, pg[K - 1]) ? 0.0 : g - pg[K - 1], off_h = arrives(h, ph[K - 1]) ? 0.0 : h - ph[K - 1];
+        if (__ballot(!(off_g == 0.0 && off_h == 0.0)) == 0ull) break;
+        pg[K - 1] = g + row_lanes.before(row_lanes.prefix(off_g));
+        ph[K - 1] = h + row_lanes.before(row_lanes.prefix(off_h));
       }
     }
     const double G = row_lanes.last(pg[K - 1], lane), H = row_lanes.last(ph[K - 1], lane);

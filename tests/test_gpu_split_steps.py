@@ -69,3 +69,30 @@ def test_siblings_formed_in_the_search(n_bins):
         if nd["left"] >= 0:
             goes = torch.from_numpy(bins[:, nd["feature"]]).cuda()[idx.long()] <= int(nd["bin"])
             rows[int(nd["left"])], rows[int(nd["right"])] = idx[goes], idx[~goes]
+
+
+@pytest.mark.parametrize("spread", [30, 60])
+@pytest.mark.parametrize("n_bins", [5, 9, 16, 31, 63, 64, 100, 128, 200, 256])
+def test_sums_that_round_are_the_ones_from_left_to_right(n_bins, spread):
+    """Every feature holds the same bins, in an order of its own on either side of the one good threshold: gains differ by the
+    rounding of the sums alone, and which is largest says whether those are the oracle's to the last bit."""
+    n_features, n_hists, lam = 75, 24, 2.0 ** -10      # (lam: the same in fp32)
+    print(f"rounding sums {n_hists} x {n_features} x {n_bins}, 2^+-{spread}", flush=True)
+    rng = np.random.default_rng(n_bins + spread)
+    h = np.zeros((n_hists, n_features, n_bins), dtype=B.BIN_DTYPE)
+    t = n_bins // 2
+    for i in range(n_hists):
+        scale = 2.0 ** rng.integers(-spread, 1, size=n_bins) * (1 + i)
+        grad = (rng.uniform(0.5, 1, size=n_bins) * np.where(np.arange(n_bins) < t, 1, -1) * scale).astype(np.float32)
+        hess = (rng.uniform(0.5, 1, size=n_bins) * scale ** 0.5).astype(np.float32)
+        for f in range(n_features):
+            order = np.concatenate([rng.permutation(t), t + rng.permutation(n_bins - t)])
+            h["grad"][i, f], h["hess"][i, f] = grad[order], hess[order]
+    h["count"] = 3
+    d = torch.from_numpy(h.view(np.float32).reshape(h.shape + (3,)).copy()).to("cuda:0")
+    got = B.splits_to_dicts(B.gbdt_best_split_batch(d, lam, 0.0))
+    filtered = B.splits_to_dicts(B.gbdt_best_split_batch(d, lam, 1e-30))
+    for i in range(n_hists):
+        ref = orc.best_split(orc.from_f32_hist(h["grad"][i], h["hess"][i], h["count"][i]), lam, 0.0)
+        for one in (got[i], filtered[i]):
+            assert (one["feature"], one["bin"]) == (ref["feature"], ref["bin"]), (i, one, ref)
