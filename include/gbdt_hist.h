@@ -529,6 +529,9 @@ int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int
  * [3 * i + 1] = half, [3 * i + 2] = workgroup of block i.  Returns the blocks of the launch. */
 int gbdt_debug_half_blocks(int32_t n_features, int64_t n_rows, int32_t cols, int32_t by_column, int32_t* block_out,
                            int32_t max_blocks);
+/* How gbdt_hist_build_batch gathers the statistics of n_leaves lists by parts: launch_out[l] = the launch that list l
+ * is of, position_out[l] = the entry of row_idx it starts at.  Returns the launches.  Host only. */
+int gbdt_debug_gather_plan(const int64_t* leaf_offsets, int32_t n_leaves, int32_t* launch_out, int64_t* position_out);
 /* The column plan gbdt_bins_fuse makes for features with the given numbers of levels (1..64
  * each): col_out[f] / stride_out[f] = the column of feature f and the weight of its bin in the
  * column's joint value; *n_cols_out the number of columns.  Host only. */

@@ -24,7 +24,7 @@ EXPORTS = [
     "gbdt_last_hip_error", "gbdt_debug_geometry", "gbdt_debug_locate",
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
     "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
-    "gbdt_debug_leaf_plan", "gbdt_debug_half_blocks",
+    "gbdt_debug_leaf_plan", "gbdt_debug_half_blocks", "gbdt_debug_gather_plan",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -608,6 +608,19 @@ def gbdt_debug_half_blocks(n_features: int, n_rows: int, cols: int, by_column: b
     blocks = np.zeros((n, 3), np.int32)
     lib.gbdt_debug_half_blocks(n_features, n_rows, cols, 1 if by_column else 0, blocks.ctypes.data, n)
     return blocks
+
+
+def gbdt_debug_gather_plan(leaf_offsets):
+    """(launch, first entry of row_idx) of every list of a batch whose statistics are gathered by parts."""
+    lib = load()
+    offs = np.ascontiguousarray(leaf_offsets, dtype=np.int64)
+    launch, position = np.zeros(len(offs) - 1, np.int32), np.zeros(len(offs) - 1, np.int64)
+    lib.gbdt_debug_gather_plan.restype = ctypes.c_int
+    lib.gbdt_debug_gather_plan.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p]
+    n = lib.gbdt_debug_gather_plan(offs.ctypes.data, len(offs) - 1, launch.ctypes.data, position.ctypes.data)
+    if n < 0:
+        _check(n, "gbdt_debug_gather_plan")
+    return launch, position
 
 
 def gbdt_debug_cell_sums(grad_q, hess_q):

@@ -802,6 +802,25 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
   return b;
 }
 
+// The table of one launch of stats_gather_lists_kernel, for lists l0, l0 + 1, ... of the call: as many as fit the table, and
+// as start within 2^32 positions of list l0 (each is shorter than 2^31).  Without seg_off positions are relative to list l0's.
+// Returns the blocks of an eighth of the lists.
+uint32_t fill_gather_table(const int64_t* leaf_offsets, const uint32_t* seg_off, int32_t l0, int32_t n_leaves,
+                           GatherTable* t) {
+  uint32_t blocks = 0;
+  int32_t i = 0;
+  for (; i < kGatherLists && l0 + i < n_leaves; ++i) {
+    const int64_t n = leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i];
+    if (!seg_off && leaf_offsets[l0 + i + 1] - leaf_offsets[l0] >= ((int64_t)1 << 32)) break;
+    t->first[i] = seg_off ? seg_off[l0 + i] : (uint32_t)(leaf_offsets[l0 + i] - leaf_offsets[l0]);
+    t->n[i] = (uint32_t)n;
+    t->first_block[i] = blocks;
+    blocks += (uint32_t)(((n + kXcds - 1) / kXcds + kGatherRows - 1) / kGatherRows);
+  }
+  t->n_lists = i;
+  return blocks;
+}
+
 // Split search of n_hists (<= kSplitMaxHists) histograms, hist_stride bins apart, in one
 // launch; splits_out[i] receives the record of histogram i.
 int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, float lambda,
@@ -1457,18 +1476,10 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
                          row_idx + leaf_offsets[0], grad, hess, total_rows, g_list, h_list);
       HIP_TRY(hipGetLastError());
     }
-    for (int32_t l0 = 0; by_parts && l0 < n_leaves; l0 += kGatherLists) {
-      GatherTable t;
-      t.n_lists = n_leaves - l0 < kGatherLists ? n_leaves - l0 : kGatherLists;
+    GatherTable t;
+    for (int32_t l0 = 0; by_parts && l0 < n_leaves; l0 += t.n_lists) {
+      const uint32_t blocks = fill_gather_table(leaf_offsets, seg_off, l0, n_leaves, &t);
       const int64_t base = seg_off ? 0 : leaf_offsets[l0], before = seg_off ? 0 : base - leaf_offsets[0];
-      uint32_t blocks = 0;
-      for (int32_t i = 0; i < t.n_lists; ++i) {
-        const int64_t n = leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i];
-        t.first[i] = seg_off ? seg_off[l0 + i] : (uint32_t)(leaf_offsets[l0 + i] - base);
-        t.n[i] = (uint32_t)n;
-        t.first_block[i] = blocks;
-        blocks += (uint32_t)(((n + kXcds - 1) / kXcds + kGatherRows - 1) / kGatherRows);
-      }
       if (blocks == 0) continue;
       hipLaunchKernelGGL(stats_gather_lists_kernel, dim3(blocks * kXcds), dim3(256), 0, s, row_idx + base, grad, hess, t,
                          seg_wrap, g_list + before, h_list + before);
@@ -2370,6 +2381,22 @@ int gbdt_debug_half_blocks(int32_t n_features, int64_t n_rows, int32_t cols, int
     block_out[3 * i + 2] = (int32_t)b.col;
   }
   return (int)blocks;
+}
+
+int gbdt_debug_gather_plan(const int64_t* leaf_offsets, int32_t n_leaves, int32_t* launch_out, int64_t* position_out) {
+  if (!leaf_offsets || n_leaves < 1 || !launch_out || !position_out) return GBDT_EINVAL;
+  for (int32_t l = 0; l < n_leaves; ++l)
+    if (leaf_offsets[l + 1] < leaf_offsets[l] || leaf_offsets[l + 1] - leaf_offsets[l] >= ((int64_t)1 << 31)) return GBDT_EINVAL;
+  int32_t launches = 0;
+  GatherTable t;
+  for (int32_t l0 = 0; l0 < n_leaves; l0 += t.n_lists, ++launches) {
+    (void)fill_gather_table(leaf_offsets, nullptr, l0, n_leaves, &t);
+    for (int32_t i = 0; i < t.n_lists; ++i) {
+      launch_out[l0 + i] = launches;
+      position_out[l0 + i] = leaf_offsets[l0] + (int64_t)t.first[i];
+    }
+  }
+  return launches;
 }
 
 int gbdt_debug_fusion_plan(const uint32_t* levels, int32_t n_features, int32_t* col_out, int32_t* stride_out,
