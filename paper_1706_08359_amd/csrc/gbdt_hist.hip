@@ -828,8 +828,10 @@ int launch_split(const gbdt_bin_t* hists, int64_t hist_stride, int32_t n_hists, 
                  hipStream_t s, gbdt_split_t* mirror = nullptr, const SplitSiblings* siblings = nullptr) {
   const SplitGrouping sg = split_grouping(n_features, n_bins, n_hists);
   void* ws = nullptr;
-  int rc = get_workspace((size_t)n_hists * sg.n_wg * sizeof(SplitCand), s, &ws);
-  if (rc != GBDT_OK) return rc;
+  if (sg.n_wg > 1) {  // (a lone workgroup hands nothing over)
+    const int rc = get_workspace((size_t)n_hists * sg.n_wg * sizeof(SplitCand), s, &ws);
+    if (rc != GBDT_OK) return rc;
+  }
   // (only with siblings does the kernel write to the histograms)
   auto launch = [&](auto kernel, const auto& sib) {
     hipLaunchKernelGGL(kernel, dim3(sg.n_wg, n_hists), dim3(64 * sg.waves), 0, s, const_cast<gbdt_bin_t*>(hists),
