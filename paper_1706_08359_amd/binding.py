@@ -25,6 +25,7 @@ EXPORTS = [
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
     "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
     "gbdt_debug_leaf_plan", "gbdt_debug_half_blocks", "gbdt_debug_gather_plan",
+    "gbdt_debug_host_blocks",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -621,6 +622,16 @@ def gbdt_debug_gather_plan(leaf_offsets):
     if n < 0:
         _check(n, "gbdt_debug_gather_plan")
     return launch, position
+
+
+def gbdt_debug_host_blocks():
+    """(kept for later calls, left by failed calls): the library's blocks of page-locked host memory."""
+    lib = load()
+    out = (ctypes.c_int64 * 2)()
+    lib.gbdt_debug_host_blocks.restype = ctypes.c_int
+    lib.gbdt_debug_host_blocks.argtypes = [ctypes.c_void_p]
+    _check(lib.gbdt_debug_host_blocks(out), "gbdt_debug_host_blocks")
+    return int(out[0]), int(out[1])
 
 
 def gbdt_debug_cell_sums(grad_q, hess_q):

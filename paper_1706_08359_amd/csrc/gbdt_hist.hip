@@ -951,12 +951,14 @@ class HostRecords {
   HostRecords& operator=(const HostRecords&) = delete;
   bool ok() const { return b_.host != nullptr; }
   const gbdt_split_t& operator[](size_t i) const { return b_.host[i]; }
-  gbdt_split_t* for_search() {  // the device address, for a search to be enqueued
-    in_flight_ = true;
-    return b_.dev;
+  gbdt_split_t* device() { return b_.dev; }  // for the call that enqueues a kernel
+  // ... and what that call returned: without the scratch it needs it has enqueued nothing, and nobody writes to the block
+  int enqueued(int rc) {
+    in_flight_ = in_flight_ || rc != GBDT_ENOMEM;
+    return rc;
   }
   // the block as words, of which it holds at least n * sizeof(gbdt_split_t) / 4
-  uint32_t* words_for_kernel() { return reinterpret_cast<uint32_t*>(for_search()); }
+  uint32_t* device_words() { return reinterpret_cast<uint32_t*>(b_.dev); }
   const uint32_t* words() const { return reinterpret_cast<const uint32_t*>(b_.host); }
   hipError_t wait(hipStream_t s) {  // until the kernels that write to the block are done
     const hipError_t e = hipStreamSynchronize(s);
@@ -1283,7 +1285,8 @@ int gbdt_bins_fuse(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
     HIP_TRY(hipGetLastError());
     if (found.ok()) {
       hipLaunchKernelGGL(words_copy_kernel, dim3((n_features + 255) / 256), dim3(256), 0, s, (const uint32_t*)max_dev,
-                         n_features, found.words_for_kernel());
+                         n_features, found.device_words());
+      (void)found.enqueued(GBDT_OK);
       HIP_TRY(hipGetLastError());
       HIP_TRY(found.wait(s));
       std::copy(found.words(), found.words() + n_features, levels.begin());
@@ -1845,7 +1848,7 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
   // root: histogram and first partition without an index list
   int rc = gbdt_hist_build(bin_matrix, n_rows, n_features, n_bins, nullptr, n_rows, grad, hess, pool, s);
   if (rc != GBDT_OK) return rc;
-  rc = launch_split(pool, 0, 1, lambda, min_child_hess, recs, n_features, n_bins, s, found.for_search());
+  rc = found.enqueued(launch_split(pool, 0, 1, lambda, min_child_hess, recs, n_features, n_bins, s, found.device()));
   if (rc != GBDT_OK) return rc;
   const float2* stat_pairs = nullptr;
   if (lay.total > lay.least && scratch_bytes >= lay.total && max_leaves > 1) {
@@ -2013,8 +2016,8 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
       sib.n = k;
       sib.keep = 1;
       for (int j = 0; j < kSplitSiblings; ++j) sib.parent_slot[j] = j < k ? cands[batch[j]].slot : 0;
-      rc = launch_split(h_small, (int64_t)hist_elems, 2 * k, lambda, min_child_hess, recs + next_slot, n_features,
-                        n_bins, s, found.for_search(), &sib);
+      rc = found.enqueued(launch_split(h_small, (int64_t)hist_elems, 2 * k, lambda, min_child_hess, recs + next_slot, n_features,
+                                       n_bins, s, found.device(), &sib));
       if (rc != GBDT_OK) return rc;
     }
     {
@@ -2161,8 +2164,9 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
     if (n_open == 0) break;
     for (int h0 = 0; h0 < n_open; h0 += kSplitMaxHists) {
       const int nh = n_open - h0 < kSplitMaxHists ? n_open - h0 : kSplitMaxHists;
-      rc = launch_split(hist_buf[cur] + (size_t)h0 * hist_elems, (int64_t)hist_elems, nh, lambda, min_child_hess, recs + h0,
-                        n_features, n_bins, s, found.for_search() + h0, level_sib.n > 0 ? &level_sib : nullptr);
+      rc = found.enqueued(launch_split(hist_buf[cur] + (size_t)h0 * hist_elems, (int64_t)hist_elems, nh, lambda, min_child_hess,
+                                       recs + h0, n_features, n_bins, s, found.device() + h0,
+                                       level_sib.n > 0 ? &level_sib : nullptr));
       if (rc != GBDT_OK) return rc;
     }
     HIP_TRY(found.wait(s));
@@ -2399,6 +2403,14 @@ int gbdt_debug_gather_plan(const int64_t* leaf_offsets, int32_t n_leaves, int32_
     }
   }
   return launches;
+}
+
+int gbdt_debug_host_blocks(int64_t* out) {
+  if (!out) return GBDT_EINVAL;
+  std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
+  out[0] = (int64_t)g_rec_blocks.idle.size();
+  out[1] = (int64_t)g_rec_blocks.lost.size();
+  return GBDT_OK;
 }
 
 int gbdt_debug_fusion_plan(const uint32_t* levels, int32_t n_features, int32_t* col_out, int32_t* stride_out,
