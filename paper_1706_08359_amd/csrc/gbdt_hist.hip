@@ -322,7 +322,6 @@ int device_cu_count() {
 
 constexpr size_t kLdsPerCu = 160 * 1024;
 constexpr int64_t kPackStreamBytes = (int64_t)256 << 20;  // the memory-side cache; see pack_kernel
-constexpr int kMinRowsPerChunk = kEpochRows;
 static_assert(kPlanSlackBytes == (int64_t)kEpochRows * 64, "slack behind the tiles: one epoch of the widest tile");
 constexpr int kBuildThreads = 512;  // threads per workgroup of every build kernel variant
 
@@ -973,7 +972,10 @@ class HostRecords {
 
 // A split that sends more rows to the children than the node has cannot be: the rows of the children would not be the node's.
 bool split_fits(const gbdt_split_t& r, uint64_t count) {
-  return r.feature < 0 || (uint64_t)r.left_count + r.right_count <= count;
+  if (r.feature < 0 || (uint64_t)r.left_count + r.right_count <= count) return true;
+  snprintf(g_hip_err, sizeof g_hip_err, "a split of %u and %u rows was found for a node of %llu", r.left_count, r.right_count,
+           (unsigned long long)count);
+  return false;
 }
 
 // Scratch of gbdt_grow_tree_depthwise: two row buffers, two levels of histograms and the split records of a level.
@@ -1802,7 +1804,10 @@ int gbdt_grow_tree(const void* bin_matrix, int64_t n_rows, int32_t n_features, i
   const TreeScratch lay = tree_scratch_layout(n_rows, n_features, n_bins, max_leaves);
   if (scratch_bytes < lay.least) return GBDT_ENOMEM;
   HostRecords found(2 * kGrowRound);  // the records of the last search
-  if (!found.ok()) return GBDT_ENOMEM;
+  if (!found.ok()) {
+    snprintf(g_hip_err, sizeof g_hip_err, "no page-locked host memory for the split records");
+    return GBDT_ENOMEM;
+  }
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)scratch;
   int32_t* rows_base = (int32_t*)(base + lay.rows_a);   // row buffer b starts b * row_elems entries in
@@ -2115,7 +2120,10 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
   if (scratch_bytes < lay.total) return GBDT_ENOMEM;
   const size_t width = (size_t)1 << max_depth;  // most nodes a level can hold
   HostRecords found(width);  // the records of the last search
-  if (!found.ok()) return GBDT_ENOMEM;
+  if (!found.ok()) {
+    snprintf(g_hip_err, sizeof g_hip_err, "no page-locked host memory for the split records");
+    return GBDT_ENOMEM;
+  }
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)scratch;
   int32_t* rows_buf[2] = {(int32_t*)(base + lay.rows_a), (int32_t*)(base + lay.rows_b)};
@@ -2580,7 +2588,6 @@ int gbdt_reset(void) {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
-    auto& blocks = g_rec_blocks;
     for (auto* list : {&g_rec_blocks.idle, &g_rec_blocks.lost}) {  // (of this device: no other has been waited for)
       auto done = std::partition(list->begin(), list->end(), [&](const RecordBlock& b) { return b.device != dev; });
       for (auto it = done; it != list->end(); ++it) (void)hipHostFree(it->host);

@@ -525,7 +525,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   static_assert(!WIDE || sizeof(ACC) == 8, "wide cells are drained into fp64 accumulators");
   using S = TileShape<CAP, W, NIB, NT>;
   constexpr bool kShortRows = S::PITCH == 16;
-  constexpr int VEC = S::VEC, NWORD = S::NWORD, LPR = S::LPR, RPW = S::RPW, NBW = S::NBW;
+  constexpr int NWORD = S::NWORD, LPR = S::LPR, RPW = S::RPW, NBW = S::NBW;
   constexpr int CELLS = S::CELLS, PP = S::PP, NW = S::NW;
   constexpr int NTBL = LPR == 8 ? 1 : 2;  // LPR 4: two byte-words share a page of 32 slots
 

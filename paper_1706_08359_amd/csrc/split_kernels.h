@@ -368,7 +368,8 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
       ph[k] += bh;
       pn[k] += bn;
     }
-    bool same = (row_lanes.before(pg[K - 1]) == bg) & (row_lanes.before(ph[K - 1]) == bh);
+    bool same = row_lanes.before(pg[K - 1]) == bg;
+    same &= row_lanes.before(ph[K - 1]) == bh;
 #pragma unroll
     for (int k = 1; k < K; ++k) {
       same &= pg[k - 1] + (double)v[k].grad == pg[k];
