@@ -488,8 +488,18 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
   return u;
 }
 
-// A leaf that a build takes as sparse in the matrix (plan_halves): a list of at most a fifth of the rows.
-bool leaf_is_sparse(bool indexed, int64_t n_leaf, int64_t n_rows) { return indexed && n_leaf <= n_rows / 5; }
+// How the rows of a build lie in the matrix, for plan_halves.  Sparse: a list of at most a fifth of the rows, and all leaves of
+// a batch.  Many sparse rows: from kSparseManyRows listed ones on, in a batch if its leaves hold at most a twelfth of the rows
+// each on average (1,000,000 x 33 x 255: 32 leaves of half of the rows 45.9 us whole, 54.7 in halves, 64 of all 76 and 79;
+// 300,000 x 33 x 255: 64 of all 41 and 30; 4,000,000 x 33 x 255: four leaves of half of the rows 119 and 95).
+constexpr int64_t kSparseManyRows = 384 * 1024;
+int rows_of_leaf(bool indexed, int64_t n_leaf, int64_t n_rows) {
+  if (!indexed || n_leaf > n_rows / 5) return kRowsDense;
+  return n_leaf >= kSparseManyRows ? kRowsSparseMany : kRowsSparse;
+}
+int rows_of_batch(int64_t total_rows, int32_t n_leaves, int64_t n_rows) {
+  return total_rows >= kSparseManyRows && total_rows / n_leaves * 12 <= n_rows ? kRowsSparseMany : kRowsSparse;
+}
 
 // Kernel variants: bin capacity -> (main tile width, 4-bit, waves per SIMD the
 // register budget is set for).
@@ -1041,7 +1051,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   }
   const size_t joint_words = fused ? (size_t)n_features * n_bins * 3 : 0;
   const TilePlan plan0 = make_tile_plan(n_features, n_bins);
-  const bool halves = plan_halves(plan0, wide, leaf_is_sparse(leaf_row_idx != nullptr, n_leaf_rows, n_rows));
+  const bool halves = plan_halves(plan0, wide, rows_of_leaf(leaf_row_idx != nullptr, n_leaf_rows, n_rows));
   const int wg_per_cu = build_wg_per_cu(plan0.cap, leaf_row_idx != nullptr, wide, halves);
   BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(), wg_per_cu, wide, halves);
   if (fixed_base) {
@@ -1363,7 +1373,7 @@ size_t gbdt_workspace_bytes(int64_t n_rows, int32_t n_features, int32_t n_bins) 
   const int cap = make_tile_plan(n_features, n_bins).cap;
   const bool wide = g_wide.load() != 0;
   // (a list that is built from whole tiles has half the resident workgroups and needs as much)
-  const bool halves = plan_halves(make_tile_plan(n_features, n_bins), wide, false);
+  const bool halves = plan_halves(make_tile_plan(n_features, n_bins), wide, kRowsDense);
   const BuildGeom g0 = make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, false, wide, halves),
                                  wide, halves);
   const BuildGeom g1 = make_geom(n_features, n_bins, n_rows, device_cu_count(), build_wg_per_cu(cap, true, wide, halves),
@@ -1436,7 +1446,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
   if (n_tiles > 65535) return GBDT_EUNSUPPORTED;
   if ((n_rows + kEpochRows) * (int64_t)p.wm >= ((int64_t)1 << 32)) return GBDT_EUNSUPPORTED;
   const bool wide = g_wide.load() != 0;
-  const bool halves = plan_halves(p, wide, true);
+  const bool halves = plan_halves(p, wide, rows_of_batch(total_rows, n_leaves, n_rows));
   const int cus = device_cu_count(), wg_per_cu = build_wg_per_cu(p.cap, true, wide, halves);
   const int n_parts = plan_n_parts(p, halves);
   // words of the partial blocks of one workgroup column (two blocks each with wide accumulation)
@@ -1589,7 +1599,7 @@ size_t gbdt_hist_build_batch_workspace_bytes(int32_t n_features, int32_t n_bins,
   if (n_features <= 0 || n_bins < 2 || n_bins > 256 || n_leaves < 0) return 0;
   const TilePlan p = make_tile_plan(n_features, n_bins);
   const bool wide = g_wide.load() != 0;
-  const bool halves = plan_halves(p, wide, true);
+  const bool halves = plan_halves(p, wide, kRowsSparse);  // (a call that takes whole tiles has fewer columns)
   const int n_parts = plan_n_parts(p, halves);
   const int64_t resident = (int64_t)device_cu_count() * build_wg_per_cu(p.cap, true, wide, halves);
   const size_t col = (p.cap == 16 ? variant_column_words<GBDT_VARIANT_16>(p)
@@ -2320,7 +2330,7 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
   if (!valid_shape(n_rows, n_features, n_bins) || n_leaf_rows < 0 || !out || n_out < 6) return GBDT_EINVAL;
   const bool wide = g_wide.load() != 0;
   const TilePlan p = make_tile_plan(n_features, n_bins);
-  const bool halves = plan_halves(p, wide, leaf_is_sparse(indexed != 0, n_leaf_rows, n_rows));
+  const bool halves = plan_halves(p, wide, rows_of_leaf(indexed != 0, n_leaf_rows, n_rows));
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
                                 build_wg_per_cu(p.cap, indexed != 0, wide, halves), wide, halves);
   const UnitPlan u = plan_units(g, n_leaf_rows, indexed != 0, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());

@@ -171,9 +171,15 @@ GBDT_HD int32_t plan_cell(const TilePlan& p, int32_t w, int32_t bin, int32_t slo
 // (2,270,000 x 137 x 255, root 302 us with whole tiles, 217 in halves, 10 % of the rows 54 and 45; 10,500,000 x 28 x 255,
 // root 269 and 218, half of the rows 157 and 123.)  Not so sparse leaves of a matrix of one tile, which are bound by the
 // lines they fetch, bins and statistics, now twice: a tenth of 10,500,000 x 28 x 255 49.7 us whole, 53.5 in halves; 32 leaves
-// of 4,000,000 x 28 x 255, all its rows, in a call 217 and 225.
-GBDT_HD bool plan_halves(const TilePlan& p, bool wide, bool sparse) {
-  return wide && p.cap == 256 && !(sparse && p.n_main + (p.wr ? 1 : 0) == 1);
+// of 4,000,000 x 28 x 255, all its rows, in a call 217 and 225.  (One 16-byte tile has nothing to halve, but the kernel with two
+// workgroups a CU has more rows in flight than its lines bear too: a tenth of 10,500,000 x 16 x 255 39.7 us with one,
+// 48.5 with two, 2 % 24.1 and 29.1.)  Nor many sparse rows of one tile and a remainder: 32 leaves of 4,000,000 x 33 x 255, half
+// of its rows, 133 us whole, 177 in halves, a tenth of it in one list 36.9 and 42.7; but few, 32 leaves of a tenth of
+// 1,000,000 x 33 x 255, 31.1 and 23.2.
+constexpr int kRowsDense = 0, kRowsSparse = 1, kRowsSparseMany = 2;  // how the rows of a build lie in the matrix
+GBDT_HD bool plan_halves(const TilePlan& p, bool wide, int rows) {
+  if (!wide || p.cap != 256) return false;
+  return p.n_main > 1 || rows < (p.n_main == 1 && p.wr ? kRowsSparseMany : kRowsSparse);
 }
 
 struct FeatureSlot {
