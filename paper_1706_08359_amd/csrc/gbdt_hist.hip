@@ -362,6 +362,16 @@ bool stats_gather_pays(int n_tiles, int64_t list_rows, int64_t rows_per_leaf, in
 // leaves of 200,000 x 100 x 255, build and partition: 41.8 us in list order, 43.2 by parts.)
 constexpr int64_t kGatherListsMinRows = 1 << 19;
 
+// Batches of matrices of two and three tiles that are built in halves (plan_halves): four and more parts, each of which would
+// gather the scattered values, so small leaves of a matrix whose arrays do not fit an XCD's L2 are gathered first as well.
+// (4,000,000 rows with wide sums, 64 leaves of all rows: 64 features 298 us by row id, 243 gathered, 96 features 518 and 388; 32
+// leaves of half of the rows 157 and 140, 286 and 220.  Four leaves of half of the rows: 118 and 125, 168 and 169.  64 leaves of 1,000,000 x
+// 64: 81 and 81.)
+bool stats_gather_of_parts_pays(int n_parts, int64_t list_rows, int64_t rows_per_leaf, int64_t n_rows) {
+  return n_parts >= kStatsGatherMinTiles && list_rows >= kStatsGatherMinRows && n_rows >= (1 << 20) &&
+         rows_per_leaf * 32 <= n_rows;
+}
+
 // When a tree's leaves are not gathered that way (few tiles), gbdt_grow_tree lays gradient and hessian
 // of every row side by side once: a scattered row then costs one line of statistics instead of two, beside
 // its line of bins.  From the size on at which both arrays no longer fit an XCD's L2.
@@ -1474,7 +1484,10 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
     if (rc_ids != GBDT_OK) return rc_ids;
   }
   // grad / hess of the whole concatenated list in list order, gathered once (see stats_gather_pays)
-  bool by_pos = total_rows > 0 && stats_gather_pays(n_tiles, total_rows, total_rows / n_leaves, n_rows);
+  // (a tree's (gradient, hessian) pairs are one line a row already)
+  bool by_pos = total_rows > 0 && (stats_gather_pays(n_tiles, total_rows, total_rows / n_leaves, n_rows) ||
+                                   (halves && !stat_pairs &&
+                                    stats_gather_of_parts_pays(n_parts, total_rows, total_rows / n_leaves, n_rows)));
   size_t stats_words = by_pos ? 2 * (((size_t)(seg_off ? n_rows : total_rows) + 63) / 64 * 64) : 0;
   void* ws = nullptr;
   int rc = get_workspace((need_words + stats_words) * 4 + 256, s, &ws);

@@ -59,3 +59,31 @@ def test_levels_of_many_segments():
         if nd["left"] >= 0:
             goes = columns[idx.long(), int(nd["feature"])] <= int(nd["bin"])
             rows[int(nd["left"])], rows[int(nd["right"])] = idx[goes], idx[~goes]
+
+
+@pytest.mark.parametrize("n_rows,n_leaves", [(2 ** 20, 33), (2 ** 20, 31), (2 ** 20 - 1, 33)])
+@pytest.mark.parametrize("n_features", [64, 70])
+def test_wide_sums_gathered_by_parts(n_rows, n_leaves, n_features):
+    """Two and three tiles in halves: gathered from 2^20 rows on if a leaf holds at most a 32nd of them."""
+    print(f"gather by parts {n_rows} x {n_features}, {n_leaves} lists", flush=True)
+    rng = np.random.default_rng(n_leaves)
+    bins = rng.integers(0, 255, size=(n_rows, n_features), dtype=np.uint8)
+    grad = rng.integers(-8, 9, size=n_rows).astype(np.float32) / 4
+    hess = rng.integers(1, 9, size=n_rows).astype(np.float32) / 4
+    packed = B.gbdt_bins_pack(torch.from_numpy(bins).cuda(), 255)
+    sizes = np.full(n_leaves, 2 ** 20 // 32 + (1 if n_leaves == 31 else 0))   # (just in, just out)
+    sizes[[0, 2]] += [1000, -1000]
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    rows = rng.integers(0, n_rows, size=offs[-1]).astype(np.int32)            # (repeats are legal)
+    B.gbdt_set_wide_accumulation(True)
+    try:
+        got = B.gbdt_hist_build_batch(packed, n_rows, n_features, 255, torch.from_numpy(rows).cuda(), offs,
+                                      torch.from_numpy(grad).cuda(), torch.from_numpy(hess).cuda()).cpu().numpy()
+    finally:
+        B.gbdt_set_wide_accumulation(False)
+    for k in (0, 1, 2, n_leaves - 1):
+        mine = rows[offs[k]:offs[k + 1]]
+        for f in (0, 31, 32, 63, n_features - 1):
+            for stat, w in ((0, grad), (1, hess)):
+                assert np.array_equal(got[k, f, :, stat], np.bincount(bins[mine, f], w[mine].astype(np.float64), 255)), (k, f, stat)
+            assert np.array_equal(got[k, f].view(np.uint32)[:, 2], np.bincount(bins[mine, f], minlength=255)), (k, f)
