@@ -501,11 +501,12 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
 // How the rows of a build lie in the matrix, for plan_halves.  Sparse: a list of at most a fifth of the rows, and all leaves of
 // a batch.  Many sparse rows: from kSparseManyRows listed ones on, in a batch if its leaves hold at most a twelfth of the rows
 // each on average (1,000,000 x 33 x 255: 32 leaves of half of the rows 45.9 us whole, 54.7 in halves, 64 of all 76 and 79;
-// 300,000 x 33 x 255: 64 of all 41 and 30; 4,000,000 x 33 x 255: four leaves of half of the rows 119 and 95).
+// 300,000 x 33 x 255: 64 of all 41 and 30; 4,000,000 x 33 x 255: four leaves of half of the rows 119 and 95), half as many in one
+// list (2,000,000 x 33 x 255, a tenth 27.6 and 29.7, 1,000,000, 19 % 26.4 and 25.5).
 constexpr int64_t kSparseManyRows = 384 * 1024;
 int rows_of_leaf(bool indexed, int64_t n_leaf, int64_t n_rows) {
   if (!indexed || n_leaf > n_rows / 5) return kRowsDense;
-  return n_leaf >= kSparseManyRows ? kRowsSparseMany : kRowsSparse;
+  return n_leaf >= kSparseManyRows / 2 ? kRowsSparseMany : kRowsSparse;
 }
 int rows_of_batch(int64_t total_rows, int32_t n_leaves, int64_t n_rows) {
   return total_rows >= kSparseManyRows && total_rows / n_leaves * 12 <= n_rows ? kRowsSparseMany : kRowsSparse;

@@ -174,7 +174,7 @@ GBDT_HD int32_t plan_cell(const TilePlan& p, int32_t w, int32_t bin, int32_t slo
 // of 4,000,000 x 28 x 255, all its rows, in a call 217 and 225.  (One 16-byte tile has nothing to halve, but the kernel with two
 // workgroups a CU has more rows in flight than its lines bear too: a tenth of 10,500,000 x 16 x 255 39.7 us with one,
 // 48.5 with two, 2 % 24.1 and 29.1.)  Nor many sparse rows of one tile and a remainder: 32 leaves of 4,000,000 x 33 x 255, half
-// of its rows, 133 us whole, 177 in halves, a tenth of it in one list 36.9 and 42.7; but few, 32 leaves of a tenth of
+// of its rows, 133 us whole, 177 in halves, a tenth of them in one list 36.9 and 42.7; but few, 32 leaves of a tenth of
 // 1,000,000 x 33 x 255, 31.1 and 23.2.
 constexpr int kRowsDense = 0, kRowsSparse = 1, kRowsSparseMany = 2;  // how the rows of a build lie in the matrix
 GBDT_HD bool plan_halves(const TilePlan& p, bool wide, int rows) {
