@@ -888,7 +888,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     // 2,000,000 x 500 x 64 283 us with and 318 without, of 400,000 x 2,000 x 63 234 and 250; waiting for all of the next
     // epoch's bins instead 287 and 239.  32-byte tiles do not wait: a workgroup spends longer on an epoch there, in the
     // drain, and roots are the same either way (192.1 and 192.0 us for 1,000,000 x 500 x 255), but half and a quarter
-    // of the rows go from 119 / 76 to 125 / 80 us with the wait.)
+    // of the rows go from 119 / 76 to 125 / 80 us with the wait.  A remainder does beside the one tile whose lines it shares:
+    // it has half the cells to drain and runs ahead, two leaves of all of 4,000,000 x 33 x 255 108 us with the wait and 120
+    // without, four 108 and 121; 64 leaves of 48 features 168 and 164.)
     if (paced) __builtin_amdgcn_s_waitcnt(GPE == 8 ? 0x0f74 : 0x0f72);  // vmcnt(GPE / 2)
     __syncthreads();  // all atomics of the epoch have landed
 
@@ -1024,7 +1026,7 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
   const TileAt at = plan_tile_at(WM, n_main, wr, n_rows, line_tiles, t);
   const uint8_t* tile = packed + at.off;
   const uint32_t stride = (uint32_t)at.stride;
-  const bool paced = WM == 64 && at.shared;
+  const bool paced = WM == 64 && at.shared;  // (see the wait in build_tile)
   const DirectOut direct = {direct_hist, t, WM, n_main, wr, 16 * half, n_features, n_bins};
   constexpr size_t kMainBlock = (size_t)block_words<CAP, BS::kMainW, NIB, NT>();
   if (t < n_main) {
@@ -1040,7 +1042,8 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
     constexpr int W = decltype(width)::value;
     constexpr size_t kBlock = (size_t)block_words<CAP, W, NIB, NT>();
     build_tile<CAP, W, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, TileShape<CAP, W, NIB, NT>::VEC, idx, grad, hess, by_pos,
-                                                    stat_shift, paced, rest..., lds, rem_base + wg * kBlock, direct,
+                                                    stat_shift, paced || (!WIDE && WM == 32 && n_main == 1 && at.shared),
+                                                    rest..., lds, rem_base + wg * kBlock, direct,
                                                     rem_base + (wgs + wg) * kBlock);
   };
   if (wr == 16) {
