@@ -1201,7 +1201,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   m.chunks_rem = p.wr ? a.chunks : 0;
   m.halves = halves ? 1 : 0;
   m.counters = uses_counters ? counters : nullptr;
-  const int64_t tile_cells = (int64_t)n_bins * plan_slots(p, p.wm);
+  const int64_t tile_cells = merge_tile_cells(p, n_bins);
   const int parts = merge_parts(tile_cells, plan_n_tiles(p), a.chunks);
   const dim3 merge_grid((unsigned)((tile_cells + merge_wg_cells(parts) - 1) / merge_wg_cells(parts)), plan_n_tiles(p));
   auto merge = [&](auto kernel) { hipLaunchKernelGGL(kernel, merge_grid, dim3(merge_wg_threads(parts)), 0, s, m); };
@@ -1584,7 +1584,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       if (rc != GBDT_OK) return rc;
     }
     if (n_merge == 0) continue;
-    const int64_t tile_cells = (int64_t)n_bins * plan_slots(p, p.wm);
+    const int64_t tile_cells = merge_tile_cells(p, n_bins);
     int32_t most_chunks = 0;
     for (int i = 0; i < n_merge; ++i) {
       const int32_t c = (int32_t)batch_wgs(m.leaf[i]) * (wide ? 2 : 1);
