@@ -534,7 +534,7 @@ int gbdt_debug_half_blocks(int32_t n_features, int64_t n_rows, int32_t cols, int
  * is of, position_out[l] = the entry of row_idx it starts at.  Returns the launches.  Host only. */
 int gbdt_debug_gather_plan(const int64_t* leaf_offsets, int32_t n_leaves, int32_t* launch_out, int64_t* position_out);
 /* Blocks of page-locked host memory that the library keeps: out[0] for later calls, out[1] left by calls that failed with
- * work under way, until gbdt_reset.  Host only. */
+ * work under way, until gbdt_reset; out[2] = bytes of the largest block kept.  Host only. */
 int gbdt_debug_host_blocks(int64_t* out);
 /* The column plan gbdt_bins_fuse makes for features with the given numbers of levels (1..64
  * each): col_out[f] / stride_out[f] = the column of feature f and the weight of its bin in the

@@ -625,13 +625,13 @@ def gbdt_debug_gather_plan(leaf_offsets):
 
 
 def gbdt_debug_host_blocks():
-    """(kept for later calls, left by failed calls): the library's blocks of page-locked host memory."""
+    """(kept for later calls, left by failed calls, bytes of the largest kept): blocks of page-locked host memory."""
     lib = load()
-    out = (ctypes.c_int64 * 2)()
+    out = (ctypes.c_int64 * 3)()
     lib.gbdt_debug_host_blocks.restype = ctypes.c_int
     lib.gbdt_debug_host_blocks.argtypes = [ctypes.c_void_p]
     _check(lib.gbdt_debug_host_blocks(out), "gbdt_debug_host_blocks")
-    return int(out[0]), int(out[1])
+    return int(out[0]), int(out[1]), int(out[2])
 
 
 def gbdt_debug_cell_sums(grad_q, hess_q):

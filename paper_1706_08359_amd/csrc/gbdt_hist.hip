@@ -959,6 +959,10 @@ class HostRecords {
     if (!b_.host) return;
     std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
     if (!in_flight_ && g_rec_blocks.idle.size() >= kIdleRecordBlocks) {
+      // the largest are kept: a small one serves fewer calls, and allocating and freeing takes longer than most calls
+      auto least = std::min_element(g_rec_blocks.idle.begin(), g_rec_blocks.idle.end(),
+                                    [](const RecordBlock& x, const RecordBlock& y) { return x.n < y.n; });
+      if (least->n < b_.n) std::swap(*least, b_);
       (void)hipHostFree(b_.host);
       return;
     }
@@ -2442,6 +2446,8 @@ int gbdt_debug_host_blocks(int64_t* out) {
   std::lock_guard<std::mutex> lk(g_rec_blocks.mu);
   out[0] = (int64_t)g_rec_blocks.idle.size();
   out[1] = (int64_t)g_rec_blocks.lost.size();
+  out[2] = 0;
+  for (const RecordBlock& b : g_rec_blocks.idle) out[2] = std::max(out[2], (int64_t)(b.n * sizeof(gbdt_split_t)));
   return GBDT_OK;
 }
 
