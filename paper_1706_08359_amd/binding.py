@@ -540,7 +540,7 @@ def gbdt_debug_split_plan(n_features: int, n_bins: int, n_hists: int) -> dict:
     lib.gbdt_debug_split_plan.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p,
                                           ctypes.c_int32]
     _check(lib.gbdt_debug_split_plan(n_features, n_bins, n_hists, out, 4), "gbdt_debug_split_plan")
-    return dict(zip(("group", "passes", "workgroups", "lds_bytes"), (int(v) for v in out)))
+    return dict(zip(("group", "passes", "workgroups", "waves"), (int(v) for v in out)))
 
 
 def gbdt_debug_partition_plan(n_leaf_rows: int) -> dict:

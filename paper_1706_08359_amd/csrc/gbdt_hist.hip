@@ -2483,7 +2483,7 @@ int gbdt_debug_split_plan(int32_t n_features, int32_t n_bins, int32_t n_hists, i
   out[0] = g.group;
   out[1] = g.passes;
   out[2] = g.n_wg;
-  out[3] = (int64_t)kSplitMaxWaves * (sizeof(SplitCand) + sizeof(int32_t));
+  out[3] = g.waves;
   return GBDT_OK;
 }
 

@@ -509,9 +509,9 @@ split_gain_kernel(gbdt_bin_t* hist, int64_t hist_stride, int32_t n_features,
     // needs, and the reader needs no acquire because it reads the candidates with device-scope
     // atomic loads only.  A release / acquire pair in the language's sense would also write back
     // and invalidate every line of the L2, which costs tens of microseconds here -- several
-    // times the whole kernel.  tests/test_gpu_robustness.py runs 20 launches of 64 histograms whose workgroups hand
-    // off so, and every split test of more than one workgroup goes through it; on a part where the assumption
-    // did not hold those tests would show stale candidates.
+    // times the whole kernel.  tests/test_gpu_robustness.py runs 20 launches of 64 histograms of 16 workgroups
+    // that hand off so, and launches of up to 256 a histogram; every split test of more than one workgroup goes through it.  On a
+    // part where the assumption did not hold those tests would show stale candidates.
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0); expcnt, lgkmcnt untouched
     unsigned int* ticket = split_ticket(blockIdx.y);
     const unsigned int old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

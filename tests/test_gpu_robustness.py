@@ -119,10 +119,11 @@ def test_growth_of_the_library_scratch_is_refused_under_capture_and_noalloc_is_c
 
 def test_split_search_over_many_workgroups_is_stable():
     """The arg-max over the workgroups' candidates runs in the workgroup that draws the last
-    ticket; candidates cross between workgroups (and XCDs) through device-scope atomics.  4,000
-    features = 256 workgroups per histogram, 64 histograms per launch, the winner planted in a
+    ticket; candidates cross between workgroups (and XCDs) through device-scope atomics.  64
+    histograms per launch, 4,000 features = 16 workgroups each, the winner planted in a
     different feature of every histogram; repeated launches must all find it."""
     F, nb, H = 4000, 16, 64
+    assert B.gbdt_debug_split_plan(F, nb, H)["workgroups"] == 16
     rng = np.random.default_rng(14)
     hists = np.zeros((H, F, nb, 3), np.float32)
     hists[..., 1] = 1.0                               # hessian 1 per bin
@@ -145,3 +146,30 @@ def test_split_search_over_many_workgroups_is_stable():
     # and against the oracle's scan of the same numbers, one histogram
     o = orc.best_split(orc.from_f32_hist(grad[3], hists[3, ..., 1], cnt[3]), 1.0, 1e-3)
     assert (o["feature"], o["bin"]) == want[3]
+
+
+@pytest.mark.parametrize("n_features,n_hists,workgroups", [(2000, 2, 125), (4096, 1, 256), (1100, 3, 69)])
+def test_split_search_over_more_workgroups_than_lanes(n_features, n_hists, workgroups):
+    """More than 64 workgroups a histogram: a lane of the last one compares several candidates.  The best threshold lies in two
+    features, 64 workgroups (one turn of the lanes) or one workgroup apart: the smaller one wins, in every one of repeated launches."""
+    nb = 255
+    plan = B.gbdt_debug_split_plan(n_features, nb, n_hists)
+    assert plan["workgroups"] == workgroups and plan["group"] == 1
+    rng = np.random.default_rng(n_features)
+    hists = np.zeros((n_hists, n_features, nb), dtype=B.BIN_DTYPE)
+    hists["hess"], hists["count"] = 1.0, 10
+    noise = rng.normal(0, 0.01, size=hists.shape).astype(np.float32)
+    for apart in (64, 1):
+        for turn in range(8):
+            hists["grad"] = noise
+            want = []
+            for h in range(n_hists):
+                f = int(rng.integers(0, n_features - apart * plan["passes"]))
+                g, t = f + apart * plan["passes"], int(rng.integers(0, nb - 1))
+                for at in (f, g):
+                    hists["grad"][h, at, : t + 1], hists["grad"][h, at, t + 1:] = 50.0, -50.0
+                want.append((f, t))
+            d = torch.from_numpy(hists.view(np.float32).reshape(hists.shape + (3,)).copy()).cuda()
+            for rep in range(5):
+                got = [(r["feature"], r["bin"]) for r in B.splits_to_dicts(B.gbdt_best_split_batch(d, 1.0, 1e-3))]
+                assert got == want, (apart, turn, rep, got, want)

@@ -275,24 +275,22 @@ def test_fuse_reads_small_matrices_once():
 
 
 @pytest.mark.parametrize("n_bins", [2, 16, 63, 64, 100, 255, 256])
-def test_split_search_plan_covers_every_feature_within_the_lds_budget(n_bins):
+def test_split_search_plan_covers_every_feature(n_bins):
     """The work split of the split search follows the number of histograms of the launch; whatever
-    it picks, the groups of all workgroups cover the features, a group fits the kernel's local
-    memory budget, and a launch never has more candidates per histogram than a lone histogram
-    (the scratch of gbdt_workspace_bytes is sized by that)."""
+    it picks, the steps of all workgroups cover the features, a workgroup has between 1 and 16 wavefronts (the
+    kernel's local memory has a place for each) and a step for every one of them, and a launch never has more
+    candidates per histogram than a lone histogram (the scratch of gbdt_workspace_bytes is sized by that)."""
     for n_features in (1, 2, 7, 28, 137, 255, 256, 257, 700, 2000, 4000, 20000):
         lone = B.gbdt_debug_split_plan(n_features, n_bins, 1)
         for n_hists in (1, 2, 3, 8, 31, 64, 256, 1024, 32768):
             p = B.gbdt_debug_split_plan(n_features, n_bins, n_hists)
             assert p["group"] >= 1 and p["passes"] >= 1 and p["workgroups"] >= 1
-            assert p["lds_bytes"] <= 48 * 1024
+            assert p["group"] == 64 // max(4, 2 ** int(np.ceil(np.log2((n_bins + 3) // 4))))   # (4 bins a lane)
+            assert 1 <= p["waves"] <= 16 and p["waves"] <= p["passes"]
             assert p["group"] * p["passes"] * p["workgroups"] >= n_features
             # no workgroup without a feature
             assert p["group"] * p["passes"] * (p["workgroups"] - 1) < n_features
             assert p["workgroups"] <= lone["workgroups"]
-            # the prefix sums run on one lane per (feature, statistic) of ONE wavefront, which then reads
-            # across its lanes without a workgroup barrier
-            assert 3 * p["group"] <= 64
 
 
 LINE_SHAPES = [(1, 64), (40, 255), (32, 255), (64, 256), (96, 200), (100, 255), (137, 255), (64, 63), (70, 64), (100, 64),
