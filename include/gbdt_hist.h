@@ -127,7 +127,9 @@ int gbdt_bins_pack(const uint8_t* bins_rowmajor, int64_t n_rows, int32_t n_featu
  * at least 8192 rows and a third of the matrix's rows from the fused copy (sparser leaves are
  * bound by HBM traffic, where the plain tiles' narrower rows win; also not with wide
  * accumulation, whose stored sums are exact sums rounded once).  Results and error bound are those of the plain path.  Unlike the
- * other calls it WAITS for the stream (it reads the maxima on the host).
+ * other calls it WAITS for the stream (it reads the maxima on the host, through a few KB of
+ * page-locked memory that it shares with the tree growers: at most four blocks, the largest ones
+ * asked for, are kept until gbdt_reset; without any it copies).
  *   bins_rowmajor   DEVICE, the matrix gbdt_bins_pack packed
  *   packed          DEVICE address gbdt_bins_pack wrote to (used as a key only; a buffer
  *                   copied elsewhere is simply built from its plain tiles)
@@ -394,13 +396,16 @@ typedef struct {
  *                    (two row lists, about 3 x max_leaves histograms, the split records, and for large matrices of few
  *                    features 8 bytes per row for gradient and hessian side by side; a buffer without
  *                    room for those last still serves, slower); the calls inside also use the
- *                    library's scratch workspace
+ *                    library's scratch workspace: what gbdt_hist_build_batch needs for the nodes of
+ *                    a round and, to gather gradients and hessians first, 8 bytes per row of the
+ *                    MATRIX (a node's rows keep their place), without which they are read by row id
  *   nodes_out        HOST gbdt_tree_node_t [2 * max_leaves - 1]
  *   n_nodes_out      HOST, receives the number of nodes written (always odd)
  *   row_order_out    DEVICE int32 [n_rows] or NULL: all row ids, grouped by leaf, ascending
  *                    inside each node's segment (see row_begin)
  * Unlike the other calls this one WAITS for `stream` (once per round, to read the new split
- * records) and allocates a few KB of page-locked host memory on first use.  The histograms
+ * records) and borrows a block of page-locked host memory, 36 bytes a record, allocated on first
+ * use and kept as gbdt_bins_fuse says (GBDT_ENOMEM if there is none).  The histograms
  * of a round are built by gbdt_hist_build_batch, whose split of rows among workgroups is
  * fixed; the root's is built by gbdt_hist_build, so that with gbdt_set_deterministic the same call
  * gives the same tree, bit for bit, every time.
