@@ -259,7 +259,7 @@ int gbdt_set_deterministic(int enable);
  * affects later gbdt_hist_build / gbdt_hist_build_batch calls and the tree growers,
  * which build through them) a workgroup sums gradients and hessians in 54-bit fixed
  * point and fp64 instead of 27-bit fixed point and fp32: a stored sum is the exact sum
- * rounded to fp32, up to 5e-13 of the leaf's sum of magnitudes.  1.6-2.1x the build
+ * rounded to fp32, up to 5e-13 of the leaf's sum of magnitudes.  1.5-1.9x the build
  * time; twice the LDS and twice the scratch for partial results, so query
  * gbdt_workspace_bytes / gbdt_hist_build_batch_workspace_bytes AFTER setting the mode
  * when the caller owns the scratch.  Together with gbdt_set_deterministic the sums are

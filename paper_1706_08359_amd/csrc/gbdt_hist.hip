@@ -2191,7 +2191,7 @@ int gbdt_grow_tree_depthwise(const void* bin_matrix, int64_t n_rows, int32_t n_f
   SplitSiblings level_sib;  // the level's siblings, where the split search forms them
   level_sib.n = 0;
   for (int depth = 0;; ++depth) {
-    // ---- best split of every open node of the level, one launch, one read-back
+    // ---- best split of every open node of the level, one launch, one wait
     std::vector<int> open;  // indices into frontier, in histogram slot order
     for (size_t i = 0; i < frontier.size(); ++i)
       if (frontier[i].slot >= 0) open.push_back((int)i);
