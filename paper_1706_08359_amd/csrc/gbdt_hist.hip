@@ -503,13 +503,18 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
 // each on average (1,000,000 x 33 x 255: 32 leaves of half of the rows 45.9 us whole, 54.7 in halves, 64 of all 76 and 79;
 // 300,000 x 33 x 255: 64 of all 41 and 30; 4,000,000 x 33 x 255: four leaves of half of the rows 119 and 95), half as many in one
 // list (2,000,000 x 33 x 255, a tenth 27.6 and 29.7, 1,000,000, 19 % 26.4 and 25.5).
+// Large: many sparse rows of a matrix of kLargeMatrixRows on (64 features, 64 leaves of all rows: 4,000,000 252 us whole, 243 in
+// halves, 10,000,000 580 and 639; 96 features, a tenth in one list: 7,000,000 74.2 and 76.7, 4,000,000 50.7 and 47.1).
 constexpr int64_t kSparseManyRows = 384 * 1024;
+constexpr int64_t kLargeMatrixRows = 1 << 23;
 int rows_of_leaf(bool indexed, int64_t n_leaf, int64_t n_rows) {
   if (!indexed || n_leaf > n_rows / 5) return kRowsDense;
-  return n_leaf >= kSparseManyRows / 2 ? kRowsSparseMany : kRowsSparse;
+  if (n_leaf < kSparseManyRows / 2) return kRowsSparse;
+  return n_rows >= kLargeMatrixRows ? kRowsLargeList : kRowsSparseMany;
 }
 int rows_of_batch(int64_t total_rows, int32_t n_leaves, int64_t n_rows) {
-  return total_rows >= kSparseManyRows && total_rows / n_leaves * 12 <= n_rows ? kRowsSparseMany : kRowsSparse;
+  if (total_rows < kSparseManyRows || total_rows / n_leaves * 12 > n_rows) return kRowsSparse;
+  return n_rows >= kLargeMatrixRows ? kRowsLargeBatch : kRowsSparseMany;
 }
 
 // Kernel variants: bin capacity -> (main tile width, 4-bit, waves per SIMD the

@@ -176,10 +176,18 @@ GBDT_HD int32_t plan_cell(const TilePlan& p, int32_t w, int32_t bin, int32_t slo
 // 48.5 with two, 2 % 24.1 and 29.1.)  Nor many sparse rows of one tile and a remainder: 32 leaves of 4,000,000 x 33 x 255, half
 // of its rows, 133 us whole, 177 in halves, a tenth of them in one list 36.9 and 42.7; but few, 32 leaves of a tenth of
 // 1,000,000 x 33 x 255, 31.1 and 23.2.
-constexpr int kRowsDense = 0, kRowsSparse = 1, kRowsSparseMany = 2;  // how the rows of a build lie in the matrix
+// A matrix of two or three tiles that is too big for the two halves' lines to meet in the caches (large: see rows_of_leaf): many
+// sparse rows of one list stay whole, 5 % of 20,000,000 x 64 x 255 75.9 us, 94.4 in halves, x 70 97 and 124, a tenth of 10,000,000 x 96
+// 92.7 and 112 (19 % of 20,000,000 x 70 278 and 264); of a batch with two full tiles only, 32 leaves of half of 20,000,000 x 64 592 and
+// 741, x 70 1111 and 888 (64 leaves of all 2184 and 2331), 64 of all of 10,000,000 x 96 1108 and 1039.  With four tiles halves win.
+// how the rows of a build lie in the matrix:
+constexpr int kRowsDense = 0, kRowsSparse = 1, kRowsSparseMany = 2, kRowsLargeBatch = 3, kRowsLargeList = 4;
 GBDT_HD bool plan_halves(const TilePlan& p, bool wide, int rows) {
   if (!wide || p.cap != 256) return false;
-  return p.n_main > 1 || rows < (p.n_main == 1 && p.wr ? kRowsSparseMany : kRowsSparse);
+  const int n_tiles = p.n_main + (p.wr ? 1 : 0);
+  if (n_tiles > 3) return true;
+  if (n_tiles == 1) return rows < kRowsSparse;
+  return rows < (n_tiles == 3 ? kRowsLargeList : (p.wr ? kRowsSparseMany : kRowsLargeBatch));
 }
 
 struct FeatureSlot {
