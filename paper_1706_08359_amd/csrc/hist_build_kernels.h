@@ -848,70 +848,35 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   __syncthreads();  // also orders the LDS clearing before the first atomics
   scales_from(request_scales(0, lane), kg, kh);
 
-  uint32_t parity = 0;
-  while (p0.row < end) {  // uniform over the workgroup
-    const bool takes = !fixed_stride && p0.left == 3;
-    uint32_t taken = 0;
-    if (takes && tid == 0)
-      taken = counter_base + __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // ---- requests for later epochs
-    const uint32_t row_nn = load_row_id(p2.row);
-    const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
-    const float g_nxt = load_stat(grad, stat_nxt);
-    const float h_nxt = load_stat(hess, stat_nxt);
-    // ---- this lane's row -> 64-bit addend (cell_format.h)
-    //      (wide: 1 + gq * 2^10 into the gradient cell, hq * 2^10 into the hessian cell)
-    uint32_t lo, hi, lo2 = 0u, hi2 = 0u;
+  // The row that a lane owns -> what it adds to its cells (cell_format.h; wide: 1 + gq * 2^10 to the gradient cell, hq * 2^10 to
+  // the hessian cell); ok: there is such a row.
+  struct Addend {
+    uint32_t lo, hi, lo2, hi2;
+  };
+  auto quantise = [&](bool ok) {
+    Addend a = {0u, 0u, 0u, 0u};
     if constexpr (WIDE) {
       const long long gq = rint_to_i64((double)g_cur * pow2d(kg + kWideShift));
       const long long hq = rint_to_i64((double)h_cur * pow2d(kh + kWideShift));
       const unsigned long long ag = ((unsigned long long)gq << kCountBits) + 1ull;
       const unsigned long long ah = (unsigned long long)hq << kCountBits;
-      const bool ok = own_valid(p0.row);
-      lo = ok ? (uint32_t)ag : 0u;
-      hi = ok ? (uint32_t)(ag >> 32) : 0u;
-      lo2 = ok ? (uint32_t)ah : 0u;
-      hi2 = ok ? (uint32_t)(ah >> 32) : 0u;
+      a.lo = ok ? (uint32_t)ag : 0u;
+      a.hi = ok ? (uint32_t)(ag >> 32) : 0u;
+      a.lo2 = ok ? (uint32_t)ah : 0u;
+      a.hi2 = ok ? (uint32_t)(ah >> 32) : 0u;
     } else {
       const CellWords add = cell_addend(__float2int_rn(g_cur * pow2f(kg)), __float2int_rn(h_cur * pow2f(kh)));
-      lo = add.lo;
-      hi = add.hi;
-      const bool ok = own_valid(p0.row);
-      lo = ok ? lo : 0u;
-      hi = ok ? hi : 0u;
+      a.lo = ok ? add.lo : 0u;
+      a.hi = ok ? add.hi : 0u;
     }
-    // The atomics are what the kernel is bound by; the drain of a co-resident workgroup is
-    // mostly VALU work.  Raised priority lets the waves that feed the LDS pipe issue first,
-    // and the other workgroup's drain fills the gaps (8-12 % on the 256-bin variants).
-    __builtin_amdgcn_s_setprio(1);
-    add_and_reload(w, lo, hi, lo2, hi2, row_nxt, p1.row);
-    __builtin_amdgcn_s_setprio(0);
-
-    parity ^= 1u;
-    {
-      const bool ok = own_valid(p1.row);
-      reduce_abs(ok ? fabsf(g_nxt) : 0.0f, ok ? fabsf(h_nxt) : 0.0f, (int)parity);
-    }
-    if (takes && tid == 0) unit_box[0] = taken;
-    // Workgroups that share cache lines (tile_plan.h) drift apart if nothing holds them together, and a
-    // line is then fetched twice.  Waiting here for half of the next epoch's bins lets a workgroup that runs
-    // ahead, whose requests miss, be caught up by the one whose requests hit.  (First pass over the rows of
-    // 2,000,000 x 500 x 64 283 us with and 318 without, of 400,000 x 2,000 x 63 234 and 250; waiting for all of the next
-    // epoch's bins instead 287 and 239.  32-byte tiles do not wait: a workgroup spends longer on an epoch there, in the
-    // drain, and roots are the same either way (192.1 and 192.0 us for 1,000,000 x 500 x 255), but half and a quarter
-    // of the rows go from 119 / 76 to 125 / 80 us with the wait.  A remainder does beside the one tile whose lines it shares:
-    // it has half the cells to drain and runs ahead, two leaves of all of 4,000,000 x 33 x 255 108 us with the wait and 120
-    // without, four 108 and 121; 64 leaves of 48 features 168 and 164.)
-    if (paced) __builtin_amdgcn_s_waitcnt(GPE == 8 ? 0x0f74 : 0x0f72);  // vmcnt(GPE / 2)
-    __syncthreads();  // all atomics of the epoch have landed
-
-    // ---- drain: integer sums -> registers, clear the cells for the next epoch
+    return a;
+  };
+  // The integer sums of an epoch -> registers, and the cells cleared for the next one.  All requests leave before the first
+  // answer is waited for, those that `first` makes first of all: answers come back in order, so the cells are then decoded one by
+  // one as they arrive.  (The scheduling barrier keeps the arithmetic of `second` from being waited for between the requests.)
+  auto drain = [&](auto&& first, auto&& second) {
     const float inv_g = pow2f(-kg) * (1.0f / (1 << kSumPad)), inv_h = pow2f(-kh) * (1.0f / (1 << kSumPad));
     const double inv_gw = pow2d(-kg - kWideShift), inv_hw = pow2d(-kh - kWideShift);
-    // All requests leave before the first answer is waited for, the next epoch's scales and the taken
-    // unit first: answers come back in order, so the cells are then decoded one by one as they
-    // arrive.  (The scheduling barrier keeps the scales' arithmetic, which the next phase needs, from
-    // being waited for between the requests.)
     if (WIDE && (kg <= kWidePastExp || kh <= kWidePastExp)) {
       // kWidePastExp: rare, so here, cell by cell (the registers are taken), and what follows then finds empty cells.  (As the
       // other branch of what follows it costs all wide kernels 10 to 40 registers.)
@@ -933,8 +898,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(drain_lane));
     }
     const int drain_cell0 = owned_cell(drain_lane);
-    const float next_sums = request_scales((int)parity, drain_lane);
-    const uint32_t box = unit_box[0];
+    first(drain_lane);
     unsigned long long cell[PP], cell_h[WIDE ? PP : 1];
 #pragma unroll
     for (int m = 0; m < PP; ++m) {
@@ -942,10 +906,62 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       if constexpr (WIDE) cell_h[m] = request_cell(CELLS + drain_cell0 + m * kOwnedStep);
     }
     __builtin_amdgcn_sched_barrier(0);
-    scales_from(next_sums, kg, kh);
-    if (takes) next_unit = __builtin_amdgcn_readfirstlane(box);
+    second();
 #pragma unroll
     for (int m = 0; m < PP; ++m) drain_cell(m, cell[m], cell_h[WIDE ? m : 0], inv_g, inv_h, inv_gw, inv_hw);
+  };
+
+  uint32_t parity = 0;
+  while (p0.row + (uint32_t)kEpochRows <= end) {  // uniform over the workgroup
+    const bool takes = !fixed_stride && p0.left == 3;
+    uint32_t taken = 0;
+    if (takes && tid == 0)
+      taken = counter_base + __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // ---- requests for later epochs
+    const uint32_t row_nn = load_row_id(p2.row);
+    const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
+    const float g_nxt = load_stat(grad, stat_nxt);
+    const float h_nxt = load_stat(hess, stat_nxt);
+    const Addend add = quantise(true);
+    // The atomics are what the kernel is bound by; the drain of a co-resident workgroup is
+    // mostly VALU work.  Raised priority lets the waves that feed the LDS pipe issue first,
+    // and the other workgroup's drain fills the gaps (8-12 % on the 256-bin variants).
+    __builtin_amdgcn_s_setprio(1);
+    add_and_reload(w, add.lo, add.hi, add.lo2, add.hi2, row_nxt, p1.row);
+    __builtin_amdgcn_s_setprio(0);
+
+    parity ^= 1u;
+    {
+      const bool ok = own_valid(p1.row);
+      reduce_abs(ok ? fabsf(g_nxt) : 0.0f, ok ? fabsf(h_nxt) : 0.0f, (int)parity);
+    }
+    if (takes && tid == 0) unit_box[0] = taken;
+    // Workgroups that share cache lines (tile_plan.h) drift apart if nothing holds them together, and a
+    // line is then fetched twice.  Waiting here for half of the next epoch's bins lets a workgroup that runs
+    // ahead, whose requests miss, be caught up by the one whose requests hit.  (First pass over the rows of
+    // 2,000,000 x 500 x 64 283 us with and 318 without, of 400,000 x 2,000 x 63 234 and 250; waiting for all of the next
+    // epoch's bins instead 287 and 239.  32-byte tiles do not wait: a workgroup spends longer on an epoch there, in the
+    // drain, and roots are the same either way (192.1 and 192.0 us for 1,000,000 x 500 x 255), but half and a quarter
+    // of the rows go from 119 / 76 to 125 / 80 us with the wait.  A remainder does beside the one tile whose lines it shares:
+    // it has half the cells to drain and runs ahead, two leaves of all of 4,000,000 x 33 x 255 108 us with the wait and 120
+    // without, four 108 and 121; 64 leaves of 48 features 168 and 164.)
+    if (paced) __builtin_amdgcn_s_waitcnt(GPE == 8 ? 0x0f74 : 0x0f72);  // vmcnt(GPE / 2)
+    __syncthreads();  // all atomics of the epoch have landed
+
+    float next_sums = 0.0f;
+    uint32_t box = 0u;
+    int kg_nxt = 0, kh_nxt = 0;
+    drain(
+        [&](int drain_lane) {
+          next_sums = request_scales((int)parity, drain_lane);
+          box = unit_box[0];
+        },
+        [&] {
+          scales_from(next_sums, kg_nxt, kh_nxt);
+          if (takes) next_unit = __builtin_amdgcn_readfirstlane(box);
+        });
+    kg = kg_nxt;
+    kh = kh_nxt;
     p0 = p1;
     p1 = p2;
     p2 = after(p2);
@@ -954,6 +970,30 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     g_cur = g_nxt;
     h_cur = h_nxt;
     __syncthreads();  // cells are clear, `red` and the unit box are read, before reuse
+  }
+  // The leaf's last epoch, where rows are missing: nothing follows it, and wavefronts without a row add nothing.  (As one more
+  // turn of the loop, which adds zeros and requests rows that nobody takes: 128 leaves of half of 400,000 x 2,000 x 63 174 us, 162
+  // so; 64 leaves of 1,500,000 x 500 x 255 371 and 353; 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions
+  // inside the loop makes every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
+  if (p0.row < end) {
+    const Addend add = quantise(own_valid(p0.row));
+    if (p0.row + (uint32_t)wave * 64u < end) {
+      auto step = [&](auto gi_tag) {
+        add_group(w[decltype(gi_tag)::value], add.lo, add.hi, add.lo2, add.hi2, gi_tag);
+      };
+      step(std::integral_constant<int, 0>{});
+      step(std::integral_constant<int, 1>{});
+      step(std::integral_constant<int, 2>{});
+      step(std::integral_constant<int, 3>{});
+      if constexpr (GPE == 8) {
+        step(std::integral_constant<int, 4>{});
+        step(std::integral_constant<int, 5>{});
+        step(std::integral_constant<int, 6>{});
+        step(std::integral_constant<int, 7>{});
+      }
+    }
+    __syncthreads();  // all atomics have landed
+    drain([](int) {}, [] {});
   }
 
   if (direct.hist) {
