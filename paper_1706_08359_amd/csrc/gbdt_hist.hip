@@ -532,7 +532,8 @@ template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED
 int query_occupancy() {
   int n = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &n, reinterpret_cast<const void*>(hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, INDEXED, WIDE, HALVES>), NT, 0);
+      &n, reinterpret_cast<const void*>(hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, INDEXED, WIDE, HALVES, WIDE && CAP == 256>),
+      NT, 0);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return 0;
@@ -667,16 +668,24 @@ struct BuildTimer {
 };
 
 template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false, bool LISTS_ONLY = false>
-int launch_build(const BuildArgs& a, int blocks, hipStream_t s, bool timed = true) {
+int launch_build(const BuildArgs& a, int blocks, hipStream_t s, bool timed, bool is_short) {
   BuildTimer timer;
   int rc = timed ? timer.begin(s) : GBDT_OK;
   if (rc != GBDT_OK) return rc;
-  if (a.idx) {
-    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, true, WIDE, HALVES>), dim3(blocks), dim3(NT), 0, s,
-                       a);
-  } else if constexpr (!LISTS_ONLY) {
-    hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, false, WIDE, HALVES>), dim3(blocks), dim3(NT), 0, s,
-                       a);
+  auto launch = [&](auto short_tag) {
+    constexpr bool kShort = decltype(short_tag)::value;
+    if (a.idx) {
+      hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, true, WIDE, HALVES, kShort>), dim3(blocks), dim3(NT), 0,
+                         s, a);
+    } else if constexpr (!LISTS_ONLY) {
+      hipLaunchKernelGGL((hist_build_kernel<CAP, WM, NIB, NT, WPE, ACC, false, WIDE, HALVES, kShort>), dim3(blocks), dim3(NT), 0,
+                         s, a);
+    }
+  };
+  if (is_short) {
+    launch(std::true_type{});
+  } else if constexpr (!(WIDE && CAP == 256)) {
+    launch(std::false_type{});
   }
   HIP_TRY(hipGetLastError());
   return timer.end(s);
@@ -1176,23 +1185,24 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   // From here until the reduction pass has been enqueued the counters are in use.
   if (uses_counters && !capturing) set_counters_zero(counters, false);
 
+  const bool is_short = g.one_unit_each || (wide && p.cap == 256);  // (which have one kernel for both)
   const bool timed = fixed_base == nullptr;  // the profiling events are created on the fly: an allocation
   if (wide) {
     if (p.cap == 16) {
-      rc = launch_build<GBDT_VARIANT_16W, true>(a, blocks, s, timed);
+      rc = launch_build<GBDT_VARIANT_16W, true>(a, blocks, s, timed, is_short);
     } else if (p.cap == 64) {
-      rc = launch_build<GBDT_VARIANT_64W, true>(a, blocks, s, timed);
+      rc = launch_build<GBDT_VARIANT_64W, true>(a, blocks, s, timed, is_short);
     } else if (halves) {
-      rc = launch_build<GBDT_VARIANT_256W_HALVES, true, true>(a, blocks, s, timed);
+      rc = launch_build<GBDT_VARIANT_256W_HALVES, true, true>(a, blocks, s, timed, is_short);
     } else {
-      rc = launch_build<GBDT_VARIANT_256W, true, false, true>(a, blocks, s, timed);
+      rc = launch_build<GBDT_VARIANT_256W, true, false, true>(a, blocks, s, timed, is_short);
     }
   } else if (p.cap == 16) {
-    rc = launch_build<GBDT_VARIANT_16>(a, blocks, s, timed);
+    rc = launch_build<GBDT_VARIANT_16>(a, blocks, s, timed, is_short);
   } else if (p.cap == 64) {
-    rc = launch_build<GBDT_VARIANT_64>(a, blocks, s, timed);
+    rc = launch_build<GBDT_VARIANT_64>(a, blocks, s, timed, is_short);
   } else {
-    rc = launch_build<GBDT_VARIANT_256>(a, blocks, s, timed);
+    rc = launch_build<GBDT_VARIANT_256>(a, blocks, s, timed, is_short);
   }
   if (rc != GBDT_OK) return rc;
   if (a.direct_out) {  // one workgroup per tile: the histogram is written

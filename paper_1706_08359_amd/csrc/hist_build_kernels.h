@@ -448,12 +448,9 @@ struct TileShape {
   static constexpr int CELLS = PAGES * CAP * PITCH;
   static constexpr int NW = NT / 64;
   static constexpr int PP = CELLS / NT;             // cells drained by one thread
-  static constexpr int RUNS = CELLS / (16 * CAP);   // groups of 16 slots (those of a page without features among them)
-  static constexpr int WAVE_BINS = CAP * RUNS / NW; // bins of a group of slots that one wavefront drains
   static constexpr int GPE = 64 / RPW;              // row groups per wavefront per epoch
   static_assert(NT == kEpochRows, "an epoch gives every lane one row of its own");
   static_assert(CELLS % NT == 0, "every thread drains the same number of cells");
-  static_assert(NW % RUNS == 0 && WAVE_BINS == 4 * PP, "a thread drains cells of one slot, four bins apart");
   static_assert(LPR == 4 || LPR == 8, "a row is shared by a quad or by two quads");
 };
 
@@ -513,7 +510,7 @@ struct TileShape {
 //
 // chunk_stride: bytes from a lane-chunk of a row to the next: VEC, or more where the workgroup takes a part of every
 // chunk only (plan_halves).
-template <int CAP, int W, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE = false>
+template <int CAP, int W, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE, bool SHORT>
 __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uint32_t row_stride, uint32_t chunk_stride,
                                            const int32_t* __restrict__ idx,
                                            const float* __restrict__ grad,
@@ -561,14 +558,22 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
 
 #pragma unroll
   for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = 0ull;
-  // The cells a thread drains: PP of one slot, every fourth bin.  A wavefront takes 16 slots and 4 bins at a time: 16 cells
-  // in a row cover all banks once, and a finished histogram leaves as 48 bytes of a feature side by side.  (32 slots and 2 bins
-  // at a time touch twice as many lines: 128 leaves of half of 400,000 x 2,000 x 63 179 us, 174 so, of 1,000,000 x 100 x
-  // 255 47.0 and 44.8.)
-  const int slot_run = wave % S::RUNS, wave_bin = wave / S::RUNS * S::WAVE_BINS;
-  const int run_cell = (slot_run * 16 / S::PITCH) * (CAP * S::PITCH) + slot_run * 16 % S::PITCH + wave_bin * S::PITCH;  // scalar
-  auto owned_cell = [&](int l) { return run_cell + (l >> 4) * S::PITCH + (l & 15); };  // of lane l, the first one
-  constexpr int kOwnedStep = 4 * S::PITCH;                                             // ... to the next
+  // The cells a thread drains: PP of one slot.  A wavefront takes a run of 32 slots and 2 bins at a time, 512 bytes of cells
+  // one after the other, and the wavefronts take turns in the bins.  With SHORT it takes 16 slots and 4 bins (16 cells in a row still
+  // cover all banks once) of bins of its own: a finished histogram leaves as 48 bytes of a feature side by side and not 24,
+  // half as many lines a store, and the words of a partial block one after the other.  128 leaves of half of 400,000 x 2,000 x 63
+  // 179 us with turns of 32 slots, 174 so; of 1,000,000 x 100 x 255 47.0 and 44.8; root of 100,000 x 28 x 255, an epoch a
+  // workgroup, 22.3 with turns of 16, 18.7 so.  Long leaves are faster with turns: 1,500,000 x 500 x 255 254 us, 259 with
+  // bins of a wavefront's own.
+  constexpr int RUN = SHORT || S::PITCH == 16 ? 16 : 32, BINS = 64 / RUN;
+  constexpr int RUNS = CELLS / (RUN * CAP);      // (those of a page without features among them)
+  constexpr int WAVES = NW / RUNS;               // wavefronts of a run
+  static_assert(NW % RUNS == 0 && CAP == BINS * WAVES * PP, "a thread drains cells of one slot");
+  constexpr int kStepBins = SHORT ? BINS : BINS * WAVES;  // from a thread's bin to its next
+  const int first_slot = wave % RUNS * RUN, first_bin = wave / RUNS * (SHORT ? BINS * PP : BINS);
+  const int run_cell = first_slot / S::PITCH * (CAP * S::PITCH) + first_slot % S::PITCH + first_bin * S::PITCH;  // scalar
+  auto owned_cell = [&](int l) { return run_cell + l / RUN * S::PITCH + l % RUN; };  // of lane l, the first one
+  constexpr int kOwnedStep = kStepBins * S::PITCH;                                   // ... to the next
   ACC acc_g[PP], acc_h[PP];
   uint32_t acc_c[PP];
 #pragma unroll
@@ -859,7 +864,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       const long long gq = rint_to_i64((double)g_cur * pow2d(kg + kWideShift));
       const long long hq = rint_to_i64((double)h_cur * pow2d(kh + kWideShift));
       const unsigned long long ag = ((unsigned long long)gq << kCountBits) + 1ull;
-      const unsigned long long ah = (unsigned long long)hq << kCountBits;
+      const unsigned long long ah = ((unsigned long long)hq << kCountBits);
       a.lo = ok ? (uint32_t)ag : 0u;
       a.hi = ok ? (uint32_t)(ag >> 32) : 0u;
       a.lo2 = ok ? (uint32_t)ah : 0u;
@@ -912,17 +917,23 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   };
 
   uint32_t parity = 0;
-  while (p0.row + (uint32_t)kEpochRows <= end) {  // uniform over the workgroup
+  uint32_t row_nn = 0u;
+  float g_nxt = 0.0f, h_nxt = 0.0f;
+  // Whether the leaf's last epoch, where rows may be missing, has code of its own (below).  Long leaves, to which it is nothing, are
+  // a little faster with one loop: 2,270,000 x 137 x 255 124.0 us, 125.2 with two; 1,500,000 x 330 x 64 with wide sums 215 and 219.
+  constexpr bool kLastApart = SHORT;
+  // An epoch of 512 rows: requests for later ones, its additions, and the sums of the next.  Returns whether a unit was taken.
+  auto add_epoch = [&] {
     const bool takes = !fixed_stride && p0.left == 3;
     uint32_t taken = 0;
     if (takes && tid == 0)
       taken = counter_base + __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // ---- requests for later epochs
-    const uint32_t row_nn = load_row_id(p2.row);
+    row_nn = load_row_id(p2.row);
     const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
-    const float g_nxt = load_stat(grad, stat_nxt);
-    const float h_nxt = load_stat(hess, stat_nxt);
-    const Addend add = quantise(true);
+    g_nxt = load_stat(grad, stat_nxt);
+    h_nxt = load_stat(hess, stat_nxt);
+    const Addend add = quantise(kLastApart || own_valid(p0.row));
     // The atomics are what the kernel is bound by; the drain of a co-resident workgroup is
     // mostly VALU work.  Raised priority lets the waves that feed the LDS pipe issue first,
     // and the other workgroup's drain fills the gaps (8-12 % on the 256-bin variants).
@@ -947,7 +958,19 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     // without, four 108 and 121; 64 leaves of 48 features 168 and 164.)
     if (paced) __builtin_amdgcn_s_waitcnt(GPE == 8 ? 0x0f74 : 0x0f72);  // vmcnt(GPE / 2)
     __syncthreads();  // all atomics of the epoch have landed
-
+    return takes;
+  };
+  auto to_next_epoch = [&] {
+    p0 = p1;
+    p1 = p2;
+    p2 = after(p2);
+    row_cur = row_nxt;
+    row_nxt = row_nn;
+    g_cur = g_nxt;
+    h_cur = h_nxt;
+  };
+  while (p0.row + (kLastApart ? (uint32_t)kEpochRows - 1u : 0u) < end) {  // uniform over the workgroup
+    const bool takes = add_epoch();
     float next_sums = 0.0f;
     uint32_t box = 0u;
     int kg_nxt = 0, kh_nxt = 0;
@@ -962,20 +985,14 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
         });
     kg = kg_nxt;
     kh = kh_nxt;
-    p0 = p1;
-    p1 = p2;
-    p2 = after(p2);
-    row_cur = row_nxt;
-    row_nxt = row_nn;
-    g_cur = g_nxt;
-    h_cur = h_nxt;
+    to_next_epoch();
     __syncthreads();  // cells are clear, `red` and the unit box are read, before reuse
   }
   // The leaf's last epoch, where rows are missing: nothing follows it, and wavefronts without a row add nothing.  (As one more
   // turn of the loop, which adds zeros and requests rows that nobody takes: 128 leaves of half of 400,000 x 2,000 x 63 174 us, 162
   // so; 64 leaves of 1,500,000 x 500 x 255 371 and 353; 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions
   // inside the loop makes every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
-  if (p0.row < end) {
+  if (kLastApart && p0.row < end) {
     const Addend add = quantise(own_valid(p0.row));
     if (p0.row + (uint32_t)wave * 64u < end) {
       auto step = [&](auto gi_tag) {
@@ -1006,13 +1023,13 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     plan.n_main = direct.n_main;
     plan.wr = direct.wr;
     plan.row_bytes = plan.feat_bytes = 0;  // not used by the slot -> feature map
-    const int slot = slot_run * 16 + (lane & 15), bin0 = wave_bin + (lane >> 4);
+    const int slot = first_slot + lane % RUN, bin0 = first_bin + lane / RUN;
     const int32_t f = plan_feature_of(plan, direct.tile, direct.first_slot + slot);
     if (slot < S::SLOTS && f < direct.n_features) {
       gbdt_bin_t* to = direct.hist + (size_t)f * direct.n_bins;
 #pragma unroll
       for (int m = 0; m < PP; ++m) {
-        const int bin = bin0 + 4 * m;
+        const int bin = bin0 + kStepBins * m;
         if (bin < direct.n_bins) {
           gbdt_bin_t r;
           r.grad = (float)acc_g[m];
@@ -1070,7 +1087,7 @@ struct BuildShape {
 // One workgroup's work on (tile, half) of a leaf: build_tile with the tile's width.  leaf_out: the leaf's partial blocks,
 // `chunks` of every part (tile or half), parts back to back, wg the workgroup's among them; with wide accumulation its second
 // block lies wgs blocks behind its first.
-template <int CAP, int WM, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE, bool HALVES, typename... REST>
+template <int CAP, int WM, bool NIB, int NT, typename ACC, bool INDEXED, bool WIDE, bool HALVES, bool SHORT, typename... REST>
 __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows, int32_t n_main, int32_t wr,
                                            int32_t line_tiles, int32_t t, int32_t half, uint32_t* leaf_out, size_t chunks,
                                            size_t wg, size_t wgs, gbdt_bin_t* direct_hist, int32_t n_features,
@@ -1087,7 +1104,7 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
     constexpr uint32_t kVec = TileShape<CAP, WM, NIB, NT>::VEC;
     const size_t part = BS::kHalves ? 2 * (size_t)t + (size_t)half : (size_t)t;
     uint32_t* out = leaf_out + (part * chunks + wg) * kMainBlock;
-    build_tile<CAP, BS::kMainW, NIB, NT, ACC, INDEXED, WIDE>(tile + 4 * half, stride, kVec, idx, grad, hess, by_pos, stat_shift,
+    build_tile<CAP, BS::kMainW, NIB, NT, ACC, INDEXED, WIDE, SHORT>(tile + 4 * half, stride, kVec, idx, grad, hess, by_pos, stat_shift,
                                                              paced, rest..., lds, out, direct, out + wgs * kMainBlock);
     return;
   }
@@ -1095,7 +1112,7 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
   auto remainder = [&](auto width) {
     constexpr int W = decltype(width)::value;
     constexpr size_t kBlock = (size_t)block_words<CAP, W, NIB, NT>();
-    build_tile<CAP, W, NIB, NT, ACC, INDEXED, WIDE>(tile, stride, TileShape<CAP, W, NIB, NT>::VEC, idx, grad, hess, by_pos,
+    build_tile<CAP, W, NIB, NT, ACC, INDEXED, WIDE, SHORT>(tile, stride, TileShape<CAP, W, NIB, NT>::VEC, idx, grad, hess, by_pos,
                                                     stat_shift, paced || (!WIDE && WM == 32 && n_main == 1 && at.shared),
                                                     rest..., lds, rem_base + wg * kBlock, direct,
                                                     rem_base + (wgs + wg) * kBlock);
@@ -1107,7 +1124,9 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
   }
 }
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false>
+// SHORT: for leaves whose workgroups have one unit of a few epochs each (see build_tile).
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false,
+          bool SHORT = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 hist_build_kernel(BuildArgs a) {
   using BS = BuildShape<CAP, WM, NIB, NT, WIDE, HALVES>;
@@ -1125,7 +1144,7 @@ hist_build_kernel(BuildArgs a) {
   }
   uint32_t* counter = a.counters + plan_counter_slot(BS::kHalves ? 2 * t + half : t);
   const uint32_t n_firsts = a.first_epochs ? (uint32_t)a.wgs : 0u;
-  build_part<CAP, WM, NIB, NT, ACC, INDEXED, WIDE, HALVES>(
+  build_part<CAP, WM, NIB, NT, ACC, INDEXED, WIDE, HALVES, SHORT>(
       a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, t, half, a.partials, (size_t)a.chunks, (size_t)c, (size_t)a.wgs,
       a.direct_out, a.n_features, a.n_bins, lds, a.idx, a.grad, a.hess, a.stats_by_pos != 0, 2u, (uint32_t)a.n_leaf,
       (uint32_t)c, (uint32_t)a.first_epochs, (uint32_t)a.unit_epochs, (uint32_t)a.fixed_stride, counter, (uint32_t)a.wgs,
@@ -1279,7 +1298,7 @@ hist_build_batch_kernel(BatchArgs a) {
   const uint32_t stat_off = !by_pos ? 0u : lf.row_off >= a.stat_wrap ? lf.row_off - a.stat_wrap : lf.row_off;
   uint32_t* leaf_out =
       a.partials + (size_t)lf.first_wg * kPerWg * column_words<CAP, WM, NIB, NT>(a.n_main, a.wr);
-  build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES>(
+  build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES, true>(
       a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, blk.tile, blk.half, leaf_out, (size_t)(kPerWg * wgs),
       (size_t)blk.wg, (size_t)wgs,
       wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr, a.n_features, a.n_bins, lds,
