@@ -385,18 +385,28 @@ __device__ __forceinline__ float pow2f(int k) { return __uint_as_float((uint32_t
 // taken exactly.  Cells are drained into fp64 accumulators.  Twice the LDS atomics and twice the
 // LDS space of the default format.
 constexpr int kWideShift = 24;
+// The 256-bin variants drain their cells once in two epochs (see `pairs` in build_tile) and scale by one more power of two: an epoch's
+// sum stays below 2^51, and so the second one's, taken with the scale of the first although its own exponent may be one less
+// or one more, below 2^52 and rounded at 2^-50 of it: together they fit a cell.
+constexpr int kWideShiftOfTwo = 25;
 __device__ __forceinline__ double pow2d(int k) {
   return __longlong_as_double((long long)(k + 1023) << 52);
 }
 // An epoch whose sum of magnitudes is past the largest fp32 number has no scale of its own: it is scaled as if the sum
-// were 2^128, with this exponent.  The 54-bit field of a cell then takes fifteen rows of the largest number, which is more than
-// the 2^51 that i64_to_f64 takes: epochs of this exponent are drained by a conversion of all 53 bits of a double.
+// were 2^128, with this exponent (and kWideShift always).  The 54-bit field of a cell then takes fifteen rows of the largest number,
+// which is more than the 2^51 that i64_to_f64 takes: epochs of this exponent are drained by a conversion of all 53 bits of a double.
 constexpr int kWidePastExp = (kSumBits - 2) + 127 - 255;
 // round-to-nearest-even of |v| < 2^51 to a 64-bit integer (the sum's low mantissa bits)
 __device__ __forceinline__ long long rint_to_i64(double v) {
   return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000LL;
 }
 
+// acc + scale * (the sum of a cell, above its count) for any sum, each half of the cell exactly converted; scale is that of the cell
+// as a whole, 2^kCountBits more of it.
+__device__ __forceinline__ double add_wide_sum(double acc, uint32_t lo, uint32_t hi, double scale) {
+  acc = fma((double)(int32_t)hi, scale * 4294967296.0, acc);
+  return fma((double)(lo & ~((1u << kCountBits) - 1u)), scale, acc);
+}
 // ... and back, exactly, for |i| < 2^51: an addition and a subtraction instead of two conversions, a scaling and an
 // addition.
 __device__ __forceinline__ double i64_to_f64(long long i) {
@@ -529,6 +539,14 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   constexpr int CELLS = S::CELLS, PP = S::PP, NW = S::NW;
   constexpr int NTBL = LPR == 8 ? 1 : 2;  // LPR 4: two byte-words share a page of 32 slots
 
+  // Two epochs a drain.  With 256 bins a cell has two rows of an epoch, and draining its cells costs about as much as adding its
+  // rows.  Wide cells have room for another epoch whatever the statistics are, as long as the two exponents are one apart
+  // at most (kWideShiftOfTwo).  The second epoch is counted in the hessian cells, whose count field is free, so neither count
+  // passes 512.
+  // (Root of 2,270,000 x 137 x 255 202 us drained after every epoch, 184 so, of 1,500,000 x 500 440 and 396; 60 % of the first as a
+  // list 134 and 126; 64 leaves of all of the second 607 and 574.  With 64 or 16 bins, where a cell has more rows of an epoch,
+  // it is between 4 % faster and 3 % slower.)
+  constexpr bool kPairs = WIDE && CAP == 256;
   char* cells = reinterpret_cast<char*>(lds);
   constexpr int NCELLARR = WIDE ? 2 : 1;  // wide: gradient cells, then hessian cells
   float* red = reinterpret_cast<float*>(lds + NCELLARR * CELLS);  // [2 parities][2 stats][NW]
@@ -741,6 +759,13 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // ... and adds them to this thread's accumulators of its cell m (wide: th = the hessian cell).
   auto drain_cell = [&](int m, unsigned long long t, unsigned long long th, float inv_g, float inv_h,
                         double inv_gw, double inv_hw) {
+    if constexpr (kPairs) {
+      const uint32_t lo = (uint32_t)t, lo_h = (uint32_t)th;
+      acc_c[m] += (lo & ((1u << kCountBits) - 1u)) + (lo_h & ((1u << kCountBits) - 1u));
+      acc_g[m] = (ACC)add_wide_sum((double)acc_g[m], lo, (uint32_t)(t >> 32), inv_gw);
+      acc_h[m] = (ACC)add_wide_sum((double)acc_h[m], lo_h, (uint32_t)(th >> 32), inv_hw);
+      return;
+    }
     if constexpr (WIDE) {
       // the count sits below the gradient sum; an arithmetic shift drops it whatever the sign
       acc_c[m] += (uint32_t)t & ((1u << kCountBits) - 1u);
@@ -858,13 +883,14 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   struct Addend {
     uint32_t lo, hi, lo2, hi2;
   };
-  auto quantise = [&](bool ok) {
+  auto wide_exp = [](int k) { return k + (kPairs && k > kWidePastExp ? kWideShiftOfTwo : kWideShift); };
+  auto quantise = [&](bool ok, bool second) {  // second: of two epochs a drain
     Addend a = {0u, 0u, 0u, 0u};
     if constexpr (WIDE) {
-      const long long gq = rint_to_i64((double)g_cur * pow2d(kg + kWideShift));
-      const long long hq = rint_to_i64((double)h_cur * pow2d(kh + kWideShift));
-      const unsigned long long ag = ((unsigned long long)gq << kCountBits) + 1ull;
-      const unsigned long long ah = ((unsigned long long)hq << kCountBits);
+      const long long gq = rint_to_i64((double)g_cur * pow2d(wide_exp(kg)));
+      const long long hq = rint_to_i64((double)h_cur * pow2d(wide_exp(kh)));
+      const unsigned long long ag = ((unsigned long long)gq << kCountBits) + (kPairs && second ? 0ull : 1ull);
+      const unsigned long long ah = ((unsigned long long)hq << kCountBits) + (kPairs && second ? 1ull : 0ull);
       a.lo = ok ? (uint32_t)ag : 0u;
       a.hi = ok ? (uint32_t)(ag >> 32) : 0u;
       a.lo2 = ok ? (uint32_t)ah : 0u;
@@ -881,8 +907,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // one as they arrive.  (The scheduling barrier keeps the arithmetic of `second` from being waited for between the requests.)
   auto drain = [&](auto&& first, auto&& second) {
     const float inv_g = pow2f(-kg) * (1.0f / (1 << kSumPad)), inv_h = pow2f(-kh) * (1.0f / (1 << kSumPad));
-    const double inv_gw = pow2d(-kg - kWideShift), inv_hw = pow2d(-kh - kWideShift);
-    if (WIDE && (kg <= kWidePastExp || kh <= kWidePastExp)) {
+    // (of sums, or of whole cells)
+    const double inv_gw = pow2d(-wide_exp(kg) - (kPairs ? kCountBits : 0)), inv_hw = pow2d(-wide_exp(kh) - (kPairs ? kCountBits : 0));
+    if (WIDE && !kPairs && (kg <= kWidePastExp || kh <= kWidePastExp)) {
       // kWidePastExp: rare, so here, cell by cell (the registers are taken), and what follows then finds empty cells.  (As the
       // other branch of what follows it costs all wide kernels 10 to 40 registers.)
 #pragma unroll
@@ -921,9 +948,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   float g_nxt = 0.0f, h_nxt = 0.0f;
   // Whether the leaf's last epoch, where rows may be missing, has code of its own (below).  Long leaves, to which it is nothing, are
   // a little faster with one loop: 2,270,000 x 137 x 255 124.0 us, 125.2 with two; 1,500,000 x 330 x 64 with wide sums 215 and 219.
-  constexpr bool kLastApart = SHORT;
+  constexpr bool kLastApart = SHORT || kPairs;
   // An epoch of 512 rows: requests for later ones, its additions, and the sums of the next.  Returns whether a unit was taken.
-  auto add_epoch = [&] {
+  auto add_epoch = [&](bool second) {
     const bool takes = !fixed_stride && p0.left == 3;
     uint32_t taken = 0;
     if (takes && tid == 0)
@@ -933,7 +960,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
     g_nxt = load_stat(grad, stat_nxt);
     h_nxt = load_stat(hess, stat_nxt);
-    const Addend add = quantise(kLastApart || own_valid(p0.row));
+    const Addend add = quantise(kLastApart || own_valid(p0.row), second);
     // The atomics are what the kernel is bound by; the drain of a co-resident workgroup is
     // mostly VALU work.  Raised priority lets the waves that feed the LDS pipe issue first,
     // and the other workgroup's drain fills the gaps (8-12 % on the 256-bin variants).
@@ -970,7 +997,20 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     h_cur = h_nxt;
   };
   while (p0.row + (kLastApart ? (uint32_t)kEpochRows - 1u : 0u) < end) {  // uniform over the workgroup
-    const bool takes = add_epoch();
+    bool takes = add_epoch(false);
+    if constexpr (kPairs) {
+      if (p1.row + (uint32_t)kEpochRows <= end) {
+        int kg_nxt, kh_nxt;
+        scales_from(request_scales((int)parity, lane), kg_nxt, kh_nxt);
+        const uint32_t apart_g = (uint32_t)(kg - kg_nxt + 1), apart_h = (uint32_t)(kh - kh_nxt + 1);
+        if (apart_g <= 2u && apart_h <= 2u && kg > kWidePastExp + 1 && kh > kWidePastExp + 1) {
+          // (no barrier: `red` has another place for the next epoch, and units are taken three epochs apart at least)
+          if (takes) next_unit = __builtin_amdgcn_readfirstlane(unit_box[0]);
+          to_next_epoch();
+          takes = add_epoch(true);
+        }
+      }
+    }
     float next_sums = 0.0f;
     uint32_t box = 0u;
     int kg_nxt = 0, kh_nxt = 0;
@@ -993,7 +1033,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // so; 64 leaves of 1,500,000 x 500 x 255 371 and 353; 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions
   // inside the loop makes every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
   if (kLastApart && p0.row < end) {
-    const Addend add = quantise(own_valid(p0.row));
+    const Addend add = quantise(own_valid(p0.row), false);
     if (p0.row + (uint32_t)wave * 64u < end) {
       auto step = [&](auto gi_tag) {
         add_group(w[decltype(gi_tag)::value], add.lo, add.hi, add.lo2, add.hi2, gi_tag);
