@@ -590,7 +590,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   constexpr int kStepBins = SHORT ? BINS : BINS * WAVES;  // from a thread's bin to its next
   const int first_slot = wave % RUNS * RUN, first_bin = wave / RUNS * (SHORT ? BINS * PP : BINS);
   const int run_cell = first_slot / S::PITCH * (CAP * S::PITCH) + first_slot % S::PITCH + first_bin * S::PITCH;  // scalar
-  auto owned_cell = [&](int l) { return run_cell + l / RUN * S::PITCH + l % RUN; };  // of lane l, the first one
+  auto owned_cell = [&](int t) {  // of thread t, the first one (the same number where there is one run: one register less)
+    return !SHORT && RUNS == 1 ? t : run_cell + (t & 63) / RUN * S::PITCH + (t & 63) % RUN;
+  };
   constexpr int kOwnedStep = kStepBins * S::PITCH;                                   // ... to the next
   ACC acc_g[PP], acc_h[PP];
   uint32_t acc_c[PP];
@@ -914,7 +916,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
       // other branch of what follows it costs all wide kernels 10 to 40 registers.)
 #pragma unroll
       for (int m = 0; m < PP; ++m) {
-        const int at = owned_cell(lane) + m * kOwnedStep;
+        const int at = owned_cell(tid) + m * kOwnedStep;
         const unsigned long long t = request_cell(at), th = request_cell((WIDE ? CELLS : 0) + at);
         acc_c[m] += (uint32_t)t & ((1u << kCountBits) - 1u);
         acc_g[m] = (ACC)fma((double)((long long)t >> kCountBits), inv_gw, (double)acc_g[m]);
@@ -925,12 +927,14 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     // The 16-bin variant has 64 registers (8 wavefronts a SIMD) and no room for addresses that are only used here: kept, they
     // are spilled, and reading them back waits for everything requested before, all of the next epoch's bins.  Formed here
     // anew (32 leaves of half of 2,000,000 x 150 x 16 53.8 -> 49.4 us, 25 % of the rows 47.0 -> 44.4).
-    int drain_lane = lane;
+    int drain_tid = tid;
     if constexpr (CAP == 16 && !WIDE) {
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(drain_lane));
+      int l;
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+      drain_tid = wave * 64 + l;
     }
-    const int drain_cell0 = owned_cell(drain_lane);
-    first(drain_lane);
+    const int drain_cell0 = owned_cell(drain_tid);
+    first(drain_tid);
     unsigned long long cell[PP], cell_h[WIDE ? PP : 1];
 #pragma unroll
     for (int m = 0; m < PP; ++m) {
@@ -1015,8 +1019,8 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     uint32_t box = 0u;
     int kg_nxt = 0, kh_nxt = 0;
     drain(
-        [&](int drain_lane) {
-          next_sums = request_scales((int)parity, drain_lane);
+        [&](int drain_tid) {
+          next_sums = request_scales((int)parity, drain_tid);
           box = unit_box[0];
         },
         [&] {
@@ -1063,6 +1067,24 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     plan.n_main = direct.n_main;
     plan.wr = direct.wr;
     plan.row_bytes = plan.feat_bytes = 0;  // not used by the slot -> feature map
+    if constexpr (!SHORT && RUNS == 1) {
+      // (Rarely taken: a matrix of more tiles than workgroups that fit the machine.  What is shared by a thread's cells stays
+      // unshared, because the loop above is laid out worse otherwise: 1,500,000 x 500 x 255 258 us, 262 written as below.)
+#pragma unroll
+      for (int m = 0; m < PP; ++m) {
+        const int cell = tid + m * NT;
+        const int slot = cell % S::PITCH, bin = cell / S::PITCH % CAP;
+        const int32_t f = plan_feature_of(plan, direct.tile, direct.first_slot + slot);
+        if (slot < S::SLOTS && bin < direct.n_bins && f < direct.n_features) {
+          gbdt_bin_t r;
+          r.grad = (float)acc_g[m];
+          r.hess = (float)acc_h[m];
+          r.count = acc_c[m];
+          direct.hist[(size_t)f * direct.n_bins + bin] = r;
+        }
+      }
+      return;
+    }
     const int slot = first_slot + lane % RUN, bin0 = first_bin + lane / RUN;
     const int32_t f = plan_feature_of(plan, direct.tile, direct.first_slot + slot);
     if (slot < S::SLOTS && f < direct.n_features) {
@@ -1082,7 +1104,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     return;
   }
   // partial block layout: [stat][cell] words
-  const int cell0 = owned_cell(lane);
+  const int cell0 = owned_cell(tid);
 #pragma unroll
   for (int m = 0; m < PP; ++m) {
     out[cell0 + m * kOwnedStep] = __float_as_uint((float)acc_g[m]);
@@ -1164,7 +1186,8 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
   }
 }
 
-// SHORT: for leaves whose workgroups have one unit of a few epochs each (see build_tile).
+// SHORT: for leaves whose workgroups have one unit of a few epochs each, and in batches those that have one workgroup a tile (see
+// build_tile).
 template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false,
           bool SHORT = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
@@ -1322,7 +1345,7 @@ __device__ __host__ inline size_t column_words(int32_t n_main, int32_t wr) {
   return w;
 }
 
-template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false>
+template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE, bool HALVES, bool SHORT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 hist_build_batch_kernel(BatchArgs a) {
   using BS = BuildShape<CAP, WM, NIB, NT, WIDE, HALVES>;
@@ -1338,7 +1361,7 @@ hist_build_batch_kernel(BatchArgs a) {
   const uint32_t stat_off = !by_pos ? 0u : lf.row_off >= a.stat_wrap ? lf.row_off - a.stat_wrap : lf.row_off;
   uint32_t* leaf_out =
       a.partials + (size_t)lf.first_wg * kPerWg * column_words<CAP, WM, NIB, NT>(a.n_main, a.wr);
-  build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES, true>(
+  build_part<CAP, WM, NIB, NT, ACC, true, WIDE, HALVES, SHORT>(
       a.packed, a.n_rows, a.n_main, a.wr, a.line_tiles, blk.tile, blk.half, leaf_out, (size_t)(kPerWg * wgs),
       (size_t)blk.wg, (size_t)wgs,
       wgs == 1 ? a.hist_out + (size_t)batch_leaf_no(lf) * a.n_features * a.n_bins : nullptr, a.n_features, a.n_bins, lds,
