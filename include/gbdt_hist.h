@@ -564,6 +564,11 @@ int gbdt_debug_partition_plan(int64_t n_leaf_rows, int64_t* out, int32_t n_out);
  * whose quantised gradients and hessians are given: out[0] = sum of the gradients, out[1] = sum of the
  * hessians, out[2] = count.  Computed by the functions the kernel uses.  Host only. */
 int gbdt_debug_cell_sums(const int32_t* grad_q, const int32_t* hess_q, int32_t n, int64_t* out);
+/* What a wide cell of 256 bins holds of two epochs of n <= 512 rows each, whose gradients (or hessians) are given and all fall
+ * into the cell: out[0] = the second epoch's exponent less the first's, -1, 0 or 1, or 2 if the two do not share the cells and
+ * the second is left out; out[1] = e, the cell counts units of 2^-e; out[2] = the cell's sum; out[3] = what the second
+ * epoch adds; out[4] = count of the first.  Computed by the functions the kernel uses.  Host only. */
+int gbdt_debug_wide_pair(const float* first, const float* second, int32_t n, int64_t* out);
 int gbdt_debug_locate(int32_t n_features, int32_t n_bins, int32_t feature, int32_t* tile_out,
                       int32_t* slot_out);
 

@@ -25,7 +25,7 @@ EXPORTS = [
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
     "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
     "gbdt_debug_leaf_plan", "gbdt_debug_half_blocks", "gbdt_debug_gather_plan",
-    "gbdt_debug_host_blocks",
+    "gbdt_debug_host_blocks", "gbdt_debug_wide_pair",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -643,6 +643,19 @@ def gbdt_debug_cell_sums(grad_q, hess_q):
     lib.gbdt_debug_cell_sums.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
     _check(lib.gbdt_debug_cell_sums(g.ctypes.data, h.ctypes.data, g.size, out), "gbdt_debug_cell_sums")
     return out[0], out[1], out[2]
+
+
+def gbdt_debug_wide_pair(first, second):
+    """(exponent of the second epoch less the first's or 2, units' exponent, sum, second's part, count) of a wide 256-bin cell."""
+    lib = load()
+    a, b = (np.ascontiguousarray(v, dtype=np.float32) for v in (first, second))
+    if a.shape != b.shape:
+        raise GbdtError("epochs of different lengths")
+    out = (ctypes.c_int64 * 5)()
+    lib.gbdt_debug_wide_pair.restype = ctypes.c_int
+    lib.gbdt_debug_wide_pair.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
+    _check(lib.gbdt_debug_wide_pair(a.ctypes.data, b.ctypes.data, a.size, out), "gbdt_debug_wide_pair")
+    return tuple(int(v) for v in out)
 
 
 def gbdt_set_deterministic(enable: bool) -> None:

@@ -2519,6 +2519,29 @@ int gbdt_debug_partition_plan(int64_t n_leaf_rows, int64_t* out, int32_t n_out) 
   return GBDT_OK;
 }
 
+int gbdt_debug_wide_pair(const float* first, const float* second, int32_t n, int64_t* out) {
+  if (n < 1 || n > kEpochRows || !out || !first || !second) return GBDT_EINVAL;
+  auto exponent = [n](const float* v) {  // (as scales_from has it)
+    float sum = 0.0f;
+    for (int32_t i = 0; i < n; ++i) sum += fabsf(v[i]);
+    sum *= 1.001953125f;
+    return epoch_scale_exp(__builtin_bit_cast(uint32_t, sum));
+  };
+  const int k = exponent(first), k2 = exponent(second), exp = wide_cell_exp(k, true);
+  const bool pair = wide_pair(k, k2);
+  uint64_t cell = 0, cell2 = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    cell += ((uint64_t)wide_quantise(first[i], exp, 0) << kCountBits) + 1u;
+    if (pair) cell2 += (uint64_t)wide_quantise(second[i], exp, k2 < k) << kCountBits;
+  }
+  out[0] = pair ? k2 - k : 2;
+  out[1] = exp;
+  out[2] = (int64_t)(cell + cell2) >> kCountBits;
+  out[3] = (int64_t)cell2 >> kCountBits;
+  out[4] = (int64_t)((cell + cell2) & ((1u << kCountBits) - 1u));
+  return GBDT_OK;
+}
+
 int gbdt_debug_cell_sums(const int32_t* grad_q, const int32_t* hess_q, int32_t n, int64_t* out) {
   if (n < 0 || n > kEpochRows || !out || (n > 0 && (!grad_q || !hess_q))) return GBDT_EINVAL;
   uint64_t cell = 0;

@@ -356,50 +356,7 @@ struct BuildArgs {
 
 constexpr int kUnitEpochs = 4;  // consecutive epochs a workgroup takes from its group's counter (>= 3)
 
-// Power-of-two scale 2^k for quantising the values of one epoch to integers: the
-// largest k with 2^k * m + kEpochRows / 2 (rounding slack) < 2^26, so that no cell's
-// signed 27-bit field can overflow whatever the bins are.  m_bits: the bit pattern of
-// m = 1.002 * (fp32 sum of |v| over the epoch) (the factor covers the rounding of the
-// sum itself).  Integer arithmetic only: on a wave-uniform value it runs on the
-// scalar unit.  A zero (or denormal) sum gives k = 0; k is kept in [-126, 126] so
-// that 2^k and 2^-k are normal floats.  (The drain's 2^-(k + kSumPad) is a denormal from k = 122 on,
-// which the multiply-adds take as it is.)
-__device__ __forceinline__ int epoch_scale_exp(uint32_t m_bits) {
-  const int e = (int)((m_bits >> 23) & 0xffu);
-  const uint32_t mant = m_bits & 0x7fffffu;
-  if (e == 0) return 0;
-  int k = (kSumBits - 2) + 127 - e;  // 2^k * m in [2^25, 2^26)
-  // 2^k * m = (1 + mant / 2^23) * 2^25 > 2^26 - kEpochRows  <=>  mant > 2^23 - kEpochRows / 4
-  if (mant > (1u << 23) - (uint32_t)(kEpochRows >> (kSumBits - 25))) k -= 1;
-  if (k > 126) k = 126;
-  if (k < -126) k = -126;
-  return k;
-}
 __device__ __forceinline__ float pow2f(int k) { return __uint_as_float((uint32_t)(k + 127) << 23); }
-
-// Wide accumulation (the double precision switch of App. A.6): a (bin, feature) pair owns TWO
-// 64-bit cells, gradient and hessian, each a signed 54-bit sum above the 10-bit count field (the
-// count is kept in the gradient cell).  Values are scaled by 2^(k + kWideShift), k the exponent
-// of the narrow format, so an epoch's sum of magnitudes stays below 2^50 and a value is rounded
-// at 2^-50 of it at worst -- a fp32 value that is not 2^26 times smaller than the epoch's sum is
-// taken exactly.  Cells are drained into fp64 accumulators.  Twice the LDS atomics and twice the
-// LDS space of the default format.
-constexpr int kWideShift = 24;
-// The 256-bin variants drain their cells once in two epochs (see `pairs` in build_tile) and scale by one more power of two: an epoch's
-// sum stays below 2^51, and so the second one's, taken with the scale of the first although its own exponent may be one less
-// or one more, below 2^52 and rounded at 2^-50 of it: together they fit a cell.
-constexpr int kWideShiftOfTwo = 25;
-__device__ __forceinline__ double pow2d(int k) {
-  return __longlong_as_double((long long)(k + 1023) << 52);
-}
-// An epoch whose sum of magnitudes is past the largest fp32 number has no scale of its own: it is scaled as if the sum
-// were 2^128, with this exponent (and kWideShift always).  The 54-bit field of a cell then takes fifteen rows of the largest number,
-// which is more than the 2^51 that i64_to_f64 takes: epochs of this exponent are drained by a conversion of all 53 bits of a double.
-constexpr int kWidePastExp = (kSumBits - 2) + 127 - 255;
-// round-to-nearest-even of |v| < 2^51 to a 64-bit integer (the sum's low mantissa bits)
-__device__ __forceinline__ long long rint_to_i64(double v) {
-  return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000LL;
-}
 
 // acc + scale * (the sum of a cell, above its count) for any sum, each half of the cell exactly converted; scale is that of the cell
 // as a whole, 2^kCountBits more of it.
@@ -541,7 +498,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
 
   // Two epochs a drain.  With 256 bins a cell has two rows of an epoch, and draining its cells costs about as much as adding its
   // rows.  Wide cells have room for another epoch whatever the statistics are, as long as the two exponents are one apart
-  // at most (kWideShiftOfTwo).  The second epoch is counted in the hessian cells, whose count field is free, so neither count
+  // at most (wide_pair; what a row adds at the scale of the other epoch: wide_quantise).  The second epoch is counted in the hessian cells, whose count field is free, so neither count
   // passes 512.
   // (Root of 2,270,000 x 137 x 255 202 us drained after every epoch, 184 so, of 1,500,000 x 500 440 and 396; 60 % of the first as a
   // list 134 and 126; 64 leaves of all of the second 607 and 574.  With 64 or 16 bins, where a cell has more rows of an epoch,
@@ -885,12 +842,12 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   struct Addend {
     uint32_t lo, hi, lo2, hi2;
   };
-  auto wide_exp = [](int k) { return k + (kPairs && k > kWidePastExp ? kWideShiftOfTwo : kWideShift); };
-  auto quantise = [&](bool ok, bool second) {  // second: of two epochs a drain
+  auto wide_exp = [](int k) { return wide_cell_exp(k, kPairs); };
+  // second: of two epochs a drain; coarse_g, coarse_h: and its own exponent is one less (wide_quantise)
+  auto quantise = [&](bool ok, bool second, int coarse_g, int coarse_h) {
     Addend a = {0u, 0u, 0u, 0u};
     if constexpr (WIDE) {
-      const long long gq = rint_to_i64((double)g_cur * pow2d(wide_exp(kg)));
-      const long long hq = rint_to_i64((double)h_cur * pow2d(wide_exp(kh)));
+      const long long gq = wide_quantise(g_cur, wide_exp(kg), coarse_g), hq = wide_quantise(h_cur, wide_exp(kh), coarse_h);
       const unsigned long long ag = ((unsigned long long)gq << kCountBits) + (kPairs && second ? 0ull : 1ull);
       const unsigned long long ah = ((unsigned long long)hq << kCountBits) + (kPairs && second ? 1ull : 0ull);
       a.lo = ok ? (uint32_t)ag : 0u;
@@ -954,7 +911,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // a little faster with one loop: 2,270,000 x 137 x 255 124.0 us, 125.2 with two; 1,500,000 x 330 x 64 with wide sums 215 and 219.
   constexpr bool kLastApart = SHORT || kPairs;
   // An epoch of 512 rows: requests for later ones, its additions, and the sums of the next.  Returns whether a unit was taken.
-  auto add_epoch = [&](bool second) {
+  auto add_epoch = [&](bool second, int coarse_g, int coarse_h) {
     const bool takes = !fixed_stride && p0.left == 3;
     uint32_t taken = 0;
     if (takes && tid == 0)
@@ -964,7 +921,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     const uint32_t stat_nxt = stats_by_pos ? own_pos(p1.row) : row_nxt;
     g_nxt = load_stat(grad, stat_nxt);
     h_nxt = load_stat(hess, stat_nxt);
-    const Addend add = quantise(kLastApart || own_valid(p0.row), second);
+    const Addend add = quantise(kLastApart || own_valid(p0.row), second, coarse_g, coarse_h);
     // The atomics are what the kernel is bound by; the drain of a co-resident workgroup is
     // mostly VALU work.  Raised priority lets the waves that feed the LDS pipe issue first,
     // and the other workgroup's drain fills the gaps (8-12 % on the 256-bin variants).
@@ -1001,17 +958,16 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     h_cur = h_nxt;
   };
   while (p0.row + (kLastApart ? (uint32_t)kEpochRows - 1u : 0u) < end) {  // uniform over the workgroup
-    bool takes = add_epoch(false);
+    bool takes = add_epoch(false, 0, 0);
     if constexpr (kPairs) {
       if (p1.row + (uint32_t)kEpochRows <= end) {
         int kg_nxt, kh_nxt;
         scales_from(request_scales((int)parity, lane), kg_nxt, kh_nxt);
-        const uint32_t apart_g = (uint32_t)(kg - kg_nxt + 1), apart_h = (uint32_t)(kh - kh_nxt + 1);
-        if (apart_g <= 2u && apart_h <= 2u && kg > kWidePastExp + 1 && kh > kWidePastExp + 1) {
+        if (wide_pair(kg, kg_nxt) && wide_pair(kh, kh_nxt)) {
           // (no barrier: `red` has another place for the next epoch, and units are taken three epochs apart at least)
           if (takes) next_unit = __builtin_amdgcn_readfirstlane(unit_box[0]);
           to_next_epoch();
-          takes = add_epoch(true);
+          takes = add_epoch(true, kg_nxt < kg, kh_nxt < kh);
         }
       }
     }
@@ -1037,7 +993,7 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   // so; 64 leaves of 1,500,000 x 500 x 255 371 and 353; 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions
   // inside the loop makes every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
   if (kLastApart && p0.row < end) {
-    const Addend add = quantise(own_valid(p0.row), false);
+    const Addend add = quantise(own_valid(p0.row), false, 0, 0);
     if (p0.row + (uint32_t)wave * 64u < end) {
       auto step = [&](auto gi_tag) {
         add_group(w[decltype(gi_tag)::value], add.lo, add.hi, add.lo2, add.hi2, gi_tag);

@@ -1,6 +1,6 @@
 """Wide sums of 256 bins, whose cells are drained once in two epochs (of 512 rows) when their scales allow it: against the oracle, with
-magnitudes that stay, that change a little and that change a lot from epoch to epoch, zeros, one sign, and sums past fp32 in
-between; whole tiles and halves, roots, lists and batches, odd and even numbers of epochs.
+magnitudes that stay, that change a little and that change a lot from epoch to epoch, zeros, one sign, lone rows that hold an
+epoch's sum, heavy tails, and sums past fp32 in between; whole tiles and halves, roots, lists and batches, odd and even numbers of epochs.
 
 Where all statistics are small multiples of a power of two every sum is exact and has to agree bit for bit; elsewhere within
 2^-23 of the value, the rounding of what is stored, and 1e-12 of the sum of magnitudes."""
@@ -42,7 +42,8 @@ def agrees(got_t, p, idx, n_leaf, exact, what):
 
 
 @pytest.mark.parametrize("kind", ["plain", "one_sign", "a_little", "a_lot", "zeros", "rounded"])
-@pytest.mark.parametrize("n_features,n_bins", [(28, 255), (10, 256), (40, 200), (70, 255)])
+# (with 600 and 1,200 features the workgroups of a root of 25 epochs have two and five each, with fewer features one)
+@pytest.mark.parametrize("n_features,n_bins", [(28, 255), (10, 256), (40, 200), (70, 255), (600, 255), (1200, 255)])
 def test_two_epochs_a_drain(n_features, n_bins, kind):
     print(f"wide pairs {n_features} x {n_bins} {kind}", flush=True)
     rng = np.random.default_rng(n_features)
@@ -67,6 +68,69 @@ def test_two_epochs_a_drain(n_features, n_bins, kind):
     finally:
         B.gbdt_set_wide_accumulation(False)
         B.gbdt_set_deterministic(False)
+
+
+def lone_rows(ratio, noise, rng):
+    """One row holds (nearly) all of its epoch's sum, in every second epoch `ratio` times that of the epoch before."""
+    first = np.array([1.5, 100.0, 0.75, 1.0])[np.arange(N_ROWS) // 1024 % 4]
+    v = noise * rng.integers(-1, 2, size=N_ROWS).astype(np.float64)
+    at = np.arange(0, N_ROWS - 512, 512) + rng.integers(0, 512, size=N_ROWS // 512)
+    v[at] = first[at] * np.where(at // 512 % 2, ratio, 1.0)
+    return v.astype(np.float32)
+
+
+@pytest.mark.parametrize("noise", [0.0, 2.0 ** -11])
+@pytest.mark.parametrize("n_features", [28, 70, 600])
+def test_a_lone_row_holds_an_epochs_sum(n_features, noise):
+    """Every value is a multiple of 2^-11 and every sum below 2^12: exact, also as it is stored."""
+    rng = np.random.default_rng(n_features)
+    bins = rng.integers(0, 255, size=(N_ROWS, n_features)).astype(np.uint8)
+    ratios = [2.0, -2.0, 3.0, -3.5, 1.9375, 0.5, -0.28125, 1.0]
+    p = GpuProblem(bins, 255, np.zeros(N_ROWS, np.float32), np.zeros(N_ROWS, np.float32))
+    lists = [np.sort(rng.choice(N_ROWS, size=n, replace=False)).astype(np.int32) for n in (11_000, 2_000)]
+    lists += [np.arange(a, b, dtype=np.int32) for a, b in ((0, 2048), (2048, 3072), (1024, 5632))]  # whole epochs of the matrix
+    offs = np.concatenate([[0], np.cumsum([len(i) for i in lists])])
+    flat = torch.from_numpy(np.concatenate(lists)).to(p.dev)
+    B.gbdt_set_wide_accumulation(True)
+    try:
+        for k, r in enumerate(ratios):
+            print(f"lone rows {n_features} noise {noise} ratio {r}", flush=True)
+            for a, ratio in (("grad", r), ("hess", ratios[(k + 3) % len(ratios)])):
+                setattr(p, a + "_cpu", torch.from_numpy(lone_rows(ratio, noise, rng)))
+                setattr(p, a, getattr(p, a + "_cpu").to(p.dev))
+            for n in (N_ROWS, 1024, 2048, 6 * 512):
+                agrees(p.build(n_leaf=n), p, None, n, True, ("root", r, n))
+            for idx in lists:
+                agrees(p.build(idx), p, idx, None, True, ("list", r, len(idx)))
+            hists = B.gbdt_hist_build_batch(p.packed, N_ROWS, n_features, 255, flat, offs, p.grad, p.hess)
+            for i, idx in enumerate(lists):
+                agrees(hists[i], p, idx, None, True, ("batch", r, len(idx)))
+    finally:
+        B.gbdt_set_wide_accumulation(False)
+
+
+@pytest.mark.parametrize("n_features", [28, 600])
+def test_heavy_tails(n_features):
+    """Cauchy gradients, log-normal hessians: about one pair in a hundred has a row that is past 2^51 at the first epoch's scale."""
+    rng = np.random.default_rng(7)
+    bins = rng.integers(0, 255, size=(N_ROWS, n_features)).astype(np.uint8)
+    lists = [np.sort(rng.choice(N_ROWS, size=2_000, replace=False)).astype(np.int32) for _ in range(200)]
+    p = GpuProblem(bins, 255, rng.standard_cauchy(N_ROWS).astype(np.float32), rng.lognormal(sigma=2.5, size=N_ROWS).astype(np.float32))
+    past = 0
+    for v in (p.grad_cpu.numpy(), p.hess_cpu.numpy()):
+        for idx in lists:
+            apart, e = B.gbdt_debug_wide_pair(v[idx[:512]], v[idx[512:1024]])[:2]
+            past += apart == -1 and np.abs(v[idx[512:1024]]).max() > 2.0 ** (51 - e)
+    assert past > 0
+    B.gbdt_set_wide_accumulation(True)
+    try:
+        agrees(p.build(), p, None, None, False, "root")
+        hists = B.gbdt_hist_build_batch(p.packed, N_ROWS, n_features, 255, torch.from_numpy(np.concatenate(lists)).to(p.dev),
+                                        np.arange(201) * 2_000, p.grad, p.hess)
+        for i, idx in enumerate(lists):
+            agrees(hists[i], p, idx, None, False, ("batch", i))
+    finally:
+        B.gbdt_set_wide_accumulation(False)
 
 
 def test_long_units_of_many_epochs():
