@@ -533,24 +533,26 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
 
 #pragma unroll
   for (int m = 0; m < PP * NCELLARR; ++m) lds[tid + m * NT] = 0ull;
-  // The cells a thread drains: PP of one slot.  A wavefront takes a run of 32 slots and 2 bins at a time, 512 bytes of cells
-  // one after the other, and the wavefronts take turns in the bins.  With SHORT it takes 16 slots and 4 bins (16 cells in a row still
-  // cover all banks once) of bins of its own: a finished histogram leaves as 48 bytes of a feature side by side and not 24,
-  // half as many lines a store, and the words of a partial block one after the other.  128 leaves of half of 400,000 x 2,000 x 63
-  // 179 us with turns of 32 slots, 174 so; of 1,000,000 x 100 x 255 47.0 and 44.8; root of 100,000 x 28 x 255, an epoch a
-  // workgroup, 22.3 with turns of 16, 18.7 so.  Long leaves are faster with turns: 1,500,000 x 500 x 255 254 us, 259 with
-  // bins of a wavefront's own.
+  // The cells a thread drains: PP of one lane of slots.  Long leaves: cell t of thread t and every NT-th from there, so that a wavefront
+  // takes 512 bytes of cells one after the other, 32 slots and 2 bins, and the wavefronts take turns in the bins; with 16 bins a thread
+  // stays in one page instead (kernels of 4 pages spill less so: root of 3,000,000 x 400 x 16 238 us by thread, 229 so).  SHORT: a
+  // wavefront takes 16 slots and 4 bins (16 cells in a row still cover all banks once) of bins of its own: a finished histogram leaves as
+  // 48 bytes of a feature side by side and not 24, half as many lines a store, and the words of a partial block one after the other.
+  // 128 leaves of half of 400,000 x 2,000 x 63 179 us with turns of 32 slots, 174 so; of 1,000,000 x 100 x 255 47.0 and 44.8; root of
+  // 100,000 x 28 x 255, an epoch a workgroup, 22.3 with turns of 16, 18.7 so.  Long leaves are faster with turns: 1,500,000 x 500 x 255
+  // 254 us, 259 with bins of a wavefront's own.
+  constexpr bool kByThread = !SHORT && CAP != 16;
   constexpr int RUN = SHORT || S::PITCH == 16 ? 16 : 32, BINS = 64 / RUN;
   constexpr int RUNS = CELLS / (RUN * CAP);      // (those of a page without features among them)
   constexpr int WAVES = NW / RUNS;               // wavefronts of a run
-  static_assert(NW % RUNS == 0 && CAP == BINS * WAVES * PP, "a thread drains cells of one slot");
+  static_assert(kByThread || (NW % RUNS == 0 && CAP == BINS * WAVES * PP), "a thread drains cells of one slot");
   constexpr int kStepBins = SHORT ? BINS : BINS * WAVES;  // from a thread's bin to its next
   const int first_slot = wave % RUNS * RUN, first_bin = wave / RUNS * (SHORT ? BINS * PP : BINS);
   const int run_cell = first_slot / S::PITCH * (CAP * S::PITCH) + first_slot % S::PITCH + first_bin * S::PITCH;  // scalar
-  auto owned_cell = [&](int t) {  // of thread t, the first one (the same number where there is one run: one register less)
-    return !SHORT && RUNS == 1 ? t : run_cell + (t & 63) / RUN * S::PITCH + (t & 63) % RUN;
+  auto owned_cell = [&](int t) {  // of thread t, the first one
+    return kByThread ? t : run_cell + (t & 63) / RUN * S::PITCH + (t & 63) % RUN;
   };
-  constexpr int kOwnedStep = kStepBins * S::PITCH;                                   // ... to the next
+  constexpr int kOwnedStep = kByThread ? NT : kStepBins * S::PITCH;  // ... to the next
   ACC acc_g[PP], acc_h[PP];
   uint32_t acc_c[PP];
 #pragma unroll
@@ -1023,13 +1025,13 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
     plan.n_main = direct.n_main;
     plan.wr = direct.wr;
     plan.row_bytes = plan.feat_bytes = 0;  // not used by the slot -> feature map
-    if constexpr (!SHORT && RUNS == 1) {
+    if constexpr (kByThread) {
       // (Rarely taken: a matrix of more tiles than workgroups that fit the machine.  What is shared by a thread's cells stays
       // unshared, because the loop above is laid out worse otherwise: 1,500,000 x 500 x 255 258 us, 262 written as below.)
 #pragma unroll
       for (int m = 0; m < PP; ++m) {
         const int cell = tid + m * NT;
-        const int slot = cell % S::PITCH, bin = cell / S::PITCH % CAP;
+        const int bin = cell / S::PITCH % CAP, slot = cell / (CAP * S::PITCH) * S::PITCH + cell % S::PITCH;
         const int32_t f = plan_feature_of(plan, direct.tile, direct.first_slot + slot);
         if (slot < S::SLOTS && bin < direct.n_bins && f < direct.n_features) {
           gbdt_bin_t r;
