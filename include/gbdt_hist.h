@@ -523,6 +523,10 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
 int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* leaf_offsets,
                           int32_t n_leaves, int32_t n_cus, int32_t wg_per_cu, int32_t* leaf_wgs_out,
                           int32_t* leaf_unit_epochs_out, int32_t* block_out, int32_t max_blocks);
+/* 1 if a batched launch of such leaves takes the kernel for short leaves, 0 if it takes the one for long leaves; 1 where there is one
+ * kernel for both (at most 16 bins; wide sums of more than 64).  Arguments as gbdt_debug_batch_plan.  Host only. */
+int gbdt_debug_batch_is_short(int32_t n_features, int32_t n_bins, const int64_t* leaf_offsets, int32_t n_leaves, int32_t n_cus,
+                              int32_t wg_per_cu);
 /* Where the tiles of a packed matrix lie and how the blocks of a build launch with `cols` workgroups per
  * tile are dealt out: tile_out[2 t], tile_out[2 t + 1] = byte offset of tile t's first row and bytes from
  * a row to the next; block_out[2 i], block_out[2 i + 1] = (tile, workgroup of the tile) of block

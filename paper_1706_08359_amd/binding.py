@@ -25,7 +25,7 @@ EXPORTS = [
     "gbdt_profile_enable", "gbdt_profile_collect", "gbdt_debug_occupancy", "gbdt_debug_split_plan",
     "gbdt_debug_partition_plan", "gbdt_debug_cell_sums", "gbdt_debug_block_map", "gbdt_debug_fuse_sample_rows",
     "gbdt_debug_leaf_plan", "gbdt_debug_half_blocks", "gbdt_debug_gather_plan",
-    "gbdt_debug_host_blocks", "gbdt_debug_wide_pair",
+    "gbdt_debug_host_blocks", "gbdt_debug_wide_pair", "gbdt_debug_batch_is_short",
     "gbdt_calibration_copy", "gbdt_set_deterministic", "gbdt_partition_rows",
     "gbdt_hist_build_batch", "gbdt_hist_build_batch_workspace_bytes", "gbdt_best_split_batch",
     "gbdt_debug_batch_plan", "gbdt_grow_tree", "gbdt_grow_tree_scratch_bytes",
@@ -595,6 +595,19 @@ def gbdt_debug_block_map(n_features: int, n_bins: int, n_rows: int, cols: int, b
         _check(rc, "gbdt_debug_block_map")
     assert rc == blocks.shape[0]
     return tiles, blocks
+
+
+def gbdt_debug_batch_is_short(n_features: int, n_bins: int, leaf_offsets, n_cus: int, wg_per_cu: int) -> bool:
+    """Whether a batched launch of such leaves takes the kernel for short leaves, in the modes set."""
+    lib = load()
+    offs = np.ascontiguousarray(leaf_offsets, dtype=np.int64)
+    lib.gbdt_debug_batch_is_short.restype = ctypes.c_int
+    lib.gbdt_debug_batch_is_short.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32,
+                                              ctypes.c_int32]
+    rc = lib.gbdt_debug_batch_is_short(n_features, n_bins, offs.ctypes.data, len(offs) - 1, n_cus, wg_per_cu)
+    if rc < 0:
+        _check(rc, "gbdt_debug_batch_is_short")
+    return rc == 1
 
 
 def gbdt_debug_half_blocks(n_features: int, n_rows: int, cols: int, by_column: bool):

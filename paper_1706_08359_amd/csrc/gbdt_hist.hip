@@ -691,6 +691,9 @@ int launch_build(const BuildArgs& a, int blocks, hipStream_t s, bool timed, bool
   return timer.end(s);
 }
 
+// Whether batches have a kernel for long leaves, beside SHORT (batch_is_short).
+constexpr bool batch_has_long(int cap, bool wide) { return cap == 64 || (cap == 256 && !wide); }
+
 template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool WIDE = false, bool HALVES = false>
 int launch_build_batch(const BatchArgs& a, int blocks, hipStream_t s, bool is_short) {
   BuildTimer timer;
@@ -698,7 +701,7 @@ int launch_build_batch(const BatchArgs& a, int blocks, hipStream_t s, bool is_sh
   if (rc != GBDT_OK) return rc;
   if (is_short) {
     hipLaunchKernelGGL((hist_build_batch_kernel<CAP, WM, NIB, NT, WPE, ACC, WIDE, HALVES, true>), dim3(blocks), dim3(NT), 0, s, a);
-  } else if constexpr (!(WIDE && CAP == 256)) {
+  } else if constexpr (batch_has_long(CAP, WIDE)) {
     hipLaunchKernelGGL((hist_build_batch_kernel<CAP, WM, NIB, NT, WPE, ACC, WIDE, HALVES, false>), dim3(blocks), dim3(NT), 0, s, a);
   }
   HIP_TRY(hipGetLastError());
@@ -723,8 +726,10 @@ size_t variant_column_words(const TilePlan& p) {
 struct BatchPlan {
   BatchLeaf leaf[kBatchLeaves];  // most epochs per workgroup first
   int n = 0;
+  int n_live = 0;          // leaves with rows
   uint32_t total_wgs = 0;  // workgroups per tile over all leaves
   int most_unit_epochs = 1;
+  uint32_t most_each = 0;  // epochs of the busiest workgroup
 };
 constexpr double kBatchColumnEpochs = 3.0;
 constexpr double kBatchMergeEpochs = 2.0;
@@ -748,12 +753,12 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
   uint32_t epochs[kBatchLeaves], most = 1;  // (leaves hold fewer than 2^31 rows)
   uint32_t longer[kBatchLeaves];  // the leaves whose columns depend on T: those of more than kDirectEpochs epochs
   int64_t total_epochs = 0;
-  int n_live = 0, n_long = 0;
+  int n_long = 0;
   for (int i = 0; i < n; ++i) {
     epochs[i] = (uint32_t)((leaf_offsets[l0 + i + 1] - leaf_offsets[l0 + i] + kEpochRows - 1) / kEpochRows);
     total_epochs += epochs[i];
     if (epochs[i] > most) most = epochs[i];
-    n_live += epochs[i] > 0;
+    b.n_live += epochs[i] > 0;
     if (epochs[i] > (uint32_t)kDirectEpochs) longer[n_long++] = epochs[i];
   }
   int64_t budget = resident / n_tiles;
@@ -766,13 +771,13 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
     // ceil(e / cand) by a multiplication: e and cand are below 2^22, so quotients that are no whole numbers are
     // at least 2^-22 away from one, and 2^-24 covers the rounding of those that are
     const double inv = 1.0 / (double)cand;
-    uint32_t columns = (uint32_t)(n_live - n_long), blocks = 0;  // blocks: of sums that a reduction pass moves
+    uint32_t columns = (uint32_t)(b.n_live - n_long), blocks = 0;  // blocks: of sums that a reduction pass moves
     for (int i = 0; i < n_long; ++i) {
       const uint32_t w = (uint32_t)((int32_t)((double)(int32_t)(longer[i] + cand - 1) * inv + 0x1p-24));
       columns += w;
       blocks += w > 1 ? 2 * w + 1 : 0;
     }
-    if ((int64_t)columns > budget + n_live) return;  // (the bound that the scratch is sized by)
+    if ((int64_t)columns > budget + b.n_live) return;  // (the bound that the scratch is sized by)
     const int64_t per_cu = ((int64_t)columns * n_tiles + cus - 1) / cus;  // workgroups of the fullest CU
     double cost = (double)cand * (per_cu < wg_per_cu ? share[per_cu] : 1.0) + kBatchColumnEpochs;
     if ((int64_t)columns > budget) {
@@ -803,7 +808,7 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
       if ((int64_t)k * cus >= n_tiles) consider_around((int64_t)k * cus / n_tiles, {1.0, 1.03, 1.1, 1.25});
   }
   int wgs[kBatchLeaves], unit[kBatchLeaves];
-  uint32_t each[kBatchLeaves], most_each = 0;  // epochs of a leaf's busiest workgroup
+  uint32_t each[kBatchLeaves];  // epochs of a leaf's busiest workgroup
   for (int i = 0; i < n; ++i) {
     if (epochs[i] <= (uint32_t)kDirectEpochs) {  // (as plan_leaf_units has it)
       wgs[i] = epochs[i] > 0;
@@ -814,13 +819,13 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
       plan_leaf_units((int64_t)epochs[i], (int64_t)((epochs[i] + t - 1) / t), &wgs[i], &unit[i], &one_each);
       each[i] = one_each ? (uint32_t)unit[i] : (epochs[i] + (uint32_t)wgs[i] - 1) / (uint32_t)wgs[i];
     }
-    if (each[i] > most_each) most_each = each[i];
+    if (each[i] > b.most_each) b.most_each = each[i];
     if (unit[i] > b.most_unit_epochs) b.most_unit_epochs = unit[i];
   }
   // the longest first, to within 1/128 of the longest (equal ones in the call's order): a counting sort,
   // because a call of many short leaves takes about as long on the host as on the device
   int shift = 0;
-  while ((most_each >> shift) > 255u) ++shift;
+  while ((b.most_each >> shift) > 255u) ++shift;
   uint16_t place[257] = {0};  // place[k + 1] ends as the first place of key k, keys descending
   for (int i = 0; i < n; ++i) ++place[256 - (each[i] >> shift)];
   for (int k = 1; k <= 256; ++k) place[k] = (uint16_t)(place[k] + place[k - 1]);
@@ -838,6 +843,23 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
   }
   b.total_wgs = first;
   return b;
+}
+
+// Which of its two kernels a batch takes.  SHORT spends less on a leaf's end (its last epoch, its histogram), the other one less on every
+// epoch: with 256 bins 1 to 2.7 %, with 64 mostly nothing, but for long columns dealt out as places come free.  So the epochs of
+// the busiest workgroup decide, and with 256 bins whether there are leaf ends to speak of.
+// More than kBatchLongEpochs, SHORT and long us: 1,500,000 x 500 x 255 in 24 leaves, 123 epochs each, 380 and 374, 40, 74 epochs, 452 and
+// 453, 64, 46 epochs, 353 and 373; 4,000,000 x 100 x 255 in 16, 61 epochs, 240 and 237, in 200, 40 epochs, 299.5 and 301;
+// 4,000,000 x 500 x 64 in 128, 62 epochs, 729 and 696, in 192, 41 epochs, 546 and 551.
+// Few leaves of 256 bins: all of 10,500,000 x 28 in one, 41 epochs, 152.5 and 148.3, in two 159.6 and 156.0, in eight 265.2 and 264.1, in 12
+// 285.0 and 286.5, in 32 223 and 228; half of it in one, 21 epochs, 101.2 and 98.9; a fifth in two, 9 epochs, the same.
+// With 16 bins SHORT is never the slower one (4,000,000 x 500 in 128 leaves, 62 epochs, 444 and 447), and wide 256 bins have one kernel.
+constexpr uint32_t kBatchLongEpochs = 60;
+constexpr int kBatchFewLeaves = 8;
+bool batch_is_short(const BatchPlan& b, int cap, bool wide) {
+  if (!batch_has_long(cap, wide)) return true;
+  const bool few = cap == 256 && b.n_live <= kBatchFewLeaves;
+  return b.most_each <= (few ? (uint32_t)(kUnitEpochs * kEvenSplitUnits) : kBatchLongEpochs);
 }
 
 // The table of one launch of stats_gather_lists_kernel, for lists l0, l0 + 1, ... of the call: as many as fit the table, and
@@ -1587,10 +1609,7 @@ static int hist_build_batch_impl(const void* bin_matrix, int64_t n_rows, int32_t
       a.n_bins = n_bins;
       memcpy(a.leaf, b.leaf, sizeof a.leaf);
       const int blocks = (int)b.total_wgs * n_parts;
-      // Leaves of one workgroup a tile end with their last epoch and write their histogram, which SHORT does better; with several
-      // workgroups of many epochs each it is the epochs that count (1,500,000 x 500 x 255 in 64 leaves 352 us SHORT and 362; in 16, two
-      // workgroups each, 320 and 314).
-      const bool is_short = (wide && p.cap == 256) || b.total_wgs < 2u * (uint32_t)n || b.most_unit_epochs <= kUnitEpochs * kEvenSplitUnits;
+      const bool is_short = batch_is_short(b, p.cap, wide);
       if (wide) {
         if (p.cap == 16) {
           rc = launch_build_batch<GBDT_VARIANT_16W, true>(a, blocks, s, is_short);
@@ -2407,6 +2426,17 @@ int gbdt_debug_batch_plan(int32_t n_features, int32_t n_bins, const int64_t* lea
     block_out[3 * i + 2] = k.wg;
   }
   return (int)blocks;
+}
+
+int gbdt_debug_batch_is_short(int32_t n_features, int32_t n_bins, const int64_t* leaf_offsets, int32_t n_leaves, int32_t n_cus,
+                              int32_t wg_per_cu) {
+  if (n_features <= 0 || n_bins < 2 || n_bins > 256 || !leaf_offsets || n_leaves < 1 || n_leaves > kBatchLeaves || n_cus <= 0 ||
+      wg_per_cu <= 0)
+    return GBDT_EINVAL;
+  for (int32_t l = 0; l < n_leaves; ++l)
+    if (leaf_offsets[l + 1] < leaf_offsets[l]) return GBDT_EINVAL;
+  const TilePlan p = make_tile_plan(n_features, n_bins);
+  return batch_is_short(plan_batch(leaf_offsets, 0, n_leaves, n_cus, wg_per_cu, plan_n_tiles(p)), p.cap, g_wide.load() != 0) ? 1 : 0;
 }
 
 int gbdt_debug_block_map(int32_t n_features, int32_t n_bins, int64_t n_rows, int32_t cols, int32_t by_column,

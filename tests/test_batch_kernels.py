@@ -1,0 +1,62 @@
+"""Which kernel a batched launch takes, on the CPU: both for long and for short leaves are taken, and by the epochs of the busiest
+workgroup as the plan itself reports it."""
+import numpy as np
+import pytest
+
+from paper_1706_08359_amd import binding as B
+
+
+def busiest(n_features, n_bins, offs, wg_per_cu):
+    wgs, ue, _ = B.gbdt_debug_batch_plan(n_features, n_bins, offs, 256, wg_per_cu)
+    most = 0
+    for n, w, u in zip(np.diff(offs), wgs, ue):
+        epochs = -(-int(n) // 512)
+        if epochs:
+            one_unit_each = epochs <= int(w) * int(u)
+            most = max(most, int(u) if one_unit_each else -(-epochs // int(w)))
+    return most
+
+
+def sizes(kind, rng):
+    if kind == "equal":
+        return np.full(rng.integers(1, 200), rng.integers(1, 300_000))
+    if kind == "few":
+        return rng.integers(1, 4_000_000, size=rng.integers(1, 12))
+    if kind == "with_empty":
+        return rng.integers(0, 2, size=60) * rng.integers(1, 60_000, size=60)
+    return (rng.integers(100_000, 12_000_000) * rng.dirichlet(np.ones(rng.integers(2, 200)))).astype(np.int64)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("n_features,n_bins,wg_per_cu", [(28, 255, 2), (500, 255, 2), (2000, 63, 3), (60, 64, 3), (700, 16, 4)])
+def test_the_busiest_workgroup_decides(n_features, n_bins, wg_per_cu, wide):
+    rng = np.random.default_rng(n_features)
+    one_kernel = n_bins <= 16 or (wide and n_bins > 64)
+    seen = set()
+    B.gbdt_set_wide_accumulation(wide)
+    try:
+        for trial in range(160):
+            n = sizes(["equal", "few", "with_empty", "dirichlet"][trial % 4], rng)
+            offs = np.concatenate([[0], np.cumsum(n)])
+            live, most = int((n > 0).sum()), busiest(n_features, n_bins, offs, wg_per_cu)
+            expect = one_kernel or most <= (12 if n_bins > 64 and live <= 8 else 60)
+            assert B.gbdt_debug_batch_is_short(n_features, n_bins, offs, 256, wg_per_cu) == expect, (n.tolist(), most)
+            seen.add(expect)
+    finally:
+        B.gbdt_set_wide_accumulation(False)
+    assert seen == ({True} if one_kernel else {True, False})
+
+
+def test_lines_of_the_rule():
+    """One column a leaf (more leaves than columns fit): its epochs are the leaf's."""
+    def short(n_bins, leaves, epochs):
+        offs = np.arange(leaves + 1) * (512 * epochs)
+        assert busiest(2000, n_bins, offs, 2) == epochs
+        return B.gbdt_debug_batch_is_short(2000, n_bins, offs, 256, 2)
+    for n_bins in (63, 255):
+        assert short(n_bins, 40, 60) and not short(n_bins, 40, 61)
+    assert short(255, 8, 12) and not short(255, 8, 13) and short(255, 9, 13)    # 63 tiles: eight columns fit
+    with pytest.raises(B.GbdtError):
+        B.gbdt_debug_batch_is_short(2000, 257, [0, 5], 256, 2)
+    with pytest.raises(B.GbdtError):
+        B.gbdt_debug_batch_is_short(2000, 255, [5, 0], 256, 2)
