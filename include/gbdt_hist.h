@@ -512,7 +512,8 @@ int gbdt_debug_geometry(int32_t n_features, int32_t n_bins, int64_t n_leaf_rows,
  * units), in the modes set: out[0] = workgroups per tile, out[1] = epochs per unit, out[2] = epochs of every
  * workgroup's first unit (0: no longer than the others), out[3] = 0 when units are handed out at run time, else the
  * fixed stride between a workgroup's units, out[4] = 1 or 2 when blocks are dealt out by shared lines,
- * out[5] = 1 when every workgroup has one unit.  (A fused copy of the matrix has its own plan.) */
+ * out[5] = 1 when every workgroup has one unit, out[6] (if n_out > 6) = 1 when the leaf takes the kernel for short
+ * leaves.  (A fused copy of the matrix has its own plan.) */
 int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int64_t n_leaf_rows, int32_t indexed,
                          int64_t* out, int32_t n_out);
 /* Launch plan of the first (at most 224-leaf) launch of gbdt_hist_build_batch on a device

@@ -562,13 +562,13 @@ def gbdt_debug_locate(n_features: int, n_bins: int, feature: int):
 def gbdt_debug_leaf_plan(n_rows: int, n_features: int, n_bins: int, n_leaf_rows: int, indexed: bool) -> dict:
     """How gbdt_hist_build shares out a leaf on the current device, in the modes set."""
     lib = load()
-    out = (ctypes.c_int64 * 6)()
+    out = (ctypes.c_int64 * 7)()
     lib.gbdt_debug_leaf_plan.restype = ctypes.c_int
     lib.gbdt_debug_leaf_plan.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32,
                                          ctypes.c_void_p, ctypes.c_int32]
-    _check(lib.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf_rows, 1 if indexed else 0, out, 6),
+    _check(lib.gbdt_debug_leaf_plan(n_rows, n_features, n_bins, n_leaf_rows, 1 if indexed else 0, out, 7),
            "gbdt_debug_leaf_plan")
-    return dict(zip(("wgs", "unit_epochs", "first_epochs", "fixed_stride", "deal", "one_unit_each"), out))
+    return dict(zip(("wgs", "unit_epochs", "first_epochs", "fixed_stride", "deal", "one_unit_each", "short"), out))
 
 
 def gbdt_debug_fuse_sample_rows(n_rows: int, n_features: int) -> int:

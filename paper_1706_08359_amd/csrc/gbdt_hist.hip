@@ -498,6 +498,18 @@ UnitPlan plan_units(const BuildGeom& g, int64_t n_leaf, bool indexed, int32_t li
   return u;
 }
 
+// Which of its two kernels a leaf takes.  SHORT spends less on the leaf's end: its last epoch, and the histogram, which a tile's only
+// workgroup writes.  The other one spends less on every epoch, and its last one may as well add zeros beside workgroups that are full.
+// SHORT and long us: one workgroup a tile, 28 x 255, an epoch 6.2 and 7.0, four 11.7 and 12.6; 60 x 64 5.9 and 6.5, 12.4 and 13.0; 400 x 16,
+// wide, 9.3 and 10.2, 28.2 and 28.7.  Several, 256 bins, of one epoch, root of 100,000 x 28 19.0 and 21.5, of two, 32,700 of 500 features 27.8
+// and 29.1, of three 29.0 and 28.9, of ten, a tenth of 1,500,000 x 500 as a list 49.7 and 49.0.  64 bins, of one to twelve epochs, 0 to 1 % more
+// SHORT (a fiftieth of 8,000,000 x 500 as a list 43.3 and 42.8); 16 bins, a tenth of 3,000,000 x 400 as a list 47.4 and 46.3.
+constexpr int kShortUnitEpochs = 2;
+bool leaf_is_short(const BuildGeom& g, bool wide) {
+  if (wide && g.plan.cap == 256) return true;  // (one kernel for both)
+  return g.one_unit_each && (g.wgs == 1 || (g.plan.cap == 256 && g.unit_epochs <= kShortUnitEpochs));
+}
+
 // How the rows of a build lie in the matrix, for plan_halves.  Sparse: a list of at most a fifth of the rows, and all leaves of
 // a batch.  Many sparse rows: from kSparseManyRows listed ones on, in a batch if its leaves hold at most a twelfth of the rows
 // each on average (1,000,000 x 33 x 255: 32 leaves of half of the rows 45.9 us whole, 54.7 in halves, 64 of all 76 and 79;
@@ -1211,7 +1223,7 @@ int hist_build_impl(const void* bin_matrix, int64_t n_rows, int32_t n_features, 
   // From here until the reduction pass has been enqueued the counters are in use.
   if (uses_counters && !capturing) set_counters_zero(counters, false);
 
-  const bool is_short = g.one_unit_each || (wide && p.cap == 256);  // (which have one kernel for both)
+  const bool is_short = leaf_is_short(g, wide);
   const bool timed = fixed_base == nullptr;  // the profiling events are created on the fly: an allocation
   if (wide) {
     if (p.cap == 16) {
@@ -2394,8 +2406,8 @@ int gbdt_debug_leaf_plan(int64_t n_rows, int32_t n_features, int32_t n_bins, int
   const BuildGeom g = make_geom(n_features, n_bins, n_leaf_rows, device_cu_count(),
                                 build_wg_per_cu(p.cap, indexed != 0, wide, halves), wide, halves);
   const UnitPlan u = plan_units(g, n_leaf_rows, indexed != 0, plan_line_tiles(n_rows), g_deterministic.load(), device_cu_count());
-  const int64_t v[6] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal, g.one_unit_each};
-  for (int i = 0; i < 6; ++i) out[i] = v[i];
+  const int64_t v[7] = {g.wgs, u.unit_epochs, u.first_epochs, u.fixed_stride, u.deal, g.one_unit_each, leaf_is_short(g, wide)};
+  for (int i = 0; i < 7 && i < n_out; ++i) out[i] = v[i];
   return GBDT_OK;
 }
 
