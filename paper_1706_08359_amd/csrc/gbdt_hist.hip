@@ -857,21 +857,20 @@ BatchPlan plan_batch(const int64_t* leaf_offsets, int32_t l0, int32_t n, int cus
   return b;
 }
 
-// Which of its two kernels a batch takes.  SHORT spends less on a leaf's end (its last epoch, its histogram), the other one less on every
-// epoch: with 256 bins 1 to 2.7 %, with 64 mostly nothing, but for long columns dealt out as places come free.  So the epochs of
-// the busiest workgroup decide, and with 256 bins whether there are leaf ends to speak of.
-// More than kBatchLongEpochs, SHORT and long us: 1,500,000 x 500 x 255 in 24 leaves, 123 epochs each, 380 and 374, 40, 74 epochs, 452 and
-// 453, 64, 46 epochs, 353 and 373; 4,000,000 x 100 x 255 in 16, 61 epochs, 240 and 237, in 200, 40 epochs, 299.5 and 301;
-// 4,000,000 x 500 x 64 in 128, 62 epochs, 729 and 696, in 192, 41 epochs, 546 and 551.
-// Few leaves of 256 bins: all of 10,500,000 x 28 in one, 41 epochs, 152.5 and 148.3, in two 159.6 and 156.0, in eight 265.2 and 264.1, in 12
-// 285.0 and 286.5, in 32 223 and 228; half of it in one, 21 epochs, 101.2 and 98.9; a fifth in two, 9 epochs, the same.
-// With 16 bins SHORT is never the slower one (4,000,000 x 500 in 128 leaves, 62 epochs, 444 and 447), and wide 256 bins have one kernel.
+// Which of its two kernels a batch takes (see leaf_is_short).  Leaves of about one column end where their workgroup does, which writes the
+// histogram: SHORT, unless there are many epochs before that.  With two columns a leaf and more most workgroups end elsewhere.
+// One column, SHORT and long us: a tenth of 1,500,000 x 500 x 255 in 64 leaves, 5 epochs, 61.7 and 71.8, all of it in 128, 23 epochs, 394.6 and
+// 405.7, in 64, 46 epochs, 351.4 and 354.2, in 32, 92 epochs, 304.4 and 302.0, in 24, 123 epochs, 383.2 and 378.1; half of 400,000 x 2,000 x 63 in
+// 128, 4 epochs, 164.7 and 180.9; half of 8,000,000 x 500 x 64 in 128, 62 epochs, 751 and 716.
+// More: a tenth of 1,500,000 x 500 x 255 in four, eight columns of 10 epochs, 57.7 and 56.7, all of it in 16, two of 92, 315.9 and 310.4; 30 % of
+// 2,270,000 x 137 x 255 in 20, five of 14, 82.7 and 81.2; 10,500,000 x 28 x 255 in one, 41 epochs, 151.3 and 147.3, in 64, the same, 234; a tenth of
+// 10,500,000 x 60 x 64 in 128 with wide sums 68.6 and 67.7, without 0 to 1 % either way.  (The other way round where equal leaves take every place there
+// is: 10,500,000 x 28 x 255 in 16, 32 columns each, 183 and 189.)
+// With 16 bins there is nothing between the two but on one column, where SHORT gains 1 to 5 %; wide 256 bins have one kernel.
 constexpr uint32_t kBatchLongEpochs = 60;
-constexpr int kBatchFewLeaves = 8;
 bool batch_is_short(const BatchPlan& b, int cap, bool wide) {
   if (!batch_has_long(cap, wide)) return true;
-  const bool few = cap == 256 && b.n_live <= kBatchFewLeaves;
-  return b.most_each <= (few ? (uint32_t)(kUnitEpochs * kEvenSplitUnits) : kBatchLongEpochs);
+  return b.total_wgs < 2u * (uint32_t)b.n_live && b.most_each <= kBatchLongEpochs;
 }
 
 // The table of one launch of stats_gather_lists_kernel, for lists l0, l0 + 1, ... of the call: as many as fit the table, and

@@ -1,12 +1,13 @@
-"""Which kernel a batched launch takes, on the CPU: both for long and for short leaves are taken, and by the epochs of the busiest
-workgroup as the plan itself reports it."""
+"""Which kernel a batched launch takes, on the CPU: both for long and for short leaves are taken, by the workgroups a leaf with rows has
+and the epochs of the busiest one, as the plan itself reports them."""
 import numpy as np
 import pytest
 
 from paper_1706_08359_amd import binding as B
 
 
-def busiest(n_features, n_bins, offs, wg_per_cu):
+def shares(n_features, n_bins, offs, wg_per_cu):
+    """Workgroups a tile, and epochs of the busiest workgroup."""
     wgs, ue, _ = B.gbdt_debug_batch_plan(n_features, n_bins, offs, 256, wg_per_cu)
     most = 0
     for n, w, u in zip(np.diff(offs), wgs, ue):
@@ -14,12 +15,14 @@ def busiest(n_features, n_bins, offs, wg_per_cu):
         if epochs:
             one_unit_each = epochs <= int(w) * int(u)
             most = max(most, int(u) if one_unit_each else -(-epochs // int(w)))
-    return most
+    return int(sum(wgs)), most
 
 
 def sizes(kind, rng):
     if kind == "equal":
         return np.full(rng.integers(1, 200), rng.integers(1, 300_000))
+    if kind == "short":
+        return rng.integers(1, 4_000, size=rng.integers(1, 200))
     if kind == "few":
         return rng.integers(1, 4_000_000, size=rng.integers(1, 12))
     if kind == "with_empty":
@@ -36,11 +39,11 @@ def test_the_busiest_workgroup_decides(n_features, n_bins, wg_per_cu, wide):
     B.gbdt_set_wide_accumulation(wide)
     try:
         for trial in range(160):
-            n = sizes(["equal", "few", "with_empty", "dirichlet"][trial % 4], rng)
+            n = sizes(["equal", "short", "few", "with_empty", "dirichlet"][trial % 5], rng)
             offs = np.concatenate([[0], np.cumsum(n)])
-            live, most = int((n > 0).sum()), busiest(n_features, n_bins, offs, wg_per_cu)
-            expect = one_kernel or most <= (12 if n_bins > 64 and live <= 8 else 60)
-            assert B.gbdt_debug_batch_is_short(n_features, n_bins, offs, 256, wg_per_cu) == expect, (n.tolist(), most)
+            live, (columns, most) = int((n > 0).sum()), shares(n_features, n_bins, offs, wg_per_cu)
+            expect = one_kernel or (columns < 2 * live and most <= 60)
+            assert B.gbdt_debug_batch_is_short(n_features, n_bins, offs, 256, wg_per_cu) == expect, (n.tolist(), columns, most)
             seen.add(expect)
     finally:
         B.gbdt_set_wide_accumulation(False)
@@ -48,15 +51,17 @@ def test_the_busiest_workgroup_decides(n_features, n_bins, wg_per_cu, wide):
 
 
 def test_lines_of_the_rule():
-    """One column a leaf (more leaves than columns fit): its epochs are the leaf's."""
-    def short(n_bins, leaves, epochs):
+    def short(n_bins, leaves, epochs, columns):
         offs = np.arange(leaves + 1) * (512 * epochs)
-        assert busiest(2000, n_bins, offs, 2) == epochs
+        assert shares(2000, n_bins, offs, 2) == (columns, -(-epochs * leaves // columns))
         return B.gbdt_debug_batch_is_short(2000, n_bins, offs, 256, 2)
+    # more leaves than columns fit: one each, whose epochs are the leaf's
     for n_bins in (63, 255):
-        assert short(n_bins, 40, 60) and not short(n_bins, 40, 61)
-    assert short(255, 8, 12) and not short(255, 8, 13) and short(255, 9, 13)    # 63 tiles: eight columns fit
+        assert short(n_bins, 40, 60, 40) and not short(n_bins, 40, 61, 40)
+    assert short(255, 8, 12, 8) and short(255, 8, 60, 8) and not short(255, 8, 61, 8)    # 63 tiles: eight columns fit
+    assert not short(255, 1, 40, 8) and not short(63, 1, 10, 5)
     with pytest.raises(B.GbdtError):
         B.gbdt_debug_batch_is_short(2000, 257, [0, 5], 256, 2)
     with pytest.raises(B.GbdtError):
         B.gbdt_debug_batch_is_short(2000, 255, [5, 0], 256, 2)
+    assert not B.gbdt_debug_batch_is_short(2000, 255, [0, 0, 0], 256, 2)                  # nothing is launched

@@ -1,5 +1,5 @@
 """Batches that take the kernel for long leaves, against the oracle: one workgroup a tile and leaf, which writes the histogram itself, and
-several; few leaves of 256 bins; leaves that end inside an epoch, of one row and of none beside them.
+several of few and of many epochs; leaves that end inside an epoch, of one row and of none beside them.
 
 Statistics are small multiples of a power of two: every sum is exact and has to agree bit for bit."""
 import numpy as np
@@ -16,11 +16,15 @@ MANY = [31_300 + 97 * i for i in range(30)] + [1, 0, 512, 20_000]
 
 
 @pytest.mark.parametrize("n_features,n_bins,wide,lengths", [
-    (2000, 255, False, [N_ROWS, 40_001, 700, 0, 1]),
+    (2000, 255, False, [N_ROWS]),
+    (1999, 255, False, [N_ROWS, 40_001, 700, 0, 1]),
+    (500, 256, False, [N_ROWS, 40_001, 20_000, 0, 1]),
+    (70, 255, False, [N_ROWS]),
+    (70, 255, False, [2_049, 2_600, 5_000, 9_999]),      # one epoch a workgroup
     (1999, 255, False, MANY),
-    (70, 255, False, [N_ROWS]),           # (short: in few epochs each, beside the long ones)
     (2000, 63, False, MANY),
     (1990, 64, False, [N_ROWS + 5_000 * i for i in range(12)]),
+    (200, 63, True, [N_ROWS, 40_001, 20_000, 0, 1]),
     (2000, 63, True, MANY),
 ])
 def test_long_leaves_in_a_batch(n_features, n_bins, wide, lengths):
@@ -35,8 +39,7 @@ def test_long_leaves_in_a_batch(n_features, n_bins, wide, lengths):
     flat = torch.from_numpy(np.concatenate(lists)).to(p.dev)
     B.gbdt_set_wide_accumulation(wide)
     try:
-        short = B.gbdt_debug_batch_is_short(n_features, n_bins, offs, 256, 2 if wide else B.gbdt_debug_occupancy(n_bins, True))
-        assert short == (n_features == 70)
+        assert not B.gbdt_debug_batch_is_short(n_features, n_bins, offs, 256, 2 if wide else B.gbdt_debug_occupancy(n_bins, True))
         hists = B.gbdt_hist_build_batch(p.packed, N_ROWS, n_features, n_bins, flat, offs, p.grad, p.hess)
     finally:
         B.gbdt_set_wide_accumulation(False)
