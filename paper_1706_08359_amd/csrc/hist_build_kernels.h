@@ -459,9 +459,9 @@ struct TileShape {
 // the largest power-of-two scales that cannot overflow a 27-bit field, and each lane
 // quantises its own row once into a 64-bit addend that carries count, gradient and
 // hessian.  The lanes that then work on a row fetch its addend with DPP moves, and
-// every (row, feature) costs ONE 64-bit integer atomic.  After each epoch the cells
-// are drained into accumulators held in registers (each thread owns PP cells) and
-// cleared.
+// every (row, feature) costs ONE 64-bit integer atomic.  After each epoch (kPairs:
+// after every second one) the cells are drained into accumulators held in registers
+// (each thread owns PP cells) and cleared.
 // Error: each value is rounded once, by at most half a quantum; the quantum is at
 // most sum|g|_epoch / (2^25 - 256), so a bin is off by at most 512 / (2^26 - 512) =
 // 7.7e-6 of the leaf's sum |g| (likewise for h), and integer addition is
@@ -498,8 +498,8 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
 
   // Two epochs a drain.  With 256 bins a cell has two rows of an epoch, and draining its cells costs about as much as adding its
   // rows.  Wide cells have room for another epoch whatever the statistics are, as long as the two exponents are one apart
-  // at most (wide_pair; what a row adds at the scale of the other epoch: wide_quantise).  The second epoch is counted in the hessian cells, whose count field is free, so neither count
-  // passes 512.
+  // at most (wide_pair; what a row adds at the scale of the other epoch: wide_quantise).  The second epoch is counted in the
+  // hessian cells, whose count field is free, so neither count passes 512.
   // (Root of 2,270,000 x 137 x 255 202 us drained after every epoch, 184 so, of 1,500,000 x 500 440 and 396; 60 % of the first as a
   // list 134 and 126; 64 leaves of all of the second 607 and 574.  With 64 or 16 bins, where a cell has more rows of an epoch,
   // it is between 4 % faster and 3 % slower.)
@@ -992,8 +992,9 @@ __device__ __forceinline__ void build_tile(const uint8_t* __restrict__ tile, uin
   }
   // The leaf's last epoch, where rows are missing: nothing follows it, and wavefronts without a row add nothing.  (As one more
   // turn of the loop, which adds zeros and requests rows that nobody takes: 128 leaves of half of 400,000 x 2,000 x 63 174 us, 162
-  // so; 64 leaves of 1,500,000 x 500 x 255 371 and 353; 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions
-  // inside the loop makes every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
+  // so; 64 equal leaves of 1,500,000 x 500 x 255, 46 epochs a workgroup, 371 and 353 (with the drains of then; unequal leaves, of which the
+  // longest count, gain nothing); 32 of half of 100,000 x 50 x 64 15.9 and 14.3.  A branch around the additions inside the loop makes
+  // every turn wait for all requests: root of 10,500,000 x 28 x 255 127 us, 146 so.)
   if (kLastApart && p0.row < end) {
     const Addend add = quantise(own_valid(p0.row), false, 0, 0);
     if (p0.row + (uint32_t)wave * 64u < end) {
@@ -1144,8 +1145,7 @@ __device__ __forceinline__ void build_part(const uint8_t* packed, int64_t n_rows
   }
 }
 
-// SHORT: for leaves whose workgroups have one unit of a few epochs each, and in batches those that have one workgroup a tile (see
-// build_tile).
+// SHORT: for leaves whose end is much of a workgroup's work (leaf_is_short, batch_is_short; what differs: build_tile).
 template <int CAP, int WM, bool NIB, int NT, int WPE, typename ACC, bool INDEXED, bool WIDE = false, bool HALVES = false,
           bool SHORT = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
